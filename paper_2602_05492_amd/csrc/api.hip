@@ -287,7 +287,7 @@ int bem_eval(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int6
     if ((rc = prepare_forward(ctx, theta, H, prec == BEM_PREC_MIXED, stream))) return rc;
     const int K = H * ctx->opts.segs_per_handle;
     if (prec == BEM_PREC_FP64) return launch_sweep_f64(ctx, x, N, K, cbar, (double*)u, stream);
-    return launch_sweep_mixed(ctx, x, N, K, cbar, (float*)u, stream);
+    return launch_sweep_eval(ctx, x, N, K, cbar, (float*)u, stream);
 }
 
 constexpr int64_t kVjpCellOrderMin = 65536;     // samples from which MIXED bem_vjp reorders them
@@ -484,7 +484,7 @@ void bem_destroy(bem_ctx* ctx)
     DevBuf* bufs[] = {&ctx->A, &ctx->Apinv, &ctx->LU, &ctx->piv, &ctx->un, &ctx->vn, &ctx->flag, &ctx->scal,
                       &ctx->seg64, &ctx->seg32, &ctx->F, &ctx->U, &ctx->elem64, &ctx->elem32, &ctx->red,
                       &ctx->tmp0, &ctx->tmp1, &ctx->tmp2, &ctx->tmp3, &ctx->tmp4, &ctx->tmp5, &ctx->lmw,
-                      &ctx->nearw, &ctx->nearv, &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw,
+                      &ctx->nearw, &ctx->nearv, &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
                       &ctx->tilew};
     for (DevBuf* b : bufs) release(*b);
     for (hipEvent_t e : ctx->ev)

@@ -1,0 +1,251 @@
+// cells.hip - the cell plan of the mixed sweeps: samples grouped by grid cell (a stable counting
+// sort without readback) and, per cell, which segments and outer elements are too near for its
+// interpolated far field.
+#include "cells.hpp"
+
+#include <cmath>
+
+namespace bem {
+
+namespace {
+
+// Histogram of the cell labels of one chunk of samples.
+__global__ void __launch_bounds__(256) k_cell_hist(const double* __restrict__ x, int64_t N, int chunk, CellGrid g,
+                                                   int nb, int* __restrict__ cnt)
+{
+    __shared__ int h[kMaxCellLabels];
+    for (int d = threadIdx.x; d <= g.nc; d += 256) h[d] = 0;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < N ? lo + chunk : N;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
+        atomicAdd(&h[cell_of(g, x[2 * i], x[2 * i + 1])], 1);
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d <= g.nc; d += 256) cnt[(size_t)d * nb + blockIdx.x] = h[d];
+}
+
+__device__ inline int wave_scan(int v)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int w = __shfl_up(v, o);
+        if (lane >= o) v += w;
+    }
+    return v;
+}
+
+// Per label the exclusive scan of its chunk counts, in place, and the label's total: a wavefront a
+// label.
+__global__ void __launch_bounds__(256) k_cell_scan(int* __restrict__ cnt, int nlab, int nb, int* __restrict__ total)
+{
+    const int d = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (d >= nlab) return;
+    int run = 0;
+    for (int b0 = 0; b0 < nb; b0 += 64) {
+        const int b = b0 + lane;
+        const int c = b < nb ? cnt[(size_t)d * nb + b] : 0;
+        const int s = wave_scan(c);
+        if (b < nb) cnt[(size_t)d * nb + b] = run + s - c;
+        run += __shfl(s, 63);
+    }
+    if (lane == 0) total[d] = run;
+}
+
+// First sample, first wavefront and first run of every label (one block, two labels a thread).
+__global__ void __launch_bounds__(1024) k_cell_offsets(const int* __restrict__ total, int nlab, int run,
+                                                       int* __restrict__ off, int* __restrict__ wave0,
+                                                       int* __restrict__ run0)
+{
+    __shared__ int part[3][16];
+    const int t = threadIdx.x, w = t >> 6;
+    int v[3][2], s[3];
+    for (int k = 0; k < 2; ++k) {
+        const int d = 2 * t + k;
+        const int n = d < nlab ? total[d] : 0;
+        v[0][k] = n;
+        v[1][k] = (n + 63) / 64;
+        v[2][k] = (n + run - 1) / run;
+    }
+    for (int q = 0; q < 3; ++q) {
+        s[q] = wave_scan(v[q][0] + v[q][1]);
+        if ((t & 63) == 63) part[q][w] = s[q];
+    }
+    __syncthreads();
+    int* out[3] = {off, wave0, run0};
+    for (int q = 0; q < 3; ++q) {
+        int before = 0;
+        for (int k = 0; k < w; ++k) before += part[q][k];
+        const int e = before + s[q] - v[q][0] - v[q][1];
+        if (2 * t <= nlab) out[q][2 * t] = e;
+        if (2 * t + 1 <= nlab) out[q][2 * t + 1] = e + v[q][0];
+    }
+}
+
+// Stable scatter of one chunk: 64 samples at a time take consecutive places of their labels in lane
+// order (equal labels found by one ballot per label bit), the block's wavefronts in turn.
+__global__ void __launch_bounds__(256) k_cell_scatter(const double* __restrict__ x, int64_t N, int chunk, CellGrid g,
+                                                      int nb, const int* __restrict__ base, const int* __restrict__ off,
+                                                      int* __restrict__ perm, double* __restrict__ xs)
+{
+    __shared__ int cur[kMaxCellLabels];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    for (int d = t; d <= g.nc; d += 256) cur[d] = off[d] + base[(size_t)d * nb + blockIdx.x];
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < N ? lo + chunk : N;
+    __syncthreads();
+    for (int64_t r0 = lo; r0 < hi; r0 += 256) {
+        const int64_t i = r0 + t;
+        const bool live = i < hi;
+        const double X = live ? x[2 * i] : 0.0, Y = live ? x[2 * i + 1] : 0.0;
+        const int l = live ? cell_of(g, X, Y) : -1;
+        uint64_t peers = __ballot(live);
+#pragma unroll
+        for (int b = 0; b < 11; ++b) {          // labels are below 2048
+            const bool bit = (l >> b) & 1;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+        int dest = -1;
+        for (int k = 0; k < 4; ++k) {
+            if (w == k && live) dest = cur[l] + rank;
+            __syncthreads();
+            if (w == k && live && rank == 0) cur[l] += __popcll(peers);
+            __syncthreads();
+        }
+        if (live) {
+            perm[dest] = (int)i;
+            reinterpret_cast<double2*>(xs)[dest] = make_double2(X, Y);
+        }
+    }
+}
+
+// Near bits: a lane a segment (or outer element), two words a wavefront.  A segment is far from the cell
+// when its extent stays kFarCells cell widths away from the cell's square in x or in y and no sample of
+// the square can have both of its end points within the near radius (the pairs the mixed sweeps
+// evaluate in float64; margins far above the float32 rounding of that test).  NaN geometry is near
+// everywhere.
+__global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, const float* __restrict__ seg32, int K,
+                                                   const float* __restrict__ el32, int M, float near2, int seg_words,
+                                                   int words, uint32_t* __restrict__ bits)
+{
+    const int c = blockIdx.y, lane = threadIdx.x & 63;
+    const int w = blockIdx.x * 8 + (threadIdx.x >> 5);
+    const bool seg = w < seg_words;
+    const int i = seg ? w * 32 + (lane & 31) : (w - seg_words) * 32 + (lane & 31);
+    bool near = false;
+    if (w < words && i < (seg ? K : M)) {
+        float ax, ay, bx, by, L2;
+        if (seg) {
+            const float* s = seg32 + (size_t)i * kSegStride;
+            ax = s[0]; ay = s[1]; bx = s[2]; by = s[3]; L2 = s[6];
+        } else {
+            const float* e = el32 + (size_t)i * kElemStride;
+            ax = e[0]; ay = e[1]; bx = e[0] + e[2]; by = e[1] + e[3]; L2 = e[2] * e[2] + e[3] * e[3];
+        }
+        double cx, cy;
+        cell_corner(g, c, cx, cy);
+        const float m = (float)(kFarCells * g.h);
+        const float x0 = (float)cx, y0 = (float)cy, x1 = (float)(cx + g.h), y1 = (float)(cy + g.h);
+        auto dist2 = [&](float px, float py) {
+            const float dx = fmaxf(0.0f, fmaxf(x0 - px, px - x1)), dy = fmaxf(0.0f, fmaxf(y0 - py, py - y1));
+            return dx * dx + dy * dy;
+        };
+        const bool clear = fminf(ax, bx) >= x1 + m || fmaxf(ax, bx) <= x0 - m || fminf(ay, by) >= y1 + m ||
+                           fmaxf(ay, by) <= y0 - m;
+        const float r2 = 1.01f * near2 * L2 + 1e-9f;
+        near = c == g.nc || !(clear && !(dist2(ax, ay) < r2 && dist2(bx, by) < r2));
+    }
+    const uint64_t m = __ballot(near);
+    if ((lane & 31) == 0 && w < words) bits[(size_t)c * words + w] = (uint32_t)(lane ? m >> 32 : m);
+}
+
+}  // namespace
+
+// Cells a side.  Direct sums evaluate N (K + M) pairs; a grid of n cells evaluates kFarNodes n (K + M) at
+// its nodes and about (2 kFarCells + 1)^2 / n of the direct ones sample by sample, least at
+// n = (5 / 8) sqrt(N).
+int cells_for(const bem_ctx* ctx, int64_t N, int K)
+{
+    const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
+    if (!(bw > 0.0) || !(bh > 0.0) || N < 8192 || N > ((int64_t)1 << 30)) return 0;
+    const double reach = 2.0 * kFarCells + 1.0;
+    // cells are square: the longer side takes g of them
+    const double aspect = bw > bh ? bh / bw : bw / bh;
+    double g = std::sqrt(reach / kFarQ * std::sqrt((double)N) / aspect);
+    if (g > kMaxGrid) g = kMaxGrid;
+    const int n = (int)g;
+    const double cells = (double)n * std::ceil(n * aspect);
+    const double share = kFarNodes * cells / (double)N + reach * reach / cells;
+    // the plan, the bits and the node sums cost about as much as 2e7 pairs
+    return n >= 2 && (1.0 - share) * (double)N * ((double)K + 0.4 * ctx->M) > 2e7 ? n : 0;
+}
+
+int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s)
+{
+    int rc;
+    const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
+    CellGrid& G = p->grid;
+    G.x0 = ctx->bbox[0];
+    G.y0 = ctx->bbox[1];
+    G.h = (bw > bh ? bw : bh) / g;
+    G.inv_h = 1.0 / G.h;
+    auto cells = [&](double w) {
+        const int n = (int)std::ceil(w * G.inv_h - 1e-9);
+        return n < 1 ? 1 : (n > g ? g : n);
+    };
+    G.nx = cells(bw);
+    G.ny = cells(bh);
+    G.nc = G.nx * G.ny;
+    const int nlab = G.nc + 1;
+    int chunk = 256;
+    while (chunk < 4096 && N / chunk > 512) chunk *= 2;
+    const int nb = blocks_for(N, chunk);
+    // perm [N] | xs [N][2] | counts [nlab][nb] | totals, off, wave0, run0 [nlab + 1] each
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    const size_t pb = up((size_t)N * sizeof(int)), xb = up((size_t)N * 2 * sizeof(double)),
+                 cb = up((size_t)nlab * nb * sizeof(int)), lb = up((size_t)(nlab + 1) * sizeof(int));
+    if ((rc = ensure(ctx, ctx->cellw, pb + xb + cb + 4 * lb, s))) return rc;
+    char* base = (char*)ctx->cellw.ptr;
+    int* perm = (int*)base;
+    double* xs = (double*)(base + pb);
+    int* cnt = (int*)(base + pb + xb);
+    int* total = (int*)(base + pb + xb + cb);
+    int* off = (int*)((char*)total + lb);
+    int* wave0 = (int*)((char*)off + lb);
+    int* run0 = (int*)((char*)wave0 + lb);
+    // runs of samples for the adjoint: enough of them to fill the chip, long enough to pay for their sums
+    int run = 64;
+    while (run < 1024 && N / run > 4096) run *= 2;
+    p->run = run;
+    hipLaunchKernelGGL(k_cell_hist, dim3(nb), dim3(256), 0, s, x, N, chunk, G, nb, cnt);
+    hipLaunchKernelGGL(k_cell_scan, dim3(blocks_for(nlab, 4)), dim3(256), 0, s, cnt, nlab, nb, total);
+    hipLaunchKernelGGL(k_cell_offsets, dim3(1), dim3(1024), 0, s, (const int*)total, nlab, run, off, wave0, run0);
+    hipLaunchKernelGGL(k_cell_scatter, dim3(nb), dim3(256), 0, s, x, N, chunk, G, nb, (const int*)cnt, (const int*)off,
+                       perm, xs);
+    p->perm = perm;
+    p->xs = xs;
+    p->off = off;
+    p->wave0 = wave0;
+    p->run0 = run0;
+    p->max_waves = N / 64 + nlab;
+    p->max_runs = N / run + nlab;
+    return check_launch(ctx, "cell plan");
+}
+
+int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, hipStream_t s)
+{
+    int rc;
+    const double nf = near_radius(ctx->opts.near_factor);
+    p->seg_words = (K + 31) / 32;
+    p->words = p->seg_words + (M + 31) / 32;
+    const int64_t n = (int64_t)(p->grid.nc + 1) * p->words;
+    if ((rc = ensure(ctx, ctx->cellb, (size_t)n * sizeof(uint32_t), s))) return rc;
+    hipLaunchKernelGGL(k_cell_bits, dim3(blocks_for(p->words, 8), p->grid.nc + 1), dim3(256), 0, s, p->grid, (const float*)ctx->seg32.ptr, K,
+                       (const float*)ctx->elem32.ptr, M, (float)(nf * nf), p->seg_words, p->words,
+                       (uint32_t*)ctx->cellb.ptr);
+    p->bits = (const uint32_t*)ctx->cellb.ptr;
+    return check_launch(ctx, "cell bits");
+}
+
+}  // namespace bem

@@ -1,0 +1,107 @@
+// cells.hpp - samples grouped by the cells of a square grid, and the far field of a cell by
+// interpolation (cells.hip).
+//
+// Seen from one cell of the grid, the handle term of every segment that stays kFarCells cell widths
+// away is a smooth function of the sample: it is evaluated at the kFarQ x kFarQ Chebyshev nodes of
+// the cell instead of at the cell's samples, and expanded there in products T_a(xi) T_b(eta) of
+// Chebyshev polynomials.  The nearest singularity in either coordinate lies at least kFarCells cell
+// widths = 4 half widths off the cell, on an ellipse of parameter 4 + sqrt(17) = 8.1, so that eight
+// nodes a side leave a relative error of a few 1e-9 in the field and a few 1e-8 in its derivatives
+// with respect to the end points (measured against float64 sums over cells of 1/16 and 1/32 and
+// segments of 1/100): below the float32 rounding of a pair.
+// The other pairs of the cell, and those the mixed precision evaluates in float64, are evaluated
+// sample by sample.
+#pragma once
+
+#include "common.hpp"
+#include "sweep_common.hpp"
+
+namespace bem {
+
+constexpr int kFarQ = 8;                       // nodes a side: 64 nodes, one wavefront
+constexpr int kFarNodes = kFarQ * kFarQ;
+constexpr double kFarCells = 2.0;              // a segment nearer than this many cell widths is not far
+constexpr int kMaxGrid = 32;                   // cells a side
+constexpr int kMaxCellLabels = kMaxGrid * kMaxGrid + 1;
+
+// Square cells of width h from (x0, y0); label nc = nx ny holds the samples outside the grid (and
+// those that are not finite): no segment is far for them.
+struct CellGrid {
+    double x0, y0, h, inv_h;
+    int nx, ny, nc;
+};
+
+__device__ inline int cell_of(const CellGrid& g, double X, double Y)
+{
+    const double fx = (X - g.x0) * g.inv_h, fy = (Y - g.y0) * g.inv_h;
+    if (!(fx >= 0.0 && fy >= 0.0 && fx <= (double)g.nx && fy <= (double)g.ny)) return g.nc;
+    const int cx = (int)fx < g.nx ? (int)fx : g.nx - 1;
+    const int cy = (int)fy < g.ny ? (int)fy : g.ny - 1;
+    return cy * g.nx + cx;
+}
+__device__ inline void cell_corner(const CellGrid& g, int c, double& X, double& Y)
+{
+    X = g.x0 + (double)(c % g.nx) * g.h;
+    Y = g.y0 + (double)(c / g.nx) * g.h;
+}
+// Chebyshev node i of kFarQ: cos((2 i + 1) pi / (2 kFarQ))
+__device__ inline double cheb_node(int i)
+{
+    constexpr double t[4] = {0.98078528040323044913, 0.83146961230254523708, 0.55557023301960222474,
+                             0.19509032201612826785};
+    return i < 4 ? t[i] : -t[7 - i];
+}
+__device__ inline void cell_node(const CellGrid& g, int c, int node, double& X, double& Y)
+{
+    cell_corner(g, c, X, Y);
+    X += 0.5 * g.h * (1.0 + cheb_node(node & (kFarQ - 1)));
+    Y += 0.5 * g.h * (1.0 + cheb_node(node / kFarQ));
+}
+// T_0 .. T_7 at t
+template <class T>
+__device__ inline void cheb_values(T t, T (&v)[kFarQ])
+{
+    v[0] = T(1);
+    v[1] = t;
+#pragma unroll
+    for (int k = 2; k < kFarQ; ++k) v[k] = T(2) * t * v[k - 1] - v[k - 2];
+}
+
+// The samples of a call in cell order, on the device (workspace of the context, valid until the
+// next plan): sorted sample i is sample perm[i]; cell c holds the sorted samples off[c] ..
+// off[c + 1] - 1 and the wavefronts wave0[c] .. wave0[c + 1] - 1 of 64 of them (the last one
+// short), and likewise the runs run0[c] .. of `run` samples.
+struct CellPlan {
+    CellGrid grid;
+    const int* perm = nullptr;
+    const double* xs = nullptr;
+    const int* off = nullptr;
+    const int* wave0 = nullptr;
+    const int* run0 = nullptr;
+    int run = 64;
+    int64_t max_waves = 0, max_runs = 0;       // bounds known on the host
+    // near bits of the current tables: word w of cell c at bits[c * words + w]; the segments' words
+    // first (bit k % 32 of word k / 32), then the outer elements'
+    const uint32_t* bits = nullptr;
+    int seg_words = 0, words = 0;
+};
+
+// Cells a side for N samples, or 0 where the direct sums are the better choice.
+int cells_for(const bem_ctx* ctx, int64_t N, int K);
+int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s);
+// near bits of the segment and element tables (expanded before) for every cell of the plan
+int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, hipStream_t s);
+
+// label of unit u in a first-unit table t[0 .. nl] (t[nl] = number of units > u)
+__device__ inline int unit_label(const int* __restrict__ t, int nl, int u)
+{
+    int lo = 0, hi = nl;                        // t[lo] <= u < t[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (t[mid] <= u) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+}  // namespace bem

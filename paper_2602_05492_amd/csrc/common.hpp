@@ -102,7 +102,7 @@ struct bem_ctx {
     bem::DevBuf A, Apinv, LU, piv, un, vn, flag, scal, egeo;   // egeo: outer elements [M][4] (a, b)
     // per-call workspaces
     bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearw, nearv, nearf, regw, cholw, sortw,
-        boxw;
+        boxw, cellw, cellb, farw;
     // Gram work list of the normal equations on the device, uploaded once per (W, H, handle
     // model, Gram arithmetic) and kept, so that later calls enqueue without a host synchronisation
     bem::DevBuf tilew;
@@ -150,6 +150,7 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
 // the adjoint and the normal equations take such a list for the same samples
 // and parameters, or classify the samples themselves when given none.
 struct NearList;
+int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar_host, float* u, hipStream_t s);
 int launch_sweep_mixed(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar_host, float* u, hipStream_t s,
                        NearList* out = nullptr);
 int near_classify(bem_ctx* ctx, DevBuf& buf, const double* x, int64_t N, int K, int M, NearList* out, hipStream_t s);
