@@ -82,12 +82,19 @@ typedef enum {
  *        solves and the LM solve are float64 in both modes; the boundary
  *        right-hand side (the handles' field at the elements' Gauss points)
  *        takes the same float32 / float64 split as the sweeps in MIXED.
- *        Near pairs go to a list with a per-context capacity per 64 samples
- *        (1024 at first, at most 16384 and 4 GiB of list); the samples whose
- *        pairs do not fit are evaluated by a slower sweep that handles their
- *        near pairs inline, with the same result to rounding.  lm_step raises
- *        the capacity when its sweeps overflow (a workspace for later calls of
- *        the context too); the other calls keep the capacity reached. */
+ *        With many samples (from 8,192 on, when the grouping pays) bem_eval and
+ *        bem_vjp group them by the cells of a square grid (about 100 bytes a sample
+ *        of context workspace; samples outside the outer boundary's bounding box are
+ *        evaluated against every segment); the segments and outer elements two
+ *        cell widths off a cell, none of whose pairs there is near, are summed at the cell's 64
+ *        Chebyshev nodes and interpolated (relative error below 1e-7).  Float32 pairs of the
+ *        interpolated sums and of the adjoint use Gauss-Legendre quadrature.
+ *        lm_step and bem_jtj list their near pairs with a per-context capacity
+ *        per 64 samples (1024 at first, at most 16384 and 4 GiB of list); the
+ *        samples whose pairs do not fit are evaluated by slower kernels that
+ *        handle their near pairs inline, with the same result to rounding.
+ *        lm_step raises the capacity when its list overflows (a workspace for
+ *        later calls of the context too). */
 typedef enum { BEM_PREC_FP64 = 0, BEM_PREC_MIXED = 1 } bem_prec;
 
 /* Arithmetic of the Gram contraction that forms J^T J and J^T r.
@@ -221,11 +228,6 @@ int bem_eval(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int6
  * the segment adjoints at the boundary Gauss points with cotangent mu.
  * gbar [N,3] row-major (float64 for FP64, float32 for MIXED), grad [H,Q]
  * float64, overwritten.  The mean colour does not depend on theta.
- * MIXED with N >= 65,536 samples: a copy of x and gbar reordered cell by cell
- * (a 32 x 32 grid of Morton-ordered cells over the outer boundary's bounding
- * box; 80 bytes per sample of context workspace) is processed, so that the
- * near pairs of a wavefront form long runs; the result depends on the order
- * only through rounding.
  * Errors: as bem_eval. */
 int bem_vjp(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64_t N,
             const void* gbar, double* grad, bem_prec prec, hipStream_t stream);

@@ -290,8 +290,6 @@ int bem_eval(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int6
     return launch_sweep_eval(ctx, x, N, K, cbar, (float*)u, stream);
 }
 
-constexpr int64_t kVjpCellOrderMin = 65536;     // samples from which MIXED bem_vjp reorders them
-
 int bem_vjp(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64_t N, const void* gbar, double* grad,
             bem_prec prec, hipStream_t stream)
 {
@@ -300,14 +298,6 @@ int bem_vjp(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64
     if (N > 0 && !gbar) return set_error(ctx, BEM_EINVAL, "gbar is null");
     if (H > 0 && !grad) return set_error(ctx, BEM_EINVAL, "grad is null");
     if (prec != BEM_PREC_FP64 && prec != BEM_PREC_MIXED) return set_error(ctx, BEM_EINVAL, "bad precision %d", (int)prec);
-    // MIXED with many samples: visit them cell by cell, so that the near pairs of a wavefront form
-    // long runs of one segment (one set of float64 sums per run instead of one per pair)
-    if (prec == BEM_PREC_MIXED && H > 0 && N >= kVjpCellOrderMin) {
-        const double* xo;
-        const float* go;
-        if ((rc = cell_order_f32(ctx, x, (const float*)gbar, N, &xo, &go, stream))) return rc;
-        return run_vjp(ctx, theta, H, xo, N, go, true, grad, stream);
-    }
     return run_vjp(ctx, theta, H, x, N, gbar, prec == BEM_PREC_MIXED, grad, stream);
 }
 
@@ -484,7 +474,7 @@ void bem_destroy(bem_ctx* ctx)
     DevBuf* bufs[] = {&ctx->A, &ctx->Apinv, &ctx->LU, &ctx->piv, &ctx->un, &ctx->vn, &ctx->flag, &ctx->scal,
                       &ctx->seg64, &ctx->seg32, &ctx->F, &ctx->U, &ctx->elem64, &ctx->elem32, &ctx->red,
                       &ctx->tmp0, &ctx->tmp1, &ctx->tmp2, &ctx->tmp3, &ctx->tmp4, &ctx->tmp5, &ctx->lmw,
-                      &ctx->nearw, &ctx->nearv, &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
+                      &ctx->nearw, &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
                       &ctx->tilew};
     for (DevBuf* b : bufs) release(*b);
     for (hipEvent_t e : ctx->ev)

@@ -52,33 +52,39 @@ __global__ void __launch_bounds__(256) k_cell_scan(int* __restrict__ cnt, int nl
     if (lane == 0) total[d] = run;
 }
 
-// First sample, first wavefront and first run of every label (one block, two labels a thread).
+// First sample, first wavefront and first run of every label (one block, five labels a thread).
 __global__ void __launch_bounds__(1024) k_cell_offsets(const int* __restrict__ total, int nlab, int run,
                                                        int* __restrict__ off, int* __restrict__ wave0,
                                                        int* __restrict__ run0)
 {
+    constexpr int kEach = (kMaxCellLabels + 1 + 1023) / 1024;
     __shared__ int part[3][16];
     const int t = threadIdx.x, w = t >> 6;
-    int v[3][2], s[3];
-    for (int k = 0; k < 2; ++k) {
-        const int d = 2 * t + k;
+    int v[3][kEach], s[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const int d = kEach * t + k;
         const int n = d < nlab ? total[d] : 0;
         v[0][k] = n;
         v[1][k] = (n + 63) / 64;
         v[2][k] = (n + run - 1) / run;
+        for (int q = 0; q < 3; ++q) s[q] += v[q][k];
     }
+    int e[3];
     for (int q = 0; q < 3; ++q) {
-        s[q] = wave_scan(v[q][0] + v[q][1]);
-        if ((t & 63) == 63) part[q][w] = s[q];
+        const int inc = wave_scan(s[q]);
+        if ((t & 63) == 63) part[q][w] = inc;
+        e[q] = inc - s[q];
     }
     __syncthreads();
     int* out[3] = {off, wave0, run0};
     for (int q = 0; q < 3; ++q) {
-        int before = 0;
-        for (int k = 0; k < w; ++k) before += part[q][k];
-        const int e = before + s[q] - v[q][0] - v[q][1];
-        if (2 * t <= nlab) out[q][2 * t] = e;
-        if (2 * t + 1 <= nlab) out[q][2 * t + 1] = e + v[q][0];
+        for (int k = 0; k < w; ++k) e[q] += part[q][k];
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) {
+            if (kEach * t + k <= nlab) out[q][kEach * t + k] = e[q];
+            e[q] += v[q][k];
+        }
     }
 }
 
@@ -100,7 +106,7 @@ __global__ void __launch_bounds__(256) k_cell_scatter(const double* __restrict__
         const int l = live ? cell_of(g, X, Y) : -1;
         uint64_t peers = __ballot(live);
 #pragma unroll
-        for (int b = 0; b < 11; ++b) {          // labels are below 2048
+        for (int b = 0; b < 13; ++b) {          // labels are below 8192
             const bool bit = (l >> b) & 1;
             const uint64_t m = __ballot(bit);
             peers &= bit ? m : ~m;
@@ -163,16 +169,16 @@ __global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, const float* __re
 }  // namespace
 
 // Cells a side.  Direct sums evaluate N (K + M) pairs; a grid of n cells evaluates kFarNodes n (K + M) at
-// its nodes and about (2 kFarCells + 1)^2 / n of the direct ones sample by sample, least at
-// n = (5 / 8) sqrt(N).
-int cells_for(const bem_ctx* ctx, int64_t N, int K)
+// its nodes and about (2 kFarCells + 1)^2 / n of the direct ones sample by sample, in the least time at
+// n = (5 / 8) sqrt(ratio N).
+int cells_for(const bem_ctx* ctx, int64_t N, int K, double ratio)
 {
     const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
     if (!(bw > 0.0) || !(bh > 0.0) || N < 8192 || N > ((int64_t)1 << 30)) return 0;
     const double reach = 2.0 * kFarCells + 1.0;
     // cells are square: the longer side takes g of them
     const double aspect = bw > bh ? bh / bw : bw / bh;
-    double g = std::sqrt(reach / kFarQ * std::sqrt((double)N) / aspect);
+    double g = std::sqrt(reach / kFarQ * std::sqrt(ratio * (double)N) / aspect);
     if (g > kMaxGrid) g = kMaxGrid;
     const int n = (int)g;
     const double cells = (double)n * std::ceil(n * aspect);

@@ -21,7 +21,7 @@ namespace bem {
 constexpr int kFarQ = 8;                       // nodes a side: 64 nodes, one wavefront
 constexpr int kFarNodes = kFarQ * kFarQ;
 constexpr double kFarCells = 2.0;              // a segment nearer than this many cell widths is not far
-constexpr int kMaxGrid = 32;                   // cells a side
+constexpr int kMaxGrid = 64;                   // cells a side
 constexpr int kMaxCellLabels = kMaxGrid * kMaxGrid + 1;
 
 // Square cells of width h from (x0, y0); label nc = nx ny holds the samples outside the grid (and
@@ -86,8 +86,9 @@ struct CellPlan {
     int seg_words = 0, words = 0;
 };
 
-// Cells a side for N samples, or 0 where the direct sums are the better choice.
-int cells_for(const bem_ctx* ctx, int64_t N, int K);
+// Cells a side for N samples, or 0 where the direct sums are the better choice; ratio: time of a near
+// pair over that of a far one.
+int cells_for(const bem_ctx* ctx, int64_t N, int K, double ratio);
 int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s);
 // near bits of the segment and element tables (expanded before) for every cell of the plan
 int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, hipStream_t s);

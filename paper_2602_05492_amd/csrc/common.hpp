@@ -32,13 +32,13 @@ struct DevF64 {
 constexpr double kDegenerateLength = 1e-12;
 
 // ---- layouts ----------------------------------------------------------------
-// Segment record: SegGeom (9 values) + wd_a, wd_b, wc_a, wc_b RGB (12) + 1/L2 = 22, padded.
+// Segment record: SegGeom (9 values) + wd_a, wd_b, wc_a, wc_b RGB (12) + 1/L2 + L + 1/L.
 constexpr int kSegStride = 24;
 // Element record: ax, ay, vx, vy, U0, U1, U2, pad.
 constexpr int kElemStride = 8;
 
-// density offsets inside a segment record, and the slot of 1/L2
-constexpr int kWdA = 9, kWdB = 12, kWcA = 15, kWcB = 18, kIL2 = 21;
+// density offsets inside a segment record, and the slots of 1/L2, L and 1/L (0 for a degenerate segment)
+constexpr int kWdA = 9, kWdB = 12, kWcA = 15, kWcB = 18, kIL2 = 21, kLen = 22, kILen = 23;
 
 template <class T>
 __device__ inline SegGeom<T> load_geom(const T* __restrict__ s)
@@ -101,7 +101,7 @@ struct bem_ctx {
     // one-time boundary system
     bem::DevBuf A, Apinv, LU, piv, un, vn, flag, scal, egeo;   // egeo: outer elements [M][4] (a, b)
     // per-call workspaces
-    bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearw, nearv, nearf, regw, cholw, sortw,
+    bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearw, nearf, regw, cholw, sortw,
         boxw, cellw, cellb, farw;
     // Gram work list of the normal equations on the device, uploaded once per (W, H, handle
     // model, Gram arithmetic) and kept, so that later calls enqueue without a host synchronisation
@@ -160,9 +160,6 @@ int near_boxes(bem_ctx* ctx, int K, int M, const float4** box, hipStream_t s);
 // partition.hip (off_host may be null: no readback and no host synchronisation)
 int run_partition(bem_ctx* ctx, const int32_t* labels, int64_t N, int D, const double* x, const double* T, double* xo,
                   double* To, int64_t* off_host, hipStream_t s);
-// lm.hip: samples and float32 cotangents reordered cell by cell into the sort workspace
-int cell_order_f32(bem_ctx* ctx, const double* x, const float* g, int64_t N, const double** xo, const float** go,
-                   hipStream_t s);
 // reg.hip
 bool reg_active(const bem_ctx* ctx);
 int check_reg(const bem_reg& r, char* why, size_t n);
@@ -177,7 +174,7 @@ struct Carve {
     size_t bytes;
 };
 int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, const void* gbar, bool mixed,
-            double* grad, hipStream_t s, const NearList* pre = nullptr, const Carve* carve = nullptr);
+            double* grad, hipStream_t s, const Carve* carve = nullptr);
 // api.hip: expand + element tables (no boundary solve); and the whole forward set-up
 // (expand, boundary right-hand side (float32 far pairs when mixed), boundary solve, element tables)
 int prepare_forward_tables(bem_ctx* ctx, const double* theta, int H, hipStream_t s);
@@ -220,6 +217,7 @@ namespace bem {
 struct DevF32 {
     // v_log_f32 (log2, ~1 ulp) times ln 2; arguments here are normal numbers (>= eps^2 or near 1)
     __device__ static float log(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945309f; }
+    __device__ static float log2(float x) { return __builtin_amdgcn_logf(x); }
     __device__ static float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
     __device__ static float rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
     __device__ static float sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }

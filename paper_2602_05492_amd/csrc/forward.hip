@@ -55,7 +55,8 @@ __global__ void k_expand(const double* __restrict__ theta, int H, int S, int mod
         }
     }
     rec[kIL2] = live ? 1.0 / L2 : 0.0;
-    rec[22] = rec[23] = 0.0;
+    rec[kLen] = sqrt(L2);
+    rec[kILen] = live ? 1.0 / rec[kLen] : 0.0;
     double* o = seg64 + (size_t)k * kSegStride;
     float* o32 = seg32 + (size_t)k * kSegStride;
     for (int c = 0; c < kSegStride; ++c) { o[c] = rec[c]; o32[c] = (float)rec[c]; }

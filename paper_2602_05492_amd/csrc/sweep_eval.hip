@@ -21,6 +21,8 @@ namespace bem {
 
 namespace {
 
+// time of a near pair over that of a far one
+constexpr double kEvalRatio = 2.0;
 constexpr int kListCap = 320;                        // near pairs a wavefront holds
 constexpr int kListFull = kListCap - 64;
 constexpr int kIndexBits = 26;                       // K + M < 2^26 (check_common, build_context)
@@ -85,6 +87,17 @@ __device__ inline void add_segment(const float* __restrict__ s, const SegGeom<fl
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         f[c] += on * (m.da * s[kWdA + c] + m.db * s[kWdB + c] + m.sa * s[kWcA + c] + m.sb * s[kWcB + c]);
+}
+
+// The same for a segment at least four of its lengths away (NQ = 4), or outside the near radius of a near
+// factor of at least 1 (NQ = 6), by quadrature.
+template <int NQ>
+__device__ inline void add_segment_quad(const float* __restrict__ s, float X, float Y, float eps2f, float (&f)[3])
+{
+    const Moments<float> m = quad_moments(quad_sums<float, DevF32, NQ, false>(load_geom(s), X, Y, eps2f), s[kLen]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        f[c] += m.da * s[kWdA + c] + m.db * s[kWdB + c] + m.sa * s[kWcA + c] + m.sb * s[kWcB + c];
 }
 
 constexpr int kStage = 128;                          // segment records staged at a time (12 KiB)
@@ -175,6 +188,13 @@ __global__ void __launch_bounds__(256) k_far_nodes(CellGrid g, const int* __rest
     const uint32_t* row = bits + (size_t)(used ? c : 0) * words;
     const int g0 = blockIdx.y * gpc, g1 = g0 + gpc;
     const int k0 = g0 * 32, k1 = g1 < seg_words ? g1 * 32 : t.K;
+    const float short_len = (float)(kFarCells * g.h / kQuadFar);
+    const bool outside = t.near2 >= 4.0f;
+    auto add_far = [&](const float* s, float (&f)[3]) {
+        if (s[kLen] <= short_len) add_segment_quad<4>(s, X, Y, t.eps2f, f);
+        else if (outside) add_segment_quad<6>(s, X, Y, t.eps2f, f);
+        else add_segment(s, load_geom(s), X, Y, t.eps2f, false, f);
+    };
     double d[3] = {0.0, 0.0, 0.0};
     for (int s0 = k0; s0 < k1; s0 += kStage) {
         const int n = k1 - s0 < kStage ? k1 - s0 : kStage;
@@ -188,17 +208,13 @@ __global__ void __launch_bounds__(256) k_far_nodes(CellGrid g, const int* __rest
             uint32_t far = ~row[(s0 + q) >> 5];
             float f[3] = {0.f, 0.f, 0.f};
             if (far == 0xFFFFFFFFu) {
-                for (int k = q; k < q + m; ++k) {
-                    const float* s = reinterpret_cast<const float*>(stage + k * (kSegStride / 4));
-                    add_segment(s, load_geom(s), X, Y, t.eps2f, false, f);
-                }
+                for (int k = q; k < q + m; ++k) add_far(reinterpret_cast<const float*>(stage + k * (kSegStride / 4)), f);
             } else {
                 if (m < 32) far &= (1u << m) - 1u;
                 while (far) {
                     const int k = q + __builtin_ctz(far);
                     far &= far - 1u;
-                    const float* s = reinterpret_cast<const float*>(stage + k * (kSegStride / 4));
-                    add_segment(s, load_geom(s), X, Y, t.eps2f, false, f);
+                    add_far(reinterpret_cast<const float*>(stage + k * (kSegStride / 4)), f);
                 }
             }
             for (int q3 = 0; q3 < 3; ++q3) d[q3] += (double)f[q3];
@@ -356,7 +372,7 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     const Tables t{(const float*)ctx->seg32.ptr, (const double*)ctx->seg64.ptr, (const float*)ctx->elem32.ptr,
                    (const double*)ctx->elem64.ptr, K, M, (float)eps2, (float)(nf * nf), eps2};
     const int64_t groups = (K + 31) / 32 + (M + 31) / 32;
-    const int g = cells_for(ctx, N, K);
+    const int g = cells_for(ctx, N, K, kEvalRatio);
     ProfScope ps_(ctx, PT_SWEEP_MIXED, s);
     if (g == 0) {
         const int64_t nb = blocks_for(N, 256);
