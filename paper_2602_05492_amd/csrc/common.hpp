@@ -180,10 +180,13 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
 int prepare_forward_tables(bem_ctx* ctx, const double* theta, int H, hipStream_t s);
 int prepare_forward(bem_ctx* ctx, const double* theta, int H, bool mixed, hipStream_t s);
 // gemm.hip
-// plain products and the float64 Gram on float64 MFMA; valu selects the VALU kernel (Gram mode FP64_VALU)
+// plain products on float64 MFMA; with a list of 64 x 64 output tiles on the VALU (Gram mode FP64_VALU)
 int gemm_f64(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
-             int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* tiles, int ntiles,
-             bool valu = false);
+             int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* tiles, int ntiles);
+// the float64 Gram on float64 MFMA: work entries (row tile, column tile, part) of 128 x 128 output tiles
+int gemm_f64_list(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
+                  int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* work, int nwork,
+                  int kchunk, int64_t cstride);
 // jtj.hip
 int fill_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s);
 int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, const void* resid, bool mixed,

@@ -23,14 +23,7 @@ __global__ void __launch_bounds__(256) k_gemm_f64(int m, int n, int k, double al
 {
     __shared__ double As[TK][TM + 1];
     __shared__ double Bs[TK][TN + 1];
-    int bm, bn;
-    if (tiles) {
-        bm = tiles[2 * blockIdx.x];
-        bn = tiles[2 * blockIdx.x + 1];
-    } else {
-        bm = blockIdx.y;
-        bn = blockIdx.x;
-    }
+    const int bm = tiles[2 * blockIdx.x], bn = tiles[2 * blockIdx.x + 1];
     const int row0 = bm * TM, col0 = bn * TN;
     const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
     double acc[4][4];
@@ -89,44 +82,62 @@ __global__ void __launch_bounds__(256) k_gemm_f64(int m, int n, int k, double al
 typedef double d4_t __attribute__((ext_vector_type(4)));
 constexpr int kMB = 128, kMK = 16;
 
-// element e of a BM x kMK slab of op(X) starting at (r0, k0): its slab coordinates and value
-// (0 outside the m x k operand).  Non-transposed X is row-major [row][k] (16 consecutive
-// threads read one row's 16 k values); transposed X is stored [k][row].
+// element e of a BM x kMK slab of op(X) starting at (r0, k0): its slab coordinates, and whether it lies
+// in the rows x kd operand.  Non-transposed X is row-major [row][k] (16 consecutive threads read one
+// row's 16 k values); transposed X is stored [k][row].
 template <int BM>
-__device__ inline double slab_load(const double* __restrict__ X, int64_t ldx, int tx, int r0, int k0, int rows, int kd,
-                                   int e, int& sr, int& sk)
+__device__ inline bool slab_at(int tx, int r0, int k0, int rows, int kd, int e, int& sr, int& sk)
 {
     if (tx) { sk = e / BM; sr = e % BM; }
     else { sr = e / kMK; sk = e % kMK; }
-    const int gr = r0 + sr, gk = k0 + sk;
-    const bool in = gr < rows && gk < kd;
-    const int64_t off = tx ? (int64_t)(in ? gk : 0) * ldx + (in ? gr : 0) : (int64_t)(in ? gr : 0) * ldx + (in ? gk : 0);
-    const double v = X[off];                       // always a valid address; replaced when outside
-    return in ? v : 0.0;
+    return r0 + sr < rows && k0 + sk < kd;
+}
+// The element there, or element (0, 0) of X outside the operand (replaced by 0 where the slab is stored:
+// a select beside the load would wait for it, and the loads are to stay in flight behind the products).
+template <int BM>
+__device__ inline double slab_load(const double* __restrict__ X, int64_t ldx, int tx, int r0, int k0, int rows, int kd,
+                                   int e)
+{
+    int sr, sk;
+    const bool in = slab_at<BM>(tx, r0, k0, rows, kd, e, sr, sk);
+    const int gr = in ? r0 + sr : 0, gk = in ? k0 + sk : 0;
+    return X[tx ? (int64_t)gk * ldx + gr : (int64_t)gr * ldx + gk];
 }
 
 // BM x BM output tile per block (BM = 128: each wavefront 64 x 64 as 4 x 4 MFMA tiles; BM = 64:
 // 32 x 32 as 2 x 2, for products whose 128-tile grid would leave most CUs idle).
+//
+// Blocks go to the 8 XCDs round-robin, each XCD with an L2 of its own, so XCD x is given a contiguous run
+// of the tiles: of the work list (row tile, column tile, part: k range [part kchunk, (part + 1) kchunk),
+// result at C + part cstride), or of the whole grid in bands of 8 tile columns.
 template <int BM>
-__global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m, int n, int k, double alpha,
+__global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m, int n, int k_all, double alpha,
                                                                         const double* __restrict__ A, int64_t lda, int ta,
                                                                         const double* __restrict__ B, int64_t ldb, int tb,
                                                                         double beta, double* __restrict__ C, int64_t ldc,
-                                                                        const int* __restrict__ tiles)
+                                                                        const int* __restrict__ work, int nwork,
+                                                                        int kchunk, int64_t cstride)
 {
     constexpr int LD = BM + 4;                  // LDS row stride (doubles)
     constexpr int NL = BM * kMK / 256;          // slab elements per thread and operand
     constexpr int TI = BM / 32;                 // 16 x 16 MFMA tiles per wavefront and dimension
     __shared__ double As[2][kMK][LD];
     __shared__ double Bs[2][kMK][LD];
-    int bm, bn;
-    if (tiles) {
-        bm = tiles[2 * blockIdx.x];
-        bn = tiles[2 * blockIdx.x + 1];
+    const int wi = (int)(blockIdx.x & 7) * ((nwork + 7) >> 3) + (int)(blockIdx.x >> 3);
+    if (wi >= nwork) return;
+    int bm, bn, k0 = 0;
+    if (work) {
+        bm = work[3 * wi];
+        bn = work[3 * wi + 1];
+        k0 = work[3 * wi + 2] * kchunk;
+        C += (int64_t)work[3 * wi + 2] * cstride;
     } else {
-        bm = blockIdx.y;
-        bn = blockIdx.x;
+        const int nbm = (m + BM - 1) / BM, band = wi / (8 * nbm), r = wi % (8 * nbm);
+        bm = r >> 3;
+        bn = band * 8 + (r & 7);
+        if (bn * BM >= n) return;
     }
+    const int k = k0 + kchunk < k_all ? k0 + kchunk : k_all;      // this block's k range [k0, k)
     const int row0 = bm * BM, col0 = bn * BM;
     const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
     const int wr = w >> 1, wc = w & 1;
@@ -134,34 +145,37 @@ __global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m,
     // the "row" index as the column of op(B), so its transposition flag is the opposite one
     const int tbB = tb ? 0 : 1;
     double pa[NL], pb[NL];
-    int ar[NL], ak[NL], br[NL], bk[NL];
+    auto load = [&](int ks) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        pa[i] = slab_load<BM>(A, lda, ta, row0, 0, m, k, tid + 256 * i, ar[i], ak[i]);
-        pb[i] = slab_load<BM>(B, ldb, tbB, col0, 0, n, k, tid + 256 * i, br[i], bk[i]);
-    }
+        for (int i = 0; i < NL; ++i) {
+            pa[i] = slab_load<BM>(A, lda, ta, row0, ks, m, k, tid + 256 * i);
+            pb[i] = slab_load<BM>(B, ldb, tbB, col0, ks, n, k, tid + 256 * i);
+        }
+    };
+    auto store = [&](int buf, int ks) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        As[0][ak[i]][ar[i]] = pa[i];
-        Bs[0][bk[i]][br[i]] = pb[i];
-    }
+        for (int i = 0; i < NL; ++i) {
+            int r, kk;
+            const bool ia = slab_at<BM>(ta, row0, ks, m, k, tid + 256 * i, r, kk);
+            As[buf][kk][r] = ia ? pa[i] : 0.0;
+            const bool ib = slab_at<BM>(tbB, col0, ks, n, k, tid + 256 * i, r, kk);
+            Bs[buf][kk][r] = ib ? pb[i] : 0.0;
+        }
+    };
+    load(k0);
+    store(0, k0);
     __syncthreads();
     d4_t acc[TI][TI];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TI; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
-    const int nk = (k + kMK - 1) / kMK;
+    const int nk = k > k0 ? (k - k0 + kMK - 1) / kMK : 0;
     for (int s = 0; s < nk; ++s) {
         const int cur = s & 1;
         const bool more = s + 1 < nk;
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                pa[i] = slab_load<BM>(A, lda, ta, row0, (s + 1) * kMK, m, k, tid + 256 * i, ar[i], ak[i]);
-                pb[i] = slab_load<BM>(B, ldb, tbB, col0, (s + 1) * kMK, n, k, tid + 256 * i, br[i], bk[i]);
-            }
-        }
+        if (more) load(k0 + (s + 1) * kMK);
+        __builtin_amdgcn_sched_barrier(0);        // the loads go out before the products, and are waited for after
 #pragma unroll
         for (int ks = 0; ks < kMK; ks += 4) {
             const int kk = ks + (l >> 4), rr = l & 15;
@@ -175,13 +189,8 @@ __global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m,
 #pragma unroll
                 for (int j = 0; j < TI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
         }
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                As[cur ^ 1][ak[i]][ar[i]] = pa[i];
-                Bs[cur ^ 1][bk[i]][br[i]] = pb[i];
-            }
-        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) store(cur ^ 1, k0 + (s + 1) * kMK);
         __syncthreads();
     }
 #pragma unroll
@@ -232,34 +241,41 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(int m, int n, int k, double
 
 }  // namespace
 
+// C + part cstride = alpha op(A) op(B) + beta C over the k range of each part, on the 128 x 128 output
+// tiles of a work list (row tile, column tile, part).
+int gemm_f64_list(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
+                  int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* work, int nwork,
+                  int kchunk, int64_t cstride)
+{
+    if (nwork <= 0) return BEM_OK;
+    hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(8 * ((nwork + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
+                       ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, work, nwork, kchunk, cstride);
+    return check_launch(ctx, "gemm_f64");
+}
+
 int gemm_f64(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
-             int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* tiles, int ntiles,
-             bool valu)
+             int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* tiles, int ntiles)
 {
     if (m <= 0 || n <= 0) return BEM_OK;
-    if (tiles) {
+    if (tiles) {                      // a list of 64 x 64 output tiles, on the vector ALUs
         if (ntiles <= 0) return BEM_OK;
-        if (valu)
-            hipLaunchKernelGGL(k_gemm_f64, dim3(ntiles), dim3(256), 0, s, m, n, k, alpha, A, lda, ta ? 1 : 0, B, ldb,
-                               tb ? 1 : 0, beta, C, ldc, tiles);
-        else
-            hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(ntiles), dim3(256), 0, s, m, n, k, alpha, A, lda, ta ? 1 : 0,
-                               B, ldb, tb ? 1 : 0, beta, C, ldc, tiles);
+        hipLaunchKernelGGL(k_gemm_f64, dim3(ntiles), dim3(256), 0, s, m, n, k, alpha, A, lda, ta ? 1 : 0, B, ldb,
+                           tb ? 1 : 0, beta, C, ldc, tiles);
         return check_launch(ctx, "gemm_f64");
     }
-    if (valu) {
-        hipLaunchKernelGGL(k_gemm_f64, dim3(blocks_for(n, TN), blocks_for(m, TM)), dim3(256), 0, s, m, n, k, alpha, A,
-                           lda, ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr);
-    } else if (n <= kSkinnyMaxN && !ta) {
+    const auto count = [&](int bm) { return 8 * blocks_for(blocks_for(n, bm), 8) * blocks_for(m, bm); };
+    if (n <= kSkinnyMaxN && !ta) {
         hipLaunchKernelGGL(k_gemm_skinny, dim3(blocks_for(m, 4)), dim3(256), 0, s, m, n, k, alpha, A, lda, B, ldb,
                            tb ? 1 : 0, beta, C, ldc);
     } else if ((int64_t)blocks_for(n, kMB) * blocks_for(m, kMB) >= 1024) {
-        hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(blocks_for(n, kMB), blocks_for(m, kMB)), dim3(256), 0, s, m, n, k,
-                           alpha, A, lda, ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr);
+        const int nw = count(kMB);
+        hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(8 * ((nw + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
+                           ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr, nw, k, (int64_t)0);
     } else {
         // fewer than two rounds of 128-tiles over the CUs: 64-tiles, 4x the blocks
-        hipLaunchKernelGGL(k_gemm_f64_mfma<64>, dim3(blocks_for(n, 64), blocks_for(m, 64)), dim3(256), 0, s, m, n, k,
-                           alpha, A, lda, ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr);
+        const int nw = count(64);
+        hipLaunchKernelGGL(k_gemm_f64_mfma<64>, dim3(8 * ((nw + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
+                           ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr, nw, k, (int64_t)0);
     }
     return check_launch(ctx, "gemm_f64");
 }

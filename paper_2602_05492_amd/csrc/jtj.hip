@@ -954,6 +954,9 @@ constexpr int64_t kGeoAlign = 256;   // the split-BF16 Gram's tile
 static Layout layout_of(const bem_ctx* ctx, int H)
 {
     const int64_t gh = (int64_t)ctx->ngeo * H;
+    // few handles: without the padding a tile mixes channels, but the padded rows would be most of the
+    // Gram (4 cubic handles: 1,808 rows of which 672 are padding)
+    if (gh < kGeoAlign) return Layout{ctx->ngeo, ctx->ncol, H, gh};
     return Layout{ctx->ngeo, ctx->ncol, H, (gh + kGeoAlign - 1) / kGeoAlign * kGeoAlign};
 }
 
@@ -1126,6 +1129,17 @@ static std::vector<int> gram_work(const std::vector<int>& tiles, int parts)
     return w;
 }
 
+// Sample parts of the float64 Gram: two 128 x 128 tiles run on a CU at a time, so that 90 tiles (32 cubic
+// handles) kept 90 of 256 CUs half busy; the parts make about two rounds of 512 blocks (at most 2 GiB of
+// partial Grams).
+static int f64_parts(int ntiles, int64_t W)
+{
+    int64_t p = ntiles > 0 ? 1024 / ntiles : 1;
+    const int64_t most = ((int64_t)2 << 30) / (W * W * 8);
+    if (p > most) p = most;
+    return (int)(p < 1 ? 1 : (p > 16 ? 16 : p));
+}
+
 namespace {
 // G[0] += G[1] + ... + G[parts - 1] (fixed order) over the ts x ts output tile of work entry
 // blockIdx.x, rows split over gridDim.y blocks (blockDim.x = ts, a thread per column)
@@ -1171,7 +1185,7 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     // float64 Gram on MFMA (BEM_GRAM_FP64) or on the VALU (BEM_GRAM_FP64_VALU): float64 tiles
     const bool f64 = gram == BEM_GRAM_FP64 || gram == BEM_GRAM_FP64_VALU;
     int64_t T = ctx->opts.tile_rows > 0 ? ctx->opts.tile_rows
-                                        : (gram == BEM_GRAM_FP32_MFMA ? 8192 : (f64 ? 16384 : 32768));
+                                        : (gram == BEM_GRAM_FP32_MFMA ? 8192 : 32768);
     const size_t elem = f64 ? 8 : 4;
     while (T > 1024 && (size_t)W * T * elem > ((size_t)3 << 30)) T /= 2;
     if (T > N) T = N > 0 ? N : 1;
@@ -1212,7 +1226,10 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     // split-BF16 Gram: the sample tile is split into 3 parts with partial Grams of their own,
     // so that a launch has 3x the blocks (fewer idle CUs in its last round) and stays
     // deterministic (no atomics)
-    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? 3 : 1;
+    const int ts = gram == BEM_GRAM_FP64_VALU ? 64 : (gram == BEM_GRAM_BF16X3_MFMA ? 256 : 128);
+    const std::vector<int> out_tiles = gram_tiles(L, (int)W, ts);
+    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? 3
+                      : gram == BEM_GRAM_FP64 ? f64_parts((int)out_tiles.size() / 2, W) : 1;
     const int64_t kchunk = ((T + parts - 1) / parts + 31) / 32 * 32;
     const bool overlap = shares && N > T;
     const size_t tile_bytes = ((size_t)W * T * elem + 255) / 256 * 256;
@@ -1239,9 +1256,9 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         else
             hipLaunchKernelGGL(k_to_f64<double>, dim3(blocks_for(3 * N, 256)), dim3(256), 0, s, (const double*)resid, 3 * N, r64);
     }
-    const int ts = gram == BEM_GRAM_FP64_VALU ? 64 : (gram == BEM_GRAM_BF16X3_MFMA ? 256 : 128);
-    const std::vector<int> tiles = f64 ? gram_tiles(L, (int)W, ts) : gram_work(gram_tiles(L, (int)W, ts), parts);
-    const int ntiles = f64 ? (int)tiles.size() / 2 : (int)tiles.size() / 3;
+    const bool valu = gram == BEM_GRAM_FP64_VALU;
+    const std::vector<int> tiles = valu ? out_tiles : gram_work(out_tiles, parts);
+    const int ntiles = (int)tiles.size() / (valu ? 2 : 3);
     // the work list lives on the device (tilew); it is uploaded when its configuration changes, the
     // only host synchronisation of this call apart from workspace growth
     const int64_t key[4] = {W, H, ctx->model, gram};
@@ -1306,8 +1323,12 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
                 return rc;
             {
                 ProfScope ps_(ctx, PT_GRAM_F64, s);
-                rc = gemm_f64(ctx, (int)W, (int)W, (int)n, 1.0, Xt, T, false, Xt, T, true, it > 0 ? 1.0 : 0.0, G, W, s,
-                              dtiles, ntiles, gram == BEM_GRAM_FP64_VALU);
+                if (gram == BEM_GRAM_FP64_VALU)
+                    rc = gemm_f64(ctx, (int)W, (int)W, (int)n, 1.0, Xt, T, false, Xt, T, true, it > 0 ? 1.0 : 0.0, G, W, s,
+                                  dtiles, ntiles);
+                else
+                    rc = gemm_f64_list(ctx, (int)W, (int)W, (int)n, 1.0, Xt, T, false, Xt, T, true, it > 0 ? 1.0 : 0.0, G,
+                                       W, s, dtiles, ntiles, (int)kchunk, W * W);
             }
             if (rc) return rc;
             if (want_r &&
