@@ -10,18 +10,18 @@
 #include <vector>
 
 #include "../../include/bem.h"
+#include "math64.hpp"
 #include "seg_math.hpp"
 
 namespace bem {
 
 // ---- device math policies ---------------------------------------------------
 struct DevF64 {
-    __device__ static double log(double x) { return ::log(x); }
-    __device__ static double log1p(double x) { return ::log1p(x); }
-    __device__ static double sqrt(double x) { return ::sqrt(x); }
-    __device__ static double rcp(double x) { return 1.0 / x; }
-    __device__ static double rsqrt(double x) { return 1.0 / ::sqrt(x); }
-    __device__ static double atan2(double y, double x) { return ::atan2(y, x); }
+    __device__ static double log(double x) { return log_f64(x); }
+    __device__ static double rcp(double x) { return rcp_f64(x); }
+    __device__ static double rsqrt(double x) { return rsqrt_f64(x); }
+    __device__ static double atan2(double y, double x) { return atan2_f64(y, x); }
+    __device__ static double log_ratio(double R0, double R1, double dR) { return log_ratio_f64(R0, R1, dR); }
 };
 
 // Segments no longer than this (domain-width units) are degenerate: their

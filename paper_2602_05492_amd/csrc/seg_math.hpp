@@ -67,6 +67,19 @@ struct SegGeom {
 constexpr double kPi = 3.141592653589793238462643383279502884;
 constexpr double kInv2Pi = 0.159154943091895335768883763372514362;
 
+// log(R1/R0) from the difference dR = R1 - R0: the policy's own log_ratio where it has one, else
+// log1p(dR/R0).
+template <class M, class T>
+BEM_HD inline auto log_ratio(T R0, T R1, T dR, int) -> decltype(M::log_ratio(R0, R1, dR))
+{
+    return M::log_ratio(R0, R1, dR);
+}
+template <class M, class T>
+BEM_HD inline T log_ratio(T R0, T, T dR, long)
+{
+    return M::log1p(dR * M::rcp(R0));
+}
+
 // l0 = log R0 and ell = log(R1/R0) = log1p(dR/R0), with the limits of the
 // end-point cases R0 = 0 or R1 = 0 (eps = 0 and x on an end point) when Guard.
 template <class T, class M, bool Guard>
@@ -74,11 +87,11 @@ BEM_HD inline void log_pair(T R0, T R1, T dR, T& l0, T& ell)
 {
     if (!Guard) {
         l0 = M::log(R0);
-        ell = M::log1p(dR * M::rcp(R0));
+        ell = log_ratio<M>(R0, R1, dR, 0);
         return;
     }
     l0 = R0 > T(0) ? M::log(R0) : T(0);
-    if (R0 > T(0) && R1 > T(0)) ell = M::log1p(dR * M::rcp(R0));
+    if (R0 > T(0) && R1 > T(0)) ell = log_ratio<M>(R0, R1, dR, 0);
     else if (R0 > T(0)) ell = -l0;
     else ell = R1 > T(0) ? M::log(R1) : T(0);
 }
