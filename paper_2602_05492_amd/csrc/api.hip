@@ -146,15 +146,6 @@ int check_common(bem_ctx* ctx, const double* theta, int32_t H, const double* x, 
     return BEM_OK;
 }
 
-// expand + element geometry tables (the element values are not used by callers of this one).
-int prepare_forward_tables(bem_ctx* ctx, const double* theta, int32_t H, hipStream_t s)
-{
-    int rc;
-    if ((rc = ensure(ctx, ctx->U, (size_t)ctx->M * 3 * sizeof(double), s))) return rc;
-    if ((rc = launch_expand(ctx, theta, H, s))) return rc;
-    return launch_pack_elements(ctx, (const double*)ctx->U.ptr, s);
-}
-
 // expand -> F -> U -> element table.  Leaves F in ctx->F and U in ctx->U.
 int prepare_forward(bem_ctx* ctx, const double* theta, int32_t H, bool mixed, hipStream_t s)
 {
@@ -164,8 +155,7 @@ int prepare_forward(bem_ctx* ctx, const double* theta, int32_t H, bool mixed, hi
     if ((rc = ensure(ctx, ctx->U, (size_t)ctx->M * 3 * sizeof(double), s))) return rc;
     if ((rc = launch_expand(ctx, theta, H, s))) return rc;
     if ((rc = launch_boundary_rhs(ctx, K, (double*)ctx->F.ptr, mixed, s))) return rc;
-    if ((rc = launch_boundary_solve(ctx, (const double*)ctx->F.ptr, (double*)ctx->U.ptr, false, s))) return rc;
-    return launch_pack_elements(ctx, (const double*)ctx->U.ptr, s);
+    return launch_boundary_solve(ctx, (const double*)ctx->F.ptr, (double*)ctx->U.ptr, s);
 }
 
 }  // namespace bem

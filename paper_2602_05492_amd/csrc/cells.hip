@@ -168,23 +168,22 @@ __global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, const float* __re
 
 }  // namespace
 
-// Cells a side.  Direct sums evaluate N (K + M) pairs; a grid of n cells evaluates kFarNodes n (K + M) at
-// its nodes and about (2 kFarCells + 1)^2 / n of the direct ones sample by sample, in the least time at
-// n = (5 / 8) sqrt(ratio N).
-int cells_for(const bem_ctx* ctx, int64_t N, int K, double ratio)
+// Cells a side.  Direct sums evaluate N (K + M) pairs; a grid of n cells evaluates q^2 n (K + M) at its
+// nodes and about (2 kFarCells + 1)^2 / n of the direct ones sample by sample, in the least time at
+// n = (5 / q) sqrt(ratio N).
+int cells_for(const bem_ctx* ctx, int64_t N, int K, int q, double ratio, double worth)
 {
     const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
     if (!(bw > 0.0) || !(bh > 0.0) || N < 8192 || N > ((int64_t)1 << 30)) return 0;
     const double reach = 2.0 * kFarCells + 1.0;
     // cells are square: the longer side takes g of them
     const double aspect = bw > bh ? bh / bw : bw / bh;
-    double g = std::sqrt(reach / kFarQ * std::sqrt(ratio * (double)N) / aspect);
+    double g = std::sqrt(reach / q * std::sqrt(ratio * (double)N) / aspect);
     if (g > kMaxGrid) g = kMaxGrid;
     const int n = (int)g;
     const double cells = (double)n * std::ceil(n * aspect);
-    const double share = kFarNodes * cells / (double)N + reach * reach / cells;
-    // the plan, the bits and the node sums cost about as much as 2e7 pairs
-    return n >= 2 && (1.0 - share) * (double)N * ((double)K + 0.4 * ctx->M) > 2e7 ? n : 0;
+    const double share = q * q * cells / (double)N + reach * reach / cells;
+    return n >= 2 && (1.0 - share) * (double)N * ((double)K + 0.4 * ctx->M) > worth ? n : 0;
 }
 
 int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s)
@@ -239,10 +238,10 @@ int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipS
     return check_launch(ctx, "cell plan");
 }
 
-int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, hipStream_t s)
+int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, bool mixed, hipStream_t s)
 {
     int rc;
-    const double nf = near_radius(ctx->opts.near_factor);
+    const double nf = mixed ? near_radius(ctx->opts.near_factor) : 0.0;
     p->seg_words = (K + 31) / 32;
     p->words = p->seg_words + (M + 31) / 32;
     const int64_t n = (int64_t)(p->grid.nc + 1) * p->words;

@@ -20,6 +20,10 @@ namespace bem {
 
 constexpr int kFarQ = 8;                       // nodes a side: 64 nodes, one wavefront
 constexpr int kFarNodes = kFarQ * kFarQ;
+// The float64 sweep takes the same far set with 16 nodes a side: 8.1^-16 = 3e-15 of a segment's part,
+// 1e-14 and less against direct sums (their own rounding).
+constexpr int kFarQ64 = 16;
+constexpr int kFarNodes64 = kFarQ64 * kFarQ64;
 constexpr double kFarCells = 2.0;              // a segment nearer than this many cell widths is not far
 constexpr int kMaxGrid = 64;                   // cells a side
 constexpr int kMaxCellLabels = kMaxGrid * kMaxGrid + 1;
@@ -44,27 +48,36 @@ __device__ inline void cell_corner(const CellGrid& g, int c, double& X, double& 
     X = g.x0 + (double)(c % g.nx) * g.h;
     Y = g.y0 + (double)(c / g.nx) * g.h;
 }
-// Chebyshev node i of kFarQ: cos((2 i + 1) pi / (2 kFarQ))
-__device__ inline double cheb_node(int i)
+// Chebyshev node i of Q: cos((2 i + 1) pi / (2 Q))
+template <int Q> __device__ inline double cheb_node(int i);
+template <> __device__ inline double cheb_node<8>(int i)
 {
     constexpr double t[4] = {0.98078528040323044913, 0.83146961230254523708, 0.55557023301960222474,
                              0.19509032201612826785};
     return i < 4 ? t[i] : -t[7 - i];
 }
+template <> __device__ inline double cheb_node<16>(int i)
+{
+    constexpr double t[8] = {0.99518472667219688624, 0.95694033573220886494, 0.88192126434835502971,
+                             0.77301045336273696081, 0.63439328416364549822, 0.47139673682599764856,
+                             0.29028467725446236764, 0.098017140329560601994};
+    return i < 8 ? t[i] : -t[15 - i];
+}
+template <int Q>
 __device__ inline void cell_node(const CellGrid& g, int c, int node, double& X, double& Y)
 {
     cell_corner(g, c, X, Y);
-    X += 0.5 * g.h * (1.0 + cheb_node(node & (kFarQ - 1)));
-    Y += 0.5 * g.h * (1.0 + cheb_node(node / kFarQ));
+    X += 0.5 * g.h * (1.0 + cheb_node<Q>(node & (Q - 1)));
+    Y += 0.5 * g.h * (1.0 + cheb_node<Q>(node / Q));
 }
-// T_0 .. T_7 at t
-template <class T>
-__device__ inline void cheb_values(T t, T (&v)[kFarQ])
+// T_0 .. T_{Q-1} at t
+template <class T, int Q>
+__device__ inline void cheb_values(T t, T (&v)[Q])
 {
     v[0] = T(1);
     v[1] = t;
 #pragma unroll
-    for (int k = 2; k < kFarQ; ++k) v[k] = T(2) * t * v[k - 1] - v[k - 2];
+    for (int k = 2; k < Q; ++k) v[k] = T(2) * t * v[k - 1] - v[k - 2];
 }
 
 // The samples of a call in cell order, on the device (workspace of the context, valid until the
@@ -86,12 +99,21 @@ struct CellPlan {
     int seg_words = 0, words = 0;
 };
 
-// Cells a side for N samples, or 0 where the direct sums are the better choice; ratio: time of a near
-// pair over that of a far one.
-int cells_for(const bem_ctx* ctx, int64_t N, int K, double ratio);
+// Cells a side for N samples with q nodes a side, or 0 where the direct sums are the better choice; ratio:
+// time of a near pair over that of a far one; worth: pairs that take as long as the plan, the bits and
+// the node sums' launches.
+int cells_for(const bem_ctx* ctx, int64_t N, int K, int q, double ratio, double worth);
 int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s);
-// near bits of the segment and element tables (expanded before) for every cell of the plan
-int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, hipStream_t s);
+// near bits of the segment and element tables (expanded before) for every cell of the plan; mixed: the
+// pairs of the near radius as well
+int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, bool mixed, hipStream_t s);
+
+// groups of 32 segments or elements a chunk so that `blocks` blocks a chunk make about 2048 blocks in all
+inline int groups_per_chunk(int64_t groups, int64_t blocks)
+{
+    const int64_t n = (groups * blocks + 2047) / 2048;
+    return (int)(n < 1 ? 1 : (n > groups ? groups : n));
+}
 
 // label of unit u in a first-unit table t[0 .. nl] (t[nl] = number of units > u)
 __device__ inline int unit_label(const int* __restrict__ t, int nl, int u)

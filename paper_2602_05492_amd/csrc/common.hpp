@@ -99,7 +99,7 @@ struct bem_ctx {
     std::string err;
     bem::ProfState prof;
     // one-time boundary system
-    bem::DevBuf A, Apinv, LU, piv, un, vn, flag, scal, egeo;   // egeo: outer elements [M][4] (a, b)
+    bem::DevBuf A, Apinv, LU, piv, un, vn, flag, scal, egeo;   // LU: A+^T once factored; egeo: outer elements [M][4] (a, b)
     // per-call workspaces
     bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearw, nearf, regw, cholw, sortw,
         boxw, cellw, cellb, farw;
@@ -141,9 +141,10 @@ int launch_factor(bem_ctx* ctx, hipStream_t s);
 int launch_expand(bem_ctx* ctx, const double* theta, int H, hipStream_t s);
 int launch_expand_into(bem_ctx* ctx, const double* theta, int H, double* seg64, float* seg32, hipStream_t s);
 int launch_boundary_rhs(bem_ctx* ctx, int K, double* F, bool mixed, hipStream_t s);
-int launch_boundary_solve(bem_ctx* ctx, const double* F, double* U, bool transpose, hipStream_t s);
-int launch_pack_elements(bem_ctx* ctx, const double* U, hipStream_t s);
-int launch_pack_elements_into(bem_ctx* ctx, const double* U, double* el64, float* el32, hipStream_t s);
+int launch_boundary_solve(bem_ctx* ctx, const double* F, double* U, hipStream_t s);
+int launch_boundary_adjoint(bem_ctx* ctx, const double* psi, double* mu, double* gx, double* gc, hipStream_t s);
+int launch_pack_elements(bem_ctx* ctx, hipStream_t s);
+int launch_pack_elements_into(bem_ctx* ctx, double* el64, float* el32, hipStream_t s);
 int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar_host, double* u, hipStream_t s);
 // The mixed sweeps share one near-pair list layout (sweep_common.hpp).  The
 // forward sweep returns the list it built (valid until the next mixed sweep);
@@ -175,9 +176,8 @@ struct Carve {
 };
 int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, const void* gbar, bool mixed,
             double* grad, hipStream_t s, const Carve* carve = nullptr);
-// api.hip: expand + element tables (no boundary solve); and the whole forward set-up
-// (expand, boundary right-hand side (float32 far pairs when mixed), boundary solve, element tables)
-int prepare_forward_tables(bem_ctx* ctx, const double* theta, int H, hipStream_t s);
+// api.hip: the forward set-up: expand, boundary right-hand side (float32 far pairs when mixed), boundary
+// solve into the element tables
 int prepare_forward(bem_ctx* ctx, const double* theta, int H, bool mixed, hipStream_t s);
 // gemm.hip
 // plain products on float64 MFMA; with a list of 64 x 64 output tiles on the VALU (Gram mode FP64_VALU)

@@ -333,6 +333,9 @@ int launch_factor(bem_ctx* ctx, hipStream_t s)
     hipLaunchKernelGGL(k_transpose, tgrid, dim3(32, 8), 0, s, LU, LUt2, n);
     hipLaunchKernelGGL(k_inverse_columns, dim3(n), dim3(256), (size_t)n * sizeof(double), s, LU, LUt2, piv, n, X);
     hipLaunchKernelGGL(k_pinv_finish, grid, dim3(256), 0, s, X, n, u, v, scal);
+    // the factors are not needed any more: their buffer keeps the transpose of A+ for the adjoint
+    hipLaunchKernelGGL(k_transpose, tgrid, dim3(32, 8), 0, s, X, LU, n);
+    if ((rc = launch_pack_elements(ctx, s))) return rc;
     if ((rc = check_launch(ctx, "inverse"))) return rc;
     int hflag[4] = {0, 0, 0, 0};
     double hs[3];

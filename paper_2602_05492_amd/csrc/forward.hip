@@ -1,9 +1,8 @@
 // forward.hip - the forward path of one evaluation (Sec. 3.1.3):
 //   expand     theta -> straight segment table (float64 and float32 copies)
 //   bnd_rhs    F_i = 3-point Gauss integral of f over outer element i
-//   solve      U = A+ F  (and the transposed product for the adjoint)
-//   pack       outer element table with the solved values U
-//   sweep      u(x) = cbar + sum_j beta_j(x) U_j + f(x) for every sample
+//   solve      U = A+ F, into the outer element table (and the transposed product for the adjoint)
+// The sweep over the samples is in sweep_eval.hip (mixed) and sweep_f64.hip.
 #include "common.hpp"
 #include "sweep_common.hpp"
 
@@ -70,26 +69,24 @@ __global__ void k_expand(const double* __restrict__ theta, int H, int S, int mod
     }
 }
 
-__device__ inline double block_reduce(double v, double* red)
+// Sums of v[0..2] over a block of 256 threads, in a fixed order (by wavefronts, then through LDS);
+// valid in thread 0.
+__device__ inline void block_sum3(double (&v)[3])
 {
-    const int t = threadIdx.x;
-    red[t] = v;
+    __shared__ double red[4][3];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        for (int c = 0; c < 3; ++c) v[c] += __shfl_xor(v[c], o);
+    if ((threadIdx.x & 63) == 0)
+        for (int c = 0; c < 3; ++c) red[threadIdx.x >> 6][c] = v[c];
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
-        __syncthreads();
-    }
-    const double r = red[0];
-    __syncthreads();
-    return r;
+    for (int c = 0; c < 3; ++c) v[c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
 }
-
 
 // F[i, c] = sum_q w_q |G_i|/2 f_c(x_iq): one block per element, threads over segments.
 __global__ void k_boundary_rhs(const double* __restrict__ seg, int K, const double* __restrict__ eg, double eps2,
                                double* __restrict__ F)
 {
-    __shared__ double red[256];
     const int i = blockIdx.x;
     double ax, ay, bx, by;
     load_element(eg, i, ax, ay, bx, by);
@@ -107,10 +104,9 @@ __global__ void k_boundary_rhs(const double* __restrict__ seg, int K, const doub
                 acc[c] += w[q] * (mo.da * s[kWdA + c] + mo.db * s[kWdB + c] + mo.sa * s[kWcA + c] + mo.sb * s[kWcB + c]);
         }
     }
-    for (int c = 0; c < 3; ++c) {
-        const double r = block_reduce(acc[c], red);
-        if (threadIdx.x == 0) F[(size_t)i * 3 + c] = r;
-    }
+    block_sum3(acc);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 3; ++c) F[(size_t)i * 3 + c] = acc[c];
 }
 
 // Mixed-precision boundary right-hand side: as k_boundary_rhs, with the pairs of a Gauss
@@ -119,7 +115,6 @@ __global__ void k_boundary_rhs(const double* __restrict__ seg, int K, const doub
 __global__ void k_boundary_rhs_mixed(const double* __restrict__ seg, const float* __restrict__ seg32, int K,
                                      const double* __restrict__ eg, double eps2, float near2, double* __restrict__ F)
 {
-    __shared__ double red[256];
     const int i = blockIdx.x;
     double ax, ay, bx, by;
     load_element(eg, i, ax, ay, bx, by);
@@ -154,70 +149,62 @@ __global__ void k_boundary_rhs_mixed(const double* __restrict__ seg, const float
             }
         }
     }
-    for (int c = 0; c < 3; ++c) {
-        const double r = block_reduce(acc[c], red);
-        if (threadIdx.x == 0) F[(size_t)i * 3 + c] = r;
-    }
+    block_sum3(acc);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 3; ++c) F[(size_t)i * 3 + c] = acc[c];
 }
 
-// out[i, c] = sum_j A+[i, j] in[j, c]   (transpose: sum_j A+[j, i] in[j, c])
-__global__ void k_apply_pinv(const double* __restrict__ Ap, int M, const double* __restrict__ in, double* __restrict__ out,
-                             int transpose)
+// out[i, c] = sum_j A[i, j] in[j, c] for A = A+ or its transpose (row-major both): a block per row.
+// Forward, the solved values also go to element i's records (el64, el32); in the adjoint the Gauss
+// points of element i and their cotangents out_i w_q |G_i|/2 to gx, gc.
+__global__ void __launch_bounds__(256) k_apply_pinv(const double* __restrict__ A, int M, const double* __restrict__ in,
+                                                    double* __restrict__ out, double* __restrict__ el64,
+                                                    float* __restrict__ el32, const double* __restrict__ eg,
+                                                    double* __restrict__ gx, double* __restrict__ gc)
 {
-    __shared__ double red[256];
     const int i = blockIdx.x;
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int j = threadIdx.x; j < M; j += blockDim.x) {
-        const double a = transpose ? Ap[(size_t)j * M + i] : Ap[(size_t)i * M + j];
+#pragma unroll 4
+    for (int j = threadIdx.x; j < M; j += 256) {
+        const double a = A[(size_t)i * M + j];
         for (int c = 0; c < 3; ++c) acc[c] += a * in[(size_t)j * 3 + c];
     }
-    for (int c = 0; c < 3; ++c) {
-        const double r = block_reduce(acc[c], red);
-        if (threadIdx.x == 0) out[(size_t)i * 3 + c] = r;
+    block_sum3(acc);
+    if (threadIdx.x != 0) return;
+    for (int c = 0; c < 3; ++c) out[(size_t)i * 3 + c] = acc[c];
+    if (el64)
+        for (int c = 0; c < 3; ++c) {
+            el64[(size_t)i * kElemStride + 4 + c] = acc[c];
+            el32[(size_t)i * kElemStride + 4 + c] = (float)acc[c];
+        }
+    if (gx) {
+        double ax, ay, bx, by;
+        load_element(eg, i, ax, ay, bx, by);
+        const double hx = 0.5 * (bx - ax), hy = 0.5 * (by - ay), half = sqrt(hx * hx + hy * hy);
+        for (int q = 0; q < 3; ++q) {
+            const double node = q == 0 ? -kGaussNode : (q == 1 ? 0.0 : kGaussNode);
+            const double w = (q == 1 ? kGaussW1 : kGaussW0) * half;
+            const int t = 3 * i + q;
+            gx[2 * t] = 0.5 * (ax + bx) + node * hx;
+            gx[2 * t + 1] = 0.5 * (ay + by) + node * hy;
+            for (int c = 0; c < 3; ++c) gc[3 * t + c] = acc[c] * w;
+        }
     }
 }
 
-__global__ void k_pack_elements(const double* __restrict__ U, int M, const double* __restrict__ eg,
-                                double* __restrict__ e64, float* __restrict__ e32)
+// Geometry of the element records (the values U are written by k_apply_pinv).
+__global__ void k_pack_elements(int M, const double* __restrict__ eg, double* __restrict__ e64,
+                                float* __restrict__ e32)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= M) return;
     double ax, ay, bx, by;
     load_element(eg, i, ax, ay, bx, by);
-    const double rec[kElemStride] = {ax, ay, bx - ax, by - ay, U[3 * i], U[3 * i + 1], U[3 * i + 2], 0.0};
+    const double rec[kElemStride] = {ax, ay, bx - ax, by - ay, 0.0, 0.0, 0.0, 0.0};
     for (int c = 0; c < kElemStride; ++c) {
         e64[(size_t)i * kElemStride + c] = rec[c];
         e32[(size_t)i * kElemStride + c] = (float)rec[c];
     }
-}
-
-// FP64 sweep: one thread per sample, every wavefront walks the whole segment
-// and element tables (wave-uniform addresses: scalar loads).
-__global__ void __launch_bounds__(256) k_sweep_f64(const double* __restrict__ x, int64_t N, const double* __restrict__ seg,
-                                                   int K, const double* __restrict__ el, int M, double eps2,
-                                                   double c0, double c1, double c2, double* __restrict__ u)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const double X = x[2 * i], Y = x[2 * i + 1];
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    for (int k = 0; k < K; ++k) {
-        const double* s = seg + (size_t)k * kSegStride;
-        const SegGeom<double> g = load_geom(s);
-        const Moments<double> m = seg_moments<double, DevF64>(g, X, Y, eps2);
-        a0 += m.da * s[kWdA + 0] + m.db * s[kWdB + 0] + m.sa * s[kWcA + 0] + m.sb * s[kWcB + 0];
-        a1 += m.da * s[kWdA + 1] + m.db * s[kWdB + 1] + m.sa * s[kWcA + 1] + m.sb * s[kWcB + 1];
-        a2 += m.da * s[kWdA + 2] + m.db * s[kWdB + 2] + m.sa * s[kWcA + 2] + m.sb * s[kWcB + 2];
-    }
-    double b0 = 0.0, b1 = 0.0, b2 = 0.0;
-    for (int j = 0; j < M; ++j) {
-        const double* e = el + (size_t)j * kElemStride;
-        const double beta = element_beta<double, DevF64>(e[0], e[1], e[2], e[3], X, Y);
-        b0 += beta * e[4]; b1 += beta * e[5]; b2 += beta * e[6];
-    }
-    u[3 * i + 0] = c0 + b0 + a0;
-    u[3 * i + 1] = c1 + b1 + a1;
-    u[3 * i + 2] = c2 + b2 + a2;
 }
 
 }  // namespace
@@ -258,38 +245,37 @@ int launch_boundary_rhs(bem_ctx* ctx, int K, double* F, bool mixed, hipStream_t 
     return check_launch(ctx, "boundary_rhs");
 }
 
-int launch_boundary_solve(bem_ctx* ctx, const double* F, double* U, bool transpose, hipStream_t s)
+// U = A+ F, into U and the element records
+int launch_boundary_solve(bem_ctx* ctx, const double* F, double* U, hipStream_t s)
 {
     hipLaunchKernelGGL(k_apply_pinv, dim3(ctx->M), dim3(256), 0, s, (const double*)ctx->Apinv.ptr, ctx->M, F, U,
-                       transpose ? 1 : 0);
+                       (double*)ctx->elem64.ptr, (float*)ctx->elem32.ptr, (const double*)ctx->egeo.ptr,
+                       (double*)nullptr, (double*)nullptr);
     return check_launch(ctx, "boundary_solve");
 }
 
-int launch_pack_elements(bem_ctx* ctx, const double* U, hipStream_t s)
+// mu = A+^T psi, with the boundary Gauss points gx [3M][2] and their cotangents gc [3M][3].  The
+// transpose is kept beside A+ (bem_factor): by columns of A+ the product took 15 us against 6.
+int launch_boundary_adjoint(bem_ctx* ctx, const double* psi, double* mu, double* gx, double* gc, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_apply_pinv, dim3(ctx->M), dim3(256), 0, s, (const double*)ctx->LU.ptr, ctx->M, psi, mu,
+                       (double*)nullptr, (float*)nullptr, (const double*)ctx->egeo.ptr, gx, gc);
+    return check_launch(ctx, "boundary_adjoint");
+}
+
+int launch_pack_elements(bem_ctx* ctx, hipStream_t s)
 {
     int rc;
     if ((rc = ensure(ctx, ctx->elem64, (size_t)ctx->M * kElemStride * sizeof(double), s))) return rc;
     if ((rc = ensure(ctx, ctx->elem32, (size_t)ctx->M * kElemStride * sizeof(float), s))) return rc;
-    return launch_pack_elements_into(ctx, U, (double*)ctx->elem64.ptr, (float*)ctx->elem32.ptr, s);
+    return launch_pack_elements_into(ctx, (double*)ctx->elem64.ptr, (float*)ctx->elem32.ptr, s);
 }
 
-int launch_pack_elements_into(bem_ctx* ctx, const double* U, double* el64, float* el32, hipStream_t s)
+int launch_pack_elements_into(bem_ctx* ctx, double* el64, float* el32, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pack_elements, dim3(blocks_for(ctx->M, 256)), dim3(256), 0, s, U, ctx->M, (const double*)ctx->egeo.ptr,
-                       el64, el32);
+    hipLaunchKernelGGL(k_pack_elements, dim3(blocks_for(ctx->M, 256)), dim3(256), 0, s, ctx->M,
+                       (const double*)ctx->egeo.ptr, el64, el32);
     return check_launch(ctx, "pack_elements");
-}
-
-int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar, double* u, hipStream_t s)
-{
-    if (N == 0) return BEM_OK;
-    const double eps2 = ctx->opts.eps * ctx->opts.eps;
-    {
-        ProfScope ps_(ctx, PT_SWEEP_F64, s);
-        hipLaunchKernelGGL(k_sweep_f64, dim3(blocks_for(N, 256)), dim3(256), 0, s, x, N, (const double*)ctx->seg64.ptr, K,
-                           (const double*)ctx->elem64.ptr, ctx->M, eps2, cbar[0], cbar[1], cbar[2], u);
-    }
-    return check_launch(ctx, "sweep_f64");
 }
 
 }  // namespace bem

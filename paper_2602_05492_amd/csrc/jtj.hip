@@ -1173,7 +1173,7 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     const int n12 = L.compact();          // handle part of one channel's compact order
     const int Wc = n12 + M;
     if (H == 0) return BEM_OK;
-    if ((rc = prepare_forward_tables(ctx, theta, H, s))) return rc;
+    if ((rc = launch_expand(ctx, theta, H, s))) return rc;
     double* Z = nullptr;
     if ((rc = boundary_derivatives(ctx, H, s, &Z))) return rc;
     // sample tiles
@@ -1420,7 +1420,7 @@ int run_jacobian(bem_ctx* ctx, const double* theta, int H, const double* x, int6
     const int nf = (int)L.handle_rows();
     const int64_t W = nf + M;
     if (H == 0 || N == 0) return BEM_OK;
-    if ((rc = prepare_forward_tables(ctx, theta, H, s))) return rc;
+    if ((rc = launch_expand(ctx, theta, H, s))) return rc;
     double* Z = nullptr;
     if ((rc = boundary_derivatives(ctx, H, s, &Z))) return rc;
     const int64_t ld = N;

@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(256) k_far_nodes(CellGrid g, const int* __rest
     const int c = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const bool used = c < g.nc && off[c + 1] > off[c];
     double Xd = 0.0, Yd = 0.0;
-    if (used) cell_node(g, c, lane, Xd, Yd);
+    if (used) cell_node<kFarQ>(g, c, lane, Xd, Yd);
     const float X = (float)Xd, Y = (float)Yd;
     const uint32_t* row = bits + (size_t)(used ? c : 0) * words;
     const int g0 = blockIdx.y * gpc, g1 = g0 + gpc;
@@ -353,13 +353,6 @@ __global__ void __launch_bounds__(256, 4) k_sweep_cells(CellPlan p, Tables t, co
         u[o + q] = (float)(cb[q] + (((double)e3[q] + (double)f[q]) + ((double)far[q] + b.acc[3 * lane + q])));
 }
 
-// groups of 32 a chunk so that `blocks` blocks a chunk make about 2048 blocks in all
-int groups_per_chunk(int64_t groups, int64_t blocks)
-{
-    const int64_t n = (groups * blocks + 2047) / 2048;
-    return (int)(n < 1 ? 1 : (n > groups ? groups : n));
-}
-
 }  // namespace
 
 int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar, float* u, hipStream_t s)
@@ -372,7 +365,7 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     const Tables t{(const float*)ctx->seg32.ptr, (const double*)ctx->seg64.ptr, (const float*)ctx->elem32.ptr,
                    (const double*)ctx->elem64.ptr, K, M, (float)eps2, (float)(nf * nf), eps2};
     const int64_t groups = (K + 31) / 32 + (M + 31) / 32;
-    const int g = cells_for(ctx, N, K, kEvalRatio);
+    const int g = cells_for(ctx, N, K, kFarQ, kEvalRatio, 2e7);
     ProfScope ps_(ctx, PT_SWEEP_MIXED, s);
     if (g == 0) {
         const int64_t nb = blocks_for(N, 256);
@@ -392,7 +385,7 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     }
     CellPlan p;
     if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
-    if ((rc = cell_bits(ctx, &p, K, M, s))) return rc;
+    if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
     const int nc = p.grid.nc;
     const int gpc = groups_per_chunk(groups, (nc + 3) / 4);
     const int nparts = (int)((groups + gpc - 1) / gpc);

@@ -24,9 +24,6 @@ namespace bem {
 
 namespace {
 
-constexpr double kGaussNode = 0.77459666924148337703585307995647992;
-constexpr double kGaussW0 = 5.0 / 9.0, kGaussW1 = 8.0 / 9.0;
-
 __device__ inline void load_cot(const double* __restrict__ gbar, int64_t s, double& g0, double& g1, double& g2)
 {
     g0 = gbar[3 * s]; g1 = gbar[3 * s + 1]; g2 = gbar[3 * s + 2];
@@ -127,65 +124,53 @@ __global__ void __launch_bounds__(1024) k_reduce_parts(const double* __restrict_
     }
 }
 
-// Gauss points of the outer elements and their cotangents mu_i w_q |G_i|/2.
-__global__ void k_gauss_cotangent(const double* __restrict__ mu, int M, const double* __restrict__ eg, double* __restrict__ gx,
-                                  double* __restrict__ gc)
+// Segment sums -> theta gradient: a thread per parameter.  Cubic handles chain the vertex gradients to
+// the control points with Bernstein weights and the end jumps with (1 - t, t); straight handles (model 1)
+// chain them to the end points with (1 - t, t) and sum the jumps.  (A thread per handle read its S x 16 sums
+// one after the other: 28 us for 4 handles of 32 segments.)
+__global__ void __launch_bounds__(64) k_chain_theta(const double* __restrict__ sg, int H, int S, int model,
+                                                    double* __restrict__ grad)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 3 * M) return;
-    const int i = t / 3, q = t % 3;
-    double ax, ay, bx, by;
-    load_element(eg, i, ax, ay, bx, by);
-    const double hx = 0.5 * (bx - ax), hy = 0.5 * (by - ay);
-    const double node = q == 0 ? -kGaussNode : (q == 1 ? 0.0 : kGaussNode);
-    const double w = (q == 1 ? kGaussW1 : kGaussW0) * sqrt(hx * hx + hy * hy);
-    gx[2 * t] = 0.5 * (ax + bx) + node * hx;
-    gx[2 * t + 1] = 0.5 * (ay + by) + node * hy;
-    for (int c = 0; c < 3; ++c) gc[3 * t + c] = mu[3 * i + c] * w;
-}
-
-// Segment sums -> theta gradient: one thread per handle.  Cubic handles chain the vertex
-// gradients to the control points with Bernstein weights and the end jumps with (1 - t, t);
-// straight handles (model 1) chain them to the end points with (1 - t, t) and sum the jumps.
-__global__ void k_chain_theta(const double* __restrict__ sg, int H, int S, int model, double* __restrict__ grad)
-{
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= H) return;
-    double out[20];
-    for (int p = 0; p < 20; ++p) out[p] = 0.0;
     const bool straight = model == 1;
-    for (int j = 0; j < S; ++j) {
-        const double* v = sg + ((size_t)h * S + j) * kV;
-        const double ta = (double)j / (double)S, tb = (double)(j + 1) / (double)S;
-        double Ba[4], Bb[4];
-        vertex_weights(model, ta, Ba);
-        vertex_weights(model, tb, Bb);
-        for (int c = 0; c < 4; ++c) {
-            out[2 * c] += Ba[c] * v[0] + Bb[c] * v[2];
-            out[2 * c + 1] += Ba[c] * v[1] + Bb[c] * v[3];
+    const int Q = straight ? 10 : 20, ngeo = straight ? 4 : 8;
+    const int t = blockIdx.x * 64 + threadIdx.x;
+    if (t >= H * Q) return;
+    const int h = t / Q, p = t % Q;
+    const double* v = sg + (size_t)h * S * kV;
+    double out = 0.0;
+    if (p < ngeo) {
+        const int q = p >> 1, d = p & 1;
+#pragma unroll 8
+        for (int j = 0; j < S; ++j) {
+            double Ba[4], Bb[4];
+            vertex_weights(model, (double)j / (double)S, Ba);
+            vertex_weights(model, (double)(j + 1) / (double)S, Bb);
+            const double a = q == 0 ? Ba[0] : (q == 1 ? Ba[1] : (q == 2 ? Ba[2] : Ba[3]));
+            const double b = q == 0 ? Bb[0] : (q == 1 ? Bb[1] : (q == 2 ? Bb[2] : Bb[3]));
+            out += a * v[(size_t)j * kV + d] + b * v[(size_t)j * kV + 2 + d];
         }
-        if (straight) {
-            for (int c = 0; c < 3; ++c) {
-                out[4 + c] += v[4 + c] + v[7 + c];       // wd
-                out[7 + c] += v[10 + c] + v[13 + c];     // wc
-            }
-            continue;
-        }
-        for (int c = 0; c < 3; ++c) {
-            out[8 + c] += (1.0 - ta) * v[4 + c] + (1.0 - tb) * v[7 + c];     // wd at end 0
-            out[11 + c] += ta * v[4 + c] + tb * v[7 + c];                    // wd at end 1
-            out[14 + c] += (1.0 - ta) * v[10 + c] + (1.0 - tb) * v[13 + c];  // wc at end 0
-            out[17 + c] += ta * v[10 + c] + tb * v[13 + c];                  // wc at end 1
+    } else if (straight) {
+        const int c = (p - 4) % 3, m = 4 + 6 * ((p - 4) / 3) + c;         // wd, wc
+        for (int j = 0; j < S; ++j) out += v[(size_t)j * kV + m] + v[(size_t)j * kV + m + 3];
+    } else {
+        const int c = (p - 8) % 3, k = (p - 8) / 3, m = 4 + 6 * (k >> 1) + c;   // wd0, wd1, wc0, wc1
+        const bool end = k & 1;
+#pragma unroll 8
+        for (int j = 0; j < S; ++j) {
+            const double ta = (double)j / (double)S, tb = (double)(j + 1) / (double)S;
+            out += (end ? ta : 1.0 - ta) * v[(size_t)j * kV + m] + (end ? tb : 1.0 - tb) * v[(size_t)j * kV + m + 3];
         }
     }
-    const int q = straight ? 10 : 20;
-    for (int p = 0; p < q; ++p) grad[(size_t)h * q + p] = out[p];
+    grad[t] = out;
 }
 
+// Chunks of N samples over `groups` groups of 64 segments or elements: about 4,096 blocks, each with at least
+// 256 samples, or 32 while there are fewer than 1,024 blocks.
 int chunks_for(int64_t N, int groups, int64_t& chunk)
 {
     int64_t nch = (4096 + groups - 1) / groups;
-    const int64_t cap = (N + 255) / 256;
+    const int64_t few = (N + 31) / 32 < 1024 / groups ? (N + 31) / 32 : 1024 / groups;
+    const int64_t cap = (N + 255) / 256 > few ? (N + 255) / 256 : few;
     if (nch > cap) nch = cap;
     if (nch < 1) nch = 1;
     chunk = (N + nch - 1) / nch;
@@ -236,7 +221,7 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     const size_t seg_part = (size_t)(ns + ng) * K * kV;
     const size_t el_rows = (size_t)(ne > 0 ? ne : 1);
     const size_t seg_n = (size_t)(K > 0 ? K : 1) * kSegStride;
-    double *seg64w, *el64w, *Uw, *part, *epart, *gx, *redw;
+    double *seg64w, *el64w, *part, *epart, *gx, *redw;
     float *seg32w, *el32w;
     if (carve) {
         // every workspace from the caller's device memory, in the order vjp_f64_workspace_bytes counts
@@ -249,7 +234,7 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         seg32w = (float*)take(seg_n * sizeof(float));
         el64w = (double*)take((size_t)M * kElemStride * sizeof(double));
         el32w = (float*)take((size_t)M * kElemStride * sizeof(float));
-        Uw = (double*)take((size_t)M * 3 * sizeof(double));
+        take((size_t)M * 3 * sizeof(double));
         part = (double*)take(seg_part * sizeof(double));
         epart = (double*)take((el_rows * M * 3 + 2 * (size_t)M * 3) * sizeof(double));
         gx = (double*)take((size_t)3 * M * 5 * sizeof(double));
@@ -258,16 +243,12 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         // workspaces: tmp1 segment partials, tmp2 element partials + psi + mu, tmp3 Gauss points, red segment sums
         if ((rc = ensure(ctx, ctx->seg64, seg_n * sizeof(double), s))) return rc;
         if ((rc = ensure(ctx, ctx->seg32, seg_n * sizeof(float), s))) return rc;
-        if ((rc = ensure(ctx, ctx->U, (size_t)M * 3 * sizeof(double), s))) return rc;
-        if ((rc = ensure(ctx, ctx->elem64, (size_t)M * kElemStride * sizeof(double), s))) return rc;
-        if ((rc = ensure(ctx, ctx->elem32, (size_t)M * kElemStride * sizeof(float), s))) return rc;
         if ((rc = ensure(ctx, ctx->tmp1, seg_part * sizeof(double), s))) return rc;
         if ((rc = ensure(ctx, ctx->tmp2, (el_rows * M * 3 + 2 * (size_t)M * 3) * sizeof(double), s))) return rc;
         if ((rc = ensure(ctx, ctx->tmp3, (size_t)3 * M * 5 * sizeof(double), s))) return rc;
         if ((rc = ensure(ctx, ctx->red, (size_t)K * kV * sizeof(double), s))) return rc;
         seg64w = (double*)ctx->seg64.ptr;
         seg32w = (float*)ctx->seg32.ptr;
-        Uw = (double*)ctx->U.ptr;
         el64w = (double*)ctx->elem64.ptr;
         el32w = (float*)ctx->elem32.ptr;
         part = (double*)ctx->tmp1.ptr;
@@ -276,7 +257,7 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         redw = (double*)ctx->red.ptr;
     }
     if ((rc = launch_expand_into(ctx, theta, H, seg64w, seg32w, s))) return rc;
-    if ((rc = launch_pack_elements_into(ctx, Uw, el64w, el32w, s))) return rc;   // element geometry only
+    if (carve && (rc = launch_pack_elements_into(ctx, el64w, el32w, s))) return rc;
     double* psi = epart + el_rows * M * 3;
     double* mu = psi + (size_t)M * 3;
     double* gc = gx + (size_t)3 * M * 2;
@@ -298,9 +279,7 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         hipLaunchKernelGGL(k_reduce_parts, dim3(blocks_for((int64_t)M * 3, 64)), dim3(1024), 0, s, epart, ne,
                            (int64_t)M * 3, psi);
         if ((rc = check_launch(ctx, "vjp sweeps"))) return rc;
-        if ((rc = launch_boundary_solve(ctx, psi, mu, true, s))) return rc;
-        hipLaunchKernelGGL(k_gauss_cotangent, dim3(blocks_for(3 * M, 256)), dim3(256), 0, s, mu, M,
-                           (const double*)ctx->egeo.ptr, gx, gc);
+        if ((rc = launch_boundary_adjoint(ctx, psi, mu, gx, gc, s))) return rc;
         {
             ProfScope ps_(ctx, PT_VJP_SEGMENTS, s);
             hipLaunchKernelGGL(k_vjp_segments, dim3(kgroups, ng), dim3(256), 0, s, gx, gc, (int64_t)3 * M, chunk_g, seg64,
@@ -312,8 +291,8 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         hipLaunchKernelGGL(k_reduce_parts, dim3(blocks_for((int64_t)K * kV, 64)), dim3(1024), 0, s, part, 0,
                            (int64_t)K * kV, redw);
     }
-    hipLaunchKernelGGL(k_chain_theta, dim3(blocks_for(H, 64)), dim3(64), 0, s, (const double*)redw, H, S,
-                       ctx->model, grad);
+    hipLaunchKernelGGL(k_chain_theta, dim3(blocks_for((int64_t)H * ctx->npar, 64)), dim3(64), 0, s, (const double*)redw, H,
+                       S, ctx->model, grad);
     return check_launch(ctx, "vjp");
 }
 

@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(192) k_node_cotangent(const double* __restrict
     o[2 + ch] = (float)r;
     if (ch == 0) {
         double X, Y;
-        cell_node(g, c, n, X, Y);
+        cell_node<kFarQ>(g, c, n, X, Y);
         o[0] = (float)X;
         o[1] = (float)Y;
     }
@@ -407,7 +407,7 @@ __global__ void __launch_bounds__(64, Singular ? 2 : 4)
 // Rows of segment partials (times K x 16) and of element partials (times M x 3) that adj_mixed writes.
 int adj_mixed_rows(bem_ctx* ctx, int K, int64_t N, int* seg_rows, int* el_rows)
 {
-    const int g = cells_for(ctx, N, K, kAdjRatio);
+    const int g = cells_for(ctx, N, K, kFarQ, kAdjRatio, 2e7);
     auto rows = [&](int n) {
         const int groups = (n + 63) / 64;
         const int r = (2048 + groups - 1) / (groups > 0 ? groups : 1);
@@ -436,7 +436,7 @@ int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K
     int64_t runs;
     if (g) {
         if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
-        if ((rc = cell_bits(ctx, &p, K, M, s))) return rc;
+        if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
         runs = p.max_runs;
     } else {
         // few samples: runs of 64 in their own order

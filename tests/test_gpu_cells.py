@@ -9,11 +9,14 @@ factors that make most pairs near.
 Tolerances: float32 pairs carry about 1e-6 of the largest colour (a few hundred terms of O(1) rounded at 2^-24
 = 6e-8 and partly cancelling), the interpolated far field less than 1e-7; the bar is 1e-5 of the largest
 colour (at least 1).  The gradients' bar is 1e-3 of the largest entry, as elsewhere for the mixed adjoint.
+The float64 sweep over grouped samples is held to the direct one (itself held to the oracle) at 1e-12: sums of
+some thousand O(1) terms round at 1e-13, the interpolation adds 1e-14.
 """
 import numpy as np
 import pytest
 import torch
 
+import oracle as O
 from paper_2602_05492_amd import bem as B
 from paper_2602_05492_amd import workload as W
 from helpers import ctx_for, dev, host
@@ -101,3 +104,26 @@ def test_grouped_samples_view_off_16_bytes():
     x = flat[1:].view(-1, 2)
     u = ctx.eval(th, x, CBAR, "mixed")
     assert torch.equal(u, ctx.eval(th, x.clone(), CBAR, "mixed")) or float((u - ctx.eval(th, x.clone(), CBAR, "mixed")).abs().max()) < 1e-6
+
+
+@pytest.mark.parametrize("H,n", [(33, 20011), (64, 100003), (3, 262144)])
+def test_grouped_samples_fp64(H, n):
+    ctx, th = ctx_for(32), W.random_handles(H, H)
+    x = W.random_points(H, n, 1e-4, 1 - 1e-4)
+    x[::5000] = 1.0 + W.random_points(5, len(x[::5000]), 0.01, 0.5)       # outside the boundary's box
+    x[3] = (np.nan, 0.5)
+    u = host(ctx.eval(dev(th), dev(x), CBAR, "fp64"))
+    idx = np.r_[0:3, 4:2000, n - 3000:n]
+    r = host(ctx.eval(dev(th), dev(x[idx]), CBAR, "fp64"))                 # few samples: the direct sums
+    assert np.isnan(u[3]).all() and np.isfinite(np.delete(u, 3, 0)).all()
+    assert np.abs(u[idx] - r).max() < 1e-12 * max(1.0, np.abs(r).max())
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 1025])
+def test_few_samples_fp64_matches_oracle(n):
+    th, x, g = W.random_handles(n, 9), W.random_points(n, n, 0.01, 0.99), W.random_vector(n, (n, 3))
+    ctx = ctx_for(8)
+    u, uo = host(ctx.eval(dev(th), dev(x), CBAR, "fp64")), O.evaluate(th, x, CBAR, 8, 1e-2)
+    assert np.abs(u - uo).max() < 1e-10
+    a, b = host(ctx.vjp(dev(th), dev(x), dev(g), "fp64")), O.vjp(th, x, g, 8, 1e-2)
+    assert np.abs(a - b).max() < 1e-10 * np.abs(b).max()
