@@ -97,14 +97,15 @@ typedef enum {
  *        later calls of the context too). */
 typedef enum { BEM_PREC_FP64 = 0, BEM_PREC_MIXED = 1 } bem_prec;
 
-/* Arithmetic of the Gram contraction that forms J^T J and J^T r.
+/* Arithmetic of the Gram contraction that forms J^T J.
  * FP64         : float64 tiles, float64 products and accumulation on float64
  *                MFMA (v_mfma_f64_16x16x4f64).
  * FP32_MFMA    : float32 J tiles, float32 MFMA, float32 accumulation within
  *                a sample tile, float64 across tiles.
  * BF16X3_MFMA  : J split as hi + lo bfloat16, hi*hi + hi*lo + lo*hi on bf16
  *                MFMA with float32 accumulation within a third of a sample
- *                tile, float64 across thirds and tiles (fixed order).
+ *                tile, float64 across thirds and tiles (fixed order; lm_step's sums
+ *                over grid cells add the near rows with float64 atomics).
  * FP64_VALU    : as FP64, with the products on the float64 vector ALUs.
  * Every float64 product of the library (the Gram's contraction to J^T J, the
  * boundary derivatives Z = A+ dF/dtheta) runs on float64 MFMA in all modes. */
@@ -255,7 +256,8 @@ int bem_vjp_noalloc(bem_ctx* ctx, const double* theta, int32_t H, const double* 
  *   JtJ = (1/N) sum_x sum_c J_c(x)^T J_c(x)   [P,P] float64 (full, symmetric)
  *   Jtr = (1/N) sum_x sum_c J_c(x)^T r_c(x)   [P]   float64
  * with J_c(x) = du_c(x)/dtheta.  resid [N,3] (float64 for FP64, float32 for
- * MIXED).  The Gram contraction runs in `gram` arithmetic.  The Gram's work
+ * MIXED).  Jtr is the adjoint's (bem_vjp with resid, over N).  The Gram contraction
+ * runs in `gram` arithmetic.  The Gram's work
  * list is uploaded (with a host synchronisation) on the first call for a given
  * H, handle model and `gram` and kept on the device; later calls only enqueue.
  * Errors: as bem_eval. */
@@ -266,8 +268,8 @@ int bem_jtj(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64
 /* One Levenberg-Marquardt step (Eq. optimstep, Sec. 4.3) on the samples x
  * with targets T [N,3] float64, m = state->data_count (0: m = N):
  *   cbar update (state->mean_rule), u = u(theta), r = u - T, loss L0 = (1/2m) sum r^2,
- *   g = (1/m) sum J^T r by the adjoint (bem_vjp), H = (1/m) sum J^T J (bem_jtj's
- *   Gram; J^T r itself is not formed again),
+ *   g = (1/m) sum J^T r by the adjoint (bem_vjp), H = (1/m) sum J^T J (as bem_jtj;
+ *   MIXED with BEM_GRAM_BF16X3_MFMA: see below),
  *   delta = (lambda diag(H) + H)^{-1} g by float64 Cholesky,
  *   theta' = theta - delta, L1 = loss at theta' on the same samples with cbar fixed;
  *   accept iff L1 < L0: theta <- theta', lambda /= 10; else lambda *= 10.
@@ -287,13 +289,19 @@ int bem_jtj(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64
  * subdomain (Sec. 4.3, block-diagonal Hessian) sums its own N samples and sets
  * data_count to the image's total, so that its data terms keep their weight
  * against the regularisation terms.
- * MIXED: the step works on a copy of x and target reordered cell by cell (a
+ * MIXED with BEM_GRAM_BF16X3_MFMA, near_factor >= 1 and tile_rows = 0, where the
+ * samples are many against the near pairs: J^T J over grid cells.  The far part of
+ * a cell's J rows, interpolated from 64 nodes, is summed over the cell exactly through
+ * 64 columns (in float16 pairs, 22 bits); the cell's samples enter only the sums of the
+ * rows near it (in bfloat16 pairs).  Without memory
+ * for its workspaces the step takes its other form.
+ * MIXED otherwise: the step works on a copy of x and target reordered cell by cell (a
  * 32 x 32 grid of Morton-ordered cells over the outer boundary's bounding box),
  * so that neighbouring samples share wavefronts; x and target themselves are
  * not modified, and the result depends on the order only through rounding.
- * If the near-pair list of the sweep at theta overflows, its capacity is raised
- * (to 1.25 times the largest wavefront count, rounded up to 256) and the sweep
- * repeated before the adjoint and the normal equations.
+ * If the near-pair list of the J rows overflows, its capacity is raised
+ * (to 1.25 times the largest wavefront count, rounded up to 256) and the list
+ * built again before the normal equations.
  * If the Cholesky fails, lambda is multiplied by 10 and the solve retried (at
  * most 10 times) before ENOTPD.  theta [H,Q] (device) is updated in place;
  * state (host) is read and written.  Synchronises the stream.

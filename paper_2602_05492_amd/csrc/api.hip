@@ -301,7 +301,11 @@ int bem_jtj(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64
     if (prec != BEM_PREC_FP64 && prec != BEM_PREC_MIXED) return set_error(ctx, BEM_EINVAL, "bad precision %d", (int)prec);
     if (gram != BEM_GRAM_FP64 && gram != BEM_GRAM_FP32_MFMA && gram != BEM_GRAM_BF16X3_MFMA && gram != BEM_GRAM_FP64_VALU)
         return set_error(ctx, BEM_EINVAL, "bad gram mode %d", (int)gram);
-    return run_jtj(ctx, theta, H, x, N, resid, prec == BEM_PREC_MIXED, (int)gram, JtJ, Jtr, stream);
+    // J^T r is the adjoint of the residuals
+    const bool mixed = prec == BEM_PREC_MIXED;
+    if ((rc = run_vjp(ctx, theta, H, x, N, resid, mixed, Jtr, stream))) return rc;
+    if (N > 0 && (rc = scale_f64(ctx, Jtr, (int64_t)ctx->npar * H, 1.0 / (double)N, stream))) return rc;
+    return run_jtj(ctx, theta, H, x, N, mixed, (int)gram, JtJ, stream);
 }
 
 int lm_step(bem_ctx* ctx, double* theta, int32_t H, const double* x, int64_t N, const double* target,
@@ -464,7 +468,8 @@ void bem_destroy(bem_ctx* ctx)
     DevBuf* bufs[] = {&ctx->A, &ctx->Apinv, &ctx->LU, &ctx->piv, &ctx->un, &ctx->vn, &ctx->flag, &ctx->scal,
                       &ctx->seg64, &ctx->seg32, &ctx->F, &ctx->U, &ctx->elem64, &ctx->elem32, &ctx->red,
                       &ctx->tmp0, &ctx->tmp1, &ctx->tmp2, &ctx->tmp3, &ctx->tmp4, &ctx->tmp5, &ctx->lmw,
-                      &ctx->nearw, &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
+                      &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
+                      &ctx->necw, &ctx->nezw, &ctx->neew,
                       &ctx->tilew};
     for (DevBuf* b : bufs) release(*b);
     for (hipEvent_t e : ctx->ev)

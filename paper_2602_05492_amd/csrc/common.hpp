@@ -50,6 +50,16 @@ __device__ inline SegGeom<T> load_geom(const T* __restrict__ s)
 }
 
 // ---- device buffers -----------------------------------------------------------
+// A grid cell in the normal equations over cells (jtj_cells.hip)
+struct CellInfo {
+    int n;             // samples
+    int nh, ne;        // near handles and outer elements
+    int rows;          // near rows: (3 G + C) nh + ne
+    int tb;            // first 32-sample block of the basis tile
+    int rb;            // first row of the cell in the projections
+    int64_t eoff;      // first element of its near tile
+};
+
 struct DevBuf {
     void* ptr = nullptr;
     size_t bytes = 0;
@@ -89,11 +99,9 @@ struct bem_ctx {
     // diagonal blocks) and its events, created on first use
     hipStream_t s2 = nullptr;
     hipEvent_t ev[7] = {};
-    // near-pair slots per wavefront of the mixed-precision sweeps (a multiple of 256, raised by
-    // lm_step when a wavefront's near pairs overflow it), and the device word in which the last
-    // mixed forward sweep left its largest overflowing count (0: none overflowed)
+    // near-pair slots per wavefront of the mixed J tiles' lists (a multiple of 256, raised by
+    // lm_step when a wavefront's near pairs overflow it)
     int near_slots = 1024;
-    int* sweep_need = nullptr;
     double bbox[4] = {0.0, 0.0, 1.0, 1.0};   // outer boundary's bounding box (x0, y0, x1, y1)
     double sigma_n = 0.0, shift = 0.0;
     std::string err;
@@ -101,8 +109,11 @@ struct bem_ctx {
     // one-time boundary system
     bem::DevBuf A, Apinv, LU, piv, un, vn, flag, scal, egeo;   // LU: A+^T once factored; egeo: outer elements [M][4] (a, b)
     // per-call workspaces
-    bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearw, nearf, regw, cholw, sortw,
-        boxw, cellw, cellb, farw;
+    bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearf, regw, cholw, sortw,
+        boxw, cellw, cellb, farw, necw, nezw, neew;
+    // cell table and work list of the normal equations over cells, kept until their upload has ended
+    std::vector<bem::CellInfo> ne_info;
+    std::vector<int> ne_work;
     // Gram work list of the normal equations on the device, uploaded once per (W, H, handle
     // model, Gram arithmetic) and kept, so that later calls enqueue without a host synchronisation
     bem::DevBuf tilew;
@@ -146,14 +157,11 @@ int launch_boundary_adjoint(bem_ctx* ctx, const double* psi, double* mu, double*
 int launch_pack_elements(bem_ctx* ctx, hipStream_t s);
 int launch_pack_elements_into(bem_ctx* ctx, double* el64, float* el32, hipStream_t s);
 int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar_host, double* u, hipStream_t s);
-// The mixed sweeps share one near-pair list layout (sweep_common.hpp).  The
-// forward sweep returns the list it built (valid until the next mixed sweep);
-// the adjoint and the normal equations take such a list for the same samples
-// and parameters, or classify the samples themselves when given none.
-struct NearList;
+// mixed forward sweep (sweep_eval.hip)
 int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar_host, float* u, hipStream_t s);
-int launch_sweep_mixed(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar_host, float* u, hipStream_t s,
-                       NearList* out = nullptr);
+// Near-pair list of the mixed J tiles (sweep_common.hpp): the samples' near pairs with segments (and with
+// outer elements when M > 0)
+struct NearList;
 int near_classify(bem_ctx* ctx, DevBuf& buf, const double* x, int64_t N, int K, int M, NearList* out, hipStream_t s);
 // culling boxes of the current segment table (groups of kBoxGroup segments, then of M outer
 // elements) into the context's box buffer
@@ -189,22 +197,20 @@ int gemm_f64_list(bem_ctx* ctx, int m, int n, int k, double alpha, const double*
                   int kchunk, int64_t cstride);
 // jtj.hip
 int fill_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s);
-int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, const void* resid, bool mixed,
-            int gram, double* JtJ, double* Jtr, hipStream_t s, const NearList* pre = nullptr, double norm = 0.0);
+int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, bool mixed, int gram, double* JtJ,
+            hipStream_t s, const NearList* pre = nullptr, double norm = 0.0);
 int run_jacobian(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, double* J, hipStream_t s);
 // gram_mfma.hip
 int launch_gram_mfma(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xlo, int64_t ld, int W, int64_t n,
                      const int* work, int nwork, int64_t kchunk, double* G, int64_t gstride, bool accumulate,
                      hipStream_t s);
-int launch_xr(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xlo, int64_t ld, int W, int64_t n,
-              const double* r, double* R, double* Rp, hipStream_t s, int f0 = 0);
-constexpr int kXrPartials = 32;   // sample-block groups of the split-BF16 X r (workspace kXrPartials * W * 3)
 // chol.hip
 int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, double* A, int* dflag, double* dscal,
                 hipStream_t s);
 int chol_solve(bem_ctx* ctx, const double* A, int64_t P, double* B, int nrhs, hipStream_t s);
 // lm.hip
 int fill_i32(bem_ctx* ctx, int* p, int64_t n, int v, hipStream_t s);
+int scale_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s);
 int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, const double* T, bem_lm_state* st,
                 int gram, bool mixed, hipStream_t s);
 

@@ -3,8 +3,6 @@
 // k_gemm_f64_mfma: 128 x 128 (or 64 x 64) output tiles on float64 MFMA (v_mfma_f64_16x16x4f64), 16-deep
 //   k slabs staged through LDS (double buffered, the next slab prefetched into registers while
 //   the current one is multiplied); also the float64 Gram restricted to a list of output tiles.
-// k_gemm_skinny: products with at most 4 columns (J^T r of the float64 Gram path): a wavefront
-//   per output row streaming the row of A, a wavefront reduction at the end.
 // k_gemm_f64: the plain VALU product (64 x 64 tiles, 4 x 4 outputs per thread), kept for the
 //   float64 VALU Gram mode.
 #include "common.hpp"
@@ -208,37 +206,6 @@ __global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m,
             }
 }
 
-// ---- products with at most kSkinnyMaxN columns ---------------------------------------------
-// C[r][j] = alpha sum_t A[r][t] op(B)[t][j] + beta C[r][j]: a wavefront per row r (4 per block),
-// lanes striding over t, then a wavefront reduction (fixed order, reproducible).
-constexpr int kSkinnyMaxN = 4;
-__global__ void __launch_bounds__(256) k_gemm_skinny(int m, int n, int k, double alpha, const double* __restrict__ A,
-                                                     int64_t lda, const double* __restrict__ B, int64_t ldb, int tb,
-                                                     double beta, double* __restrict__ C, int64_t ldc)
-{
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
-    if (r >= m) return;
-    double acc[kSkinnyMaxN] = {0.0, 0.0, 0.0, 0.0};
-    const double* a = A + (size_t)r * lda;
-    for (int t = l; t < k; t += 64) {
-        const double v = a[t];
-#pragma unroll
-        for (int j = 0; j < kSkinnyMaxN; ++j)
-            if (j < n) acc[j] += v * (tb ? B[(size_t)j * ldb + t] : B[(size_t)t * ldb + j]);
-    }
-#pragma unroll
-    for (int j = 0; j < kSkinnyMaxN; ++j)
-        for (int off = 32; off > 0; off >>= 1) acc[j] += __shfl_xor(acc[j], off, 64);
-    if (l < n) {
-        double v = acc[0];
-#pragma unroll
-        for (int j = 1; j < kSkinnyMaxN; ++j)
-            if (l == j) v = acc[j];
-        double* o = C + (size_t)r * ldc + l;
-        *o = alpha * v + (beta == 0.0 ? 0.0 : beta * *o);
-    }
-}
-
 }  // namespace
 
 // C + part cstride = alpha op(A) op(B) + beta C over the k range of each part, on the 128 x 128 output
@@ -264,10 +231,7 @@ int gemm_f64(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, i
         return check_launch(ctx, "gemm_f64");
     }
     const auto count = [&](int bm) { return 8 * blocks_for(blocks_for(n, bm), 8) * blocks_for(m, bm); };
-    if (n <= kSkinnyMaxN && !ta) {
-        hipLaunchKernelGGL(k_gemm_skinny, dim3(blocks_for(m, 4)), dim3(256), 0, s, m, n, k, alpha, A, lda, B, ldb,
-                           tb ? 1 : 0, beta, C, ldc);
-    } else if ((int64_t)blocks_for(n, kMB) * blocks_for(m, kMB) >= 1024) {
+    if ((int64_t)blocks_for(n, kMB) * blocks_for(m, kMB) >= 1024) {
         const int nw = count(kMB);
         hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(8 * ((nw + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
                            ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr, nw, k, (int64_t)0);

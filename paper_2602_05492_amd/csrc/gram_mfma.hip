@@ -11,14 +11,14 @@
 // across tiles and parts (the epilogue adds into the float64 Gram of the part).
 // The A and B operands of every MFMA come from rows of the same matrix with the
 // same lane -> (row, k-slot) assignment, so each k of the slab is summed once.
-#include "common.hpp"
-#include "sweep_common.hpp"
+#include "normal.hpp"
 
 namespace bem {
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
@@ -130,17 +130,79 @@ __global__ void __launch_bounds__(256) k_gram_f32(const float* __restrict__ X, i
 // load instruction fills 1 KiB of LDS (16 rows) in lane order, so each lane
 // fetches the global chunk whose swizzled position is its own.
 constexpr int G2_T = 256, G2_BK = 32;
+constexpr int kCellColumns = 64;
 
 __device__ inline int g2_lds(int r, int c)   // element offset of chunk c of row r in one slab
 {
     return (r << 5) + ((c ^ (((r >> 1) ^ (r >> 2)) & 3)) << 3);
 }
 
+// Three uses (Mode):
+//   kGramSamples  bfloat16 pairs of all samples.
+//   kGramHalf     float16 pairs of rows scaled by powers of two (rscale [row] undoes them): 22 bits instead of 16,
+//                 for the 64 columns a cell that stand for its samples (jtj_cells.hip), whose rounding
+//                 averages over fewer columns.  With bfloat16 pairs the LM step of 8,192 segments was 2.3e-4
+//                 from the float64 step, against 5.4e-5 from all samples.
+//   kGramCells    bfloat16 pairs of the near rows of grid cells (jtj_cells.hip).  A work entry is (cell,
+//                 row tile, column tile) of the cell's near tile E [n / 32][rows][32]; the cell's 64 projected
+//                 columns Z follow its samples, negated on the column side (E E^T - Z Z^T), as three terms
+//                 h + m + l of bfloat16 (24 bits): a stage multiplies (a, b) (c, d) as ac + ad + bc, so the pairs
+//                 (h, m)(h, l), (h, m)(m, 0), (l, 0)(h, 0) give hh + hl + mh + hm + mm + lh.  The sums are added
+//                 into the entries of the whole Gram that the cell's rows map to (float64 atomics; cells are
+//                 spread over the partial Grams).
+enum { kGramSamples, kGramHalf, kGramCells };
+struct CellGram {
+    const uint16_t* zt[5];                                 // Z: h, m, l, zeros; and -Z: h (m, l follow at zstep)
+    int64_t zstep;
+    const CellInfo* ci;
+    const int *hl, *el;
+    int nc, H, M, parts;
+    Layout L;
+    int64_t W;
+};
+
+// Row of the whole Gram of near row i of a cell, and its channel (-1: shared by the channels)
+__device__ inline int cell_row(const CellGram& cg, int c, const CellInfo& q, int i, int& ch)
+{
+    const int gh = cg.L.G * q.nh;
+    ch = -1;
+    if (i < 3 * gh) {
+        ch = i / gh;
+        const int r = i - ch * gh;
+        return ch * (int)cg.L.Gp + cg.L.G * cg.hl[(size_t)c * cg.H + r / cg.L.G] + r % cg.L.G;
+    }
+    i -= 3 * gh;
+    if (i < cg.L.C * q.nh) return 3 * (int)cg.L.Gp + cg.L.C * cg.hl[(size_t)c * cg.H + i / cg.L.C] + i % cg.L.C;
+    return (int)cg.L.handle_rows() + cg.el[(size_t)c * cg.M + (i - cg.L.C * q.nh)];
+}
+
+template <int Mode>
+__device__ inline floatx16 mfma_pair(bf16x8 a, bf16x8 b, floatx16 c)
+{
+    if constexpr (Mode == kGramHalf)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// First (i = 0) or second member of the pair that operand ab (0 rows: Z, 1 columns: -Z) takes in pass z
+__device__ inline const uint16_t* z_term(const CellGram& cg, int ab, int i, int z)
+{
+    // terms 0 h, 1 m, 2 l, 3 zeros: rows (h, m), (h, m), (l, 0), columns (h, l), (m, 0), (h, 0)
+    const int first = ab == 0 ? (z == 2 ? 2 : 0) : (z == 1 ? 1 : 0);
+    const int second = ab == 0 ? (z == 2 ? 3 : 1) : (z == 0 ? 2 : 3);
+    const int t = i == 0 ? first : second;
+    return t == 3 ? cg.zt[3] : (ab == 0 ? cg.zt[t] : cg.zt[4] + t * cg.zstep);
+}
+
+template <int Mode>
 __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restrict__ Xh, const uint16_t* __restrict__ Xl,
                                                          int W, int n_all, const int* __restrict__ work,
                                                          int nwork, int kchunk, double* __restrict__ G,
-                                                         int64_t gstride, int accumulate)
+                                                         int64_t gstride, int accumulate, const float* __restrict__ rscale,
+                                                         CellGram cg)
 {
+    constexpr bool Cells = Mode == kGramCells;
     __shared__ __attribute__((aligned(16))) uint16_t sm0[4][G2_T * G2_BK];   // [A hi, A lo, B hi, B lo]
     __shared__ __attribute__((aligned(16))) uint16_t sm1[4][G2_T * G2_BK];
     const int wi = work_index(nwork);
@@ -148,13 +210,27 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int li = lane & 31, lk = lane >> 5;
-    const int row0 = work[3 * wi] * G2_T;
-    const int col0 = work[3 * wi + 1] * G2_T;
+    const int row0 = work[3 * wi + (Cells ? 1 : 0)] * G2_T;
+    const int col0 = work[3 * wi + (Cells ? 2 : 1)] * G2_T;
     // samples [kb, n) of this entry's part; partial Gram of the part
-    const int kb = work[3 * wi + 2] * kchunk;
-    const int n = kb + kchunk < n_all ? kb + kchunk : n_all;
-    G += (int64_t)work[3 * wi + 2] * gstride;
-    if (kb >= n) {                                         // part beyond a ragged last tile
+    const int cell = Cells ? work[3 * wi] : 0;
+    const int kb = Cells ? 0 : work[3 * wi + 2] * kchunk;
+    int n = kb + kchunk < n_all ? kb + kchunk : n_all;
+    int nE = 0;                                            // stages from here on are projected columns
+    int64_t zoff = 0;
+    if constexpr (Cells) {
+        const CellInfo q = cg.ci[cell];
+        W = q.rows;
+        Xh += q.eoff;
+        Xl += q.eoff;
+        nE = (q.n + 31) & ~31;
+        n = nE + (cell < cg.nc ? 3 * kCellColumns : 0);    // the samples outside the grid have none
+        zoff = (int64_t)q.rb * kCellColumns;
+        G += (int64_t)(cell % cg.parts) * gstride;
+    } else {
+        G += (int64_t)work[3 * wi + 2] * gstride;
+    }
+    if (!Cells && kb >= n) {                                         // part beyond a ragged last tile
         if (!accumulate) zero_tile(G, row0, col0, G2_T, W);
         return;
     }
@@ -175,14 +251,19 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
     }
 #define G2_LOAD_STAGE(SM, K0)                                                                  \
     {                                                                                          \
-        const int kb_ = ((K0) >> 5) * W32;                                                     \
-        _Pragma("unroll") for (int ab = 0; ab < 2; ++ab)                                       \
-        _Pragma("unroll") for (int j = 0; j < 2; ++j) {                                        \
-            const int d_ = (wave + 8 * j) * 16 * 32;                                           \
-            __builtin_amdgcn_global_load_lds((const void*)(Xh + kb_ + gsrc[ab][j]),            \
-                                             (void*)&SM[2 * ab][d_], 16, 0, 0);                \
-            __builtin_amdgcn_global_load_lds((const void*)(Xl + kb_ + gsrc[ab][j]),            \
-                                             (void*)&SM[2 * ab + 1][d_], 16, 0, 0);            \
+        const bool tail_ = Cells && (K0) >= nE;                                                \
+        const int z_ = tail_ ? ((K0) - nE) >> 6 : 0;       /* which pairs of the terms of Z */  \
+        const int kb_ = ((tail_ ? ((K0) - nE) & 63 : (K0)) >> 5) * W32;                        \
+        _Pragma("unroll") for (int ab = 0; ab < 2; ++ab) {                                     \
+            const uint16_t* h_ = (tail_ ? z_term(cg, ab, 0, z_) + zoff : Xh) + kb_;            \
+            const uint16_t* l_ = (tail_ ? z_term(cg, ab, 1, z_) + zoff : Xl) + kb_;            \
+            _Pragma("unroll") for (int j = 0; j < 2; ++j) {                                    \
+                const int d_ = (wave + 8 * j) * 16 * 32;                                       \
+                __builtin_amdgcn_global_load_lds((const void*)(h_ + gsrc[ab][j]),              \
+                                                 (void*)&SM[2 * ab][d_], 16, 0, 0);            \
+                __builtin_amdgcn_global_load_lds((const void*)(l_ + gsrc[ab][j]),              \
+                                                 (void*)&SM[2 * ab + 1][d_], 16, 0, 0);        \
+            }                                                                                  \
         }                                                                                      \
     }
     // operand read offsets: rows of this lane, chunk 2 * h + lk for half h of the stage.  Rows 32 m
@@ -207,9 +288,9 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
     bl = __builtin_bit_cast(bf16x8, *(const u16x8*)&SM[3][boff[h] + 1024 * (nj)]);
 #define G2_STEP(ah, al, bh, bl, nj)                                                           \
     _Pragma("unroll") for (int mi = 0; mi < 2; ++mi) {                                        \
-        acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[mi], bh, acc[mi][nj], 0, 0, 0); \
-        acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[mi], bl, acc[mi][nj], 0, 0, 0); \
-        acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[mi], bh, acc[mi][nj], 0, 0, 0); \
+        acc[mi][nj] = mfma_pair<Mode>(ah[mi], bh, acc[mi][nj]);                               \
+        acc[mi][nj] = mfma_pair<Mode>(ah[mi], bl, acc[mi][nj]);                               \
+        acc[mi][nj] = mfma_pair<Mode>(al[mi], bh, acc[mi][nj]);                               \
     }
 // order inside a step: its LDS reads (for the next step) first, then its 6 MFMAs; no
 // instruction crosses a step boundary
@@ -275,6 +356,32 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
 #undef G2_HEAD
 #undef G2_BODY
 #undef G2_TURN
+    if constexpr (Cells) {
+        // rows and channels of the tile's rows (then columns) in the whole Gram, in the first operand buffer
+        __syncthreads();
+        int* map = (int*)&sm0[0][0];
+        const CellInfo q = cg.ci[cell];
+        const int i = (tid < G2_T ? row0 : col0 - G2_T) + tid;
+        int ch = -1;
+        map[tid] = i < W ? cell_row(cg, cell, q, i, ch) : -1;
+        map[2 * G2_T + tid] = ch;
+        __syncthreads();
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int nj = 0; nj < 4; ++nj) {
+                const int jl = wc * 128 + 32 * nj + li, gj = map[G2_T + jl], cj = map[3 * G2_T + jl];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int il = wr * 64 + 32 * mi + 4 * lk + 8 * (r >> 2) + (r & 3);
+                    const int gi = map[il], ci = map[2 * G2_T + il];
+                    // the upper triangle of each channel and of the shared rows (row order is kept by the map)
+                    if (gi >= 0 && gj >= gi && (ci < 0 || cj < 0 || ci == cj))
+                        atomicAdd(G + (int64_t)gi * cg.W + gj, (double)acc[mi][nj][r]);
+                }
+            }
+        return;
+    }
     // epilogue: G += acc (G = acc for the first sample tile).  A tile inside the matrix reads its 16
     // values of an MFMA tile in one batch (one wait instead of 16); tiles at the matrix edge go
     // element by element.
@@ -285,6 +392,18 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
         for (int nj = 0; nj < 4; ++nj) {
             const int ib = row0 + wr * 64 + 32 * mi + 4 * lk;
             const int j = col0 + wc * 128 + 32 * nj + li;
+            if constexpr (Mode == kGramHalf) {             // undo the rows' scales (powers of two)
+                const float sj = j < W ? rscale[j] : 0.0f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int i = ib + 8 * (r >> 2) + (r & 3);
+                    if (i < W && j < W) {
+                        double* g = G + (int64_t)i * W + j;
+                        *g = (accumulate ? *g : 0.0) + (double)acc[mi][nj][r] * ((double)sj * (double)rscale[i]);
+                    }
+                }
+                continue;
+            }
             if (inside) {
                 double* g = G + (int64_t)ib * W + j;
                 double v[16];
@@ -303,80 +422,6 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
         }
 }
 
-// R[f][c] += sum_t X[f][t] r[t][c]  (float64 sums; float rows of stride ld)
-__global__ void __launch_bounds__(256) k_xr_f32(const float* __restrict__ X, int64_t ld, int64_t n,
-                                                const double* __restrict__ r, double* __restrict__ R, int f0)
-{
-    __shared__ double red[3][256];
-    const int64_t f = f0 + (int64_t)blockIdx.x;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int64_t t = threadIdx.x; t < n; t += blockDim.x) {
-        const double v = (double)X[f * ld + t];
-        s0 += v * r[3 * t]; s1 += v * r[3 * t + 1]; s2 += v * r[3 * t + 2];
-    }
-    red[0][threadIdx.x] = s0; red[1][threadIdx.x] = s1; red[2][threadIdx.x] = s2;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st)
-            for (int c = 0; c < 3; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int c = 0; c < 3; ++c) R[f * 3 + c] += red[c][0];
-}
-
-// Blocked split-bfloat16 tile: partial sums over sample-block group g,
-// Rp[g][f][c] = sum over the group's samples of (hi + lo)[f][t] r[t][c].  A
-// wavefront reads 16 rows x 4 chunks of 8 samples of one 32-sample block (1 KiB
-// contiguous); the 4 chunk lanes of a row are summed by shuffles.
-constexpr int kXrGroups = kXrPartials;
-
-__global__ void __launch_bounds__(256) k_xr_bf16(const uint16_t* __restrict__ Xh, const uint16_t* __restrict__ Xl, int W,
-                                                 int64_t n, int64_t blocks_per_group, const double* __restrict__ r,
-                                                 double* __restrict__ Rp, int f0)
-{
-    const int lane = threadIdx.x & 63;
-    const int f = f0 + blockIdx.x * 64 + (threadIdx.x >> 6) * 16 + (lane >> 2);
-    const int cq = lane & 3;
-    const int64_t nb = (n + 31) / 32;
-    const int64_t b0 = (int64_t)blockIdx.y * blocks_per_group;
-    const int64_t b1 = b0 + blocks_per_group < nb ? b0 + blocks_per_group : nb;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    if (f < W) {
-        for (int64_t b = b0; b < b1; ++b) {
-            const size_t i = (size_t)b * ((size_t)W << 5) + ((size_t)f << 5) + (size_t)(cq << 3);
-            const u16x8 h = *(const u16x8*)(Xh + i);
-            const u16x8 l = *(const u16x8*)(Xl + i);
-            const int64_t t0 = b * 32 + cq * 8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int64_t t = t0 + e;
-                if (t < n) {
-                    const double v = (double)__uint_as_float((uint32_t)h[e] << 16) +
-                                     (double)__uint_as_float((uint32_t)l[e] << 16);
-                    s0 += v * r[3 * t]; s1 += v * r[3 * t + 1]; s2 += v * r[3 * t + 2];
-                }
-            }
-        }
-    }
-    s0 += __shfl_xor(s0, 1); s1 += __shfl_xor(s1, 1); s2 += __shfl_xor(s2, 1);
-    s0 += __shfl_xor(s0, 2); s1 += __shfl_xor(s1, 2); s2 += __shfl_xor(s2, 2);
-    if (cq == 0 && f < W) {
-        double* o = Rp + ((size_t)blockIdx.y * W + f) * 3;
-        o[0] = s0; o[1] = s1; o[2] = s2;
-    }
-}
-
-// R[f][c] += sum_g Rp[g][f][c] (fixed order), rows f >= f0
-__global__ void k_xr_finish(const double* __restrict__ Rp, int W, int groups, double* __restrict__ R, int f0)
-{
-    const int i = 3 * f0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 3 * W) return;
-    double v = 0.0;
-    for (int g = 0; g < groups; ++g) v += Rp[(size_t)g * 3 * W + i];
-    R[i] += v;
-}
-
 }  // namespace
 
 // G[part] += X X^T over the work entries (row tile, column tile, part): part p covers
@@ -393,8 +438,8 @@ int launch_gram_mfma(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xl
             ProfScope ps_(ctx, PT_GRAM_MFMA, s);
             // blocked tile (ld unused); element offsets inside one operand array are 32-bit
             // (W * tile rows < 2^31 is checked by the caller)
-            hipLaunchKernelGGL(k_gram_bf16x3_lds, dim3(grid), dim3(512), 0, s, (const uint16_t*)Xhi, Xlo, W, (int)n,
-                               work, nwork, (int)kchunk, G, gstride, accumulate ? 1 : 0);
+            hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramSamples>, dim3(grid), dim3(512), 0, s, (const uint16_t*)Xhi, Xlo, W, (int)n,
+                               work, nwork, (int)kchunk, G, gstride, accumulate ? 1 : 0, (const float*)nullptr, CellGram{});
         }
     else
         {
@@ -405,25 +450,29 @@ int launch_gram_mfma(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xl
     return check_launch(ctx, "gram_mfma");
 }
 
-// R += X r over one sample tile for the rows [f0, W); Rp is a workspace of kXrGroups * W * 3 doubles
-// (split-BF16 only).
-int launch_xr(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xlo, int64_t ld, int W, int64_t n,
-              const double* r, double* R, double* Rp, hipStream_t s, int f0)
+// G = Y Y^T (G += with accumulate) of float16 pairs of scaled rows over n columns (blocked tile, work entries with parts)
+int launch_gram_half(bem_ctx* ctx, const uint16_t* Yh, const uint16_t* Yl, int W, int64_t n, const float* rscale,
+                     const int* work, int nwork, int64_t kchunk, double* G, int64_t gstride, bool accumulate,
+                     hipStream_t s)
 {
-    if (n <= 0 || f0 >= W) return BEM_OK;
-    ProfScope ps_(ctx, PT_XR, s);
-    const int rows = W - f0;
-    if (gram == BEM_GRAM_BF16X3_MFMA) {
-        const int64_t nb = (n + 31) / 32;
-        const int64_t per = (nb + kXrGroups - 1) / kXrGroups;
-        hipLaunchKernelGGL(k_xr_bf16, dim3((rows + 63) / 64, kXrGroups), dim3(256), 0, s, (const uint16_t*)Xhi, Xlo, W,
-                           n, per, r, Rp, f0);
-        hipLaunchKernelGGL(k_xr_finish, dim3((3 * rows + 255) / 256), dim3(256), 0, s, (const double*)Rp, W, kXrGroups,
-                           R, f0);
-    } else {
-        hipLaunchKernelGGL(k_xr_f32, dim3(rows), dim3(256), 0, s, (const float*)Xhi, ld, n, r, R, f0);
-    }
-    return check_launch(ctx, "xr");
+    ProfScope ps_(ctx, PT_GRAM_MFMA, s);
+    hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramHalf>, dim3(8 * ((nwork + 7) / 8)), dim3(512), 0, s, Yh, Yl, W, (int)n, work,
+                       nwork, (int)kchunk, G, gstride, accumulate ? 1 : 0, rscale, CellGram{});
+    return check_launch(ctx, "gram_half");
+}
+
+// G += E E^T - Z Z^T of the cells' near rows, into the partial Grams.  Z: the terms h, m, l of Z, zeros, and
+// those of -Z, each zstep elements after the one before
+int launch_gram_cells(bem_ctx* ctx, const uint16_t* Eh, const uint16_t* El, const uint16_t* Z, int64_t zstep,
+                      const CellInfo* ci, int nc, const int* hl, const int* el, int H, int M, const Layout& L, int64_t W,
+                      const int* work, int nwork, double* G, int64_t gstride, hipStream_t s)
+{
+    if (nwork <= 0) return BEM_OK;
+    ProfScope ps_(ctx, PT_GRAM_MFMA, s);
+    const CellGram cg{{Z, Z + zstep, Z + 2 * zstep, Z + 3 * zstep, Z + 4 * zstep}, zstep, ci, hl, el, nc, H, M, kGramParts, L, W};
+    hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramCells>, dim3(8 * ((nwork + 7) / 8)), dim3(512), 0, s, Eh, El, 0, 0, work, nwork,
+                       0, G, gstride, 1, (const float*)nullptr, cg);
+    return check_launch(ctx, "gram_cells");
 }
 
 }  // namespace bem

@@ -11,20 +11,16 @@
 // C = 2 (the constant wd and wc).
 // Sample tiles of feature rows Xt = [g_1 | g_2 | g_3 | e | beta] (feature-major,
 // W = (3G + C)H + M rows) are formed by the feature kernels and contracted into the
-// Gram G = sum_x Xt Xt^T (only the blocks the three channels need), and into
-// R = sum_x Xt r.  Afterwards, per channel,
+// Gram G = sum_x Xt Xt^T (only the blocks the three channels need).  Afterwards, per channel,
 //   J^T J += E_c^T A_c E_c + sym(E_c^T B_c Z_c') + Z_c'^T D Z_c'
-// with A_c, B_c, D the channel's blocks of G, and J^T r likewise.
+// with A_c, B_c, D the channel's blocks of G.  J^T r is the adjoint's (vjp.hip).
 #include <algorithm>
 #include <cstring>
 #include <tuple>
 #include <type_traits>
 #include <vector>
 
-#include <cstring>
-
-#include "common.hpp"
-#include "sweep_common.hpp"
+#include "normal.hpp"
 
 namespace bem {
 
@@ -34,14 +30,6 @@ constexpr double kGaussNode = 0.77459666924148337703585307995647992;
 constexpr double kGaussW0 = 5.0 / 9.0, kGaussW1 = 8.0 / 9.0;
 
 // ---- output element types of the feature kernels ------------------------------
-__device__ inline uint16_t bf16_bits(float v)
-{
-    // round to nearest even (inputs are finite)
-    const uint32_t u = __float_as_uint(v);
-    return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-__device__ inline float bf16_value(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
 // Feature element (f, t) of a tile.  float64 / float32 tiles are row-major with
 // row stride ld; the split-bfloat16 tile is stored in blocks of 32 samples,
 // [t / 32][f][t % 32] with ld = the number of rows, so that one 32-sample stage
@@ -105,122 +93,6 @@ __global__ void k_zero_pad(OutT* __restrict__ Xt, uint16_t* __restrict__ Xlo, in
     Store<OutT>::put(Xt, Xlo, (r / pad) * gp + gh + r % pad, t, ld, 0.0);
 }
 
-// ---- J^T r of the handle rows, formed with the features -------------------------------
-// Per (sample, handle) the products of its feature rows with the sample's residuals:
-// v[8 c + q] = geo[c][q] r_c (the channel-c geometry rows), v[24 + 3 m + c] = col[m] r_c (the
-// channel-shared colour rows against each channel's residual): 36 values, summed over the 256
-// samples of a block in float32 (wavefront reduction, then the 4 wavefronts through LDS) and
-// stored per block; k_jtr_handles adds the blocks in float64.
-constexpr int kJtrVals = 36;
-
-// Sum of v over the 64 lanes of a wavefront for v[0..31] by recursive halving (after the steps
-// with offsets 32, 16, 8, 4, 2 lane l holds the sum over its half-wavefront of v[(l >> 1) & 31],
-// the offset-1 step completes it), and for v[32..35] by butterflies; the 4 wavefronts' sums are
-// then added through LDS and written to out[0..35].
-template <class A>
-__device__ inline void handle_jtr_block(const A (&geo)[3][8], const A (&col)[4], float r0, float r1, float r2,
-                                        float (*red)[kJtrVals], float* __restrict__ out)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float v[32];
-    float e[4];
-    const float r[3] = {r0, r1, r2};
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[8 * c + q] = (float)geo[c][q] * r[c];
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const int i = 24 + 3 * m + c;
-            const float p = (float)col[m] * r[c];
-            if (i < 32) v[i] = p;
-            else e[i - 32] = p;
-        }
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const int half = 16 >> k, o = 32 >> k;
-        const bool up = (lane & o) != 0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (i < half) {
-                const float keep = up ? v[i + half] : v[i];
-                const float send = up ? v[i] : v[i + half];
-                v[i] = keep + __shfl_xor(send, o, 64);
-            }
-        }
-    }
-    v[0] += __shfl_xor(v[0], 1, 64);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int k = 0; k < 6; ++k) e[i] += __shfl_xor(e[i], 32 >> k, 64);
-    if ((lane & 1) == 0) red[wave][(lane >> 1) & 31] = v[0];
-    if (lane < 4) red[wave][32 + lane] = e[lane];
-    __syncthreads();
-    if (threadIdx.x < kJtrVals)
-        out[threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-}
-
-// Feature row of product v of handle h (cubic: rows as store_handle_rows; straight: geometry q < 4,
-// the colour products of m = 0, 1 (wd) and m = 2, 3 (wc) go to the one constant-jump row) and its
-// channel; -1 for a product that has no row (straight geometry q >= 4).
-__host__ __device__ inline int64_t jtr_row(int model, int v, int h, int64_t gp, int* c)
-{
-    if (v < 24) {
-        const int cc = v / 8, q = v % 8;
-        *c = cc;
-        if (model == 1) return q < 4 ? (int64_t)cc * gp + 4 * h + q : -1;
-        return (int64_t)cc * gp + 8 * h + q;
-    }
-    const int m = (v - 24) / 3;
-    *c = (v - 24) % 3;
-    if (model == 1) return 3 * gp + 2 * h + (m >> 1);
-    return 3 * gp + 4 * h + m;
-}
-
-// R[row][c] += sum over the tile's blocks of rpart[block][h][v] (float64, fixed order): a block per
-// handle h, lane v of each wavefront a product, the 4 wavefronts splitting the blocks (b = w mod 4)
-// and adding their partial sums in a fixed order through LDS.  For straight handles the two
-// products that share a row are added by the lane of the first (m even) of them.
-__global__ void __launch_bounds__(256) k_jtr_handles(const float* __restrict__ rpart, int nblocks, int H, int model,
-                                                     int64_t gp, double* __restrict__ R)
-{
-    __shared__ double part[4][kJtrVals];
-    const int h = blockIdx.x;
-    const int v = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double acc = 0.0;
-    if (v < kJtrVals)
-        for (int b = wave; b < nblocks; b += 4) acc += (double)rpart[((size_t)b * H + h) * kJtrVals + v];
-    if (v < kJtrVals) part[wave][v] = acc;
-    __syncthreads();
-    if (wave != 0 || v >= kJtrVals) return;
-    int c;
-    const int64_t row = jtr_row(model, v, h, gp, &c);
-    if (row < 0) return;
-    const bool pair = model == 1 && v >= 24 && (((v - 24) / 3) & 1) == 0;   // m even: also take m + 1
-    if (model == 1 && v >= 24 && !pair) return;
-    double tot = (part[0][v] + part[1][v]) + (part[2][v] + part[3][v]);
-    if (pair) tot += (part[0][v + 3] + part[1][v + 3]) + (part[2][v + 3] + part[3][v + 3]);
-    R[row * 3 + c] += tot;
-}
-
-// J^T r of one flagged sample's handle rows (the inline kernel): float64 atomics into R.
-template <class A>
-__device__ inline void handle_jtr_atomic(int model, int h, int64_t gp, const A (&geo)[3][8], const A (&col)[4],
-                                         const float* rr, double* __restrict__ R)
-{
-#pragma unroll
-    for (int v = 0; v < kJtrVals; ++v) {
-        int c;
-        const int64_t row = jtr_row(model, v, h, gp, &c);
-        if (row < 0) continue;
-        const double f = v < 24 ? (double)geo[v / 8][v % 8] : (double)col[(v - 24) / 3];
-        atomicAdd(R + row * 3 + c, f * (double)rr[c]);
-    }
-}
-
 // Handle features of one point and one handle (thread per (point, handle)):
 //   rows c*8H + 8h + 2j + d : d f_c / d P_{h,j,d}      (c = 0..2, j = 0..3, d = x, y)
 //   rows 24H + 4h + m       : coefficient of wd0, wd1, wc0, wc1 of handle h (any channel)
@@ -235,8 +107,7 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
                                                   const double* __restrict__ seg64, const float* __restrict__ seg32,
                                                   int H, int S, int model, int64_t gp, double eps2, float eps2f,
                                                   float near2, const uint8_t* __restrict__ only,
-                                                  OutT* __restrict__ Xt, uint16_t* __restrict__ Xlo, int64_t ld,
-                                                  const float* __restrict__ rr = nullptr, double* __restrict__ R = nullptr)
+                                                  OutT* __restrict__ Xt, uint16_t* __restrict__ Xlo, int64_t ld)
 {
     using A = typename std::conditional<Mixed, float, double>::type;
     const int h = blockIdx.y;
@@ -310,50 +181,30 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
             }
         }
         store_handle_rows(model, Xt, Xlo, H, h, t, ld, gp, geo, col);
-        if (rr) handle_jtr_atomic(model, h, gp, geo, col, rr + 3 * t, R);     // J^T r of a flagged sample
     }
 }
 
-// One (sample, segment) pair of the mixed feature kernel: its moments and its end-point gradient
-// matrix, chained into col and geo (V: the vertex table at the segment's a end).  With Test the
-// values are masked to zero where the pair is near or the segment degenerate (every lane takes the
-// same path, with no branch-local copies of the loop-carried sums).  Without Test (a group of
-// segments whose box is out of the wavefront's reach: every pair far) a degenerate segment still
-// gives zeros: its float32 record is a far point with v = 0 and kd = ks = 0.
-__device__ __forceinline__ void feature_pair(const float* __restrict__ s32, const float* __restrict__ V, float Xf,
-                                             float Yf, float eps2f, float near2, bool Test, float (&geo)[3][8],
-                                             float (&col)[4], float (&pv)[3][2])
+// One (sample, segment) pair of the mixed feature kernel by the closed forms: its moments and end-point
+// gradients, chained into col and geo (V: the vertex table at the segment's a end); nothing where !on.
+__device__ __forceinline__ void closed_pair_features(const float* __restrict__ s32, const float* __restrict__ V, float X,
+                                                     float Y, float eps2f, bool on, float (&geo)[3][8], float (&col)[4])
 {
-    const SegGeom<float> gf = load_geom(s32);
-    const PairState<float> st = pair_forward<float, DevF32, false>(gf, Xf, Yf, eps2f);
-    Moments<float> m = pair_moments(gf, st);
+    const SegGeom<float> g = load_geom(s32);
+    const PairState<float> st = pair_forward<float, DevF32, false>(g, X, Y, eps2f);
+    const Moments<float> m = pair_moments(g, st);
     // the end-point gradient is linear in the channel's end densities: one matrix per pair serves
     // the three channels
-    GradMatrix<float> G = pair_grad_matrix(gf, st, eps2f);
-    if (Test) {
-        const bool far = gf.L2 != 0.0f && !near_segment(gf.ax, gf.ay, gf.bx, gf.by, gf.L2, Xf, Yf, near2);
-        m.da = far ? m.da : 0.f;
-        m.db = far ? m.db : 0.f;
-        m.sa = far ? m.sa : 0.f;
-        m.sb = far ? m.sb : 0.f;
-        for (int r = 0; r < 4; ++r)
-            for (int k = 0; k < 4; ++k) G.g[r][k] = far ? G.g[r][k] : 0.f;
-    }
-    const float ta = V[4], sa_ = V[5];
-    const float tb = V[12], sb_ = V[13];
-    col[0] += m.da * sa_ + m.db * sb_;
-    col[1] += m.da * ta + m.db * tb;
-    col[2] += m.sa * sa_ + m.sb * sb_;
-    col[3] += m.sa * ta + m.sb * tb;
+    const GradMatrix<float> G = pair_grad_matrix(g, st, eps2f);
+    col[0] += on ? m.da * V[5] + m.db * V[13] : 0.f;
+    col[1] += on ? m.da * V[4] + m.db * V[12] : 0.f;
+    col[2] += on ? m.sa * V[5] + m.sb * V[13] : 0.f;
+    col[3] += on ? m.sa * V[4] + m.sb * V[12] : 0.f;
     for (int c = 0; c < 3; ++c) {
         const Grad4<float> gr = grad_apply(G, s32[kWdA + c], s32[kWdB + c], s32[kWcA + c], s32[kWcB + c]);
-        const float gx = gr.ax + pv[c][0], gy = gr.ay + pv[c][1];
         for (int q = 0; q < 4; ++q) {
-            geo[c][2 * q] += V[q] * gx;
-            geo[c][2 * q + 1] += V[q] * gy;
+            geo[c][2 * q] += on ? V[q] * gr.ax + V[8 + q] * gr.bx : 0.f;
+            geo[c][2 * q + 1] += on ? V[q] * gr.ay + V[8 + q] * gr.by : 0.f;
         }
-        pv[c][0] = gr.bx;
-        pv[c][1] = gr.by;
     }
 }
 
@@ -365,19 +216,20 @@ constexpr int kFeatVals = 28;   // chained contributions of one pair: geo[3][8] 
 // handle's entries in the wavefront's slice; the wavefront walks it with uniform
 // (scalar) loads and each lane takes the entries of its own sample.  x points at the
 // tile's first sample, whose global index is t0 (a multiple of 64); flagged samples
-// are rewritten afterwards by k_features<true>.
-template <class OutT>
-__global__ void __launch_bounds__(256, 6) k_features_far(const double* __restrict__ x, int64_t npts, int64_t t0,
+// are rewritten afterwards by k_features<true>.  The float32 pairs go by quadrature: cheaper than the closed
+// forms and their gradients, and without their cancellation at a distance, which beside a gradient from the
+// adjoint cost the full-size LM step (FP32 Gram) 8.6e-3 against 7.7e-4.  Band (near radius below two lengths): pairs
+// with both end points within two lengths keep the closed forms.
+template <bool Band, class OutT>
+__global__ void __launch_bounds__(256, Band ? 4 : 6) k_features_far(const double* __restrict__ x, int64_t npts, int64_t t0,
                                                       const float* __restrict__ seg32, int H, int S, int model,
                                                       int64_t gp, float eps2f,
                                                       float near2, const NearPair* __restrict__ list, int slots,
                                                       const int2* __restrict__ runs,
                                                       const uint8_t* __restrict__ flag, const float* __restrict__ corr,
                                                       const float* __restrict__ vtab, const float4* __restrict__ box,
-                                                      OutT* __restrict__ Xt, uint16_t* __restrict__ Xlo, int64_t ld,
-                                                      const float* __restrict__ rr, float* __restrict__ rpart)
+                                                      OutT* __restrict__ Xt, uint16_t* __restrict__ Xlo, int64_t ld)
 {
-    __shared__ float jtr_red[4][kJtrVals];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int h = blockIdx.y;
     const bool valid = t < npts;
@@ -385,7 +237,6 @@ __global__ void __launch_bounds__(256, 6) k_features_far(const double* __restric
     float col[4] = {0.f, 0.f, 0.f, 0.f};
     for (int c = 0; c < 3; ++c)
         for (int q = 0; q < 8; ++q) geo[c][q] = 0.f;
-    bool take = false;
     // the wavefront's sample box (every lane takes part in the reductions, so before the branch on
     // valid): groups of segments farther than their near radius take the loop without near tests
     // (handles of few segments keep every near test: there a box lookup per pair and the box itself
@@ -401,11 +252,6 @@ __global__ void __launch_bounds__(256, 6) k_features_far(const double* __restric
     }
     if (valid) {
         const float Xf = Xv, Yf = Yv;
-        // pv[c]: the b-end gradient of segment j - 1, carried to vertex j; each channel's a-end
-        // gradient is chained into geo as soon as it is formed, so that only one channel's
-        // end-point gradients are live at a time
-        float pv[3][2];
-        for (int c = 0; c < 3; ++c) pv[c][0] = pv[c][1] = 0.f;
         // test: whether the pairs need the near test (false once the segment's group of kBoxGroup
         // segments is out of the wavefront's reach; wave-uniform, looked up at each group's start)
         bool test = true;
@@ -413,18 +259,19 @@ __global__ void __launch_bounds__(256, 6) k_features_far(const double* __restric
         for (int j = 0; j < S; ++j) {
             const int k = h * S + j;
             if (cull && (j == 0 || k % kBoxGroup == 0)) test = !box_culled(box, k / kBoxGroup, wx0, wy0, wx1, wy1);
-            feature_pair(seg32 + (size_t)k * kSegStride, vtab + 8 * j, Xf, Yf, eps2f, near2, test, geo, col, pv);
-        }
-        {
-            const float* B = vtab + 8 * S;                  // the last vertex takes the carried b end
-            for (int c = 0; c < 3; ++c)
-                for (int q = 0; q < 4; ++q) {
-                    geo[c][2 * q] += B[q] * pv[c][0];
-                    geo[c][2 * q + 1] += B[q] * pv[c][1];
-                }
+            const float* s = seg32 + (size_t)k * kSegStride;
+            const float* V = vtab + 8 * j;
+            const bool on = !(test & near_segment(s[0], s[1], s[2], s[3], s[6], Xf, Yf, near2));
+            if (Band) {
+                const bool band = on & near_segment(s[0], s[1], s[2], s[3], s[6], Xf, Yf, 4.0f);
+                add_pair_features<6>(s, V, V + 8, Xf, Yf, eps2f, on & !band, geo, col);
+                if (__any(band)) closed_pair_features(s, V, Xf, Yf, eps2f, band, geo, col);
+            } else {
+                add_pair_features<6>(s, V, V + 8, Xf, Yf, eps2f, on, geo, col);
+            }
         }
         const int64_t i = t0 + t;
-        take = !flag[i];
+        const bool take = !flag[i];
         // the wavefront's index within the tile (the same for all its lanes, as t0 is a multiple of 64)
         const int wl = __builtin_amdgcn_readfirstlane((int)(t >> 6));
         const int2 run = runs[(size_t)wl * H + h];
@@ -439,18 +286,6 @@ __global__ void __launch_bounds__(256, 6) k_features_far(const double* __restric
             for (int q = 0; q < 4; ++q) col[q] += cr[24 + q];
         }
         store_handle_rows(model, Xt, Xlo, H, h, t, ld, gp, geo, col);
-    }
-    // with rr (the tile's residuals) the block also forms its part of J^T r over its samples and
-    // this handle's rows; every thread joins the reduction (samples past the tile and flagged
-    // samples, whose rows and J^T r the inline kernel rewrites, with zero residual)
-    if (rr) {
-        float r0 = 0.f, r1 = 0.f, r2 = 0.f;
-        if (valid && take) {
-            r0 = rr[3 * t];
-            r1 = rr[3 * t + 1];
-            r2 = rr[3 * t + 2];
-        }
-        handle_jtr_block(geo, col, r0, r1, r2, jtr_red, rpart + ((size_t)blockIdx.x * H + h) * kJtrVals);
     }
 }
 
@@ -598,93 +433,23 @@ __global__ void __launch_bounds__(256) k_beta_rows(const double* __restrict__ x,
 // at one chunk fall in different banks; 16 KiB, so that a block fits beside a Gram block.
 // Samples past npts in a written block are zeros.
 constexpr int kBetaRunBlocked = 16;
-constexpr int kBetaJtrVals = 3 * kBetaRunBlocked;   // 16 beta rows x 3 residual channels
-
-// J^T r of a block's beta rows: value 3 jj + c = sum over the block's 256 samples of
-// beta[jj] r_c, in float32.  Values 0..31 by recursive halving over the wavefront (lane l ends
-// with value (l >> 1) & 31 summed over its lane pair, the offset-1 step completes it), values
-// 32..47 likewise with four halving steps (lane l: value 32 + ((l >> 2) & 15)) and two
-// butterflies; the 4 wavefronts are added through LDS and values 0 .. nv-1 written to out.
-__device__ inline void beta_jtr_block(const float (&bv)[kBetaRunBlocked], float r0, float r1, float r2,
-                                      float (*red)[kBetaJtrVals], float* __restrict__ out, int nv)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float r[3] = {r0, r1, r2};
-    float v[32], e[16];
-#pragma unroll
-    for (int i = 0; i < kBetaJtrVals; ++i) {
-        const float p = bv[i / 3] * r[i % 3];
-        if (i < 32) v[i] = p;
-        else e[i - 32] = p;
-    }
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const int half = 16 >> k, o = 32 >> k;
-        const bool up = (lane & o) != 0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (i < half) {
-                const float keep = up ? v[i + half] : v[i];
-                const float send = up ? v[i] : v[i + half];
-                v[i] = keep + __shfl_xor(send, o, 64);
-            }
-        }
-    }
-    v[0] += __shfl_xor(v[0], 1, 64);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int half = 8 >> k, o = 32 >> k;
-        const bool up = (lane & o) != 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (i < half) {
-                const float keep = up ? e[i + half] : e[i];
-                const float send = up ? e[i] : e[i + half];
-                e[i] = keep + __shfl_xor(send, o, 64);
-            }
-        }
-    }
-    e[0] += __shfl_xor(e[0], 2, 64);
-    e[0] += __shfl_xor(e[0], 1, 64);
-    if ((lane & 1) == 0) red[wave][(lane >> 1) & 31] = v[0];
-    if ((lane & 3) == 0) red[wave][32 + ((lane >> 2) & 15)] = e[0];
-    __syncthreads();
-    if (threadIdx.x < nv)
-        out[threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-}
-
-// R[row0 + j][c] += sum over the tile's sample blocks b of bpart[b][j][c] (float64, fixed order):
-// a thread per (j, c).
-__global__ void __launch_bounds__(256) k_jtr_beta(const float* __restrict__ bpart, int nblocks, int M, int64_t row0,
-                                                  double* __restrict__ R)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 3 * M) return;
-    double acc = 0.0;
-    for (int b = 0; b < nblocks; ++b) acc += (double)bpart[(size_t)b * 3 * M + i];
-    R[row0 * 3 + i] += acc;
-}
 template <bool Mixed>
 __global__ void __launch_bounds__(256) k_beta_rows_blocked(const double* __restrict__ x, int64_t npts,
                                                            const double* __restrict__ el64,
                                                            const float* __restrict__ el32, int M, float near2,
                                                            uint16_t* __restrict__ Xh, uint16_t* __restrict__ Xl,
-                                                           int64_t ld, int64_t row0, const float* __restrict__ rr,
-                                                           float* __restrict__ bpart)
+                                                           int64_t ld, int64_t row0)
 {
     constexpr int R = kBetaRunBlocked;
     __shared__ __attribute__((aligned(16))) uint16_t sh[2][R][256];
-    __shared__ float jtr_red[4][kBetaJtrVals];
     const int64_t t0 = (int64_t)blockIdx.x * 256;
     const int64_t t = t0 + threadIdx.x;
     const int j0 = blockIdx.y * R, nj = M - j0 < R ? M - j0 : R;
     const bool live = t < npts;
     const double X = live ? x[2 * t] : 0.0, Y = live ? x[2 * t + 1] : 0.0;
     const float Xf = (float)X, Yf = (float)Y;
-    float bv[R];                                      // this sample's beta values (the J^T r products)
 #pragma unroll
     for (int jj = 0; jj < R; ++jj) {
-        bv[jj] = 0.0f;
         if (jj >= nj) continue;
         const int j = j0 + jj;
         const double* e = el64 + (size_t)j * kElemStride;
@@ -701,7 +466,6 @@ __global__ void __launch_bounds__(256) k_beta_rows_blocked(const double* __restr
             }
         }
         const float v = (float)b;
-        bv[jj] = v;
         const uint16_t h = bf16_bits(v);
         const int col = threadIdx.x ^ ((jj & 7) << 3);
         sh[0][jj][col] = h;
@@ -722,11 +486,6 @@ __global__ void __launch_bounds__(256) k_beta_rows_blocked(const double* __restr
         uint16_t* dst = (which ? Xl : Xh) + (size_t)((t0 >> 5) + sb) * (size_t)(ld << 5) +
                         (size_t)((row0 + j0 + jj) << 5) + c * 8;
         *reinterpret_cast<uint4*>(dst) = v;
-    }
-    // with residuals (mixed J^T r): the block's sums of beta r over its samples, rows j0 .. j0+nj-1
-    if (rr) {
-        const float r0 = live ? rr[3 * t] : 0.0f, r1 = live ? rr[3 * t + 1] : 0.0f, r2 = live ? rr[3 * t + 2] : 0.0f;
-        beta_jtr_block(bv, r0, r1, r2, jtr_red, bpart + ((size_t)blockIdx.x * M + j0) * 3, 3 * nj);
     }
 }
 
@@ -760,30 +519,6 @@ __global__ void k_fill(double* __restrict__ p, int64_t n, double v)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
-
-template <class T>
-__global__ void k_to_f64(const T* __restrict__ in, int64_t n, double* __restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (double)in[i];
-}
-
-// Feature layout of the normal equations: G geometry rows per handle and channel, C
-// channel-shared colour rows per handle, H handles (the rows of Xt are
-// [g_0 (GH) | g_1 | g_2 | e (CH) | beta (M)]).
-struct Layout {
-    int G, C, H;
-    int64_t Gp;     // rows of one channel's geometry block in Xt (G H rounded up to the Gram tile)
-    __host__ __device__ int64_t geo() const { return (int64_t)G * H; }
-    __host__ __device__ int64_t handle_rows() const { return 3 * Gp + (int64_t)C * H; }
-    __host__ __device__ int compact() const { return (G + C) * H; }
-    __host__ __device__ int params() const { return G + 3 * C; }
-    // row of Xt of compact index a of channel c ([g_c | e | beta])
-    __host__ __device__ int64_t row(int a, int c) const
-    {
-        return a < geo() ? (int64_t)c * Gp + a : 3 * Gp + (a - geo());
-    }
-};
 
 // Channel-c augmented Gram in compact order [g_c (GH) | e (CH) | beta (M)],
 // symmetric fill from the upper triangle of G.  The compact-to-row map is increasing, so
@@ -831,15 +566,6 @@ __global__ void k_gather_z(const double* __restrict__ Z, Layout L, int M, int c,
     const int n = L.compact();
     if (a >= n) return;
     Zc[(size_t)i * n + a] = Z[(size_t)i * L.handle_rows() + L.row(a, c)];
-}
-
-// theta column of compact index a of channel c: geometry (G per handle, shared by the
-// channels) first, then the colour parameters, 3 per colour coefficient (RGB)
-__device__ inline int64_t param_col(int a, Layout L, int c)
-{
-    if (a < L.geo()) return (int64_t)L.params() * (a / L.G) + (a % L.G);
-    const int b = a - (int)L.geo();
-    return (int64_t)L.params() * (b / L.C) + L.G + 3 * (b % L.C) + c;
 }
 
 // Every entry of J^T J from the three channels' blocks v_c(a, b) = Gc_c[a][b] + (S_c[a][b] +
@@ -893,27 +619,6 @@ __global__ void __launch_bounds__(256) k_scatter_jtj(const double* __restrict__ 
     }
 }
 
-// Jtr[col(a)] += s * (R[row(a)][c] + sum_i Zc[i][a] R[beta row i][c]): a block per 64 compact
-// indices a, its 4 wavefronts splitting the M beta rows (coalesced reads of Zc along a), the four
-// partial sums added in a fixed order through LDS.
-__global__ void __launch_bounds__(256) k_scatter_g(const double* __restrict__ R, const double* __restrict__ Zc,
-                                                   Layout L, int M, int c, double s, double* __restrict__ Jtr)
-{
-    __shared__ double part[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int a = blockIdx.x * 64 + lane;
-    const int n = L.compact();
-    const int64_t rb = L.handle_rows();
-    double v = 0.0;
-    if (a < n)
-        for (int i = wave; i < M; i += 4) v += Zc[(size_t)i * n + a] * R[(rb + i) * 3 + c];
-    part[wave][lane] = v;
-    __syncthreads();
-    if (wave == 0 && a < n)
-        Jtr[param_col(a, L, c)] += s * (R[(size_t)L.row(a, c) * 3 + c] + ((part[0][lane] + part[1][lane]) +
-                                                                            (part[2][lane] + part[3][lane])));
-}
-
 // J[n][c][p] assembly for the explicit Jacobian: features + beta . Z
 __global__ void k_assemble_jacobian(const double* __restrict__ Xt, int64_t ld, const double* __restrict__ BZ, Layout L,
                                     int64_t npts, double* __restrict__ J)
@@ -951,7 +656,7 @@ int fill_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s)
 }
 
 constexpr int64_t kGeoAlign = 256;   // the split-BF16 Gram's tile
-static Layout layout_of(const bem_ctx* ctx, int H)
+Layout layout_of(const bem_ctx* ctx, int H)
 {
     const int64_t gh = (int64_t)ctx->ngeo * H;
     // few handles: without the padding a tile mixes channels, but the padded rows would be most of the
@@ -967,14 +672,11 @@ static Layout layout_of(const bem_ctx* ctx, int H)
 // first global sample index t0 (a multiple of 64), the global samples xg and a
 // correction buffer of ceil(npts / 64) * nl->slots * 28 floats and a run table of
 // ceil(npts / 64) * H entries.
-// With rr (float residuals of the npts samples, mixed only) J^T r of the handle rows is added into
-// R [W][3] as the features are formed (block partial sums in rpart, ceil(npts / 256) * H * 36 floats).
 template <class OutT>
 static int launch_features(bem_ctx* ctx, const double* x, int64_t npts, int H, bool mixed, bool with_beta, OutT* Xt,
                            uint16_t* Xlo, int64_t ld, hipStream_t s, const NearList* nl = nullptr, int64_t t0 = 0,
                            const double* xg = nullptr, float* corr = nullptr, const float* vtab = nullptr,
-                           int2* runs = nullptr, const float* rr = nullptr, float* rpart = nullptr, double* R = nullptr,
-                           const float4* box = nullptr, float* bpart = nullptr)
+                           int2* runs = nullptr, const float4* box = nullptr)
 {
     if (npts == 0) return BEM_OK;
     const int S = ctx->opts.segs_per_handle;
@@ -999,17 +701,15 @@ static int launch_features(bem_ctx* ctx, const double* x, int64_t npts, int H, b
                                    nl->count, t0 >> 6, nw, H, S, runs);
             }
             ProfScope ps_(ctx, PT_FEATURES, s);
-            hipLaunchKernelGGL((k_features_far<OutT>), grid, dim3(256), 0, s, x, npts, t0, (const float*)ctx->seg32.ptr,
+            const auto far = nf < 2.0 ? k_features_far<true, OutT> : k_features_far<false, OutT>;
+            hipLaunchKernelGGL(far, grid, dim3(256), 0, s, x, npts, t0, (const float*)ctx->seg32.ptr,
                                H, S, model, gp, (float)eps2, near2, nl->list, nl->slots, (const int2*)runs, nl->flag, corr,
-                               vtab, box, Xt, Xlo, ld, rr, rpart);
-            if (rr)
-                hipLaunchKernelGGL(k_jtr_handles, dim3(H), dim3(256), 0, s, (const float*)rpart, (int)grid.x, H, model,
-                                   gp, R);
+                               vtab, box, Xt, Xlo, ld);
             const int fb = blocks_for(npts, 256) < 16 ? blocks_for(npts, 256) : 16;
             if (nl->overflowed)
                 hipLaunchKernelGGL((k_features<true, OutT>), dim3(fb, H), dim3(256), 0, s, x, npts, (const double*)ctx->seg64.ptr,
                                (const float*)ctx->seg32.ptr, H, S, model, gp, eps2, (float)eps2, near2, nl->flag + t0,
-                               Xt, Xlo, ld, rr, R);
+                               Xt, Xlo, ld);
         } else {
             ProfScope ps_(ctx, PT_FEATURES, s);
             hipLaunchKernelGGL((k_features<false, OutT>), grid, dim3(256), 0, s, x, npts, (const double*)ctx->seg64.ptr,
@@ -1024,19 +724,12 @@ static int launch_features(bem_ctx* ctx, const double* x, int64_t npts, int H, b
     if (with_beta && std::is_same<OutT, uint16_t>::value) {
         const dim3 gb(blocks_for(npts, 256), blocks_for(ctx->M, kBetaRunBlocked));
         ProfScope ps_(ctx, PT_BETA_ROWS, s);
-        // with residuals and a partials buffer (mixed J^T r) the beta rows' J^T r is summed here as well
-        const float* brr = mixed && rr && bpart && R ? rr : nullptr;
         if (mixed)
             hipLaunchKernelGGL((k_beta_rows_blocked<true>), gb, dim3(256), 0, s, x, npts, (const double*)ctx->elem64.ptr,
-                               (const float*)ctx->elem32.ptr, ctx->M, near2, (uint16_t*)Xt, Xlo, ld, beta_row0, brr,
-                               bpart);
+                               (const float*)ctx->elem32.ptr, ctx->M, near2, (uint16_t*)Xt, Xlo, ld, beta_row0);
         else
             hipLaunchKernelGGL((k_beta_rows_blocked<false>), gb, dim3(256), 0, s, x, npts, (const double*)ctx->elem64.ptr,
-                               (const float*)ctx->elem32.ptr, ctx->M, near2, (uint16_t*)Xt, Xlo, ld, beta_row0,
-                               (const float*)nullptr, (float*)nullptr);
-        if (brr)
-            hipLaunchKernelGGL(k_jtr_beta, dim3(blocks_for(3 * (int64_t)ctx->M, 256)), dim3(256), 0, s, (const float*)bpart,
-                               (int)gb.x, ctx->M, beta_row0, R);
+                               (const float*)ctx->elem32.ptr, ctx->M, near2, (uint16_t*)Xt, Xlo, ld, beta_row0);
     } else if (with_beta) {
         const dim3 gb(blocks_for(npts, 256), blocks_for(ctx->M, kBetaRun));
         if (mixed)
@@ -1055,7 +748,7 @@ static int launch_features(bem_ctx* ctx, const double* x, int64_t npts, int H, b
     return check_launch(ctx, "features");
 }
 
-// Z = A+ dF/dtheta in feature columns [M][(3G + C)H] -> ctx->tmp4 (also leaves Gauss features in tmp3)
+// also leaves Gauss features in tmp3
 int boundary_derivatives(bem_ctx* ctx, int H, hipStream_t s, double** Zout)
 {
     int rc;
@@ -1162,16 +855,73 @@ __global__ void __launch_bounds__(256) k_sum_parts(double* __restrict__ G, int p
 }
 }  // namespace
 
-int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, const void* resid, bool mixed,
-            int gram, double* JtJ, double* Jtr, hipStream_t s, const NearList* pre, double norm)
+// The work list lives on the device (tilew); it is uploaded when its configuration changes, the only host
+// synchronisation of bem_jtj apart from workspace growth.
+static int upload_tiles(bem_ctx* ctx, const std::vector<int>& tiles, int64_t W, int H, int gram, hipStream_t s)
+{
+    int rc;
+    const int64_t key[4] = {W, H, ctx->model, gram};
+    if (std::memcmp(key, ctx->tiles_key, sizeof(key)) == 0) return BEM_OK;
+    ctx->tiles_key[0] = -1;
+    if ((rc = ensure(ctx, ctx->tilew, tiles.size() * sizeof(int), s))) return rc;
+    if (hipMemcpyAsync(ctx->tilew.ptr, tiles.data(), tiles.size() * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)           // the host copy goes out of scope at the caller
+        return set_error(ctx, BEM_EHIP, "tile list upload");
+    std::memcpy(ctx->tiles_key, key, sizeof(key));
+    return BEM_OK;
+}
+
+int contract_gram(bem_ctx* ctx, int H, const Layout& L, int64_t W, double* G, int parts, int ts, const int* work, int nwork,
+                  const double* Z, double sc, double* JtJ, hipStream_t s)
+{
+    int rc;
+    const int M = ctx->M;
+    const int64_t P = (int64_t)L.params() * H;
+    const int n12 = L.compact();          // handle part of one channel's compact order
+    const int Wc = n12 + M;
+    if (parts > 1) {
+        // the first nwork / parts work entries are part 0's, one per tile of the list
+        hipLaunchKernelGGL(k_sum_parts, dim3(nwork / parts, 8), dim3(256), 0, s, G, parts, W, work, ts);
+        if ((rc = check_launch(ctx, "gram parts"))) return rc;
+    }
+    // contraction: per channel the compact Gram and S, then every entry of J^T J in one pass
+    const size_t wc2 = (size_t)Wc * Wc;
+    const size_t szc = (size_t)M * n12;
+    const size_t sn = (size_t)n12 * n12;
+    if ((rc = ensure(ctx, ctx->tmp2, (3 * wc2 + szc + 3 * sn) * sizeof(double), s))) return rc;
+    double* Gc3 = (double*)ctx->tmp2.ptr;
+    double* Zc = Gc3 + 3 * wc2;
+    double* S3 = Zc + szc;
+    for (int c = 0; c < 3; ++c) {
+        double* Gc = Gc3 + c * wc2;
+        double* S1 = S3 + c * sn;
+        hipLaunchKernelGGL(k_gather_gram, dim3(blocks_for(Wc, 32), blocks_for(Wc, 32)), dim3(256), 0, s, G, W, L, c,
+                           Wc, Gc);
+        hipLaunchKernelGGL(k_gather_z, dim3(blocks_for(n12, 256), M), dim3(256), 0, s, Z, L, M, c, Zc);
+        if ((rc = check_launch(ctx, "gather"))) return rc;
+        // The channel's block of J^T J is G + B Zc + (B Zc)^T + Zc^T D Zc with B = Gc[0:n12, n12:Wc]
+        // and D = Gc[n12:, n12:] (symmetric), which equals G + S + S^T with S = Y Zc and
+        // Y = B + (1/2) Zc^T D: two products instead of three.  Y overwrites B in Gc.
+        if ((rc = gemm_f64(ctx, n12, M, M, 0.5, Zc, n12, true, Gc + (size_t)n12 * Wc + n12, Wc, false, 1.0, Gc + n12, Wc, s,
+                           nullptr, 0)))
+            return rc;
+        if ((rc = gemm_f64(ctx, n12, n12, M, 1.0, Gc + n12, Wc, false, Zc, n12, false, 0.0, S1, n12, s, nullptr, 0))) return rc;
+    }
+    if (n12 > 0) {
+        hipLaunchKernelGGL(k_scatter_jtj, dim3(blocks_for(n12, 32), blocks_for(n12, 32)), dim3(256), 0, s, Gc3,
+                           (int64_t)wc2, Wc, S3, (int64_t)sn, L, sc, JtJ, P);
+        if ((rc = check_launch(ctx, "scatter"))) return rc;
+    }
+    return BEM_OK;
+}
+
+int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, bool mixed, int gram, double* JtJ,
+            hipStream_t s, const NearList* pre, double norm)
 {
     int rc;
     const int M = ctx->M;
     const Layout L = layout_of(ctx, H);
-    const int64_t P = (int64_t)L.params() * H;
     const int64_t W = L.handle_rows() + M;
-    const int n12 = L.compact();          // handle part of one channel's compact order
-    const int Wc = n12 + M;
     if (H == 0) return BEM_OK;
     if ((rc = launch_expand(ctx, theta, H, s))) return rc;
     double* Z = nullptr;
@@ -1228,49 +978,23 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     // deterministic (no atomics)
     const int ts = gram == BEM_GRAM_FP64_VALU ? 64 : (gram == BEM_GRAM_BF16X3_MFMA ? 256 : 128);
     const std::vector<int> out_tiles = gram_tiles(L, (int)W, ts);
-    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? 3
+    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? kGramParts
                       : gram == BEM_GRAM_FP64 ? f64_parts((int)out_tiles.size() / 2, W) : 1;
     const int64_t kchunk = ((T + parts - 1) / parts + 31) / 32 * 32;
     const bool overlap = shares && N > T;
     const size_t tile_bytes = ((size_t)W * T * elem + 255) / 256 * 256;
     hipStream_t sg = s;
     if (overlap && (rc = aux_stream(ctx, &sg))) return rc;
-    // tmp0: feature tile(s); tmp1: R [W][3] + G [parts][W][W] + X r partials; tmp2: residual in f64
+    // tmp0: feature tile(s); tmp1: G [parts][W][W]
     if ((rc = ensure(ctx, ctx->tmp0, tile_bytes * (overlap ? 2 : 1), s))) return rc;
-    if ((rc = ensure(ctx, ctx->tmp1,
-                     ((size_t)parts * W * W + (size_t)W * 3 + (size_t)kXrPartials * W * 3) * sizeof(double), s)))
-        return rc;
-    if ((rc = ensure(ctx, ctx->tmp2, (size_t)(N > 0 ? N : 1) * 3 * sizeof(double), s))) return rc;
-    double* R = (double*)ctx->tmp1.ptr;
-    double* G = R + (size_t)W * 3;
-    double* Rp = G + (size_t)parts * W * W;
-    double* r64 = (double*)ctx->tmp2.ptr;
-    // the first sample tile's Gram writes G (every entry of its tile list, in every part), so only
-    // J^T r's partials (and G itself without samples) start from zero
-    if ((rc = fill_f64(ctx, R, N > 0 ? W * 3 : (int64_t)parts * W * W + W * 3, 0.0, s))) return rc;
-    // Jtr == nullptr: J^T J only (the LM step takes its gradient from the adjoint)
-    const bool want_r = Jtr != nullptr;
-    if (N > 0 && want_r) {
-        if (mixed)
-            hipLaunchKernelGGL(k_to_f64<float>, dim3(blocks_for(3 * N, 256)), dim3(256), 0, s, (const float*)resid, 3 * N, r64);
-        else
-            hipLaunchKernelGGL(k_to_f64<double>, dim3(blocks_for(3 * N, 256)), dim3(256), 0, s, (const double*)resid, 3 * N, r64);
-    }
+    if ((rc = ensure(ctx, ctx->tmp1, (size_t)parts * W * W * sizeof(double), s))) return rc;
+    double* G = (double*)ctx->tmp1.ptr;
+    // the first sample tile's Gram writes G (every entry of its tile list, in every part)
+    if (N == 0 && (rc = fill_f64(ctx, G, (int64_t)parts * W * W, 0.0, s))) return rc;
     const bool valu = gram == BEM_GRAM_FP64_VALU;
     const std::vector<int> tiles = valu ? out_tiles : gram_work(out_tiles, parts);
     const int ntiles = (int)tiles.size() / (valu ? 2 : 3);
-    // the work list lives on the device (tilew); it is uploaded when its configuration changes, the
-    // only host synchronisation of this call apart from workspace growth
-    const int64_t key[4] = {W, H, ctx->model, gram};
-    if (std::memcmp(key, ctx->tiles_key, sizeof(key)) != 0) {
-        ctx->tiles_key[0] = -1;
-        if ((rc = ensure(ctx, ctx->tilew, tiles.size() * sizeof(int), s))) return rc;
-        if (hipMemcpyAsync(ctx->tilew.ptr, tiles.data(), tiles.size() * sizeof(int), hipMemcpyHostToDevice, s) !=
-                hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)       // the host copy goes out of scope below
-            return set_error(ctx, BEM_EHIP, "tile list upload");
-        std::memcpy(ctx->tiles_key, key, sizeof(key));
-    }
+    if ((rc = upload_tiles(ctx, tiles, W, H, gram, s))) return rc;
     const int* dtiles = (const int*)ctx->tilew.ptr;
     // tmp5: the vertex table, then the near-pair corrections and run table of one sample tile
     const int S = ctx->opts.segs_per_handle;
@@ -1282,23 +1006,10 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     }
     const size_t corr_bytes = mixed ? ((size_t)((T + 63) / 64) * nl.slots * kFeatVals * sizeof(float) + 255) / 256 * 256 : 0;
     const size_t runs_bytes = mixed ? ((size_t)((T + 63) / 64) * H * sizeof(int2) + 255) / 256 * 256 : 0;
-    // mixed tiles for an MFMA Gram: J^T r of the handle rows is summed as the features are formed
-    // (float32 per 256-sample block, float64 across blocks); only the beta rows are read back
-    const bool fused_r = want_r && mixed && !f64;
-    const size_t rpart_bytes = fused_r ? (size_t)blocks_for(T, 256) * H * kJtrVals * sizeof(float) : 0;
-    // the split-BF16 tile's beta rows sum their J^T r in the beta-row kernel too (no read-back pass)
-    const bool fused_beta = fused_r && gram == BEM_GRAM_BF16X3_MFMA;
-    const size_t bpart_bytes = fused_beta ? ((size_t)blocks_for(T, 256) * M * 3 * sizeof(float) + 255) / 256 * 256 : 0;
-    if ((rc = ensure(ctx, ctx->tmp5, vtab_bytes + corr_bytes + runs_bytes + rpart_bytes + bpart_bytes + 256, s)))
-        return rc;
+    if ((rc = ensure(ctx, ctx->tmp5, vtab_bytes + corr_bytes + runs_bytes + 256, s))) return rc;
     float* vtab = (float*)ctx->tmp5.ptr;
     float* corr = mixed ? (float*)((char*)ctx->tmp5.ptr + vtab_bytes) : nullptr;
     int2* runs = mixed ? (int2*)((char*)ctx->tmp5.ptr + vtab_bytes + corr_bytes) : nullptr;
-    float* rpart = fused_r ? (float*)((char*)ctx->tmp5.ptr + vtab_bytes + corr_bytes + runs_bytes) : nullptr;
-    float* bpart = fused_beta ? (float*)((char*)ctx->tmp5.ptr + vtab_bytes + corr_bytes + runs_bytes + rpart_bytes)
-                              : nullptr;
-    const float* rr = fused_r ? (const float*)resid : nullptr;
-    const int xr_row0 = fused_r ? (int)L.handle_rows() : 0;
     hipLaunchKernelGGL(k_vertex_table, dim3(blocks_for(S + 1, 64)), dim3(64), 0, s, S, ctx->model, vtab);
     const float4* box = nullptr;        // culling boxes of the segment groups (mixed feature kernel)
     if (mixed && (rc = near_boxes(ctx, H * S, 0, &box, s))) return rc;
@@ -1319,7 +1030,7 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         if (f64) {
             double* Xt = (double*)tile;
             if ((rc = launch_features<double>(ctx, xt, n, H, mixed, true, Xt, nullptr, T, s, &nl, t0, x, corr, vtab, runs,
-                                              nullptr, nullptr, nullptr, box)))
+                                              box)))
                 return rc;
             {
                 ProfScope ps_(ctx, PT_GRAM_F64, s);
@@ -1331,35 +1042,27 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
                                        W, s, dtiles, ntiles, (int)kchunk, W * W);
             }
             if (rc) return rc;
-            if (want_r &&
-                (rc = gemm_f64(ctx, (int)W, 3, (int)n, 1.0, Xt, T, false, r64 + 3 * t0, 3, false, 1.0, R, 3, s, nullptr, 0)))
-                return rc;
         } else if (gram == BEM_GRAM_FP32_MFMA) {
             float* Xt = (float*)tile;
             if ((rc = launch_features<float>(ctx, xt, n, H, mixed, true, Xt, nullptr, T, s, &nl, t0, x, corr, vtab, runs,
-                                             rr ? rr + 3 * t0 : nullptr, rpart, R, box)))
+                                             box)))
                 return rc;
             if (overlap && (hipEventRecord(evF[buf], s) != hipSuccess || hipStreamWaitEvent(sg, evF[buf], 0) != hipSuccess))
                 return set_error(ctx, BEM_EHIP, "stream wait");
             if ((rc = launch_gram_mfma(ctx, gram, Xt, nullptr, T, (int)W, n, dtiles, ntiles, kchunk, G, W * W, it > 0, sg)))
-                return rc;
-            if (want_r && (rc = launch_xr(ctx, gram, Xt, nullptr, T, (int)W, n, r64 + 3 * t0, R, Rp, sg, xr_row0)))
                 return rc;
         } else {
             uint16_t* Xh = (uint16_t*)tile;
             uint16_t* Xl = Xh + (size_t)W * T;
             // blocked layout: ld is the row count
             if ((rc = launch_features<uint16_t>(ctx, xt, n, H, mixed, true, Xh, Xl, W, s, &nl, t0, x, corr, vtab, runs,
-                                                rr ? rr + 3 * t0 : nullptr, rpart, R, box, bpart)))
+                                                box)))
                 return rc;
             if (n & 31)
                 hipLaunchKernelGGL(k_zero_tail, dim3(blocks_for(W * (32 - (n & 31)), 256)), dim3(256), 0, s, Xh, Xl, W, n);
             if (overlap && (hipEventRecord(evF[buf], s) != hipSuccess || hipStreamWaitEvent(sg, evF[buf], 0) != hipSuccess))
                 return set_error(ctx, BEM_EHIP, "stream wait");
             if ((rc = launch_gram_mfma(ctx, gram, Xh, Xl, T, (int)W, n, dtiles, ntiles, kchunk, G, W * W, it > 0, sg)))
-                return rc;
-            if (want_r && !fused_beta &&
-                (rc = launch_xr(ctx, gram, Xh, Xl, T, (int)W, n, r64 + 3 * t0, R, Rp, sg, xr_row0)))
                 return rc;
         }
         if (overlap && hipEventRecord(evG[buf], sg) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream event");
@@ -1368,48 +1071,25 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
         if (hipEventRecord(ctx->ev[5], sg) != hipSuccess || hipStreamWaitEvent(s, ctx->ev[5], 0) != hipSuccess)
             return set_error(ctx, BEM_EHIP, "stream join");
     }
-    if (parts > 1 && N > 0) {
-        // the first ntiles / parts work entries are part 0's, one per tile of the list
-        hipLaunchKernelGGL(k_sum_parts, dim3(ntiles / parts, 8), dim3(256), 0, s, G, parts, W, dtiles, ts);
-        if ((rc = check_launch(ctx, "gram parts"))) return rc;
-    }
-    // contraction: per channel the compact Gram and S, then every entry of J^T J in one pass
     // (1/N) sum over the samples, or (1/norm): the samples drawn over the whole image
     const double sc = N > 0 ? 1.0 / (norm > 0.0 ? norm : (double)N) : 0.0;
-    if (want_r && (rc = fill_f64(ctx, Jtr, P, 0.0, s))) return rc;
-    const size_t wc2 = (size_t)Wc * Wc;
-    const size_t szc = (size_t)M * n12;
-    const size_t sn = (size_t)n12 * n12;
-    if ((rc = ensure(ctx, ctx->tmp2, (3 * wc2 + szc + 3 * sn + (size_t)(N > 0 ? N : 1) * 3) * sizeof(double), s)))
-        return rc;
-    double* Gc3 = (double*)ctx->tmp2.ptr + (size_t)(N > 0 ? N : 1) * 3;   // after r64 (no longer needed)
-    double* Zc = Gc3 + 3 * wc2;
-    double* S3 = Zc + szc;
-    for (int c = 0; c < 3; ++c) {
-        double* Gc = Gc3 + c * wc2;
-        double* S1 = S3 + c * sn;
-        hipLaunchKernelGGL(k_gather_gram, dim3(blocks_for(Wc, 32), blocks_for(Wc, 32)), dim3(256), 0, s, G, W, L, c,
-                           Wc, Gc);
-        hipLaunchKernelGGL(k_gather_z, dim3(blocks_for(n12, 256), M), dim3(256), 0, s, Z, L, M, c, Zc);
-        if ((rc = check_launch(ctx, "gather"))) return rc;
-        // The channel's block of J^T J is G + B Zc + (B Zc)^T + Zc^T D Zc with B = Gc[0:n12, n12:Wc]
-        // and D = Gc[n12:, n12:] (symmetric), which equals G + S + S^T with S = Y Zc and
-        // Y = B + (1/2) Zc^T D: two products instead of three.  Y overwrites B in Gc.
-        if ((rc = gemm_f64(ctx, n12, M, M, 0.5, Zc, n12, true, Gc + (size_t)n12 * Wc + n12, Wc, false, 1.0, Gc + n12, Wc, s,
-                           nullptr, 0)))
-            return rc;
-        if ((rc = gemm_f64(ctx, n12, n12, M, 1.0, Gc + n12, Wc, false, Zc, n12, false, 0.0, S1, n12, s, nullptr, 0))) return rc;
-        if (want_r) {
-            hipLaunchKernelGGL(k_scatter_g, dim3(blocks_for(n12, 64)), dim3(256), 0, s, R, Zc, L, M, c, sc, Jtr);
-            if ((rc = check_launch(ctx, "scatter"))) return rc;
-        }
-    }
-    if (n12 > 0) {
-        hipLaunchKernelGGL(k_scatter_jtj, dim3(blocks_for(n12, 32), blocks_for(n12, 32)), dim3(256), 0, s, Gc3,
-                           (int64_t)wc2, Wc, S3, (int64_t)sn, L, sc, JtJ, P);
-        if ((rc = check_launch(ctx, "scatter"))) return rc;
-    }
-    return BEM_OK;
+    return contract_gram(ctx, H, L, W, G, N > 0 ? parts : 1, ts, dtiles, ntiles, Z, sc, JtJ, s);
+}
+
+int launch_vertex_table(bem_ctx* ctx, float* vtab, hipStream_t s)
+{
+    const int S = ctx->opts.segs_per_handle;
+    hipLaunchKernelGGL(k_vertex_table, dim3(blocks_for(S + 1, 64)), dim3(64), 0, s, S, ctx->model, vtab);
+    return check_launch(ctx, "vertex table");
+}
+
+int gram_work_bf16(bem_ctx* ctx, const Layout& L, int64_t W, const int** work, int* nwork, hipStream_t s)
+{
+    const std::vector<int> w = gram_work(gram_tiles(L, (int)W, 256), kGramParts);
+    *nwork = (int)w.size() / 3;
+    const int rc = upload_tiles(ctx, w, W, L.H, BEM_GRAM_BF16X3_MFMA, s);
+    *work = (const int*)ctx->tilew.ptr;
+    return rc;
 }
 
 int run_jacobian(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, double* J, hipStream_t s)

@@ -1,0 +1,793 @@
+// jtj_cells.hip - J^T J of the mixed LM step over grid cells (cells.hpp).
+//
+// Over the n samples of a cell every feature row is X = V Phi + E: Phi [64][n] the cell's interpolation
+// weights, V [W][64] the row's far part at the cell's nodes, and E the part of the near segments and elements,
+// zero but for the rows of the handles and elements near the cell.  With Phi Phi^T = R R^T (Cholesky, 64 x 64)
+// and Q = R^-1 Phi, whose rows are orthonormal,
+//     sum over the cell of X X^T = Y Y^T + E E^T - Z Z^T,     Z = E Q^T,   Y = V R + Z.
+// So 64 columns Y stand for the cell's samples in the Gram of all W rows, and the samples themselves
+// enter only the Gram of the cell's near rows.  The identity needs R R^T = Phi Phi^T and R Q = Phi only, so
+// a rank-deficient cell (fewer than 64 samples) is exact as well: its empty pivots are dropped.
+//
+//   k_cell_rows       near handles and elements of every cell
+//   k_cell_gramian    Phi Phi^T from the 15 x 15 Chebyshev moments of the samples (float64)
+//   k_cell_factor     R, and C = R^-1 D^T with which q(x) = C T(x)
+//   k_cell_basis      Q in split bfloat16, 32-sample blocks
+//   k_near_features   E in split bfloat16, 32-sample blocks; pairs within the near radius in float64
+//   k_near_project    Z on bf16 MFMA
+//   k_far_features    V at the nodes, times R, plus Z: Y in float32
+//   k_split_half      Y as scaled float16 pairs
+//   launch_gram_half  Y Y^T, launch_gram_cells: E E^T - Z Z^T, added into the same float64 Gram
+// Rounding.  The split-bfloat16 products of E average over the samples as those of the Gram over all
+// samples do; the fewer columns Y and Z carry 22 and 24 bits instead of 16.  Accumulation in float32 within a
+// run and in float64 beyond is the same.  Pairs by quadrature (seg_math.hpp), so near factors of at least 1.
+// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 8.8 ms, far features
+// 7.7 ms, near Gram 6.8 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
+// step against float64: 7.5e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
+#include <cmath>
+#include <numeric>
+
+#include "cells.hpp"
+#include "normal.hpp"
+
+namespace bem {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kFeatVals = 28;                  // geo[3][8], col[4] of a handle at a point
+constexpr double kNeRatio = 2.0;               // near pair over far pair, in time
+constexpr int kMom = 16;                       // moments a side (15 used)
+constexpr int kGramianParts = 4;
+
+// Near handles (any near segment) and near elements of every cell, in order; hpos / epos the place of a
+// handle / element in its cell's list, or -1.  Counts: n, nh, ne per cell.
+__global__ void __launch_bounds__(256) k_cell_rows(const int* __restrict__ off, const uint32_t* __restrict__ bits,
+                                                   int words, int seg_words, int H, int S, int M, int nc,
+                                                   int* __restrict__ hl, int* __restrict__ el, int* __restrict__ hpos,
+                                                   int* __restrict__ epos, int* __restrict__ cnt)
+{
+    __shared__ int part[4];
+    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n = off[c + 1] - off[c];
+    const uint32_t* row = bits + (size_t)c * words;
+    for (int pass = 0; pass < 2; ++pass) {
+        const int total = pass ? M : H;
+        int* list = (pass ? el : hl) + (size_t)c * total;
+        int* pos = (pass ? epos : hpos) + (size_t)c * total;
+        int base = 0;
+        for (int i0 = 0; i0 < total; i0 += 256) {
+            const int i = i0 + tid;
+            bool near = false;
+            if (n > 0 && i < total) {
+                const int b0 = pass ? i : i * S, b1 = pass ? i + 1 : (i + 1) * S;      // bits [b0, b1)
+                const int w0 = pass ? seg_words : 0;
+                for (int w = b0 >> 5; w <= (b1 - 1) >> 5; ++w) {
+                    uint32_t m = 0xFFFFFFFFu;
+                    if (w == b0 >> 5) m &= 0xFFFFFFFFu << (b0 & 31);
+                    if (w == (b1 - 1) >> 5) m &= 0xFFFFFFFFu >> (31 - ((b1 - 1) & 31));
+                    near |= (row[w0 + w] & m) != 0u;
+                }
+            }
+            const uint64_t mask = __ballot(near);
+            if (lane == 0) part[wv] = __popcll(mask);
+            __syncthreads();
+            int at = base + __popcll(mask & ((1ull << lane) - 1ull));
+            for (int k = 0; k < wv; ++k) at += part[k];
+            if (i < total) {
+                pos[i] = near ? at : -1;
+                if (near) list[at] = i;
+            }
+            base += part[0] + part[1] + part[2] + part[3];
+            __syncthreads();
+        }
+        if (tid == 0) cnt[3 * c + 1 + pass] = base;
+    }
+    if (tid == 0) cnt[3 * c] = n;
+}
+
+// Chebyshev moments mu_pq = sum over the cell of T_p(xi) T_q(eta), p, q < 15, in float64: block (cell,
+// part), a wavefront stages 32 samples and its lane (p, q / 4) sums four q.
+__global__ void __launch_bounds__(256) k_cell_gramian(CellPlan p, double* __restrict__ part)
+{
+    __shared__ double sx[4][32][kMom + 1], sy[4][32][kMom + 1];
+    const int c = blockIdx.x, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int i0 = p.off[c], i1 = p.off[c + 1];
+    if (i0 == i1) return;
+    double cx, cy;
+    cell_corner(p.grid, c, cx, cy);
+    double m[4] = {0.0, 0.0, 0.0, 0.0};
+    const int pp = lane & 15, q4 = (lane >> 4) * 4;
+    for (int s0 = i0 + (blockIdx.y * 4 + wv) * 32; s0 < i1; s0 += kGramianParts * 4 * 32) {
+        const int n = i1 - s0 < 32 ? i1 - s0 : 32;
+        if ((lane & 31) < n) {                       // lanes 0..31: T(xi), 32..63: T(eta)
+            const size_t i = s0 + (lane & 31);
+            const double t = lane < 32 ? (p.xs[2 * i] - cx) * (2.0 * p.grid.inv_h) - 1.0
+                                       : (p.xs[2 * i + 1] - cy) * (2.0 * p.grid.inv_h) - 1.0;
+            double* o = lane < 32 ? sx[wv][lane] : sy[wv][lane - 32];
+            double a = 1.0, b = t;
+            for (int k = 0; k < kMom; ++k) {
+                o[k] = a;
+                const double d = 2.0 * t * b - a;
+                a = b;
+                b = d;
+            }
+        }
+        __threadfence_block();
+        for (int s = 0; s < n; ++s) {
+            const double t = sx[wv][s][pp];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) m[k] += t * sy[wv][s][q4 + k];
+        }
+        __threadfence_block();
+    }
+    __syncthreads();
+    double* red = &sx[0][0][0];                      // [4][16 * 16]
+    for (int k = 0; k < 4; ++k) red[wv * 256 + (q4 + k) * kMom + pp] = m[k];
+    __syncthreads();
+    const int t = threadIdx.x;
+    part[((size_t)blockIdx.y * p.grid.nc + c) * 256 + t] = (red[t] + red[256 + t]) + (red[512 + t] + red[768 + t]);
+}
+
+// Block a cell.  A = D^T M D, M[(a, b), (a', b')] = sum T_a T_b T_a' T_b' from the moments (T_a T_a' is the
+// mean of T_{a + a'} and T_{|a - a'|}) and D the nodes' Chebyshev coefficients; its Cholesky factor R
+// (Rf [n][k], float32) and C = R^-1 D^T ([k][ab], float64).  Pivots below 1e-12 of the largest are dropped.
+__global__ void __launch_bounds__(256) k_cell_factor(const double* __restrict__ part, int nc, const int* __restrict__ off,
+                                                     float* __restrict__ Rf, double* __restrict__ Cq)
+{
+    constexpr int Q = kFarQ, NN = kFarNodes;
+    __shared__ double A[NN][NN + 1], B[NN][NN + 1], mu[256], d[Q][Q], dinv[NN];
+    const int c = blockIdx.x, t = threadIdx.x;
+    if (off[c + 1] == off[c]) {
+        for (int e = t; e < NN * NN; e += 256) Rf[(size_t)c * NN * NN + e] = 0.0f;
+        return;
+    }
+    double s = 0.0;
+    for (int p = 0; p < kGramianParts; ++p) s += part[((size_t)p * nc + c) * 256 + t];
+    mu[t] = s;                                       // mu[q * 16 + p]
+    if (t < Q * Q) {
+        const int a = t / Q, i = t % Q;              // d[a][i] = s_a T_a(t_i)
+        d[a][i] = cospi((double)(a * (2 * i + 1)) / (2.0 * Q)) * (a == 0 ? 1.0 / Q : 2.0 / Q);
+    }
+    __syncthreads();
+    // index of (a, b): b * 8 + a, of node (i, j): j * 8 + i
+    for (int e = t; e < NN * NN; e += 256) {
+        const int r = e >> 6, q = e & 63;
+        const int a = r & 7, b = r >> 3, a2 = q & 7, b2 = q >> 3;
+        const int ad = a > a2 ? a - a2 : a2 - a, bd = b > b2 ? b - b2 : b2 - b;
+        A[r][q] = 0.25 * ((mu[(b + b2) * 16 + a + a2] + mu[(b + b2) * 16 + ad]) + (mu[bd * 16 + a + a2] + mu[bd * 16 + ad]));
+    }
+    __syncthreads();
+    // the four index transforms a -> i, b -> j, a' -> i', b' -> j'
+    for (int e = t; e < NN * NN; e += 256) {
+        const int r = e >> 6, q = e & 63, i = r & 7, b = r >> 3;
+        double v = 0.0;
+        for (int a = 0; a < Q; ++a) v += d[a][i] * A[b * 8 + a][q];
+        B[r][q] = v;
+    }
+    __syncthreads();
+    for (int e = t; e < NN * NN; e += 256) {
+        const int r = e >> 6, q = e & 63, i = r & 7, j = r >> 3;
+        double v = 0.0;
+        for (int b = 0; b < Q; ++b) v += d[b][j] * B[b * 8 + i][q];
+        A[r][q] = v;
+    }
+    __syncthreads();
+    for (int e = t; e < NN * NN; e += 256) {
+        const int r = e >> 6, q = e & 63, i = q & 7, b = q >> 3;
+        double v = 0.0;
+        for (int a = 0; a < Q; ++a) v += d[a][i] * A[r][b * 8 + a];
+        B[r][q] = v;
+    }
+    __syncthreads();
+    for (int e = t; e < NN * NN; e += 256) {
+        const int r = e >> 6, q = e & 63, i = q & 7, j = q >> 3;
+        double v = 0.0;
+        for (int b = 0; b < Q; ++b) v += d[b][j] * B[r][b * 8 + i];
+        A[r][q] = v;
+    }
+    __syncthreads();
+    double top = 0.0;
+    for (int k = 0; k < NN; ++k) top = fmax(top, A[k][k]);
+    __syncthreads();
+    for (int k = 0; k < NN; ++k) {                   // right-looking, lower triangle
+        const double piv = A[k][k];
+        const bool keep = piv > 1e-12 * top;
+        const double inv = keep ? 1.0 / sqrt(piv) : 0.0;
+        __syncthreads();
+        if (t >= k && t < NN) A[t][k] = t == k ? piv * inv : A[t][k] * inv;
+        if (t == 0) dinv[k] = inv;
+        __syncthreads();
+        const int m = NN - 1 - k;
+        for (int e = t; e < m * m; e += 256) {
+            const int r = k + 1 + e / m, q = k + 1 + e % m;
+            if (q <= r) A[r][q] -= A[r][k] * A[q][k];
+        }
+        __syncthreads();
+    }
+    for (int e = t; e < NN * NN; e += 256) {
+        const int r = e >> 6, q = e & 63;
+        Rf[(size_t)c * NN * NN + e] = q <= r ? (float)A[r][q] : 0.0f;
+    }
+    // C = R^-1 D^T, column ab by forward substitution
+    if (t < NN) {
+        const int a = t & 7, b = t >> 3;
+        for (int k = 0; k < NN; ++k) {
+            double v = d[a][k & 7] * d[b][k >> 3];
+            for (int m = 0; m < k; ++m) v -= A[k][m] * B[m][t];
+            B[k][t] = v * dinv[k];
+        }
+    }
+    __syncthreads();
+    for (int e = t; e < NN * NN; e += 256) Cq[(size_t)c * NN * NN + e] = B[e >> 6][e & 63];
+}
+
+__device__ inline void put_split(uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, size_t i, float v)
+{
+    const uint16_t h = bf16_bits(v);
+    hi[i] = h;
+    lo[i] = bf16_bits(v - bf16_value(h));
+}
+
+// q(x) = C T(x) of every sample, in float64, stored split: a wavefront of a cell's samples.
+__global__ void __launch_bounds__(256) k_cell_basis(CellPlan p, const CellInfo* __restrict__ ci,
+                                                    const double* __restrict__ Cq, uint16_t* __restrict__ Qh,
+                                                    uint16_t* __restrict__ Ql)
+{
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int nl = p.grid.nc + 1;
+    if (w >= p.wave0[nl]) return;
+    const int c = unit_label(p.wave0, nl, w);
+    if (c == p.grid.nc) return;
+    const int n = ci[c].n, t = (w - p.wave0[c]) * 64 + lane;
+    if (t >= ((n + 31) & ~31)) return;
+    const bool live = t < n;
+    const size_t i = (size_t)p.off[c] + (live ? t : 0);
+    double cx, cy, Ta[kFarQ], Tb[kFarQ];
+    cell_corner(p.grid, c, cx, cy);
+    cheb_values<double, kFarQ>((p.xs[2 * i] - cx) * (2.0 * p.grid.inv_h) - 1.0, Ta);
+    cheb_values<double, kFarQ>((p.xs[2 * i + 1] - cy) * (2.0 * p.grid.inv_h) - 1.0, Tb);
+    const double* C = Cq + (size_t)c * kFarNodes * kFarNodes;
+    const size_t o = ((size_t)ci[c].tb + (t >> 5)) * (kFarNodes * 32) + (t & 31);
+#pragma unroll 1
+    for (int k = 0; k < kFarNodes; ++k) {
+        const double* r = C + k * kFarNodes;
+        double v = 0.0;
+#pragma unroll
+        for (int b = 0; b < kFarQ; ++b) {
+            double u = r[8 * b];
+#pragma unroll
+            for (int a = 1; a < kFarQ; ++a) u += r[8 * b + a] * Ta[a];
+            v += Tb[b] * u;
+        }
+        put_split(Qh, Ql, o + (size_t)k * 32, live ? (float)v : 0.0f);
+    }
+}
+
+constexpr int kListCap = 256, kListFull = kListCap - 64;
+struct NearFeat {
+    uint32_t list[kListCap];                       // lane << 26 | segment
+    float corr[64][kFeatVals + 1];
+};
+
+// Float64 features of one listed pair, added to its sample's row of corr.
+__device__ inline void near_pair_features(const double* __restrict__ s64, int j, int S, int model, double X, double Y,
+                                          double eps2, float* __restrict__ corr)
+{
+    const SegGeom<double> g = load_geom(s64);
+    const double ta = (double)j / (double)S, tb = (double)(j + 1) / (double)S;
+    double Ba[4], Bb[4];
+    vertex_weights(model, ta, Ba);
+    vertex_weights(model, tb, Bb);
+    const PairState<double> st = pair_forward<double, DevF64, true>(g, X, Y, eps2);
+    const Moments<double> m = pair_moments(g, st);
+    for (int c = 0; c < 3; ++c) {
+        const Grad4<double> gr = pair_backward(g, st, eps2, s64[kWdA + c], s64[kWdB + c], s64[kWcA + c], s64[kWcB + c]);
+        for (int q = 0; q < 4; ++q) {
+            atomicAdd(corr + 8 * c + 2 * q, (float)(Ba[q] * gr.ax + Bb[q] * gr.bx));
+            atomicAdd(corr + 8 * c + 2 * q + 1, (float)(Ba[q] * gr.ay + Bb[q] * gr.by));
+        }
+    }
+    atomicAdd(corr + 24, (float)(m.da * (1.0 - ta) + m.db * (1.0 - tb)));
+    atomicAdd(corr + 25, (float)(m.da * ta + m.db * tb));
+    atomicAdd(corr + 26, (float)(m.sa * (1.0 - ta) + m.sb * (1.0 - tb)));
+    atomicAdd(corr + 27, (float)(m.sa * ta + m.sb * tb));
+}
+
+// E of a cell: a wavefront of its samples, every gridDim.y-th near handle and element.  Rows in the order of
+// the whole Gram: [g_0 (G nh) | g_1 | g_2 | e (C nh) | beta (ne)].
+__global__ void __launch_bounds__(256, 2)
+    k_near_features(CellPlan p, const CellInfo* __restrict__ ci, const int* __restrict__ hl, const int* __restrict__ el,
+                    Layout L, int S, int M, int model, const float* __restrict__ seg32, const double* __restrict__ seg64,
+                    const float* __restrict__ el32, const double* __restrict__ el64, const float* __restrict__ vtab,
+                    float eps2f, double eps2, float near2, uint16_t* __restrict__ Eh, uint16_t* __restrict__ El)
+{
+    __shared__ NearFeat nf[4];
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int nl = p.grid.nc + 1;
+    if (w >= p.wave0[nl]) return;
+    const int c = unit_label(p.wave0, nl, w);
+    const int n = ci[c].n, nh = ci[c].nh, ne = ci[c].ne, rows = ci[c].rows;
+    const int t0 = (w - p.wave0[c]) * 64, t = t0 + lane;
+    const bool live = t < n, store = t < ((n + 31) & ~31);
+    const double* xw = p.xs + 2 * ((size_t)p.off[c] + t0);
+    const float X = live ? (float)xw[2 * lane] : 0.0f, Y = live ? (float)xw[2 * lane + 1] : 0.0f;
+    const uint32_t* bits = p.bits + (size_t)c * p.words;
+    NearFeat& nb = nf[threadIdx.x >> 6];
+    const size_t base = (size_t)ci[c].eoff + (size_t)(t >> 5) * ((size_t)rows << 5) + (t & 31);
+    auto put = [&](int row, float v) {
+        if (store) put_split(Eh, El, base + ((size_t)row << 5), live ? v : 0.0f);
+    };
+    for (int hi = blockIdx.y; hi < nh; hi += gridDim.y) {
+        const int h = hl[(size_t)c * L.H + hi];
+        float geo[3][8], col[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) geo[q][k] = 0.f;
+        int cnt = 0;
+        bool any = false;
+        const int k1 = (h + 1) * S;
+        for (int k = h * S; k < k1;) {
+            for (; k < k1 && cnt <= kListFull; ++k) {
+                if (!((bits[k >> 5] >> (k & 31)) & 1u)) continue;
+                const float* s = seg32 + (size_t)k * kSegStride;
+                const bool near = live & near_segment(s[0], s[1], s[2], s[3], s[6], X, Y, near2);
+                const uint64_t mask = __ballot(near);
+                if (mask != 0) {
+                    if (near) nb.list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = ((uint32_t)lane << 26) | (uint32_t)k;
+                    cnt += __popcll(mask);
+                }
+                const float* V = vtab + 8 * (k - h * S);
+                add_pair_features<6>(s, V, V + 8, X, Y, eps2f, !near, geo, col);
+            }
+            if (cnt > kListFull || (k == k1 && cnt > 0)) {
+                if (!any)
+                    for (int q = 0; q < kFeatVals; ++q) nb.corr[lane][q] = 0.0f;
+                any = true;
+                __threadfence_block();
+                for (int e = lane; e < cnt; e += 64) {
+                    const uint32_t v = nb.list[e];
+                    const int ls = v >> 26, kk = v & 0x3FFFFFFu;
+                    near_pair_features(seg64 + (size_t)kk * kSegStride, kk - h * S, S, model, xw[2 * ls], xw[2 * ls + 1], eps2,
+                                       nb.corr[ls]);
+                }
+                __threadfence_block();
+                cnt = 0;
+            }
+        }
+        if (any) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) geo[q][k] += nb.corr[lane][8 * q + k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) col[k] += nb.corr[lane][24 + k];
+            __threadfence_block();
+        }
+        if (model == 1) {
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) put((q * nh + hi) * 4 + k, geo[q][k]);
+            put(12 * nh + 2 * hi, col[0] + col[1]);
+            put(12 * nh + 2 * hi + 1, col[2] + col[3]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) put((q * nh + hi) * 8 + k, geo[q][k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) put(24 * nh + 4 * hi + k, col[k]);
+        }
+    }
+    const int b0 = (3 * L.G + L.C) * nh;
+    for (int i = blockIdx.y; i < ne; i += gridDim.y) {
+        const int j = el[(size_t)c * M + i];
+        const float* e = el32 + (size_t)j * kElemStride;
+        const bool near = live & near_element(e[0], e[1], e[2], e[3], X, Y, near2);
+        float b = element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y);
+        if (near) {
+            const double* e64 = el64 + (size_t)j * kElemStride;
+            b = (float)element_beta<double, DevF64>(e64[0], e64[1], e64[2], e64[3], xw[2 * lane], xw[2 * lane + 1]);
+        }
+        put(b0 + i, b);
+    }
+}
+
+// Z = E Q^T of 128 rows of a cell (work entry: cell, row block), a wavefront 32 rows x 64 columns on bf16
+// MFMA: float32 to Zf [row][64], and as three bfloat16 terms in the 32-column blocks of the near tile's layout:
+// Zt = terms of Z, zeros, terms of -Z, zstep apart.
+__global__ void __launch_bounds__(256) k_near_project(const CellInfo* __restrict__ ci, const int* __restrict__ work,
+                                                      const uint16_t* __restrict__ Eh, const uint16_t* __restrict__ El,
+                                                      const uint16_t* __restrict__ Qh, const uint16_t* __restrict__ Ql,
+                                                      float* __restrict__ Zf, uint16_t* __restrict__ Zt, int64_t zstep)
+{
+    const int c = work[2 * blockIdx.x], wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int li = lane & 31, lk = lane >> 5;
+    const int rows = ci[c].rows, r0 = work[2 * blockIdx.x + 1] * 128 + wv * 32;
+    if (r0 >= rows) return;
+    const int ra = r0 + li < rows ? r0 + li : rows - 1;
+    const int nb = (ci[c].n + 31) >> 5;
+    const uint16_t* eh = Eh + ci[c].eoff + ((size_t)ra << 5) + 8 * lk;
+    const uint16_t* elo = El + ci[c].eoff + ((size_t)ra << 5) + 8 * lk;
+    const size_t qo = (size_t)ci[c].tb * (kFarNodes * 32) + ((size_t)li << 5) + 8 * lk;
+    floatx16 acc[2];
+    for (int j = 0; j < 2; ++j)
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+    auto ld = [](const uint16_t* q) { return __builtin_bit_cast(bf16x8, *(const u16x8*)q); };
+#pragma unroll 2
+    for (int b = 0; b < nb; ++b) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const size_t ao = (size_t)b * ((size_t)rows << 5) + 16 * h;
+            const bf16x8 ah = ld(eh + ao), al = ld(elo + ao);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const size_t bo = qo + (size_t)b * (kFarNodes * 32) + 1024 * j + 16 * h;
+                const bf16x8 bh = ld(Qh + bo), bl = ld(Ql + bo);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc[j], 0, 0, 0);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc[j], 0, 0, 0);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc[j], 0, 0, 0);
+            }
+        }
+    }
+    const size_t zb = (size_t)ci[c].rb * kFarNodes;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = r0 + 8 * (r >> 2) + 4 * lk + (r & 3);
+            if (row >= rows) continue;
+            const float v = acc[j][r];
+            Zf[((size_t)ci[c].rb + row) * kFarNodes + 32 * j + li] = v;
+            const size_t o = zb + (size_t)j * ((size_t)rows << 5) + ((size_t)row << 5) + li;
+            const uint16_t h = bf16_bits(v);
+            const float v1 = v - bf16_value(h);
+            const uint16_t m = bf16_bits(v1);
+            const uint16_t l = bf16_bits(v1 - bf16_value(m));
+            const uint16_t term[3] = {h, m, l};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                Zt[o + k * zstep] = term[k];
+                Zt[o + (4 + k) * zstep] = term[k] ^ 0x8000u;
+            }
+            Zt[o + 3 * zstep] = 0;
+        }
+}
+
+// Y of one cell: block (cell, part), four wavefronts that share the cell's R.  A wavefront takes a handle (or
+// kFeatVals elements) at a time: the far part at the 64 nodes (lane = node) into LDS, then lane k sums
+// column k of V R, adds Z on near rows and stores the value (float32); rmax: largest magnitude of every row, as
+// float bits.
+__global__ void __launch_bounds__(256, 2)
+    k_far_features(CellGrid g, const int* __restrict__ off, const CellInfo* __restrict__ ci,
+                   const int* __restrict__ hpos, const int* __restrict__ epos, const uint32_t* __restrict__ bits, int words,
+                   int seg_words, Layout L, int S, int M, int model, const float* __restrict__ seg32,
+                   const float* __restrict__ el32, const float* __restrict__ vtab, float eps2f, const float* __restrict__ Rf,
+                   const float* __restrict__ Zf, int64_t W, int stride, float* __restrict__ Yf,
+                   uint32_t* __restrict__ rmax)
+{
+    constexpr int NN = kFarNodes;
+    __shared__ float R[NN][NN];
+    __shared__ __attribute__((aligned(16))) float V[4][kFeatVals][NN];
+    const int c = blockIdx.x, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int e = threadIdx.x; e < NN * NN; e += 256) R[e >> 6][e & 63] = Rf[(size_t)c * NN * NN + e];
+    __syncthreads();
+    const bool used = off[c + 1] > off[c];
+    const int nh = ci[c].nh;
+    double Xd, Yd;
+    cell_node<kFarQ>(g, c, lane, Xd, Yd);
+    const float X = (float)Xd, Y = (float)Yd;
+    const uint32_t* row = bits + (size_t)c * words;
+    const float short_len = (float)(kFarCells * g.h / kQuadFar);
+    // the cells' columns are dealt out in a stride permutation: in cell order the float32 sums over
+    // consecutive columns see long coherent runs, and their partial sums wander
+    const size_t yb = (size_t)(2 * ((int64_t)c * stride % g.nc) + (lane >> 5)) * ((size_t)W << 5) + (lane & 31);
+    float(*v)[NN] = V[wv];
+    auto put = [&](int64_t f, float t) {
+        Yf[yb + ((size_t)f << 5)] = t;
+        const float m = wave_max(fabsf(t));
+        if (lane == 0 && m > 0.0f) atomicMax(rmax + f, __float_as_uint(m));
+    };
+    const int batches = (M + kFeatVals - 1) / kFeatVals;
+    for (int it = wv + 4 * blockIdx.y; it < L.H + batches; it += 4 * gridDim.y) {
+        const bool handle = it < L.H;
+        const int j0 = (it - L.H) * kFeatVals;
+        if (used) {
+            if (handle) {
+                float geo[3][8], col[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) geo[q][k] = 0.f;
+                for (int j = 0; j < S; ++j) {
+                    const int k = it * S + j;
+                    if ((row[k >> 5] >> (k & 31)) & 1u) continue;
+                    const float* s = seg32 + (size_t)k * kSegStride;
+                    const float* B = vtab + 8 * j;
+                    if (s[kLen] <= short_len) add_pair_features<4>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+                    else add_pair_features<6>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[8 * q + k][lane] = geo[q][k];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[24 + k][lane] = col[k];
+            } else {
+#pragma unroll 4
+                for (int i = 0; i < kFeatVals; ++i) {
+                    const int j = j0 + i < M ? j0 + i : M - 1;
+                    const float* e = el32 + (size_t)j * kElemStride;
+                    const bool far = !((row[seg_words + (j >> 5)] >> (j & 31)) & 1u);
+                    v[i][lane] = far ? element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y) : 0.0f;
+                }
+            }
+        }
+        __threadfence_block();
+        float y[kFeatVals];
+#pragma unroll
+        for (int i = 0; i < kFeatVals; ++i) y[i] = 0.0f;
+        if (used) {
+#pragma unroll 2
+            for (int n = 0; n < NN; n += 4) {
+                const float r0 = R[n][lane], r1 = R[n + 1][lane], r2 = R[n + 2][lane], r3 = R[n + 3][lane];
+#pragma unroll
+                for (int i = 0; i < kFeatVals; ++i) {
+                    const float4 q = *reinterpret_cast<const float4*>(&v[i][n]);
+                    y[i] += (q.x * r0 + q.y * r1) + (q.z * r2 + q.w * r3);
+                }
+            }
+        }
+        __threadfence_block();
+        if (handle) {
+            const int hp = used ? hpos[(size_t)c * L.H + it] : -1;
+            const float* z = Zf + (size_t)ci[c].rb * NN + lane;
+            if (model == 1) {
+                float o[14];
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) o[4 * q + k] = y[8 * q + k];
+                o[12] = y[24] + y[25];
+                o[13] = y[26] + y[27];
+#pragma unroll
+                for (int i = 0; i < 14; ++i) {
+                    const int q = i >> 2, k = i & 3;
+                    if (hp >= 0) o[i] += z[(size_t)(i < 12 ? (q * nh + hp) * 4 + k : 12 * nh + 2 * hp + (i - 12)) * NN];
+                    const int64_t f = i < 12 ? (int64_t)q * L.Gp + 4 * it + k : 3 * L.Gp + 2 * it + (i - 12);
+                    put(f, o[i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kFeatVals; ++i) {
+                    const int q = i >> 3, k = i & 7;
+                    if (hp >= 0) y[i] += z[(size_t)(i < 24 ? (q * nh + hp) * 8 + k : 24 * nh + 4 * hp + (i - 24)) * NN];
+                    const int64_t f = i < 24 ? (int64_t)q * L.Gp + 8 * it + k : 3 * L.Gp + 4 * it + (i - 24);
+                    put(f, y[i]);
+                }
+            }
+        } else {
+            const int b0 = (3 * L.G + L.C) * nh;
+#pragma unroll
+            for (int i = 0; i < kFeatVals; ++i) {
+                const int j = j0 + i;
+                if (j >= M) break;
+                const int ep = used ? epos[(size_t)c * M + j] : -1;
+                if (ep >= 0) y[i] += Zf[((size_t)ci[c].rb + b0 + ep) * NN + lane];
+                put(L.handle_rows() + j, y[i]);
+            }
+        }
+    }
+}
+
+// Rows scaled by powers of two to magnitudes below 2^14 and split into float16 pairs; the padding rows of
+// the geometry blocks are zero.  rscale undoes the scale.
+__global__ void __launch_bounds__(256) k_split_half(const float* __restrict__ Yf, const uint32_t* __restrict__ rmax,
+                                                    Layout L, int64_t W, int64_t nblk, uint16_t* __restrict__ Yh,
+                                                    uint16_t* __restrict__ Yl, float* __restrict__ rscale)
+{
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;      // four columns of one row
+    if (i >= nblk * W * 32) return;
+    const int64_t f = (i >> 5) % W;
+    const float m = __uint_as_float(rmax[f]);
+    const int e = m > 0.0f ? 14 - __builtin_amdgcn_frexp_expf(m) : 0;
+    const float4 v = *reinterpret_cast<const float4*>(Yf + i);
+    const bool pad = f < 3 * L.Gp && f % L.Gp >= L.geo();
+    const float x[4] = {v.x, v.y, v.z, v.w};
+    uint16_t h[4], l[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float t = pad ? 0.0f : __builtin_amdgcn_ldexpf(x[k], e);
+        const _Float16 a = (_Float16)t, b = (_Float16)(t - (float)a);
+        h[k] = __builtin_bit_cast(uint16_t, a);
+        l[k] = __builtin_bit_cast(uint16_t, b);
+    }
+    *reinterpret_cast<uint2*>(Yh + i) = make_uint2(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16);
+    *reinterpret_cast<uint2*>(Yl + i) = make_uint2(l[0] | (uint32_t)l[1] << 16, l[2] | (uint32_t)l[3] << 16);
+    if (i < W * 32 && (i & 31) == 0) rscale[f] = __builtin_amdgcn_ldexpf(1.0f, -e);
+}
+
+}  // namespace
+
+int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, double* JtJ, double norm,
+                  bool* done, hipStream_t s)
+{
+    *done = false;
+    int rc;
+    const int S = ctx->opts.segs_per_handle, K = H * S, M = ctx->M;
+    const double nf = near_radius(ctx->opts.near_factor), eps2 = ctx->opts.eps * ctx->opts.eps;
+    const float near2 = (float)(nf * nf);
+    const Layout L = layout_of(ctx, H);
+    const int64_t W = L.handle_rows() + M;
+    // a tile of the caller's own size is kept to
+    const int g = near2 >= 4.0f && ctx->opts.tile_rows <= 0 ? cells_for(ctx, N, K, kFarQ, kNeRatio, 0.0) : 0;
+    if (g == 0) return BEM_OK;
+    CellPlan p;
+    if ((rc = launch_expand(ctx, theta, H, s))) return rc;
+    if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
+    if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
+    const int nc = p.grid.nc, nl = nc + 1;
+    if (W * 64 * (int64_t)nc >= ((int64_t)1 << 31)) return BEM_OK;            // 32-bit offsets in the Gram
+    // necw: counts | lists | vertex table | cell table | R | C | Gramian parts
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    const size_t cb = up((size_t)3 * nl * sizeof(int)), hb = up((size_t)nl * H * sizeof(int)), eb = up((size_t)nl * M * sizeof(int)),
+                 vb = up((size_t)(S + 1) * 8 * sizeof(float)), ib = up((size_t)nl * sizeof(CellInfo)),
+                 rb = up((size_t)nc * kFarNodes * kFarNodes * sizeof(float)),
+                 qb = up((size_t)nc * kFarNodes * kFarNodes * sizeof(double)),
+                 gb = up((size_t)kGramianParts * nc * 256 * sizeof(double));
+    if ((rc = ensure(ctx, ctx->necw, cb + 2 * hb + 2 * eb + vb + ib + rb + qb + gb, s))) return rc;
+    char* b = (char*)ctx->necw.ptr;
+    auto take = [&](size_t n) { char* q = b; b += n; return q; };
+    int* cnt = (int*)take(cb);
+    int *hl = (int*)take(hb), *hpos = (int*)take(hb), *el = (int*)take(eb), *epos = (int*)take(eb);
+    float* vtab = (float*)take(vb);
+    CellInfo* ci = (CellInfo*)take(ib);
+    float* Rf = (float*)take(rb);
+    double* Cq = (double*)take(qb);
+    double* gpart = (double*)take(gb);
+    hipLaunchKernelGGL(k_cell_rows, dim3(nl), dim3(256), 0, s, p.off, p.bits, p.words, p.seg_words, H, S, M, nc, hl, el,
+                       hpos, epos, cnt);
+    if ((rc = check_launch(ctx, "cell rows"))) return rc;
+    // the counts decide the sizes of what follows, and whether it is worth it
+    std::vector<int> hc(3 * (size_t)nl);
+    if (hipMemcpyAsync(hc.data(), cnt, hc.size() * sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return set_error(ctx, BEM_EHIP, "cell rows readback");
+    std::vector<CellInfo>& info = ctx->ne_info;
+    std::vector<int>& work = ctx->ne_work;           // Gram entries (cell, row tile, column tile), then (cell, row block)
+    info.assign(nl, CellInfo{});
+    work.clear();
+    int64_t blocks = 0, rows = 0, elems = 0;
+    double near = 0.0;                               // near Gram, in 256 x 256 tiles x samples
+    for (int c = 0; c < nl; ++c) {
+        CellInfo& q = info[c];
+        q.n = hc[3 * c];
+        q.nh = q.n ? hc[3 * c + 1] : 0;
+        q.ne = q.n ? hc[3 * c + 2] : 0;
+        q.rows = (3 * L.G + L.C) * q.nh + q.ne;
+        q.tb = (int)blocks;
+        q.rb = (int)rows;
+        q.eoff = elems;
+        const int64_t nb = (q.n + 31) / 32, t = (q.rows + 255) / 256;
+        if (nb * 32 * q.rows >= ((int64_t)1 << 31)) return BEM_OK;            // 32-bit offsets in a near tile
+        if (c < nc) blocks += nb;
+        rows += q.rows;
+        elems += nb * 32 * q.rows;
+        near += 0.5 * t * (t + 1) * (q.n + 64.0 + 200.0);     // an entry's start and sums cost about 200 samples
+    }
+    const int *gwork;
+    int ngwork;
+    if ((rc = gram_work_bf16(ctx, L, W, &gwork, &ngwork, s))) return rc;
+    const double tiles = (double)ngwork / kGramParts;
+    // near and node Gram, and the pairs' share, against the Gram over all samples; the rest (basis, projection,
+    // factors) costs up to two fifths of that Gram at the smallest grouped sizes, so cells serve below 0.6
+    if (near + tiles * 64.0 * nc > 0.6 * tiles * (double)N || elems > ((int64_t)1 << 30) || rows >= (1 << 24)) return BEM_OK;
+    for (int c = 0; c < nl; ++c) {
+        const int t = (info[c].rows + 255) / 256;
+        for (int i = 0; i < t; ++i)
+            for (int j = i; j < t; ++j) work.insert(work.end(), {c, i, j});
+    }
+    const int nnear = (int)work.size() / 3;
+    for (int c = 0; c < nc; ++c)
+        for (int i = 0; i * 128 < info[c].rows; ++i) work.insert(work.end(), {c, i});
+    const int nproj = ((int)work.size() - 3 * nnear) / 2;
+    // nezw: work | Q hi, lo | Z float32 | Z hi, lo, -Z hi, lo
+    const size_t wb = up(work.size() * sizeof(int)), qt = up((size_t)blocks * kFarNodes * 32 * sizeof(uint16_t)),
+                 zf = up((size_t)rows * kFarNodes * sizeof(float)), zs = up((size_t)rows * kFarNodes * sizeof(uint16_t)),
+                 mb = up((size_t)W * sizeof(float));
+    // the sizes follow the parameters, so that a buffer that grows takes a quarter more; with no memory for them
+    // the samples are taken one by one
+    auto grow = [&](DevBuf& q, size_t n) { return ensure(ctx, q, n <= q.bytes ? n : n + n / 4, s); };
+    auto tiles_instead = [&](int e) {
+        for (DevBuf* q : {&ctx->nezw, &ctx->neew, &ctx->tmp0}) {
+            if (hipStreamSynchronize(s) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream sync");
+            if (q->ptr) hipFree(q->ptr);
+            q->ptr = nullptr;
+            q->bytes = 0;
+        }
+        return e == BEM_ENOMEM ? BEM_OK : e;
+    };
+    if ((rc = grow(ctx->nezw, wb + 2 * qt + zf + 7 * zs + 2 * mb + 256))) return tiles_instead(rc);
+    b = (char*)ctx->nezw.ptr;
+    int* dwork = (int*)take(wb);
+    uint16_t *Qh = (uint16_t*)take(qt), *Ql = (uint16_t*)take(qt);
+    float* Zf = (float*)take(zf);
+    uint16_t* Zt = (uint16_t*)take(7 * zs);
+    const int64_t zstep = (int64_t)(zs / sizeof(uint16_t));
+    uint32_t* rmax = (uint32_t*)take(mb);
+    float* rscale = (float*)take(mb);
+    const size_t et = up((size_t)elems * sizeof(uint16_t));
+    if ((rc = grow(ctx->neew, 2 * et + 256))) return tiles_instead(rc);
+    uint16_t *Eh = (uint16_t*)ctx->neew.ptr, *El = (uint16_t*)((char*)ctx->neew.ptr + et);
+    // Y in float32, then its float16 pairs
+    const size_t yt = up((size_t)W * 64 * nc * sizeof(uint16_t));
+    if ((rc = ensure(ctx, ctx->tmp0, 4 * yt, s))) return tiles_instead(rc);
+    float* Yf = (float*)ctx->tmp0.ptr;
+    uint16_t *Yh = (uint16_t*)((char*)ctx->tmp0.ptr + 2 * yt), *Yl = (uint16_t*)((char*)ctx->tmp0.ptr + 3 * yt);
+    if ((rc = ensure(ctx, ctx->tmp1, (size_t)kGramParts * W * W * sizeof(double), s))) return rc;
+    double* G = (double*)ctx->tmp1.ptr;
+    // info and work stay in the context until the next step, past the copies' end
+    if (hipMemcpyAsync(ci, info.data(), info.size() * sizeof(CellInfo), hipMemcpyHostToDevice, s) != hipSuccess ||
+        (!work.empty() &&
+         hipMemcpyAsync(dwork, work.data(), work.size() * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess))
+        return set_error(ctx, BEM_EHIP, "cell table upload");
+    double* Z = nullptr;
+    if ((rc = boundary_derivatives(ctx, H, s, &Z))) return rc;
+    if ((rc = launch_vertex_table(ctx, vtab, s))) return rc;
+    const float* seg32 = (const float*)ctx->seg32.ptr;
+    const double* seg64 = (const double*)ctx->seg64.ptr;
+    const float* el32 = (const float*)ctx->elem32.ptr;
+    const double* el64 = (const double*)ctx->elem64.ptr;
+    const int wblocks = (int)((p.max_waves + 3) / 4);
+    hipLaunchKernelGGL(k_cell_gramian, dim3(nc, kGramianParts), dim3(256), 0, s, p, gpart);
+    hipLaunchKernelGGL(k_cell_factor, dim3(nc), dim3(256), 0, s, (const double*)gpart, nc, p.off, Rf, Cq);
+    hipLaunchKernelGGL(k_cell_basis, dim3(wblocks), dim3(256), 0, s, p, (const CellInfo*)ci, (const double*)Cq, Qh, Ql);
+    {
+        ProfScope ps_(ctx, PT_NEAR, s);
+        const int split = p.max_waves >= 8192 ? 1 : (int)(8192 / p.max_waves);
+        hipLaunchKernelGGL(k_near_features, dim3(wblocks, split), dim3(256), 0, s, p, (const CellInfo*)ci, (const int*)hl,
+                           (const int*)el, L, S, M, ctx->model, seg32, seg64, el32, el64, (const float*)vtab, (float)eps2, eps2,
+                           near2, Eh, El);
+    }
+    if (nproj > 0)
+        hipLaunchKernelGGL(k_near_project, dim3(nproj), dim3(256), 0, s, (const CellInfo*)ci, (const int*)(dwork + 3 * nnear),
+                           (const uint16_t*)Eh, (const uint16_t*)El, (const uint16_t*)Qh, (const uint16_t*)Ql, Zf, Zt, zstep);
+    if ((rc = fill_i32(ctx, (int*)rmax, W, 0, s))) return rc;
+    {
+        ProfScope ps_(ctx, PT_FEATURES, s);
+        const int items = H + (M + kFeatVals - 1) / kFeatVals;
+        int split = (items + 3) / 4;
+        const int most = 1 + 4096 / nc;
+        if (split > most) split = most;
+        int stride = (int)(0.382 * nc) | 1;
+        while (std::gcd(stride, nc) != 1) stride += 2;
+        hipLaunchKernelGGL(k_far_features, dim3(nc, split), dim3(256), 0, s, p.grid, p.off, (const CellInfo*)ci,
+                           (const int*)hpos, (const int*)epos, p.bits, p.words, p.seg_words, L, S, M, ctx->model, seg32, el32,
+                           (const float*)vtab, (float)eps2, (const float*)Rf, (const float*)Zf, W, stride, Yf, rmax);
+        hipLaunchKernelGGL(k_split_half, dim3(blocks_for((int64_t)nc * 16 * W, 256)), dim3(256), 0, s, (const float*)Yf,
+                           (const uint32_t*)rmax, L, W, (int64_t)2 * nc, Yh, Yl, rscale);
+    }
+    if ((rc = check_launch(ctx, "cell features"))) return rc;
+    // Columns summed in float32 before they are added in float64: rounding errors of k-column sums add up to
+    // sqrt(k n) / n of the whole, so that n columns in the place of N samples summed in runs of 10,923
+    // (a third of their tile) take 10,923 sqrt(n / N)
+    const int64_t n = (int64_t)64 * nc;
+    const int64_t kchunk = (int64_t)(10923.0 * std::sqrt((double)n / (double)N) / 64.0 + 1.0) * 64;
+    for (int64_t k0 = 0; k0 < n; k0 += kGramParts * kchunk) {
+        const int64_t m = n - k0 < kGramParts * kchunk ? n - k0 : kGramParts * kchunk;
+        if ((rc = launch_gram_half(ctx, Yh + k0 * W, Yl + k0 * W, (int)W, m, rscale, gwork, ngwork, kchunk, G, W * W, k0 > 0,
+                                   s)))
+            return rc;
+    }
+    if ((rc = launch_gram_cells(ctx, Eh, El, Zt, zstep, ci, nc, hl, el, H, M, L, W, dwork, nnear, G, W * W, s))) return rc;
+    const double sc = 1.0 / (norm > 0.0 ? norm : (double)N);
+    if ((rc = contract_gram(ctx, H, L, W, G, kGramParts, 256, gwork, ngwork, Z, sc, JtJ, s))) return rc;
+    *done = true;
+    return BEM_OK;
+}
+
+}  // namespace bem

@@ -7,8 +7,7 @@
 #include <numeric>
 #include <vector>
 
-#include "common.hpp"
-#include "sweep_common.hpp"
+#include "normal.hpp"
 
 namespace bem {
 
@@ -230,6 +229,13 @@ int fill_i32(bem_ctx* ctx, int* p, int64_t n, int v, hipStream_t s)
     return check_launch(ctx, "fill_i32");
 }
 
+int scale_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s)
+{
+    if (n <= 0) return BEM_OK;
+    hipLaunchKernelGGL(k_scale, dim3(blocks_for(n, 256)), dim3(256), 0, s, p, n, v);
+    return check_launch(ctx, "scale");
+}
+
 // Three-component sums over the N rows (mode as k_rowsum) into host out[3]; synchronises.
 static int row_sums(bem_ctx* ctx, const void* u, bool f32, const double* T, int64_t N, int mode, void* r, double* out,
                     double* dpart, hipStream_t s)
@@ -351,10 +357,16 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
     const bem_prec prec = mixed ? BEM_PREC_MIXED : BEM_PREC_FP64;
     st->accepted = 0;
     st->chol_retries = 0;
-    // mixed precision: samples and targets reordered into a workspace, cell by cell and then with
-    // the cell-ordered wavefronts dealt out (the step's results depend on the order only through
-    // rounding)
-    if (mixed && N > 0) {
+    // J^T J over grid cells where that pays (it needs the samples only): the step of 8,192 segments and
+    // 2,097,152 samples 434 -> 56 ms, of 500 segments and 100,000 samples 24.8 -> 16.5 ms; otherwise the tiles
+    // of the normal equations want neighbours in a wavefront: samples and targets reordered into a workspace,
+    // cell by cell and then with the cell-ordered wavefronts dealt out (the step's results depend on the
+    // order only through rounding)
+    bool have_jtj = false;
+    if (mixed && gram == BEM_GRAM_BF16X3_MFMA && H > 0 && N > 0 &&
+        (rc = run_jtj_cells(ctx, theta, H, x, N, JtJ, nd, &have_jtj, s)))
+        return rc;
+    if (mixed && N > 0 && !have_jtj) {
         const size_t lb = ((size_t)N * sizeof(int32_t) + 255) / 256 * 256;
         if ((rc = ensure(ctx, ctx->sortw, lb + (size_t)N * 10 * sizeof(double), s))) return rc;
         int32_t* lab = (int32_t*)ctx->sortw.ptr;
@@ -391,45 +403,32 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
         if ((rc = row_sums(ctx, u, mixed, T, N, 2, nullptr, sums, dpart, s))) return rc;
         for (int c = 0; c < 3; ++c) st->cbar[c] = N > 0 ? sums[c] / (double)N : 0.0;
     }
-    // residual and loss at theta; the mixed sweep's near-pair list serves the adjoint and the
-    // normal equations below (same samples, same parameters).  Should the list overflow, its
-    // capacity is raised and the sweep repeated, so that they find every near pair in it.
-    NearList nl{};
-    if (mixed) {
-        if ((rc = prepare_forward(ctx, theta, H, true, s))) return rc;
-        for (int pass = 0;; ++pass) {
-            if ((rc = launch_sweep_mixed(ctx, x, N, H * ctx->opts.segs_per_handle, st->cbar, (float*)u, s, &nl)))
-                return rc;
-            if ((rc = row_sums(ctx, u, mixed, T, N, 0, r, sums, dpart, s))) return rc;
-            int need = 0;
-            if ((rc = read_need(ctx, nl.need, s, &need))) return rc;
-            nl.overflowed = need > 0;        // without overflow the flagged-sample kernels are skipped
-            if (pass > 0 || !raise_near_slots(ctx, need, nl.nwaves, nl.slots)) break;
-        }
-    } else {
-        if ((rc = bem_eval(ctx, theta, H, x, N, st->cbar, u, prec, s))) return rc;
-        if ((rc = row_sums(ctx, u, mixed, T, N, 0, r, sums, dpart, s))) return rc;
-    }
+    // residual and loss at theta
+    if ((rc = bem_eval(ctx, theta, H, x, N, st->cbar, u, prec, s))) return rc;
+    if ((rc = row_sums(ctx, u, mixed, T, N, 0, r, sums, dpart, s))) return rc;
     const double L0 = N > 0 ? 0.5 * sums[0] / nd : 0.0;
     st->loss_before = L0;
     st->loss_after = L0;
     if (!std::isfinite(L0)) return set_error(ctx, BEM_ENUMERIC, "non-finite loss at the current parameters");
     if (H == 0 || N == 0) return BEM_OK;
-    // gradient g = (1/m) J^T r and Hessian H = (1/m) J^T J.  Mixed precision with an MFMA Gram and
-    // handles of several segments: g is formed with the J tiles (the handle rows' J^T r summed in the
-    // feature kernel, the beta rows' read back from the tile), so no separate adjoint sweep runs
-    // (LM workload, S = 32: 512 -> 445 ms per step, A/B on one box).  With one segment per handle
-    // the in-kernel sums cost more than the adjoint (paper-native workload: 26.5 -> 26.0 ms with
-    // the adjoint), so there, and otherwise, g comes from the adjoint (bem_vjp's kernels) and the
-    // normal equations form J^T J only.
-    const bool g_from_tiles = mixed && (gram == BEM_GRAM_FP32_MFMA || gram == BEM_GRAM_BF16X3_MFMA) &&
-                              ctx->opts.segs_per_handle >= 2;
-    if (g_from_tiles) {
-        if ((rc = run_jtj(ctx, theta, H, x, N, r, mixed, gram, JtJ, g, s, &nl, nd))) return rc;
-    } else {
-        if ((rc = run_vjp(ctx, theta, H, x, N, r, mixed, g, s))) return rc;
-        hipLaunchKernelGGL(k_scale, dim3(blocks_for(P, 256)), dim3(256), 0, s, g, P, 1.0 / nd);
-        if ((rc = run_jtj(ctx, theta, H, x, N, r, mixed, gram, JtJ, nullptr, s, mixed ? &nl : nullptr, nd))) return rc;
+    // gradient g = (1/m) J^T r by the adjoint, Hessian H = (1/m) J^T J
+    if ((rc = run_vjp(ctx, theta, H, x, N, r, mixed, g, s))) return rc;
+    if ((rc = scale_f64(ctx, g, P, 1.0 / nd, s))) return rc;
+    if (!have_jtj) {
+        NearList nl{};
+        if (mixed) {
+            // near pairs for the J tiles; should the list overflow, its capacity is raised and the
+            // samples are classified again, so that it holds every near pair
+            if ((rc = launch_expand(ctx, theta, H, s))) return rc;
+            for (int pass = 0;; ++pass) {
+                if ((rc = near_classify(ctx, ctx->nearf, x, N, H * ctx->opts.segs_per_handle, 0, &nl, s))) return rc;
+                int need = 0;
+                if ((rc = read_need(ctx, nl.need, s, &need))) return rc;
+                nl.overflowed = need > 0;        // without overflow the flagged-sample kernels are skipped
+                if (pass > 0 || !raise_near_slots(ctx, need, nl.nwaves, nl.slots)) break;
+            }
+        }
+        if ((rc = run_jtj(ctx, theta, H, x, N, mixed, gram, JtJ, s, mixed ? &nl : nullptr, nd))) return rc;
     }
     // regularisation terms (Sec. 4.4): gradient and Hessian into g and J^T J, value into the loss;
     // the snapping pairs chosen here are kept for the trial point
@@ -490,16 +489,9 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
         if (hipMemcpyAsync(&st->compat_violation, cviol, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess)
             return set_error(ctx, BEM_EHIP, "violation readback");
     }
-    // trial loss on the same samples and mean colour (an overflow of its near-pair list raises the
-    // capacity for later calls)
+    // trial loss on the same samples and mean colour
     if ((rc = bem_eval(ctx, th1, H, x, N, st->cbar, u, prec, s))) return rc;
     if ((rc = row_sums(ctx, u, mixed, T, N, 0, nullptr, sums, dpart, s))) return rc;
-    if (mixed) {
-        int need = 0;
-        const int64_t nw = (int64_t)blocks_for(N, 256) * 4;
-        if ((rc = read_need(ctx, ctx->sweep_need, s, &need))) return rc;
-        raise_near_slots(ctx, need, nw, near_slots_for(ctx->near_slots, nw));
-    }
     int hflag = 0;
     if (hipMemcpy(&hflag, dflag, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
         return set_error(ctx, BEM_EHIP, "flag readback");

@@ -124,13 +124,13 @@ __global__ void __launch_bounds__(192) k_node_cotangent(const double* __restrict
     }
 }
 
-// One float32 pair of the adjoint; a masked pair (on = false) is moved far off and its cotangents are
-// zero.  NQ: by quadrature (seg_math.hpp); 0: the closed forms, for near factors below 1.
+// One float32 pair of the adjoint; a masked pair (on = false) is taken at a point eight lengths beside the
+// segment, with zero cotangents.  NQ: by quadrature (seg_math.hpp); 0: the closed forms, for near factors below 1.
 template <int NQ>
 __device__ inline void adj_pair(const SegGeom<float>& g, float len, float ilen, const float (&w)[12],
                                 const float* __restrict__ r, bool on, float eps2f, float* __restrict__ af)
 {
-    const float X = on ? r[0] : 1.0e3f, Y = on ? r[1] : 1.0e3f;
+    const float X = on ? r[0] : g.ax - 8.0f * g.vy, Y = on ? r[1] : g.ay + 8.0f * g.vx;
     const float f0 = on ? r[2] : 0.f, f1 = on ? r[3] : 0.f, f2 = on ? r[4] : 0.f;
     const float wa = f0 * w[0] + f1 * w[1] + f2 * w[2];
     const float wb = f0 * w[3] + f1 * w[4] + f2 * w[5];
