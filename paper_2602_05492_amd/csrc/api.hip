@@ -469,7 +469,7 @@ void bem_destroy(bem_ctx* ctx)
                       &ctx->seg64, &ctx->seg32, &ctx->F, &ctx->U, &ctx->elem64, &ctx->elem32, &ctx->red,
                       &ctx->tmp0, &ctx->tmp1, &ctx->tmp2, &ctx->tmp3, &ctx->tmp4, &ctx->tmp5, &ctx->lmw,
                       &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
-                      &ctx->necw, &ctx->nezw, &ctx->neew,
+                      &ctx->necw, &ctx->nezw, &ctx->neew, &ctx->gemmw,
                       &ctx->tilew};
     for (DevBuf* b : bufs) release(*b);
     for (hipEvent_t e : ctx->ev)

@@ -110,7 +110,7 @@ struct bem_ctx {
     bem::DevBuf A, Apinv, LU, piv, un, vn, flag, scal, egeo;   // LU: A+^T once factored; egeo: outer elements [M][4] (a, b)
     // per-call workspaces
     bem::DevBuf seg64, seg32, F, U, elem64, elem32, red, tmp0, tmp1, tmp2, tmp3, tmp4, tmp5, lmw, nearf, regw, cholw, sortw,
-        boxw, cellw, cellb, farw, necw, nezw, neew;
+        boxw, cellw, cellb, farw, necw, nezw, neew, gemmw;
     // cell table and work list of the normal equations over cells, kept until their upload has ended
     std::vector<bem::CellInfo> ne_info;
     std::vector<int> ne_work;
@@ -188,13 +188,28 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
 // solve into the element tables
 int prepare_forward(bem_ctx* ctx, const double* theta, int H, bool mixed, hipStream_t s);
 // gemm.hip
-// plain products on float64 MFMA; with a list of 64 x 64 output tiles on the VALU (Gram mode FP64_VALU)
-int gemm_f64(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
-             int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* tiles, int ntiles);
-// the float64 Gram on float64 MFMA: work entries (row tile, column tile, part) of 128 x 128 output tiles
-int gemm_f64_list(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
-                  int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* work, int nwork,
-                  int kchunk, int64_t cstride);
+// C = alpha A B^T + beta C, row-major, A [m][k], B [n][k]; a batch's operands sa, sb, sc apart
+constexpr int kGemmPad = 16;
+struct Gemm64 {
+    int m, n, k;                 // k a multiple of kGemmPad (zeros), rows of A and B 16-byte aligned
+    double alpha;
+    const double* A;
+    int64_t lda;
+    const double* B;
+    int64_t ldb;
+    double beta;
+    double* C;
+    int64_t ldc;
+    int64_t sa = 0, sb = 0, sc = 0;
+};
+inline int gemm_pad(int64_t k) { return (int)((k + kGemmPad - 1) / kGemmPad * kGemmPad); }
+// on float64 MFMA
+int gemm_f64(bem_ctx* ctx, const Gemm64& g, int batch, hipStream_t s);
+// the float64 Gram on float64 MFMA: work entries (row tile, column tile, part) of 128 x 128 output tiles, part p of
+// k range [p kchunk, (p + 1) kchunk) into C + p cstride
+int gemm_f64_list(bem_ctx* ctx, const Gemm64& g, hipStream_t s, const int* work, int nwork, int kchunk, int64_t cstride);
+// on the VALU (Gram mode FP64_VALU): a list of 64 x 64 output tiles
+int gemm_f64_valu(bem_ctx* ctx, const Gemm64& g, hipStream_t s, const int* tiles, int ntiles);
 // jtj.hip
 int fill_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s);
 int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, bool mixed, int gram, double* JtJ,

@@ -1,8 +1,7 @@
-// gemm.hip - float64 dense products used around the normal equations:
-//   C = alpha op(A) op(B) + beta C   (row-major, op = identity or transpose)
-// k_gemm_f64_mfma: 128 x 128 (or 64 x 64) output tiles on float64 MFMA (v_mfma_f64_16x16x4f64), 16-deep
-//   k slabs staged through LDS (double buffered, the next slab prefetched into registers while
-//   the current one is multiplied); also the float64 Gram restricted to a list of output tiles.
+// gemm.hip - float64 dense products used around the normal equations, row-major:
+// k_gemm_f64_nt: C = alpha A B^T + beta C on float64 MFMA (v_mfma_f64_16x16x4f64), k contiguous in both operands
+//   and padded with zeros to kMK, one product or a batch; also the float64 Gram restricted to a list of
+//   output tiles.
 // k_gemm_f64: the plain VALU product (64 x 64 tiles, 4 x 4 outputs per thread), kept for the
 //   float64 VALU Gram mode.
 #include "common.hpp"
@@ -15,9 +14,8 @@ namespace {
 constexpr int TM = 64, TN = 64, TK = 16;
 
 __global__ void __launch_bounds__(256) k_gemm_f64(int m, int n, int k, double alpha, const double* __restrict__ A,
-                                                  int64_t lda, int ta, const double* __restrict__ B, int64_t ldb, int tb,
-                                                  double beta, double* __restrict__ C, int64_t ldc,
-                                                  const int* __restrict__ tiles)
+                                                  int64_t lda, const double* __restrict__ B, int64_t ldb, double beta,
+                                                  double* __restrict__ C, int64_t ldc, const int* __restrict__ tiles)
 {
     __shared__ double As[TK][TM + 1];
     __shared__ double Bs[TK][TN + 1];
@@ -28,24 +26,10 @@ __global__ void __launch_bounds__(256) k_gemm_f64(int m, int n, int k, double al
     for (int i = 0; i < 4; ++i)
         for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
     for (int k0 = 0; k0 < k; k0 += TK) {
-        // load a TM x TK slab of op(A) and a TK x TN slab of op(B)
         for (int e = threadIdx.x; e < TM * TK; e += 256) {
-            int r, kk;
-            if (ta) { r = e % TM; kk = e / TM; }
-            else { kk = e % TK; r = e / TK; }
-            const int gr = row0 + r, gk = k0 + kk;
-            double v = 0.0;
-            if (gr < m && gk < k) v = ta ? A[(size_t)gk * lda + gr] : A[(size_t)gr * lda + gk];
-            As[kk][r] = v;
-        }
-        for (int e = threadIdx.x; e < TK * TN; e += 256) {
-            int c, kk;
-            if (tb) { kk = e % TK; c = e / TK; }
-            else { c = e % TN; kk = e / TN; }
-            const int gc = col0 + c, gk = k0 + kk;
-            double v = 0.0;
-            if (gc < n && gk < k) v = tb ? B[(size_t)gc * ldb + gk] : B[(size_t)gk * ldb + gc];
-            Bs[kk][c] = v;
+            const int kk = e % TK, r = e / TK, gk = k0 + kk;
+            As[kk][r] = row0 + r < m && gk < k ? A[(size_t)(row0 + r) * lda + gk] : 0.0;
+            Bs[kk][r] = col0 + r < n && gk < k ? B[(size_t)(col0 + r) * ldb + gk] : 0.0;
         }
         __syncthreads();
 #pragma unroll
@@ -72,123 +56,107 @@ __global__ void __launch_bounds__(256) k_gemm_f64(int m, int n, int k, double al
 
 
 // ---- float64 MFMA product ------------------------------------------------------------------
-// Block tile kMB x kMB, 4 wavefronts as 2 x 2, each wavefront 64 x 64 as 4 x 4 tiles of
-// v_mfma_f64_16x16x4f64.  Operand lane layout of that instruction: lane l holds A[l mod 16][l / 16]
-// of its 16 x 4 slice and B[l / 16][l mod 16] of its 4 x 16 slice; accumulator element q of lane l
-// is row 4 q + l / 16, column l mod 16 of the 16 x 16 tile.  Both operand slabs are stored in LDS
-// k-major ([k][row] and [k][col]) so that each operand is one ds_read_b64 per lane.
-typedef double d4_t __attribute__((ext_vector_type(4)));
-constexpr int kMB = 128, kMK = 16;
-
-// element e of a BM x kMK slab of op(X) starting at (r0, k0): its slab coordinates, and whether it lies
-// in the rows x kd operand.  Non-transposed X is row-major [row][k] (16 consecutive threads read one
-// row's 16 k values); transposed X is stored [k][row].
-template <int BM>
-__device__ inline bool slab_at(int tx, int r0, int k0, int rows, int kd, int e, int& sr, int& sk)
-{
-    if (tx) { sk = e / BM; sr = e % BM; }
-    else { sr = e / kMK; sk = e % kMK; }
-    return r0 + sr < rows && k0 + sk < kd;
-}
-// The element there, or element (0, 0) of X outside the operand (replaced by 0 where the slab is stored:
-// a select beside the load would wait for it, and the loads are to stay in flight behind the products).
-template <int BM>
-__device__ inline double slab_load(const double* __restrict__ X, int64_t ldx, int tx, int r0, int k0, int rows, int kd,
-                                   int e)
-{
-    int sr, sk;
-    const bool in = slab_at<BM>(tx, r0, k0, rows, kd, e, sr, sk);
-    const int gr = in ? r0 + sr : 0, gk = in ? k0 + sk : 0;
-    return X[tx ? (int64_t)gk * ldx + gr : (int64_t)gr * ldx + gk];
-}
-
-// BM x BM output tile per block (BM = 128: each wavefront 64 x 64 as 4 x 4 MFMA tiles; BM = 64:
-// 32 x 32 as 2 x 2, for products whose 128-tile grid would leave most CUs idle).
+// Block tile BM x BM, 4 wavefronts as 2 x 2, each BM/2 x BM/2 in 16 x 16 tiles of v_mfma_f64_16x16x4f64.  Operand
+// lane layout of that instruction: lane l holds A[l mod 16][l / 16] of its 16 x 4 slice and B[l / 16][l mod 16] of
+// its 4 x 16 slice; accumulator element q of lane l is row 4 q + l / 16, column l mod 16 of the 16 x 16 tile.
 //
+// Bound by the matrix cores (64 cycles an instruction): all else is to stay out of their way.  Both operands
+// are [row][k], so that a 16-deep k slab of a row is a 128-byte line, and go straight from global memory into
+// LDS (16 bytes a lane, no registers, no address arithmetic per element, no masks); the next slab is in flight
+// behind the products of the current one.  Rows past the operands' last repeat it (their products are not
+// stored); k is padded with zeros by whoever writes the operands.  LDS rows are 8 chunks of two k, chunk c of row
+// r at position c ^ ((r / 2) mod 8), so that the 16 lanes of a 16-byte read at one chunk fall in distinct
+// banks; a lane's load fetches the chunk whose position is its own.  A lane's two consecutive k go to two
+// instructions: which k an instruction sums is free as long as A and B agree.
+//
+// Gram of 1,920 rows over 32,768 samples: 2.82 ms (41 TFLOP/s, operands through registers with masks) -> 1.79 ms (65 TFLOP/s).
+typedef double d2_t __attribute__((ext_vector_type(2)));
+typedef double d4_t __attribute__((ext_vector_type(4)));
+constexpr int kMB = 128, kMK = kGemmPad;
+
 // Blocks go to the 8 XCDs round-robin, each XCD with an L2 of its own, so XCD x is given a contiguous run
 // of the tiles: of the work list (row tile, column tile, part: k range [part kchunk, (part + 1) kchunk),
-// result at C + part cstride), or of the whole grid in bands of 8 tile columns.
+// result at C + part cstride), or of the grid of tiles (part-major, bands of 8 tile columns).
 template <int BM>
-__global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m, int n, int k_all, double alpha,
-                                                                        const double* __restrict__ A, int64_t lda, int ta,
-                                                                        const double* __restrict__ B, int64_t ldb, int tb,
-                                                                        double beta, double* __restrict__ C, int64_t ldc,
-                                                                        const int* __restrict__ work, int nwork,
-                                                                        int kchunk, int64_t cstride)
+__global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_nt(Gemm64 g, const int* __restrict__ work, int nwork,
+                                                                      int kchunk, int64_t cstride)
 {
-    constexpr int LD = BM + 4;                  // LDS row stride (doubles)
-    constexpr int NL = BM * kMK / 256;          // slab elements per thread and operand
     constexpr int TI = BM / 32;                 // 16 x 16 MFMA tiles per wavefront and dimension
-    __shared__ double As[2][kMK][LD];
-    __shared__ double Bs[2][kMK][LD];
+    constexpr int NL = BM / 32;                 // load instructions (8 rows) per wavefront, slab and operand
+    __shared__ __attribute__((aligned(1024))) double Sm[2][2][BM][kMK];
     const int wi = (int)(blockIdx.x & 7) * ((nwork + 7) >> 3) + (int)(blockIdx.x >> 3);
     if (wi >= nwork) return;
-    int bm, bn, k0 = 0;
+    int bm, bn, part;
     if (work) {
         bm = work[3 * wi];
         bn = work[3 * wi + 1];
-        k0 = work[3 * wi + 2] * kchunk;
-        C += (int64_t)work[3 * wi + 2] * cstride;
+        part = work[3 * wi + 2];
     } else {
-        const int nbm = (m + BM - 1) / BM, band = wi / (8 * nbm), r = wi % (8 * nbm);
+        const int nbm = (g.m + BM - 1) / BM, per = 8 * nbm * ((g.n + 8 * BM - 1) / (8 * BM));
+        part = wi / per;
+        const int t = wi % per, r = t % (8 * nbm);
         bm = r >> 3;
-        bn = band * 8 + (r & 7);
-        if (bn * BM >= n) return;
+        bn = t / (8 * nbm) * 8 + (r & 7);
+        if (bn * BM >= g.n) return;
     }
-    const int k = k0 + kchunk < k_all ? k0 + kchunk : k_all;      // this block's k range [k0, k)
+    const int k0 = part * kchunk, k1 = k0 + kchunk < g.k ? k0 + kchunk : g.k;
+    const int ns = k1 > k0 ? (k1 - k0) / kMK : 0;
     const int row0 = bm * BM, col0 = bn * BM;
-    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+    const double* A = g.A + blockIdx.y * g.sa + k0;
+    const double* B = g.B + blockIdx.y * g.sb + k0;
+    double* C = g.C + blockIdx.y * g.sc + part * cstride;
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = w >> 1, wc = w & 1;
-    // B as a (k x n) operand: op(B) row-major [k][col] unless transposed ([col][k]); slab_load takes
-    // the "row" index as the column of op(B), so its transposition flag is the opposite one
-    const int tbB = tb ? 0 : 1;
-    double pa[NL], pb[NL];
-    auto load = [&](int ks) {
+    // wavefront w loads rows BM/4 w .. BM/4 (w + 1) - 1 of both slabs
+    const double *ga[NL], *gb[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const int r = BM / 4 * w + 8 * i + (l >> 3), c = 2 * ((l & 7) ^ ((r >> 1) & 7));
+        ga[i] = A + (int64_t)(row0 + r < g.m ? row0 + r : g.m - 1) * g.lda + c;
+        gb[i] = B + (int64_t)(col0 + r < g.n ? col0 + r : g.n - 1) * g.ldb + c;
+    }
+    auto load = [&](int buf, int s) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            pa[i] = slab_load<BM>(A, lda, ta, row0, ks, m, k, tid + 256 * i);
-            pb[i] = slab_load<BM>(B, ldb, tbB, col0, ks, n, k, tid + 256 * i);
+            __builtin_amdgcn_global_load_lds((const void*)(ga[i] + s * kMK), (void*)&Sm[buf][0][BM / 4 * w + 8 * i][0], 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const void*)(gb[i] + s * kMK), (void*)&Sm[buf][1][BM / 4 * w + 8 * i][0], 16, 0, 0);
         }
     };
-    auto store = [&](int buf, int ks) {
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            int r, kk;
-            const bool ia = slab_at<BM>(ta, row0, ks, m, k, tid + 256 * i, r, kk);
-            As[buf][kk][r] = ia ? pa[i] : 0.0;
-            const bool ib = slab_at<BM>(tbB, col0, ks, n, k, tid + 256 * i, r, kk);
-            Bs[buf][kk][r] = ib ? pb[i] : 0.0;
-        }
-    };
-    load(k0);
-    store(0, k0);
-    __syncthreads();
     d4_t acc[TI][TI];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TI; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
-    const int nk = k > k0 ? (k - k0 + kMK - 1) / kMK : 0;
-    for (int s = 0; s < nk; ++s) {
+    if (ns > 0) load(0, 0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const int rr = l & 15, lk = l >> 4;
+    for (int s = 0; s < ns; ++s) {
         const int cur = s & 1;
-        const bool more = s + 1 < nk;
-        if (more) load(k0 + (s + 1) * kMK);
-        __builtin_amdgcn_sched_barrier(0);        // the loads go out before the products, and are waited for after
+        if (s + 1 < ns) load(cur ^ 1, s + 1);
 #pragma unroll
-        for (int ks = 0; ks < kMK; ks += 4) {
-            const int kk = ks + (l >> 4), rr = l & 15;
-            double a[TI], b[TI];
+        for (int h = 0; h < 2; ++h) {
+            d2_t a[TI], b[TI];
 #pragma unroll
-            for (int i = 0; i < TI; ++i) a[i] = As[cur][kk][(BM / 2) * wr + 16 * i + rr];
+            for (int i = 0; i < TI; ++i) {
+                const int r = BM / 2 * wr + 16 * i + rr;
+                a[i] = *(const d2_t*)&Sm[cur][0][r][2 * ((4 * h + lk) ^ ((r >> 1) & 7))];
+            }
 #pragma unroll
-            for (int j = 0; j < TI; ++j) b[j] = Bs[cur][kk][(BM / 2) * wc + 16 * j + rr];
+            for (int j = 0; j < TI; ++j) {
+                const int r = BM / 2 * wc + 16 * j + rr;
+                b[j] = *(const d2_t*)&Sm[cur][1][r][2 * ((4 * h + lk) ^ ((r >> 1) & 7))];
+            }
 #pragma unroll
-            for (int i = 0; i < TI; ++i)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int j = 0; j < TI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TI; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j][t], acc[i][j], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (more) store(cur ^ 1, k0 + (s + 1) * kMK);
+        __builtin_amdgcn_s_waitcnt(0);          // this wavefront's share of the next slab is in LDS
         __syncthreads();
     }
 #pragma unroll
@@ -197,50 +165,88 @@ __global__ void __launch_bounds__(256, BM == 128 ? 2 : 4) k_gemm_f64_mfma(int m,
         for (int j = 0; j < TI; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int r = row0 + (BM / 2) * wr + 16 * i + 4 * q + (l >> 4);
-                const int c = col0 + (BM / 2) * wc + 16 * j + (l & 15);
-                if (r < m && c < n) {
-                    double* o = C + (size_t)r * ldc + c;
-                    *o = alpha * acc[i][j][q] + (beta == 0.0 ? 0.0 : beta * *o);
+                const int r = row0 + BM / 2 * wr + 16 * i + 4 * q + lk;
+                const int c = col0 + BM / 2 * wc + 16 * j + rr;
+                if (r < g.m && c < g.n) {
+                    double* o = C + (int64_t)r * g.ldc + c;
+                    *o = g.alpha * acc[i][j][q] + (g.beta == 0.0 ? 0.0 : g.beta * *o);
                 }
             }
 }
 
+// C = alpha sum of the parts (P + part cstride, batch entries m n apart) + beta C, in the parts' order
+__global__ void __launch_bounds__(256) k_gemm_sum(const double* __restrict__ P, int parts, int64_t cstride, Gemm64 g)
+{
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= (int64_t)g.m * g.n) return;
+    const double* p = P + blockIdx.y * (int64_t)g.m * g.n + e;
+    double v = 0.0;
+    for (int i = 0; i < parts; ++i) v += p[i * cstride];
+    double* o = g.C + blockIdx.y * g.sc + (e / g.n) * g.ldc + e % g.n;
+    *o = g.alpha * v + (g.beta == 0.0 ? 0.0 : g.beta * *o);
+}
+
+// what k_gemm_f64_nt assumes of its operands
+bool loads_aligned(const Gemm64& g)
+{
+    return g.k % kMK == 0 && !((g.lda | g.ldb | g.sa | g.sb) & 1) && !(((uintptr_t)g.A | (uintptr_t)g.B) & 15);
+}
+
 }  // namespace
 
-// C + part cstride = alpha op(A) op(B) + beta C over the k range of each part, on the 128 x 128 output
-// tiles of a work list (row tile, column tile, part).
-int gemm_f64_list(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
-                  int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* work, int nwork,
-                  int kchunk, int64_t cstride)
+int gemm_f64_list(bem_ctx* ctx, const Gemm64& g, hipStream_t s, const int* work, int nwork, int kchunk, int64_t cstride)
 {
     if (nwork <= 0) return BEM_OK;
-    hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(8 * ((nwork + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
-                       ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, work, nwork, kchunk, cstride);
+    if (!loads_aligned(g) || kchunk % kMK) return set_error(ctx, BEM_EINVAL, "float64 Gram operands (internal)");
+    hipLaunchKernelGGL(k_gemm_f64_nt<kMB>, dim3(8 * ((nwork + 7) / 8)), dim3(256), 0, s, g, work, nwork, kchunk, cstride);
     return check_launch(ctx, "gemm_f64");
 }
 
-int gemm_f64(bem_ctx* ctx, int m, int n, int k, double alpha, const double* A, int64_t lda, bool ta, const double* B,
-             int64_t ldb, bool tb, double beta, double* C, int64_t ldc, hipStream_t s, const int* tiles, int ntiles)
+int gemm_f64_valu(bem_ctx* ctx, const Gemm64& g, hipStream_t s, const int* tiles, int ntiles)
 {
-    if (m <= 0 || n <= 0) return BEM_OK;
-    if (tiles) {                      // a list of 64 x 64 output tiles, on the vector ALUs
-        if (ntiles <= 0) return BEM_OK;
-        hipLaunchKernelGGL(k_gemm_f64, dim3(ntiles), dim3(256), 0, s, m, n, k, alpha, A, lda, ta ? 1 : 0, B, ldb,
-                           tb ? 1 : 0, beta, C, ldc, tiles);
+    if (ntiles <= 0) return BEM_OK;
+    hipLaunchKernelGGL(k_gemm_f64, dim3(ntiles), dim3(256), 0, s, g.m, g.n, g.k, g.alpha, g.A, g.lda, g.B, g.ldb, g.beta, g.C,
+                       g.ldc, tiles);
+    return check_launch(ctx, "gemm_f64");
+}
+
+int gemm_f64(bem_ctx* ctx, const Gemm64& g, int batch, hipStream_t s)
+{
+    if (g.m <= 0 || g.n <= 0 || batch <= 0) return BEM_OK;
+    if (!loads_aligned(g)) return set_error(ctx, BEM_EINVAL, "float64 product operands (internal)");
+    const auto count = [&](int bm) { return 8 * blocks_for(g.n, 8 * bm) * blocks_for(g.m, bm); };
+    const auto tiles = [&](int bm) { return (int64_t)blocks_for(g.n, bm) * blocks_for(g.m, bm) * batch; };
+    if (tiles(kMB) >= 2048) {
+        const int nw = count(kMB);
+        hipLaunchKernelGGL(k_gemm_f64_nt<kMB>, dim3(8 * ((nw + 7) / 8), batch), dim3(256), 0, s, g, (const int*)nullptr, nw, g.k,
+                           (int64_t)0);
         return check_launch(ctx, "gemm_f64");
     }
-    const auto count = [&](int bm) { return 8 * blocks_for(blocks_for(n, bm), 8) * blocks_for(m, bm); };
-    if ((int64_t)blocks_for(n, kMB) * blocks_for(m, kMB) >= 1024) {
-        const int nw = count(kMB);
-        hipLaunchKernelGGL(k_gemm_f64_mfma<kMB>, dim3(8 * ((nw + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
-                           ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr, nw, k, (int64_t)0);
-    } else {
-        // fewer than two rounds of 128-tiles over the CUs: 64-tiles, 4x the blocks
-        const int nw = count(64);
-        hipLaunchKernelGGL(k_gemm_f64_mfma<64>, dim3(8 * ((nw + 7) / 8)), dim3(256), 0, s, m, n, k, alpha, A, lda,
-                           ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc, (const int*)nullptr, nw, k, (int64_t)0);
+    // fewer than four rounds of 128-tiles over the CUs: 64-tiles (500 straight handles, 89 GFLOP in three
+    // products: 2.5 -> 1.6 ms); fewer than two a CU of those: k in parts of at least 128, summed afterwards (4 cubic
+    // handles, the three products 580 -> 47 us)
+    int parts = (int)(512 / tiles(64));
+    if (parts > g.k / 128) parts = g.k / 128;
+    if (parts < 2) parts = 1;
+    const int kchunk = parts > 1 ? blocks_for(blocks_for(g.k, parts), kMK) * kMK : g.k;
+    if (parts > 1) parts = blocks_for(g.k, kchunk);
+    const int nw = count(64) * parts;
+    Gemm64 p = g;
+    const int64_t cstride = (int64_t)batch * g.m * g.n;
+    if (parts > 1) {
+        int rc;
+        if ((rc = ensure(ctx, ctx->gemmw, (size_t)parts * cstride * sizeof(double), s))) return rc;
+        p.C = (double*)ctx->gemmw.ptr;
+        p.ldc = g.n;
+        p.sc = (int64_t)g.m * g.n;
+        p.alpha = 1.0;
+        p.beta = 0.0;
     }
+    hipLaunchKernelGGL(k_gemm_f64_nt<64>, dim3(8 * ((nw + 7) / 8), batch), dim3(256), 0, s, p, (const int*)nullptr, nw, kchunk,
+                       cstride);
+    if (parts > 1)
+        hipLaunchKernelGGL(k_gemm_sum, dim3(blocks_for((int64_t)g.m * g.n, 256), batch), dim3(256), 0, s, (const double*)p.C,
+                           parts, cstride, g);
     return check_launch(ctx, "gemm_f64");
 }
 

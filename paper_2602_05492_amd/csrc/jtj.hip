@@ -501,18 +501,40 @@ __global__ void k_gauss_points(int M, const double* __restrict__ eg, double* __r
     gx[2 * t + 1] = 0.5 * (ay + by) + node * 0.5 * (by - ay);
 }
 
-// dF[i][f] = sum_q w_q |G_i|/2 Xg[f][3i + q]
-__global__ void k_boundary_features(const double* __restrict__ Xg, int nf, int M, const double* __restrict__ eg,
+// dF[f][i] = sum_q w_q |G_i|/2 Xg[f][3i + q], zeros for i in [M, Mp)
+__global__ void k_boundary_features(const double* __restrict__ Xg, int nf, int M, int Mp, const double* __restrict__ eg,
                                     double* __restrict__ dF)
 {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t f = e / Mp;
+    const int i = (int)(e % Mp);
     if (f >= nf) return;
-    double ax, ay, bx, by;
-    load_element(eg, i, ax, ay, bx, by);
-    const double half = 0.5 * sqrt((bx - ax) * (bx - ax) + (by - ay) * (by - ay));
-    const double* r = Xg + (size_t)f * 3 * M + 3 * i;
-    dF[(size_t)i * nf + f] = half * (kGaussW0 * r[0] + kGaussW1 * r[1] + kGaussW0 * r[2]);
+    double v = 0.0;
+    if (i < M) {
+        double ax, ay, bx, by;
+        load_element(eg, i, ax, ay, bx, by);
+        const double half = 0.5 * sqrt((bx - ax) * (bx - ax) + (by - ay) * (by - ay));
+        const double* r = Xg + f * 3 * M + 3 * i;
+        v = half * (kGaussW0 * r[0] + kGaussW1 * r[1] + kGaussW0 * r[2]);
+    }
+    dF[e] = v;
+}
+
+// X [rows][ldx] (transposed: [cols][ldx]) into Y [rp][cp], zeros outside
+__global__ void k_pad(const double* __restrict__ X, int64_t ldx, bool transposed, int64_t rows, int cols, int64_t rp, int cp,
+                      double* __restrict__ Y)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = e / cp, c = e % cp;
+    if (r < rp) Y[e] = r < rows && c < cols ? X[transposed ? c * ldx + r : r * ldx + c] : 0.0;
+}
+
+// Zeros in columns [n, n rounded up to kGemmPad) of a float64 tile's W rows
+__global__ void k_zero_tail_f64(double* __restrict__ Xt, int64_t W, int64_t ld, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = n + i % kGemmPad;
+    if (i < W * kGemmPad && t < (n + kGemmPad - 1) / kGemmPad * kGemmPad) Xt[i / kGemmPad * ld + t] = 0.0;
 }
 
 __global__ void k_fill(double* __restrict__ p, int64_t n, double v)
@@ -520,15 +542,17 @@ __global__ void k_fill(double* __restrict__ p, int64_t n, double v)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// Channel-c augmented Gram in compact order [g_c (GH) | e (CH) | beta (M)],
-// symmetric fill from the upper triangle of G.  The compact-to-row map is increasing, so
+// Augmented Gram of channel c = blockIdx.z in compact order [g_c (GH) | e (CH) | beta (M)], rows of Wp with zeros
+// past Wc, symmetric fill from the upper triangle of G.  The compact-to-row map is increasing, so
 // entry (a, b) comes from G[row(a)][row(b)] for a <= b and from G[row(b)][row(a)] below the
 // diagonal.  A block owns a 32 x 32 tile of (a, b); a tile below the diagonal reads its
 // mirror tile along a (coalesced) and transposes it through LDS.
-__global__ void __launch_bounds__(256) k_gather_gram(const double* __restrict__ G, int64_t W, Layout L, int c, int Wc,
+__global__ void __launch_bounds__(256) k_gather_gram(const double* __restrict__ G, int64_t W, Layout L, int Wc, int Wp,
                                                      double* __restrict__ Gc)
 {
     __shared__ double T[32][33];
+    const int c = blockIdx.z;
+    Gc += (size_t)c * Wc * Wp;
     const int a0 = blockIdx.y * 32, b0 = blockIdx.x * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     if (b0 + 31 < a0) {                  // wholly below the diagonal: T[b][a] = G[row(b)][row(a)]
@@ -541,31 +565,30 @@ __global__ void __launch_bounds__(256) k_gather_gram(const double* __restrict__ 
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int a = a0 + ty + 8 * k, b = b0 + tx;
-            if (a < Wc) Gc[(size_t)a * Wc + b] = T[tx][ty + 8 * k];
+            if (a < Wc) Gc[(size_t)a * Wp + b] = T[tx][ty + 8 * k];
         }
         return;
     }
     const int b = b0 + tx;
-    if (b >= Wc) return;
-    const int64_t ib = L.row(b, c);
+    if (b >= Wp) return;
+    const int64_t ib = b < Wc ? L.row(b, c) : 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int a = a0 + ty + 8 * k;
         if (a >= Wc) break;
         const int64_t ia = L.row(a, c);
         // the upper triangle holds every needed entry (diagonal tiles are computed whole)
-        Gc[(size_t)a * Wc + b] = ia <= ib ? G[(size_t)ia * W + ib] : G[(size_t)ib * W + ia];
+        Gc[(size_t)a * Wp + b] = b >= Wc ? 0.0 : ia <= ib ? G[(size_t)ia * W + ib] : G[(size_t)ib * W + ia];
     }
 }
 
-// Zc[i][a] = Z[i][row(a)] for the handle part of the compact order (a < (G + C)H)
-__global__ void k_gather_z(const double* __restrict__ Z, Layout L, int M, int c, double* __restrict__ Zc)
+// Zc[c][a][i] = Z[row(a, c)][i] for the handle part of the compact order (a < (G + C)H), rows of Mp
+__global__ void k_gather_z(const double* __restrict__ Z, Layout L, int Mp, double* __restrict__ Zc)
 {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    const int n = L.compact();
-    if (a >= n) return;
-    Zc[(size_t)i * n + a] = Z[(size_t)i * L.handle_rows() + L.row(a, c)];
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = blockIdx.y;
+    const int64_t a = e / Mp;
+    if (a < L.compact()) Zc[(int64_t)c * L.compact() * Mp + e] = Z[(size_t)L.row((int)a, c) * Mp + e % Mp];
 }
 
 // Every entry of J^T J from the three channels' blocks v_c(a, b) = Gc_c[a][b] + (S_c[a][b] +
@@ -574,7 +597,7 @@ __global__ void k_gather_z(const double* __restrict__ Z, Layout L, int M, int c,
 // with a colour parameter of channel c takes v_c; colour entries of two different channels
 // are zero.  A block owns a 32 x 32 tile of (a, b) and reads S_c[b][a] through LDS, so both
 // reads of S are coalesced; v_c(a, b) = v_c(b, a) bit for bit, so J^T J is exactly symmetric.
-__global__ void __launch_bounds__(256) k_scatter_jtj(const double* __restrict__ Gc, int64_t gcs, int Wc,
+__global__ void __launch_bounds__(256) k_scatter_jtj(const double* __restrict__ Gc, int64_t gcs, int Wp,
                                                      const double* __restrict__ S, int64_t ss, Layout L, double s,
                                                      double* __restrict__ JtJ, int64_t P)
 {
@@ -602,7 +625,7 @@ __global__ void __launch_bounds__(256) k_scatter_jtj(const double* __restrict__ 
         if (a >= n) break;
         double v[3];
         for (int c = 0; c < 3; ++c)
-            v[c] = Gc[c * gcs + (size_t)a * Wc + b] + (S[c * ss + (size_t)a * n + b] + T[c][tx][ty + 8 * k]);
+            v[c] = Gc[c * gcs + (size_t)a * Wp + b] + (S[c * ss + (size_t)a * n + b] + T[c][tx][ty + 8 * k]);
         const bool ga = a < geo;
         const int64_t ca = ga ? (int64_t)Q * (a / L.G) + a % L.G
                               : (int64_t)Q * ((a - geo) / L.C) + L.G + 3 * ((a - geo) % L.C);
@@ -752,23 +775,29 @@ static int launch_features(bem_ctx* ctx, const double* x, int64_t npts, int H, b
 int boundary_derivatives(bem_ctx* ctx, int H, hipStream_t s, double** Zout)
 {
     int rc;
-    const int M = ctx->M;
+    const int M = ctx->M, Mp = gemm_pad(M);
     const int nf = (int)layout_of(ctx, H).handle_rows();
-    const size_t gxs = (size_t)3 * M * 2;
-    if ((rc = ensure(ctx, ctx->tmp3, (gxs + (size_t)nf * 3 * M) * sizeof(double), s))) return rc;
-    if ((rc = ensure(ctx, ctx->tmp4, (size_t)2 * M * nf * sizeof(double), s))) return rc;
+    const size_t gxs = (size_t)3 * M * 2, xgs = (size_t)nf * 3 * M;
+    const size_t aps = Mp == M ? 0 : (size_t)Mp * Mp;
+    if ((rc = ensure(ctx, ctx->tmp3, (gxs + xgs + aps) * sizeof(double) + 16, s))) return rc;
+    if ((rc = ensure(ctx, ctx->tmp4, (size_t)2 * Mp * nf * sizeof(double), s))) return rc;
     double* gx = (double*)ctx->tmp3.ptr;
     double* Xg = gx + gxs;
+    const double* Ap = (const double*)ctx->Apinv.ptr;
     double* dF = (double*)ctx->tmp4.ptr;
-    double* Z = dF + (size_t)M * nf;
+    double* Z = dF + (size_t)Mp * nf;
+    if (aps) {
+        double* t = Xg + xgs + (xgs & 1);        // gxs is even: 16-byte aligned
+        hipLaunchKernelGGL(k_pad, dim3(blocks_for((int64_t)Mp * Mp, 256)), dim3(256), 0, s, Ap, (int64_t)M, false, (int64_t)M, M,
+                           (int64_t)Mp, Mp, t);
+        Ap = t;
+    }
     hipLaunchKernelGGL(k_gauss_points, dim3(blocks_for(3 * M, 256)), dim3(256), 0, s, M, (const double*)ctx->egeo.ptr, gx);
     if ((rc = launch_features<double>(ctx, gx, 3 * (int64_t)M, H, false, false, Xg, nullptr, 3 * (int64_t)M, s))) return rc;
-    hipLaunchKernelGGL(k_boundary_features, dim3(blocks_for(nf, 256), M), dim3(256), 0, s, Xg, nf, M,
+    hipLaunchKernelGGL(k_boundary_features, dim3(blocks_for((int64_t)nf * Mp, 256)), dim3(256), 0, s, Xg, nf, M, Mp,
                        (const double*)ctx->egeo.ptr, dF);
     if ((rc = check_launch(ctx, "boundary features"))) return rc;
-    if ((rc = gemm_f64(ctx, M, nf, M, 1.0, (const double*)ctx->Apinv.ptr, M, false, dF, nf, false, 0.0, Z, nf, s,
-                       nullptr, 0)))
-        return rc;
+    if ((rc = gemm_f64(ctx, Gemm64{nf, Mp, Mp, 1.0, dF, Mp, Ap, Mp, 0.0, Z, Mp}, 1, s))) return rc;
     *Zout = Z;
     return BEM_OK;
 }
@@ -822,15 +851,20 @@ static std::vector<int> gram_work(const std::vector<int>& tiles, int parts)
     return w;
 }
 
-// Sample parts of the float64 Gram: two 128 x 128 tiles run on a CU at a time, so that 90 tiles (32 cubic
-// handles) kept 90 of 256 CUs half busy; the parts make about two rounds of 512 blocks (at most 2 GiB of
-// partial Grams).
+// Sample parts of the float64 Gram: 512 blocks (two 128 x 128 tiles a CU) run at a time, so the parts are
+// chosen to fill one, two or three such rounds, the fewest that leave at most 2% more of them empty than the best
+// (at most 16 parts and 2 GiB of partial Grams).  45 tiles (4 cubic handles, 16,384 samples): 16 parts, 1.4 rounds,
+// 427 us and 44 us to sum them; 11 parts, one round, 412 and 12 us.
 static int f64_parts(int ntiles, int64_t W)
 {
-    int64_t p = ntiles > 0 ? 1024 / ntiles : 1;
-    const int64_t most = ((int64_t)2 << 30) / (W * W * 8);
-    if (p > most) p = most;
-    return (int)(p < 1 ? 1 : (p > 16 ? 16 : p));
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(16, ((int64_t)2 << 30) / (W * W * 8)));
+    const auto fill = [&](int64_t p) { return (double)(ntiles * p) / (double)((ntiles * p + 511) / 512 * 512); };
+    int64_t best = 1;
+    for (int rounds = 1; rounds <= 3 && ntiles > 0; ++rounds) {
+        const int64_t p = std::min<int64_t>(most, 512 * rounds / ntiles);
+        if (p >= 1 && fill(p) > fill(best) + 0.02) best = p;
+    }
+    return (int)best;
 }
 
 namespace {
@@ -881,35 +915,29 @@ int contract_gram(bem_ctx* ctx, int H, const Layout& L, int64_t W, double* G, in
     const int Wc = n12 + M;
     if (parts > 1) {
         // the first nwork / parts work entries are part 0's, one per tile of the list
-        hipLaunchKernelGGL(k_sum_parts, dim3(nwork / parts, 8), dim3(256), 0, s, G, parts, W, work, ts);
+        hipLaunchKernelGGL(k_sum_parts, dim3(nwork / parts, nwork / parts < 64 ? 32 : 8), dim3(256), 0, s, G, parts, W, work, ts);
         if ((rc = check_launch(ctx, "gram parts"))) return rc;
     }
-    // contraction: per channel the compact Gram and S, then every entry of J^T J in one pass
-    const size_t wc2 = (size_t)Wc * Wc;
-    const size_t szc = (size_t)M * n12;
-    const size_t sn = (size_t)n12 * n12;
-    if ((rc = ensure(ctx, ctx->tmp2, (3 * wc2 + szc + 3 * sn) * sizeof(double), s))) return rc;
+    // contraction: the channels' compact Grams and S, then every entry of J^T J in one pass.
+    // A channel's block of J^T J is G + B Zc + (B Zc)^T + Zc^T D Zc (Zc [M][n12] = Z's columns) with B = Gc[0:n12, n12:Wc]
+    // and D = Gc[n12:, n12:] (symmetric), which equals G + S + S^T with S = Y Zc and
+    // Y = B + (1/2) Zc^T D: two products instead of three.  Y overwrites B in Gc.
+    const int Mp = gemm_pad(M), Wp = n12 + Mp;
+    const int64_t wc2 = (int64_t)Wc * Wp, szc = (int64_t)Mp * n12, sn = (int64_t)n12 * n12;
+    if ((rc = ensure(ctx, ctx->tmp2, 3 * (wc2 + szc + sn) * sizeof(double), s))) return rc;
     double* Gc3 = (double*)ctx->tmp2.ptr;
     double* Zc = Gc3 + 3 * wc2;
-    double* S3 = Zc + szc;
-    for (int c = 0; c < 3; ++c) {
-        double* Gc = Gc3 + c * wc2;
-        double* S1 = S3 + c * sn;
-        hipLaunchKernelGGL(k_gather_gram, dim3(blocks_for(Wc, 32), blocks_for(Wc, 32)), dim3(256), 0, s, G, W, L, c,
-                           Wc, Gc);
-        hipLaunchKernelGGL(k_gather_z, dim3(blocks_for(n12, 256), M), dim3(256), 0, s, Z, L, M, c, Zc);
-        if ((rc = check_launch(ctx, "gather"))) return rc;
-        // The channel's block of J^T J is G + B Zc + (B Zc)^T + Zc^T D Zc with B = Gc[0:n12, n12:Wc]
-        // and D = Gc[n12:, n12:] (symmetric), which equals G + S + S^T with S = Y Zc and
-        // Y = B + (1/2) Zc^T D: two products instead of three.  Y overwrites B in Gc.
-        if ((rc = gemm_f64(ctx, n12, M, M, 0.5, Zc, n12, true, Gc + (size_t)n12 * Wc + n12, Wc, false, 1.0, Gc + n12, Wc, s,
-                           nullptr, 0)))
-            return rc;
-        if ((rc = gemm_f64(ctx, n12, n12, M, 1.0, Gc + n12, Wc, false, Zc, n12, false, 0.0, S1, n12, s, nullptr, 0))) return rc;
-    }
+    double* S3 = Zc + 3 * szc;
     if (n12 > 0) {
-        hipLaunchKernelGGL(k_scatter_jtj, dim3(blocks_for(n12, 32), blocks_for(n12, 32)), dim3(256), 0, s, Gc3,
-                           (int64_t)wc2, Wc, S3, (int64_t)sn, L, sc, JtJ, P);
+        hipLaunchKernelGGL(k_gather_gram, dim3(blocks_for(Wp, 32), blocks_for(Wc, 32), 3), dim3(256), 0, s, G, W, L, Wc, Wp, Gc3);
+        hipLaunchKernelGGL(k_gather_z, dim3(blocks_for((int64_t)n12 * Mp, 256), 3), dim3(256), 0, s, Z, L, Mp, Zc);
+        if ((rc = check_launch(ctx, "gather"))) return rc;
+        if ((rc = gemm_f64(ctx, Gemm64{n12, M, Mp, 0.5, Zc, Mp, Gc3 + (size_t)n12 * Wp + n12, Wp, 1.0, Gc3 + n12, Wp, szc, wc2, wc2},
+                           3, s)))
+            return rc;
+        if ((rc = gemm_f64(ctx, Gemm64{n12, n12, Mp, 1.0, Gc3 + n12, Wp, Zc, Mp, 0.0, S3, n12, wc2, szc, sn}, 3, s))) return rc;
+        hipLaunchKernelGGL(k_scatter_jtj, dim3(blocks_for(n12, 32), blocks_for(n12, 32)), dim3(256), 0, s, Gc3, wc2, Wp, S3, sn, L,
+                           sc, JtJ, P);
         if ((rc = check_launch(ctx, "scatter"))) return rc;
     }
     return BEM_OK;
@@ -1032,14 +1060,12 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
             if ((rc = launch_features<double>(ctx, xt, n, H, mixed, true, Xt, nullptr, T, s, &nl, t0, x, corr, vtab, runs,
                                               box)))
                 return rc;
+            if (n % kGemmPad)
+                hipLaunchKernelGGL(k_zero_tail_f64, dim3(blocks_for(W * kGemmPad, 256)), dim3(256), 0, s, Xt, W, T, n);
             {
                 ProfScope ps_(ctx, PT_GRAM_F64, s);
-                if (gram == BEM_GRAM_FP64_VALU)
-                    rc = gemm_f64(ctx, (int)W, (int)W, (int)n, 1.0, Xt, T, false, Xt, T, true, it > 0 ? 1.0 : 0.0, G, W, s,
-                                  dtiles, ntiles);
-                else
-                    rc = gemm_f64_list(ctx, (int)W, (int)W, (int)n, 1.0, Xt, T, false, Xt, T, true, it > 0 ? 1.0 : 0.0, G,
-                                       W, s, dtiles, ntiles, (int)kchunk, W * W);
+                const Gemm64 g{(int)W, (int)W, gemm_pad(n), 1.0, Xt, T, Xt, T, it > 0 ? 1.0 : 0.0, G, W};
+                rc = valu ? gemm_f64_valu(ctx, g, s, dtiles, ntiles) : gemm_f64_list(ctx, g, s, dtiles, ntiles, (int)kchunk, W * W);
             }
             if (rc) return rc;
         } else if (gram == BEM_GRAM_FP32_MFMA) {
@@ -1104,14 +1130,17 @@ int run_jacobian(bem_ctx* ctx, const double* theta, int H, const double* x, int6
     double* Z = nullptr;
     if ((rc = boundary_derivatives(ctx, H, s, &Z))) return rc;
     const int64_t ld = N;
-    if ((rc = ensure(ctx, ctx->tmp0, ((size_t)W * N + (size_t)N * nf) * sizeof(double), s))) return rc;
+    const int Mp = gemm_pad(M);
+    const size_t xs = ((size_t)W * N + 1) / 2 * 2;
+    if ((rc = ensure(ctx, ctx->tmp0, (xs + (size_t)N * Mp + (size_t)N * nf) * sizeof(double), s))) return rc;
     double* Xt = (double*)ctx->tmp0.ptr;
-    double* BZ = Xt + (size_t)W * N;
+    double* Bt = Xt + xs;
+    double* BZ = Bt + (size_t)N * Mp;
     if ((rc = launch_features<double>(ctx, x, N, H, false, true, Xt, nullptr, ld, s))) return rc;
-    // BZ[t][f] = sum_i beta_i(t) Z[i][f]  (beta rows of Xt transposed)
-    if ((rc = gemm_f64(ctx, (int)N, nf, M, 1.0, Xt + (size_t)nf * ld, ld, true, Z, nf, false, 0.0, BZ, nf, s, nullptr,
-                       0)))
-        return rc;
+    // BZ[t][f] = sum_i beta_i(t) Z[f][i]  (beta rows of Xt transposed)
+    hipLaunchKernelGGL(k_pad, dim3(blocks_for(N * Mp, 256)), dim3(256), 0, s, (const double*)(Xt + (size_t)nf * ld), ld, true, N, M, N, Mp,
+                       Bt);
+    if ((rc = gemm_f64(ctx, Gemm64{(int)N, nf, Mp, 1.0, Bt, Mp, Z, Mp, 0.0, BZ, nf}, 1, s))) return rc;
     hipLaunchKernelGGL(k_assemble_jacobian, dim3(blocks_for((int64_t)L.params() * H, 256), N), dim3(256), 0, s, Xt, ld,
                        BZ, L, N, J);
     return check_launch(ctx, "jacobian");

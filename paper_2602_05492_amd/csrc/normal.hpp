@@ -73,7 +73,7 @@ __device__ __forceinline__ void add_pair_features(const float* __restrict__ s, c
 
 // jtj.hip
 Layout layout_of(const bem_ctx* ctx, int H);
-// Z = A+ dF/dtheta in feature columns [M][handle rows] -> ctx->tmp4
+// Z = A+ dF/dtheta, transposed: [handle rows][M padded by zeros to kGemmPad] -> ctx->tmp4
 int boundary_derivatives(bem_ctx* ctx, int H, hipStream_t s, double** Zout);
 int launch_vertex_table(bem_ctx* ctx, float* vtab, hipStream_t s);
 // the split-BF16 Gram's work list (256 x 256 tiles, kGramParts sample parts) on the device
