@@ -1,19 +1,24 @@
 // chol.hip - float64 Cholesky of the damped approximate Hessian
 // lambda D + J^T J (Eq. optimstep: positive definite, solved by Cholesky,
 // Sec. 4.3) and the two triangular solves for the LM step.
-// Blocked right-looking factorisation with 64-column panels: the diagonal block
-// in one wavefront's registers, inverted in the same kernel; the panel as a GEMM
-// with that inverse; the trailing update as a rank-64 symmetric update.  The solves
-// use the inverted diagonal blocks too: one launch per block and direction.  A
+// Blocked right-looking factorisation with 128-column panels: the diagonal block
+// in one workgroup's LDS, inverted in the same kernel; the panel as a GEMM
+// with that inverse; the trailing update as a rank-128 symmetric update.  The solves
+// use the inverted 64 x 64 diagonal blocks: one launch per block and direction.  A
 // non-positive or non-finite pivot raises a device flag.
+#include <utility>
+
 #include "common.hpp"
+#include "math64.hpp"
 #include "sweep_common.hpp"
 
 namespace bem {
 
 namespace {
 
-constexpr int NB = 64;
+constexpr int NB = 64;       // blocks of the solves
+constexpr int KB = 2 * NB;   // columns of a factorisation step
+typedef double d2_t __attribute__((ext_vector_type(2)));
 
 // dmax[0] = max_i H_ii (one block)
 __global__ void k_diag_max(const double* __restrict__ H, int64_t P, double* __restrict__ dmax)
@@ -42,399 +47,489 @@ __global__ void k_damp(const double* __restrict__ H, int64_t P, double lam, cons
     A[i * P + j] = v;
 }
 
-__device__ inline double readlane_f64(double v, int lane)
+// lane K's value of each row of 16 lanes
+template <int K>
+__device__ inline double bcast16(double v)
 {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + K, 0xf, 0xf, false),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + K, 0xf, 0xf, false));
 }
 
-// Factor the diagonal block kb in place (lower triangle) and write its inverse to
-// Linv [64][64] (row-major).  256 threads, the block in LDS, factored by 16-column
-// sub-blocks p = 0..3: wavefront 0 factors the 16 x 16 diagonal sub-block in registers
-// (lane i < 16 holds row i; pivot and column entries by readlane, loops unrolled so every
-// lane index is a constant; a reciprocal square root per pivot, no divisions) and inverts it (lane j forms column j by forward
-// substitution); all threads then form the sub-panel below it (rows times the
-// sub-block's inverse transposed) and apply the rank-16 update to the trailing lower
-// triangle.  The inverse of the whole block follows by block rows:
-// X_ij = -D_i^{-1} sum_{k=j}^{i-1} L_ik X_kj for j < i, X_ii = D_i^{-1}.  Rows / columns
-// past the matrix are an identity block.
-constexpr int DB = 16;                  // sub-block of the diagonal-block factorization
-__global__ void __launch_bounds__(256) k_potrf_diag(double* __restrict__ A, int64_t P, int kb, int* __restrict__ flag,
-                                                    double* __restrict__ Linv)
+// ---- diagonal block ------------------------------------------------------------------------
+// A 128-column step is bound by its serial chain: the diagonal block's 128 pivots, which nothing else of the
+// step can start without.  One workgroup factors it as two 64 x 64 blocks in LDS, those by 16-column panels.
+// A panel is one wavefront's: each of its four rows of 16 lanes holds the panel's 16 x 16 diagonal block, three of
+// them 16 rows below it as well and the fourth an identity, so that a pivot's broadcasts (within 16 lanes, no
+// scalar registers) serve the factor, the rows below and the inverse of the 16 x 16 block at once.  Everything else
+// (trailing updates, the inverse's off-diagonal blocks) is float64 MFMA out of LDS, spread over 8 wavefronts.  LDS rows of kLd doubles: the 16 rows x 4 k of an operand read fall in distinct
+// banks.  Operand and accumulator layout of v_mfma_f64_16x16x4f64 (lane l, rr = l mod 16, lk = l / 16): A[rr][lk],
+// B[lk][rr], element q of the accumulator is row 4 q + lk, column rr; so element q of a product is the B operand of
+// k step q of the next product.
+// Measured: 45 us a block of 128, 57 us with its update (blocks of 64 by broadcast sums: 2 x 47 us).
+typedef double d4_t __attribute__((ext_vector_type(4)));
+constexpr int DB = 16, kLd = 68;
+typedef double Tile[NB][kLd];
+
+__device__ inline d4_t mfma(double a, double b, d4_t c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// Columns J + 1 .. 15 of a panel after pivot J: a (diagonal block) and b (rows below or identity).
+template <int J, int... D>
+__device__ __forceinline__ void panel_update(double (&a)[DB], double (&b)[DB], std::integer_sequence<int, D...>)
 {
-    __shared__ double S[NB][NB + 1];    // the block, factored in place (lower triangle)
-    __shared__ double X[NB][NB + 1];    // its inverse (lower triangle; zero above)
-    const int64_t o = (int64_t)kb * NB;
-    const int nb = (int)(P - o < NB ? P - o : NB);
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // all 16 loads of a thread in flight at once: entries outside the lower triangle load the
-    // block's first element (always in bounds) and are then replaced
-    double g[NB * NB / 256];
-#pragma unroll
-    for (int q = 0; q < NB * NB / 256; ++q) {
-        const int e = tid + 256 * q, r = e >> 6, c = e & 63;
-        const bool in = r < nb && c <= r;
-        g[q] = A[(o + (in ? r : 0)) * P + o + (in ? c : 0)];
-    }
-#pragma unroll
-    for (int q = 0; q < NB * NB / 256; ++q) {
-        const int e = tid + 256 * q, r = e >> 6, c = e & 63;
-        S[r][c] = (r < nb && c <= r) ? g[q] : ((r == c && r >= nb) ? 1.0 : 0.0);
-        X[r][c] = 0.0;
-    }
-    __syncthreads();
-    bool bad = false;
+    (
+        [&] {
+            constexpr int K = J + 1 + D;
+            const double l = bcast16<K>(a[J]);
+            a[K] = fma(-a[J], l, a[K]);
+            b[K] = fma(-b[J], l, b[K]);
+            asm volatile("" : "+v"(b[K]));          // now: not kept back, with its operands, to where b is stored
+        }(),
+        ...);
+}
+template <int... J>
+__device__ __forceinline__ void panel_factor(double (&a)[DB], double (&b)[DB], bool& bad, std::integer_sequence<int, J...>)
+{
+    (
+        [&] {
+            const double d = bcast16<J>(a[J]);
+            const bool ok = (d > 0.0) & (d < INFINITY);
+            bad |= !ok;
+            double r = rsqrt_f64(d);
+            r = ok ? r : 1.0;
+            a[J] *= r;                      // the pivot itself: d / sqrt(d)
+            b[J] *= r;
+            panel_update<J>(a, b, std::make_integer_sequence<int, DB - 1 - J>{});
+        }(),
+        ...);
+}
+
+// S [64][64] (lower triangle) -> its factor in place, X (zeros) -> the inverse (lower triangle).  All 8 wavefronts.
+__device__ __forceinline__ void factor_block(Tile& S, Tile& X, bool& bad)
+{
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rr = lane & 15, lk = lane >> 4;
     for (int p = 0; p < NB / DB; ++p) {
         const int d0 = p * DB;
         if (w == 0) {
-            double a[DB];
-#pragma unroll
-            for (int k = 0; k < DB; ++k) a[k] = (lane < DB && k <= lane) ? S[d0 + lane][d0 + k] : 0.0;
-            double ri[DB];                  // 1 / L_jj (the pivots' reciprocal square roots)
-#pragma unroll
-            for (int j = 0; j < DB; ++j) {
-                const double dj = readlane_f64(a[j], j);
-                const bool ok = dj > 0.0 && isfinite(dj);
-                bad |= !ok;
-                ri[j] = ok ? rsqrt(dj) : 1.0;
-                a[j] = lane == j ? (ok ? dj * ri[j] : 1.0) : a[j] * ri[j];
-                // entries above the diagonal of a row are never read back, so all lanes update
-#pragma unroll
-                for (int k = j + 1; k < DB; ++k) a[k] -= a[j] * readlane_f64(a[j], k);
-            }
-            if (lane < DB) {
-#pragma unroll
-                for (int k = 0; k < DB; ++k)
-                    if (k <= lane) S[d0 + lane][d0 + k] = a[k];
-            }
-            __threadfence_block();          // the stores complete before the broadcast reads below
-            // column `lane` of the sub-block's inverse: x_k = (delta_k,lane - sum_{m<k} L_km x_m) / L_kk,
-            // L_km read back from LDS by broadcast (the wavefront's own stores above, in order)
-            double x[DB];
+            const int r = d0 + DB * (lk + 1) + rr;       // this lane's row below the diagonal block
+            const bool below = lk < 3 && r < NB;
+            double a[DB], b[DB];
 #pragma unroll
             for (int k = 0; k < DB; ++k) {
-                double acc = lane == k ? 1.0 : 0.0;
-#pragma unroll
-                for (int m = 0; m < k; ++m) acc -= S[d0 + k][d0 + m] * x[m];
-                x[k] = acc * ri[k];
+                const double v = S[d0 + rr][d0 + k], u = S[below ? r : 0][d0 + k];
+                a[k] = k <= rr ? v : 0.0;
+                b[k] = below ? u : (lk == 3 && k == rr ? 1.0 : 0.0);
             }
-            if (lane < DB) {
+            panel_factor(a, b, bad, std::make_integer_sequence<int, DB>{});
 #pragma unroll
-                for (int k = 0; k < DB; ++k)
-                    if (k >= lane) X[d0 + k][d0 + lane] = x[k];
-            }
-        }
-        __syncthreads();
-        // sub-panel: rows r >= d0 + 16, columns d0 .. d0 + 15: S[r][d0 + j] = sum_{m<=j} S[r][d0 + m] X[d0 + j][d0 + m]
-        const int nr = NB - d0 - DB;
-        double v[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int e = tid + 256 * q;
-            v[q] = 0.0;
-            if (e < nr * DB) {
-                const int r = d0 + DB + e / DB, j = e % DB;
-                double acc = 0.0;
-#pragma unroll
-                for (int m = 0; m < DB; ++m) acc += S[r][d0 + m] * X[d0 + j][d0 + m];
-                v[q] = acc;
+            for (int k = 0; k < DB; ++k) {
+                if (lk == 0 && k <= rr) S[d0 + rr][d0 + k] = a[k];
+                if (below) S[r][d0 + k] = b[k];
+                if (lk == 3 && k >= rr) X[d0 + k][d0 + rr] = b[k];       // (L^-T)[rr][k]
             }
         }
         __syncthreads();
+        // trailing 16 x 16 tiles (I, J), I >= J: S -= L L^T
+        const int t = NB / DB - 1 - p;
+        for (int i = w; i < t * (t + 1) / 2; i += 8) {
+            const int I = i < 1 ? 0 : i < 3 ? 1 : 2, J = i - I * (I + 1) / 2;
+            const int r0 = d0 + DB * (I + 1), c0 = d0 + DB * (J + 1);
+            d4_t acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int e = tid + 256 * q;
-            if (e < nr * DB) S[d0 + DB + e / DB][d0 + e % DB] = v[q];
-        }
-        __syncthreads();
-        // trailing lower triangle: S[r][c] -= sum_m S[r][d0 + m] S[c][d0 + m], d0 + 16 <= c <= r
-        for (int e = tid; e < nr * nr; e += 256) {
-            const int r = d0 + DB + e / nr, c = d0 + DB + e % nr;
-            if (c > r) continue;
-            double acc = 0.0;
+            for (int k = 0; k < DB; k += 4) acc = mfma(S[r0 + rr][d0 + k + lk], S[c0 + rr][d0 + k + lk], acc);
 #pragma unroll
-            for (int m = 0; m < DB; ++m) acc += S[r][d0 + m] * S[c][d0 + m];
-            S[r][c] -= acc;
+            for (int q = 0; q < 4; ++q) S[r0 + 4 * q + lk][c0 + rr] -= acc[q];
         }
         __syncthreads();
     }
-    // off-diagonal blocks of the inverse, block row by block row
-    for (int i = 1; i < NB / DB; ++i) {
-        const int n = i * DB * DB;       // entries of the blocks (i, j), j < i
-        double v[3];
+    // off-diagonal blocks of the inverse, X_10 = -X_11 (L_10 X_00): of the two 32 x 32 blocks, then of the whole
+    if (w < 2) {
+        const int o = 32 * w;
+        d4_t t = {0.0, 0.0, 0.0, 0.0}, v = t;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {    // T_ij = sum_{k=j}^{i-1} L_ik X_kj
-            const int e = tid + 256 * q;
-            v[q] = 0.0;
-            if (e < n) {
-                // X[k][col] is zero for k below col's block, so the sum may start at 0
-                const int a = e / (i * DB), col = e % (i * DB);
-                double acc = 0.0;
-                for (int kq = 0; kq < i; ++kq) {
+        for (int k = 0; k < DB; k += 4) t = mfma(S[o + DB + rr][o + k + lk], X[o + k + lk][o + rr], t);
 #pragma unroll
-                    for (int m = 0; m < DB; ++m) acc += S[i * DB + a][kq * DB + m] * X[kq * DB + m][col];
+        for (int q = 0; q < 4; ++q) v = mfma(X[o + DB + rr][o + DB + 4 * q + lk], t[q], v);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[o + DB + 4 * q + lk][o + rr] = -v[q];
+    }
+    __syncthreads();
+    if (w < 4) {
+        const int I = 2 + (w >> 1), J = w & 1;
+        d4_t v = {0.0, 0.0, 0.0, 0.0};
+        for (int K = 2; K <= I; ++K) {
+            d4_t t = {0.0, 0.0, 0.0, 0.0};
+            for (int k = DB * J; k < 2 * DB; k += 4) t = mfma(S[DB * K + rr][k + lk], X[k + lk][DB * J + rr], t);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v = mfma(X[DB * I + rr][DB * K + 4 * q + lk], t[q], v);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[DB * I + 4 * q + lk][DB * J + rr] = -v[q];
+    }
+    __syncthreads();
+}
+
+// LDS of a step's workgroup: the diagonal block's four tiles, or the slabs [2 groups][2 stages][A, B][64][16] of the
+// trailing update.
+constexpr int kStepLds = 4 * sizeof(Tile);
+constexpr int kSlab = 16;
+// 16-byte chunk position of k pair kp (k = 2 kp) in a slab row (as k_gemm_f64_nt)
+__device__ inline int slab_pos(int row, int kp) { return 2 * (kp ^ ((row >> 1) & 7)); }
+__device__ inline void load_lds(const double* g, double* lds)
+{
+    __builtin_amdgcn_global_load_lds((const void*)g, (void*)lds, 16, 0, 0);
+}
+// every load of this wavefront has landed, then every wavefront's
+__device__ inline void loads_landed()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
+// Update diagonal block kb (128 columns) with the panel of block kb - 1 (kb > 0) and factor it in place (lower
+// triangle); inverses of its two 64 x 64 blocks to linv64 [64-block][64][64] (for the solves) and of the whole to
+// inv [128][128] (for the panel).  Rows and columns past the matrix are an identity block.
+__device__ __forceinline__ void diag_block(double* lds, double* __restrict__ A, int64_t P, int kb, int* __restrict__ flag,
+                                           double* __restrict__ linv64, double* __restrict__ inv)
+{
+    Tile& B0 = *(Tile*)lds;
+    Tile& B1 = *((Tile*)lds + 1);
+    Tile& S10 = *((Tile*)lds + 2);
+    Tile& S11 = *((Tile*)lds + 3);
+    const int64_t o = (int64_t)kb * KB;
+    const int nb = (int)(P - o < KB ? P - o : KB);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rr = lane & 15, lk = lane >> 4;
+    // wavefront w takes rows w, w + 8, ... of each block, a lane a column; all loads in flight at once (entries
+    // outside load the block's first element and are then replaced)
+    double g[3][NB / 8];
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+        for (int q = 0; q < NB / 8; ++q) {
+            const int r = (b > 0 ? NB : 0) + w + 8 * q, c = (b > 1 ? NB : 0) + lane;
+            const bool in = r < nb && c <= r;
+            g[b][q] = A[(o + (in ? r : 0)) * P + o + (in ? c : 0)];
+        }
+    // L L^T of the panel's rows at this block: 36 tiles (R, C), C <= R < 8, wavefront w takes w, w + 8, ...
+    d4_t acc[5];
+    int tr[5], tc[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const int t = w + 8 * i;
+        int R = 0;
+        while ((R + 1) * (R + 2) / 2 <= t) ++R;
+        tr[i] = R;
+        tc[i] = t - R * (R + 1) / 2;
+        acc[i] = d4_t{0.0, 0.0, 0.0, 0.0};
+    }
+    if (kb > 0) {
+        double(*sl)[KB][kSlab] = (double(*)[KB][kSlab])&B1;        // two stages
+        const double* gp[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 16 * w + 8 * i + (lane >> 3);
+            gp[i] = A + (o + (r < nb ? r : 0)) * P + (o - KB) + slab_pos(r, lane & 7);
+        }
+        auto load = [&](int buf, int s) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) load_lds(gp[i] + kSlab * s, &sl[buf][16 * w + 8 * i][0]);
+        };
+        load(0, 0);
+        loads_landed();
+        for (int s = 0; s < KB / kSlab; ++s) {
+            const int cur = s & 1;
+            if (s + 1 < KB / kSlab) load(cur ^ 1, s + 1);
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                if (w + 8 * i >= 36) continue;
+                const int ra = DB * tr[i] + rr, rb = DB * tc[i] + rr;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const d2_t a = *(const d2_t*)&sl[cur][ra][slab_pos(ra, 4 * h + lk)];
+                    const d2_t b = *(const d2_t*)&sl[cur][rb][slab_pos(rb, 4 * h + lk)];
+                    acc[i] = mfma(a[0], b[0], acc[i]);
+                    acc[i] = mfma(a[1], b[1], acc[i]);
                 }
-                v[q] = acc;
             }
+            loads_landed();
         }
-        __syncthreads();
+    }
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int e = tid + 256 * q;
-            if (e < n) X[i * DB + e / (i * DB)][e % (i * DB)] = v[q];
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+        for (int q = 0; q < NB / 8; ++q) {
+            const int r = (b > 0 ? NB : 0) + w + 8 * q, c = (b > 1 ? NB : 0) + lane;
+            const double v = r < nb && c <= r ? g[b][q] : (r == c && r >= nb ? 1.0 : 0.0);
+            Tile& T = b == 0 ? B0 : b == 1 ? S10 : S11;
+            T[w + 8 * q][lane] = v;
+            if (b == 0) B1[w + 8 * q][lane] = 0.0;
         }
-        __syncthreads();
+    __syncthreads();
+    if (kb > 0) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {    // X_ij = -D_i^{-1} T_ij
-            const int e = tid + 256 * q;
-            v[q] = 0.0;
-            if (e < n) {
-                const int a = e / (i * DB), col = e % (i * DB);
-                double acc = 0.0;
+        for (int i = 0; i < 5; ++i) {
+            if (w + 8 * i >= 36) continue;
+            Tile& T = tr[i] < 4 ? B0 : tc[i] < 4 ? S10 : S11;
 #pragma unroll
-                for (int m = 0; m < DB; ++m) acc += X[i * DB + a][i * DB + m] * X[i * DB + m][col];
-                v[q] = -acc;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int e = tid + 256 * q;
-            if (e < n) X[i * DB + e / (i * DB)][e % (i * DB)] = v[q];
+            for (int q = 0; q < 4; ++q)
+                if (DB * tr[i] + 4 * q + lk < nb) T[(DB * tr[i] & 63) + 4 * q + lk][(DB * tc[i] & 63) + rr] -= acc[i][q];
         }
         __syncthreads();
     }
+    bool bad = false;
+    factor_block(B0, B1, bad);                     // B0 = L_00, B1 = X_00
+    // L_10 = S_10 X_00^T: two 16 x 16 tiles a wavefront
+    const int I = w & 3, Ja = w >> 2, Jb = 3 - Ja;
+    d4_t t0 = {0.0, 0.0, 0.0, 0.0}, t1 = t0;
+    for (int k = 0; k < DB * (Ja + 1); k += 4) t0 = mfma(S10[DB * I + rr][k + lk], B1[DB * Ja + rr][k + lk], t0);
+    for (int k = 0; k < DB * (Jb + 1); k += 4) t1 = mfma(S10[DB * I + rr][k + lk], B1[DB * Jb + rr][k + lk], t1);
+    auto put = [&](const Tile& T, int r0, int c0) {
+#pragma unroll
+        for (int q = 0; q < NB / 8; ++q) {
+            const int r = r0 + w + 8 * q, c = c0 + lane;
+            if (r < nb && c <= r) A[(o + r) * P + o + c] = T[w + 8 * q][lane];
+        }
+    };
+    put(B0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        S10[DB * I + 4 * q + lk][DB * Ja + rr] = t0[q];
+        S10[DB * I + 4 * q + lk][DB * Jb + rr] = t1[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NB / 8; ++q) B0[w + 8 * q][lane] = 0.0;
+    __syncthreads();
+    // S_11 -= L_10 L_10^T
+    for (int i = w; i < 10; i += 8) {
+        const int R = i < 1 ? 0 : i < 3 ? 1 : i < 6 ? 2 : 3, C = i - R * (R + 1) / 2;
+        d4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < NB; k += 4) acc = mfma(S10[DB * R + rr][k + lk], S10[DB * C + rr][k + lk], acc);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) S11[DB * R + 4 * q + lk][DB * C + rr] -= acc[q];
+    }
+    put(S10, NB, 0);
+    __syncthreads();
+    factor_block(S11, B0, bad);                    // S11 = L_11, B0 = X_11
+    put(S11, NB, NB);
     if (tid == 0 && bad) flag[0] = 1;
-#pragma unroll
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int r = e >> 6, c = e & 63;
-        if (r < nb && c <= r) A[(o + r) * P + o + c] = S[r][c];
-        Linv[e] = X[r][c];
-    }
-}
-
-// Panel rows below diagonal block kb, in place: row <- row Linv_kk^T (= row L_kk^{-T}), with
-// Linv pointing at block kb's inverse [64][64].
-// 256 threads; the block stages its 64 rows and Linv_kk in LDS with coalesced loads and
-// thread (w, t) forms column t of rows w, w + 4, ...
-// skip: row blocks below the diagonal block left out (the first one may come from k_next_diag).
-__global__ void __launch_bounds__(256) k_panel(double* __restrict__ A, int64_t P, int kb,
-                                               const double* __restrict__ Linv, int skip)
-{
-    __shared__ double R[NB][NB];        // rows (read by broadcast)
-    __shared__ double LiT[NB][NB];      // LiT[k][j] = Linv[j][k]
-    const int64_t o = (int64_t)kb * NB;
-    const int64_t r0 = o + NB + (int64_t)(blockIdx.x + skip) * NB;
-    const int nr = (int)(P - r0 < NB ? P - r0 : NB);
-    const int t = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // loads first (all in flight; rows past the matrix read row r0 and are then zeroed)
-    double gr[NB / 4], gl[NB / 4];
-#pragma unroll
-    for (int q = 0; q < NB / 4; ++q) {
-        const int i = w + 4 * q;
-        gr[q] = A[(r0 + (i < nr ? i : 0)) * P + o + t];
-        gl[q] = Linv[(size_t)i * NB + t];
-    }
-#pragma unroll
-    for (int q = 0; q < NB / 4; ++q) {
-        const int i = w + 4 * q;
-        R[i][t] = i < nr ? gr[q] : 0.0;
-        LiT[t][i] = gl[q];
-    }
-    __syncthreads();
-    double out[NB / 4];
-#pragma unroll
-    for (int q = 0; q < NB / 4; ++q) out[q] = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < NB; ++k) {
-        const double l = LiT[k][t];                   // (Linv^T)[k][t]
-#pragma unroll
-        for (int q = 0; q < NB / 4; ++q) out[q] += R[w + 4 * q][k] * l;
-    }
-#pragma unroll
-    for (int q = 0; q < NB / 4; ++q)
-        if (w + 4 * q < nr) A[(r0 + w + 4 * q) * P + o + t] = out[q];
-}
-
-// Trailing update of step kb on float64 MFMA: C -= L21 L21^T on the lower triangle of the
-// trailing matrix C = A[o2:, o2:], o2 = 64 (kb + 1), with the panel L21 = A[o2:, o:o+64].
-// One block per 64 x 64 tile (I, J), I >= J (linear block index -> (I, J)); 4 waves, each a
-// 32 x 32 quarter as 2 x 2 tiles of v_mfma_f64_16x16x4f64.  The two 64-row panel slices are
-// staged in LDS transposed ([k][row], all 64 k in one pass, every global load of the block
-// issued before the first wait) so that an MFMA operand (lane l: row l mod 16, k l / 16, the
-// same pattern for both operands) is one ds_read per lane.
-// Accumulator element q of lane l is row 4 q + l / 16, column l mod 16 of its 16 x 16 tile.
-typedef double d4_t __attribute__((ext_vector_type(4)));
-constexpr int kSyrkLd = 72;              // LDS row stride (doubles) of the transposed slices
-// mode 0: every tile; 1: every tile but the first diagonal one (I = J = 0, updated by k_next_diag).
-__global__ void __launch_bounds__(256) k_syrk64(double* __restrict__ A, int64_t P, int kb, int nt, int mode)
-{
-    __shared__ double SI[NB][kSyrkLd];   // [k][row] of the panel rows of tile row I
-    __shared__ double SJ[NB][kSyrkLd];   // and of tile column J
-    const int64_t o = (int64_t)kb * NB, o2 = o + NB;
-    const int64_t rem = P - o2;
-    // tile (I, J), I >= J, from the linear index b = I (I + 1) / 2 + J
-    const int b = blockIdx.x;
-    if (mode == 1 && b == 0) return;
-    int I = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
-    while ((I + 1) * (I + 2) / 2 <= b) ++I;
-    while (I * (I + 1) / 2 > b) --I;
-    const int J = b - I * (I + 1) / 2;
-    if (I >= nt) return;
-    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
-    const int wr = w >> 1, wc = w & 1;
-    const int64_t rI = (int64_t)I * NB, rJ = (int64_t)J * NB;
-    // every global load first, all in flight: the 16 entries of C this thread updates and the two
-    // 64-row x 64-k panel slices (entries past the matrix read an in-bounds one and are then
-    // replaced)
-    double c[2][2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
+    // X_10 = -X_11 (L_10 X_00): wavefront w column tile w mod 4, row tiles 0, 1 or 2, 3
+    {
+        const int J = w & 3, I0 = 2 * (1 - (w >> 2));
+        d4_t v[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+        for (int K = 0; K <= I0 + 1; ++K) {
+            d4_t t = {0.0, 0.0, 0.0, 0.0};
+            for (int k = DB * J; k < NB; k += 4) t = mfma(S10[DB * K + rr][k + lk], B1[k + lk][DB * J + rr], t);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int64_t gr = rI + 32 * wr + 16 * i + 4 * q + (l >> 4);
-                const int64_t gc = rJ + 32 * wc + 16 * j + (l & 15);
-                const bool in = gr < rem && gc <= gr;
-                c[i][j][q] = A[(o2 + (in ? gr : 0)) * P + o2 + (in ? gc : 0)];
+                v[1] = mfma(B0[DB * (I0 + 1) + rr][DB * K + 4 * q + lk], t[q], v[1]);
+                if (K <= I0) v[0] = mfma(B0[DB * I0 + rr][DB * K + 4 * q + lk], t[q], v[0]);
             }
-    double vi[NB * NB / 256], vj[NB * NB / 256];
+        }
 #pragma unroll
-    for (int m = 0; m < NB * NB / 256; ++m) {
-        const int e = tid + 256 * m, r = e >> 6, k = e & 63;
-        const int64_t gi = rI + r, gj = rJ + r;
-        vi[m] = A[(o2 + (gi < rem ? gi : 0)) * P + o + k];
-        vj[m] = A[(o2 + (gj < rem ? gj : 0)) * P + o + k];
-    }
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int m = 0; m < NB * NB / 256; ++m) {
-        const int e = tid + 256 * m, r = e >> 6, k = e & 63;
-        SI[k][r] = rI + r < rem ? vi[m] : 0.0;
-        SJ[k][r] = rJ + r < rem ? vj[m] : 0.0;
+            for (int q = 0; q < 4; ++q) inv[(NB + DB * (I0 + i) + 4 * q + lk) * KB + DB * J + rr] = -v[i][q];
     }
-    __syncthreads();
+    double* l0 = linv64 + (size_t)2 * kb * NB * NB;
+#pragma unroll
+    for (int q = 0; q < NB / 8; ++q) {
+        const int r = w + 8 * q;
+        const double x0 = B1[r][lane], x1 = B0[r][lane];
+        inv[r * KB + lane] = x0;
+        inv[r * KB + NB + lane] = 0.0;
+        inv[(NB + r) * KB + NB + lane] = x1;
+        l0[r * NB + lane] = x0;
+        if (nb > NB) l0[NB * NB + r * NB + lane] = x1;
+    }
+}
+
+// Step kb > 0: block 0 the diagonal block above; the other blocks the rest of the trailing update with the panel of
+// block kb - 1, C -= L L^T on the 64 x 64 tiles of the lower triangle of C = A[o:, o:], o = 128 kb, but the first
+// three (row by row; they are the diagonal block).  Step 0: the diagonal block alone.  One launch for the two, because
+// on two streams the diagonal block's workgroup had to wait for a whole CU's LDS until the update drained.
+//
+// Update: a workgroup's two groups of 4 wavefronts take a tile each, 32 x 32 a wavefront, k in slabs of 16 straight
+// into LDS, the next slab (or the next tile's first) in flight behind the products; C is read when its tile starts.
+// Bound by the matrix cores at P = 5,000 (3,000 tiles of 1 MFLOP on the first step, 40 us).  Each XCD takes a contiguous
+// run of the tiles, so that its L2 holds their panel rows.
+constexpr int kStepBlocks = 256;
+__global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, int64_t P, int kb, int ntile,
+                                                   int* __restrict__ flag, double* __restrict__ linv64,
+                                                   double* __restrict__ inv)
+{
+    __shared__ __attribute__((aligned(1024))) double lds[kStepLds / sizeof(double)];
+    if (blockIdx.x == 0) {
+        diag_block(lds, A, P, kb, flag, linv64, inv);
+        return;
+    }
+    const int l = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = w8 & 3, grp = w8 >> 2;
+    const int rr = l & 15, lk = l >> 4, wr = w >> 1, wc = w & 1;
+    // this group's tiles: t0, t0 + step, ... below t1; the workgroup runs as many rounds as its first group needs
+    const int x = blockIdx.x & 7, per = (ntile + 7) >> 3;
+    const int slot = (int)(blockIdx.x >> 3) - (x == 0), step = 2 * (kStepBlocks / 8 - (x == 0));
+    const int t1 = (x + 1) * per < ntile ? (x + 1) * per : ntile;
+    const int first = x * per + 2 * slot, rounds = first < t1 ? (t1 - first + step - 1) / step : 0;
+    const int64_t o = (int64_t)kb * KB, rem = P - o;
+    double(*sl)[2][NB][kSlab] = (double(*)[2][NB][kSlab])(lds + grp * (4 * NB * kSlab));
+    const double *ga[2], *gb[2];
+    auto tile = [&](int round, int64_t& r0, int64_t& c0) {
+        const int t = first + grp + round * step;
+        const int b = (t < t1 ? t : first) + 3;              // (past the end: any tile, not stored)
+        int I = (int)((sqrtf(8.0f * b + 1.0f) - 1.0f) * 0.5f);
+        while ((I + 1) * (I + 2) / 2 <= b) ++I;
+        while (I * (I + 1) / 2 > b) --I;
+        r0 = (int64_t)I * NB;
+        c0 = (int64_t)(b - I * (I + 1) / 2) * NB;
+        return t < t1;
+    };
+    auto point = [&](int64_t r0, int64_t c0) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = 16 * w + 8 * i + (l >> 3);
+            const int c = slab_pos(r, l & 7);
+            ga[i] = A + (o + (r0 + r < rem ? r0 + r : rem - 1)) * P + (o - KB) + c;
+            gb[i] = A + (o + (c0 + r < rem ? c0 + r : rem - 1)) * P + (o - KB) + c;
+        }
+    };
+    auto load = [&](int buf, int s) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            load_lds(ga[i] + kSlab * s, &sl[buf][0][16 * w + 8 * i][0]);
+            load_lds(gb[i] + kSlab * s, &sl[buf][1][16 * w + 8 * i][0]);
+        }
+    };
+    if (rounds == 0) return;
+    int64_t r0, c0, rn = 0, cn = 0;
+    bool live = tile(0, r0, c0), next = false;
+    point(r0, c0);
+    load(0, 0);
+    loads_landed();
+    for (int round = 0; round < rounds; ++round) {
+        double c[2][2][4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t r = r0 + 32 * wr + 16 * i + 4 * q + lk, k = c0 + 32 * wc + 16 * j + rr;
+                    const bool in = r < rem && k <= r;
+                    c[i][j][q] = A[(o + (in ? r : 0)) * P + o + (in ? k : 0)];
+                }
+        d4_t acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+        for (int s = 0; s < KB / kSlab; ++s) {
+            const int cur = s & 1;
+            if (s + 1 < KB / kSlab) {
+                load(cur ^ 1, s + 1);
+            } else if (round + 1 < rounds) {
+                next = tile(round + 1, rn, cn);
+                point(rn, cn);
+                load(0, 0);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                d2_t a[2], b[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int ra = 32 * wr + 16 * i + rr, rb = 32 * wc + 16 * i + rr;
+                    a[i] = *(const d2_t*)&sl[cur][0][ra][slab_pos(ra, 4 * h + lk)];
+                    b[i] = *(const d2_t*)&sl[cur][1][rb][slab_pos(rb, 4 * h + lk)];
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a[i][t], b[j][t], acc[i][j]);
+            }
+            loads_landed();
+        }
+        if (live) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int64_t r = r0 + 32 * wr + 16 * i + 4 * q + lk, k = c0 + 32 * wc + 16 * j + rr;
+                        if (r < rem && k <= r) A[(o + r) * P + o + k] = c[i][j][q] - acc[i][j][q];
+                    }
+        }
+        live = next;
+        r0 = rn;
+        c0 = cn;
+    }
+}
+
+// Panel rows (32 a block) below block kb, in place: row <- row L_kk^{-T}, with inv the block's inverse
+// [128][128].  Operands go straight into LDS and from there to the MFMAs as in k_gemm_f64_nt (gemm.hip); a block
+// owns whole rows, so that its stores, after its last load, meet no other block's loads.  P is even (16-byte loads).
+// Bound by latency (8 slabs of 16 k); 32 rows a block for 150 blocks at P = 5,000.
+constexpr int kPanelRows = 32;
+__global__ void __launch_bounds__(256) k_panel(double* __restrict__ A, int64_t P, int kb, const double* __restrict__ inv)
+{
+    __shared__ __attribute__((aligned(1024))) double Sa[2][kPanelRows][kSlab], Sb[2][KB][kSlab];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rr = l & 15, lk = l >> 4;
+    const int64_t o = (int64_t)kb * KB, row0 = o + KB + (int64_t)blockIdx.x * kPanelRows;
+    const int ra = 8 * w + (l >> 3);
+    const double* ga = A + (row0 + ra < P ? row0 + ra : P - 1) * P + o + slab_pos(ra, l & 7);
+    const double* gb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 32 * w + 8 * i + (l >> 3);
+        gb[i] = inv + (size_t)r * KB + slab_pos(r, l & 7);
+    }
+    auto load = [&](int buf, int s) {
+        load_lds(ga + kSlab * s, &Sa[buf][8 * w][0]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_lds(gb[i] + kSlab * s, &Sb[buf][32 * w + 8 * i][0]);
+    };
     d4_t acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+    load(0, 0);
+    loads_landed();
+    for (int s = 0; s < KB / kSlab; ++s) {
+        const int cur = s & 1;
+        if (s + 1 < KB / kSlab) load(cur ^ 1, s + 1);
 #pragma unroll
-    for (int ks = 0; ks < NB; ks += 4) {
-        const int kk = ks + (l >> 4), rr = l & 15;
-        const double a0 = SI[kk][32 * wr + rr], a1 = SI[kk][32 * wr + 16 + rr];
-        const double b0 = SJ[kk][32 * wc + rr], b1 = SJ[kk][32 * wc + 16 + rr];
-        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-    }
+        for (int h = 0; h < 2; ++h) {
+            d2_t a[2], b[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t gr = rI + 32 * wr + 16 * i + 4 * q + (l >> 4);
-                const int64_t gc = rJ + 32 * wc + 16 * j + (l & 15);
-                if (gr < rem && gc <= gr) A[(o2 + gr) * P + o2 + gc] = c[i][j][q] - acc[i][j][q];
+            for (int i = 0; i < 2; ++i) {
+                const int r = 16 * i + rr, c = 32 * w + r;
+                a[i] = *(const d2_t*)&Sa[cur][r][slab_pos(r, 4 * h + lk)];
+                b[i] = *(const d2_t*)&Sb[cur][c][slab_pos(c, 4 * h + lk)];
             }
-}
-
-// Look-ahead of step kb (one block): the first row block of the panel,
-// L1 = A[o2:o2+64, o:o+64] Linv_kb^T, written in place, and the next diagonal block's update
-// A[o2:o2+64, o2:o2+64] -= L1 L1^T on its lower triangle, o2 = 64 (kb + 1).  Both products on
-// float64 MFMA with the operand and accumulator layout of k_syrk64; the rows of L1 past the
-// matrix are zero (their rows of A are neither read nor written).  Requires P > o2.
-__global__ void __launch_bounds__(256) k_next_diag(double* __restrict__ A, int64_t P, int kb,
-                                                   const double* __restrict__ Linv)
-{
-    __shared__ double SI[NB][kSyrkLd];   // [k][row]: A's row block, then L1
-    __shared__ double SJ[NB][kSyrkLd];   // [k][j] = Linv_kb[j][k]
-    const int64_t o = (int64_t)kb * NB, o2 = o + NB;
-    const int nr = (int)(P - o2 < NB ? P - o2 : NB);
-    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
-    const int wr = w >> 1, wc = w & 1;
-    // every global load first (entries past the matrix or above the diagonal read an in-bounds
-    // one and are then replaced): this thread's 16 entries of the diagonal block, the row block
-    // and the inverse
-    double c[2][2][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+                for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int gr = 32 * wr + 16 * i + 4 * q + (l >> 4), gc = 32 * wc + 16 * j + (l & 15);
-                const bool in = gr < nr && gc <= gr;
-                c[i][j][q] = A[(o2 + (in ? gr : 0)) * P + o2 + (in ? gc : 0)];
-            }
-    double va[NB * NB / 256], vl[NB * NB / 256];
-#pragma unroll
-    for (int m = 0; m < NB * NB / 256; ++m) {
-        const int e = tid + 256 * m, r = e >> 6, k = e & 63;
-        va[m] = A[(o2 + (r < nr ? r : 0)) * P + o + k];
-        vl[m] = Linv[(size_t)r * NB + k];
-    }
-#pragma unroll
-    for (int m = 0; m < NB * NB / 256; ++m) {
-        const int e = tid + 256 * m, r = e >> 6, k = e & 63;
-        SI[k][r] = r < nr ? va[m] : 0.0;
-        SJ[k][r] = vl[m];
-    }
-    __syncthreads();
-    d4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < NB; ks += 4) {
-        const int kk = ks + (l >> 4), rr = l & 15;
-        const double a0 = SI[kk][32 * wr + rr], a1 = SI[kk][32 * wr + 16 + rr];
-        const double b0 = SJ[kk][32 * wc + rr], b1 = SJ[kk][32 * wc + 16 + rr];
-        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    __syncthreads();                    // every wave is done reading SI
-    // L1 to A and, transposed ([k = column][row]), back into SI
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int gr = 32 * wr + 16 * i + 4 * q + (l >> 4), gc = 32 * wc + 16 * j + (l & 15);
-                SI[gc][gr] = acc[i][j][q];
-                if (gr < nr) A[(o2 + gr) * P + o + gc] = acc[i][j][q];
-            }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < NB; ks += 4) {
-        const int kk = ks + (l >> 4), rr = l & 15;
-        const double a0 = SI[kk][32 * wr + rr], a1 = SI[kk][32 * wr + 16 + rr];
-        const double b0 = SI[kk][32 * wc + rr], b1 = SI[kk][32 * wc + 16 + rr];
-        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+                    for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a[i][t], b[j][t], acc[i][j]);
+        }
+        loads_landed();
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int q = 0; q < 4; ++q) {
+            const int64_t r = row0 + 16 * i + 4 * q + lk;
+            if (r >= P) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int gr = 32 * wr + 16 * i + 4 * q + (l >> 4), gc = 32 * wc + 16 * j + (l & 15);
-                if (gr < nr && gc <= gr) A[(o2 + gr) * P + o2 + gc] = c[i][j][q] - acc[i][j][q];
-            }
+            for (int j = 0; j < 2; ++j) A[r * P + o + 32 * w + 16 * j + rr] = acc[i][j][q];
+        }
 }
 
 // Forward step kb of L y = b with the inverted diagonal blocks, B [P][nrhs]: every block
@@ -587,60 +682,33 @@ __global__ void __launch_bounds__(256) k_bwd_step(const double* __restrict__ A, 
 
 }  // namespace
 
-// Damp, factor and check: returns BEM_ENOTPD when a pivot fails (host sync).  Blocked
-// right-looking with 64-column panels: the diagonal block and its inverse by k_potrf_diag,
-// the panel as A21 Linv^T (in place; its first row block by k_next_diag), the trailing
-// lower triangle by a rank-64 update.  The inverted diagonal blocks stay in the context
-// for chol_solve.
+// Damp, factor and check: returns BEM_ENOTPD when a pivot fails (host sync).  Blocked right-looking with
+// 128-column steps of two launches: the panel as A21 L^{-T} (in place), then the next diagonal block (updated, factored,
+// inverted) beside the rest of the trailing lower triangle's rank-128 update.  The inverted 64 x 64 diagonal blocks stay in
+// the context for chol_solve.  P is even (handles have 14 or 20 parameters).  64-column steps, the diagonal chain and
+// the update on two streams, took 5.8 ms at P = 5,000: a 65 us chain a step, and 5 GB of reading and writing the
+// trailing matrix.  Now 2.9 ms.
 int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, double* A, int* dflag, double* dscal,
                 hipStream_t s)
 {
     int rc;
-    const int nblk = (int)((P + NB - 1) / NB);
-    // cholw: inverted diagonal blocks [nblk][64][64] | solve vector [P][4]
-    if ((rc = ensure(ctx, ctx->cholw, ((size_t)nblk * NB * NB + (size_t)P * kMaxRhs) * sizeof(double), s))) return rc;
+    const int nblk = (int)((P + KB - 1) / KB), n64 = (int)((P + NB - 1) / NB);
+    // cholw: inverted diagonal blocks [n64][64][64] | solve vector [P][4] | the step's inverse [128][128]
+    const size_t vo = (size_t)n64 * NB * NB, io = vo + (size_t)P * kMaxRhs;
+    if ((rc = ensure(ctx, ctx->cholw, (io + KB * KB) * sizeof(double), s))) return rc;
     double* linv = (double*)ctx->cholw.ptr;
+    double* inv = linv + io;
     hipLaunchKernelGGL(k_diag_max, dim3(1), dim3(256), 0, s, H, P, dscal);
     hipLaunchKernelGGL(k_damp, dim3(blocks_for(P, 256), P), dim3(256), 0, s, H, P, lam, dscal, A);
     if ((rc = fill_i32(ctx, dflag, 1, 0, s))) return rc;
     ProfScope ps_(ctx, PT_CHOLESKY, s);
-    // Look-ahead: only the next diagonal block's inputs stay on the caller's stream (k_next_diag:
-    // the panel's first row block and that block's update, then its factor); the rest of the
-    // panel and the trailing update run on the second stream.  Step kb's trailing update waits
-    // for k_next_diag(kb) (it reads the first row block), and k_next_diag(kb + 1) waits for that
-    // update (it reads the tiles it wrote).  The two streams touch disjoint tiles meanwhile.
-    hipStream_t s2 = s;
-    const bool ahead = nblk > 2;
-    if (ahead && (rc = aux_stream(ctx, &s2))) return rc;
-    hipEvent_t evP = ctx->ev[0], evN = ctx->ev[1], evS = ctx->ev[6];
-    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, A, P, 0, dflag, linv);
     for (int kb = 0; kb < nblk; ++kb) {
-        double* Li = linv + (size_t)kb * NB * NB;
-        const int64_t rem = P - (int64_t)(kb + 1) * NB;
-        if (rem <= 0) break;
-        const int nt = blocks_for(rem, NB);
-        if (!ahead) {
-            hipLaunchKernelGGL(k_panel, dim3(nt), dim3(256), 0, s, A, P, kb, (const double*)Li, 0);
-            hipLaunchKernelGGL(k_syrk64, dim3(nt * (nt + 1) / 2), dim3(256), 0, s, A, P, kb, nt, 0);
-            hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, A, P, kb + 1, dflag, Li + NB * NB);
-            continue;
-        }
-        // second stream: the panel below the next diagonal block, once block kb is factored
-        if (hipEventRecord(evP, s) != hipSuccess || hipStreamWaitEvent(s2, evP, 0) != hipSuccess)
-            return set_error(ctx, BEM_EHIP, "cholesky event");
-        if (nt > 1) hipLaunchKernelGGL(k_panel, dim3(nt - 1), dim3(256), 0, s2, A, P, kb, (const double*)Li, 1);
-        // caller's stream: the next diagonal block, once the previous trailing update is done
-        if (kb > 0 && hipStreamWaitEvent(s, evS, 0) != hipSuccess) return set_error(ctx, BEM_EHIP, "cholesky wait");
-        hipLaunchKernelGGL(k_next_diag, dim3(1), dim3(256), 0, s, A, P, kb, (const double*)Li);
-        if (nt > 1) {
-            if (hipEventRecord(evN, s) != hipSuccess || hipStreamWaitEvent(s2, evN, 0) != hipSuccess)
-                return set_error(ctx, BEM_EHIP, "cholesky event");
-            hipLaunchKernelGGL(k_syrk64, dim3(nt * (nt + 1) / 2), dim3(256), 0, s2, A, P, kb, nt, 1);
-            if (hipEventRecord(evS, s2) != hipSuccess) return set_error(ctx, BEM_EHIP, "cholesky event");
-        }
-        hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, A, P, kb + 1, dflag, Li + NB * NB);
+        const int64_t rem = P - (int64_t)kb * KB;                   // the trailing matrix of the step before
+        const int nt = blocks_for(rem, NB), ntile = kb > 0 && rem > KB ? nt * (nt + 1) / 2 - 3 : 0;
+        if (kb > 0)
+            hipLaunchKernelGGL(k_panel, dim3(blocks_for(rem, kPanelRows)), dim3(256), 0, s, A, P, kb - 1, (const double*)inv);
+        hipLaunchKernelGGL(k_chol_step, dim3(ntile > 0 ? kStepBlocks : 1), dim3(512), 0, s, A, P, kb, ntile, dflag, linv, inv);
     }
-    if (ahead && hipStreamWaitEvent(s, evS, 0) != hipSuccess) return set_error(ctx, BEM_EHIP, "cholesky join");
     if ((rc = check_launch(ctx, "cholesky"))) return rc;
     ctx->chol_P = P;
     int hflag = 0;

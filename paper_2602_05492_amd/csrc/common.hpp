@@ -98,7 +98,7 @@ struct bem_ctx {
     // formed on the caller's stream; the Cholesky's panel and trailing update run on it beside the
     // diagonal blocks) and its events, created on first use
     hipStream_t s2 = nullptr;
-    hipEvent_t ev[7] = {};
+    hipEvent_t ev[6] = {};
     // near-pair slots per wavefront of the mixed J tiles' lists (a multiple of 256, raised by
     // lm_step when a wavefront's near pairs overflow it)
     int near_slots = 1024;

@@ -329,13 +329,15 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
     const int64_t n3 = 3 * (N > 0 ? N : 1);
     // lm workspace layout (ctx->lmw): u | r | g | JtJ | (spare P) | A | delta | theta' | partials | flag |
     // compatibility vectors [3][P] | right-hand sides [P][4] | violation
-    const size_t bytes = 2 * (size_t)n3 * ue + ((size_t)P + 2 * (size_t)P * P + 2 * (size_t)P + (size_t)P +
+    // (the matrices start at 16 bytes: P is even)
+    const size_t uo = (2 * (size_t)n3 * ue + 15) / 16 * 16;
+    const size_t bytes = uo + ((size_t)P + 2 * (size_t)P * P + 2 * (size_t)P + (size_t)P +
                                                  3 * (size_t)kRedBlocks + 8 + 7 * (size_t)P + 8) * sizeof(double) + 64;
     if ((rc = ensure(ctx, ctx->lmw, bytes, s))) return rc;
     char* base = (char*)ctx->lmw.ptr;
     void* u = base;
     void* r = base + (size_t)n3 * ue;
-    double* g = (double*)(base + 2 * (size_t)n3 * ue);
+    double* g = (double*)(base + uo);
     double* JtJ = g + P;
     double* A = JtJ + (size_t)P * P + P;
     double* delta = A + (size_t)P * P;

@@ -1,0 +1,39 @@
+"""The damped Cholesky solve of the LM step (128-column steps, their diagonal block in two 64 x 64 halves, the
+trailing update in 64 x 64 tiles over a fixed number of workgroups) at the sizes where blocks end: P = 14 H within one
+half, within one block, just past a half, a block or several, and at a whole number of blocks.
+
+delta = (H + lam D)^-1 g solves a slightly perturbed system; the bar on its residual relative to ||A|| ||delta|| is
+50 P 2^-53 (the standard bound of the factorisation and two triangular solves is a small multiple of P 2^-53)."""
+import numpy as np
+import pytest
+
+from paper_2602_05492_amd import bem as B
+from paper_2602_05492_amd import workload as W
+from helpers import ctx_for, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H", [1, 4, 5, 9, 10, 19, 64, 110])
+def test_damped_solve(H):
+    rng = np.random.default_rng(H)
+    a = rng.uniform(0.2, 0.8, (H, 2))
+    ang = rng.uniform(0, 2 * np.pi, H)
+    b = np.clip(a + 0.05 * np.stack([np.cos(ang), np.sin(ang)], 1), 0.02, 0.98)
+    th = np.ascontiguousarray(np.concatenate([a, b, W.draw_straight_colours(rng, H)], axis=1))
+    ctx = ctx_for(1, per_side=16, handle_model="straight")
+    x = dev(W.random_points(H, 6000, 0.01, 0.99))
+    th0, lam, cbar = dev(th), 1.0, (0.3, 0.5, 0.7)
+    u = ctx.eval(th0, x, cbar, "fp64")
+    T = u + 0.1 * dev(W.random_vector(H, (6000, 3)))
+    t, st = th0.clone(), B.new_lm_state(lam, 0)
+    ctx.lm_step(t, x, T, st, "fp64", "fp64")
+    assert st.accepted == 1
+    r = ctx.eval(th0, x, tuple(st.cbar), "fp64") - T
+    JtJ, Jtr = (host(v) for v in ctx.jtj(th0, x, r, "fp64", "fp64"))
+    A = JtJ + lam * np.diag(np.diag(JtJ))
+    d = host(th0 - t).ravel()
+    P = len(d)
+    # theta - (theta - delta) loses theta's last bits
+    loss = np.abs(A).sum(1).max() * 2.0 ** -53 * np.abs(host(th0)).max()
+    assert np.abs(A @ d - Jtr.ravel()).max() <= 50 * P * 2.0 ** -53 * np.abs(A).sum(1).max() * np.abs(d).max() + 4 * loss
