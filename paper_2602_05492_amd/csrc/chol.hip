@@ -4,7 +4,8 @@
 // Blocked right-looking factorisation with 128-column panels: the diagonal block
 // in one workgroup's LDS, inverted in the same kernel; the panel as a GEMM
 // with that inverse; the trailing update as a rank-128 symmetric update.  The solves
-// use the inverted 64 x 64 diagonal blocks: one launch per block and direction.  A
+// use the inverted diagonal blocks: the forward one as further rows of the matrix, the
+// backward one a launch per block.  A
 // non-positive or non-finite pivot raises a device flag.
 #include <utility>
 
@@ -16,7 +17,7 @@ namespace bem {
 
 namespace {
 
-constexpr int NB = 64;       // blocks of the solves
+constexpr int NB = 64;       // half a diagonal block, and the trailing update's tile
 constexpr int KB = 2 * NB;   // columns of a factorisation step
 typedef double d2_t __attribute__((ext_vector_type(2)));
 
@@ -35,17 +36,37 @@ __global__ void k_diag_max(const double* __restrict__ H, int64_t P, double* __re
     if (threadIdx.x == 0) dmax[0] = red[0];
 }
 
-// A = H + lam * diag(max(H_ii, 1e-12 * max_j H_jj))
+// A = H + lam * diag(max(H_ii, 1e-12 * max_j H_jj)), lower triangle
 __global__ void k_damp(const double* __restrict__ H, int64_t P, double lam, const double* __restrict__ dmax,
                        double* __restrict__ A)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t i = blockIdx.y;
-    if (j >= P) return;
+    if (j > i) return;
     double v = H[i * P + j];
     if (i == j) v += lam * fmax(v, 1e-12 * dmax[0]);
     A[i * P + j] = v;
 }
+
+// The right-hand sides B [P][nrhs] as rows of A from Ar on, then KB zeros: the last block's panel loads whole slabs
+// past the rows' ends.
+__global__ void k_rhs_rows(const double* __restrict__ B, int64_t P, int nrhs, double* __restrict__ Ar)
+{
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = blockIdx.y;
+    if (c == nrhs) {
+        if (j < KB) Ar[nrhs * P + j] = 0.0;
+    } else if (j < P) {
+        Ar[c * P + j] = B[j * nrhs + c];
+    }
+}
+
+// rows of the matrix being factored: the first P and the right-hand sides'
+struct Rows {
+    int64_t P, Pr;
+    int nrhs;
+    __device__ bool has(int64_t r) const { return r < P || (r >= Pr && r < Pr + nrhs); }
+};
 
 // lane K's value of each row of 16 lanes
 template <int K>
@@ -188,10 +209,9 @@ __device__ inline void loads_landed()
 }
 
 // Update diagonal block kb (128 columns) with the panel of block kb - 1 (kb > 0) and factor it in place (lower
-// triangle); inverses of its two 64 x 64 blocks to linv64 [64-block][64][64] (for the solves) and of the whole to
-// inv [128][128] (for the panel).  Rows and columns past the matrix are an identity block.
+// triangle); its inverse to inv [128][128].  Rows and columns past the matrix are an identity block.
 __device__ __forceinline__ void diag_block(double* lds, double* __restrict__ A, int64_t P, int kb, int* __restrict__ flag,
-                                           double* __restrict__ linv64, double* __restrict__ inv)
+                                           double* __restrict__ inv)
 {
     Tile& B0 = *(Tile*)lds;
     Tile& B1 = *((Tile*)lds + 1);
@@ -334,22 +354,18 @@ __device__ __forceinline__ void diag_block(double* lds, double* __restrict__ A, 
 #pragma unroll
             for (int q = 0; q < 4; ++q) inv[(NB + DB * (I0 + i) + 4 * q + lk) * KB + DB * J + rr] = -v[i][q];
     }
-    double* l0 = linv64 + (size_t)2 * kb * NB * NB;
 #pragma unroll
     for (int q = 0; q < NB / 8; ++q) {
         const int r = w + 8 * q;
-        const double x0 = B1[r][lane], x1 = B0[r][lane];
-        inv[r * KB + lane] = x0;
+        inv[r * KB + lane] = B1[r][lane];
         inv[r * KB + NB + lane] = 0.0;
-        inv[(NB + r) * KB + NB + lane] = x1;
-        l0[r * NB + lane] = x0;
-        if (nb > NB) l0[NB * NB + r * NB + lane] = x1;
+        inv[(NB + r) * KB + NB + lane] = B0[r][lane];
     }
 }
 
 // Step kb > 0: block 0 the diagonal block above; the other blocks the rest of the trailing update with the panel of
 // block kb - 1, C -= L L^T on the 64 x 64 tiles of the lower triangle of C = A[o:, o:], o = 128 kb, but the first
-// three (row by row; they are the diagonal block).  Step 0: the diagonal block alone.  One launch for the two, because
+// three (row by row; they are the diagonal block), and on the right-hand sides' rows.  Step 0: the diagonal block alone.  One launch for the two, because
 // on two streams the diagonal block's workgroup had to wait for a whole CU's LDS until the update drained.
 //
 // Update: a workgroup's two groups of 4 wavefronts take a tile each, 32 x 32 a wavefront, k in slabs of 16 straight
@@ -357,13 +373,13 @@ __device__ __forceinline__ void diag_block(double* lds, double* __restrict__ A, 
 // Bound by the matrix cores at P = 5,000 (3,000 tiles of 1 MFLOP on the first step, 40 us).  Each XCD takes a contiguous
 // run of the tiles, so that its L2 holds their panel rows.
 constexpr int kStepBlocks = 256;
-__global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, int64_t P, int kb, int ntile,
-                                                   int* __restrict__ flag, double* __restrict__ linv64,
-                                                   double* __restrict__ inv)
+__global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, Rows R, int kb, int ntile,
+                                                   int* __restrict__ flag, double* __restrict__ inv)
 {
     __shared__ __attribute__((aligned(1024))) double lds[kStepLds / sizeof(double)];
+    const int64_t P = R.P;
     if (blockIdx.x == 0) {
-        diag_block(lds, A, P, kb, flag, linv64, inv);
+        diag_block(lds, A, P, kb, flag, inv);
         return;
     }
     const int l = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = w8 & 3, grp = w8 >> 2;
@@ -391,8 +407,8 @@ __global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, int64
         for (int i = 0; i < 2; ++i) {
             const int r = 16 * w + 8 * i + (l >> 3);
             const int c = slab_pos(r, l & 7);
-            ga[i] = A + (o + (r0 + r < rem ? r0 + r : rem - 1)) * P + (o - KB) + c;
-            gb[i] = A + (o + (c0 + r < rem ? c0 + r : rem - 1)) * P + (o - KB) + c;
+            ga[i] = A + (R.has(o + r0 + r) ? o + r0 + r : o) * P + (o - KB) + c;
+            gb[i] = A + (c0 + r < rem ? o + c0 + r : o) * P + (o - KB) + c;
         }
     };
     auto load = [&](int buf, int s) {
@@ -417,7 +433,7 @@ __global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, int64
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int64_t r = r0 + 32 * wr + 16 * i + 4 * q + lk, k = c0 + 32 * wc + 16 * j + rr;
-                    const bool in = r < rem && k <= r;
+                    const bool in = R.has(o + r) && k <= r && k < rem;
                     c[i][j][q] = A[(o + (in ? r : 0)) * P + o + (in ? k : 0)];
                 }
         d4_t acc[2][2];
@@ -460,7 +476,7 @@ __global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, int64
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int64_t r = r0 + 32 * wr + 16 * i + 4 * q + lk, k = c0 + 32 * wc + 16 * j + rr;
-                        if (r < rem && k <= r) A[(o + r) * P + o + k] = c[i][j][q] - acc[i][j][q];
+                        if (R.has(o + r) && k <= r && k < rem) A[(o + r) * P + o + k] = c[i][j][q] - acc[i][j][q];
                     }
         }
         live = next;
@@ -474,14 +490,15 @@ __global__ void __launch_bounds__(512) k_chol_step(double* __restrict__ A, int64
 // owns whole rows, so that its stores, after its last load, meet no other block's loads.  P is even (16-byte loads).
 // Bound by latency (8 slabs of 16 k); 32 rows a block for 150 blocks at P = 5,000.
 constexpr int kPanelRows = 32;
-__global__ void __launch_bounds__(256) k_panel(double* __restrict__ A, int64_t P, int kb, const double* __restrict__ inv)
+__global__ void __launch_bounds__(256) k_panel(double* __restrict__ A, Rows R, int kb, const double* __restrict__ inv)
 {
     __shared__ __attribute__((aligned(1024))) double Sa[2][kPanelRows][kSlab], Sb[2][KB][kSlab];
+    const int64_t P = R.P;
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rr = l & 15, lk = l >> 4;
     const int64_t o = (int64_t)kb * KB, row0 = o + KB + (int64_t)blockIdx.x * kPanelRows;
     const int ra = 8 * w + (l >> 3);
-    const double* ga = A + (row0 + ra < P ? row0 + ra : P - 1) * P + o + slab_pos(ra, l & 7);
+    const double* ga = A + (R.has(row0 + ra) ? row0 + ra : 0) * P + o + slab_pos(ra, l & 7);
     const double* gb[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -526,188 +543,109 @@ __global__ void __launch_bounds__(256) k_panel(double* __restrict__ A, int64_t P
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int64_t r = row0 + 16 * i + 4 * q + lk;
-            if (r >= P) continue;
+            if (!R.has(r)) continue;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) A[r * P + o + 32 * w + 16 * j + rr] = acc[i][j][q];
+            for (int j = 0; j < 2; ++j)
+                if (o + 32 * w + 16 * j + rr < P) A[r * P + o + 32 * w + 16 * j + rr] = acc[i][j][q];
         }
 }
 
-// Forward step kb of L y = b with the inverted diagonal blocks, B [P][nrhs]: every block
-// forms y_kb = Linv_kb b_kb; block 0 writes it to Y, block t >= 1 subtracts L y_kb from the
-// 64 rows starting at o + 64 t (B rows of block kb itself are not modified in this step).
-// 256 threads: operand tiles are staged in LDS, each wave loading 16 rows, and the products
-// are split over the 4 waves by k and summed in LDS.
 constexpr int kMaxRhs = 4;
-// the four waves' partial sums of row t
-__device__ inline void solve_sum(const double (*part)[NB][kMaxRhs], int t, int nrhs, double* out)
-{
-    for (int c = 0; c < nrhs; ++c) out[c] = part[0][t][c] + part[1][t][c] + part[2][t][c] + part[3][t][c];
-}
 
+// Backward step kb of L^T x = y (128 columns), Y [nrhs][P]: every block forms x_kb = L_kk^{-T} y_kb; block 0 writes it
+// to X [P][nrhs], block t >= 1 subtracts L[block kb rows, c]^T x_kb from the 64 entries of Y starting at column
+// c = 64 (t - 1) (only columns before block kb; Y's entries of block kb are only read).  Bound by latency: every element
+// of the two matrices is used once, so all of a thread's are loaded first, straight into registers.
 template <int nrhs>
-__global__ void __launch_bounds__(256) k_fwd_step(const double* __restrict__ A, int64_t P, int kb,
-                                                  const double* __restrict__ Linv, double* __restrict__ B,
-                                                  double* __restrict__ Y)
-{
-    __shared__ double T[NB][NB + 1];
-    __shared__ double At[NB][NB + 1];   // the block's rows of L (loaded with T: it does not depend on y)
-    __shared__ double bk[NB][kMaxRhs];
-    __shared__ double y[NB][kMaxRhs];
-    __shared__ double part[4][NB][kMaxRhs];
-    const int64_t o = (int64_t)kb * NB;
-    const int nb = (int)(P - o < NB ? P - o : NB);
-    const int t = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const double* L0 = Linv + (size_t)kb * NB * NB;
-    const int64_t r0 = o + (int64_t)blockIdx.x * NB;
-    const int nr = blockIdx.x == 0 ? 0 : (int)(P - r0 < NB ? P - r0 : NB);
-    // loads first (all in flight; entries past the matrix read an in-bounds one and are then zeroed)
-    double gl[NB / 4], ga[NB / 4];
-#pragma unroll
-    for (int q = 0; q < NB / 4; ++q) {
-        const int r = w + 4 * q;
-        gl[q] = L0[(size_t)r * NB + t];
-        ga[q] = blockIdx.x != 0 ? A[(r0 + (r < nr ? r : 0)) * P + o + (t < nb ? t : 0)] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < NB / 4; ++q) {
-        const int r = w + 4 * q;
-        T[r][t] = gl[q];
-        At[r][t] = (r < nr && t < nb) ? ga[q] : 0.0;
-    }
-    if (w == 0)
-        for (int c = 0; c < nrhs; ++c) bk[t][c] = t < nb ? B[(o + t) * nrhs + c] : 0.0;
-    __syncthreads();
-    {
-        double acc[nrhs] = {};
-        for (int k = 16 * w; k < 16 * w + 16; ++k) {
-            const double l = T[t][k];
-            for (int c = 0; c < nrhs; ++c) acc[c] += l * bk[k][c];
-        }
-        for (int c = 0; c < nrhs; ++c) part[w][t][c] = acc[c];
-    }
-    __syncthreads();
-    if (w == 0) {
-        double v[nrhs];
-        solve_sum(part, t, nrhs, v);
-        for (int c = 0; c < nrhs; ++c) y[t][c] = v[c];
-        if (blockIdx.x == 0 && t < nb)
-            for (int c = 0; c < nrhs; ++c) Y[(o + t) * nrhs + c] = v[c];
-    }
-    if (blockIdx.x == 0) return;
-    __syncthreads();
-    {
-        double acc[nrhs] = {};
-        for (int k = 16 * w; k < 16 * w + 16; ++k) {
-            const double l = At[t][k];
-            for (int c = 0; c < nrhs; ++c) acc[c] += l * y[k][c];
-        }
-        for (int c = 0; c < nrhs; ++c) part[w][t][c] = acc[c];
-    }
-    __syncthreads();
-    if (w == 0 && t < nr) {
-        double v[nrhs];
-        solve_sum(part, t, nrhs, v);
-        for (int c = 0; c < nrhs; ++c) B[(r0 + t) * nrhs + c] -= v[c];
-    }
-}
-
-// Backward step kb of L^T x = y: every block forms x_kb = Linv_kb^T y_kb; block 0 writes it
-// to X, block t >= 1 subtracts L[block kb rows, c]^T x_kb from the 64 entries of Y starting
-// at column c = 64 (t - 1) (only columns before block kb; Y rows of block kb are only read).
-template <int nrhs>
-__global__ void __launch_bounds__(256) k_bwd_step(const double* __restrict__ A, int64_t P, int kb,
-                                                  const double* __restrict__ Linv, double* __restrict__ Y,
+__global__ void __launch_bounds__(512) k_bwd_step(const double* __restrict__ A, int64_t P, int kb,
+                                                  const double* __restrict__ inv, double* __restrict__ Y,
                                                   double* __restrict__ X)
 {
-    __shared__ double T[NB][NB + 1];
-    __shared__ double At[NB][NB + 1];   // block kb's rows of L at this block's columns (loaded with T)
-    __shared__ double yk[NB][kMaxRhs];
-    __shared__ double x[NB][kMaxRhs];
-    __shared__ double part[4][NB][kMaxRhs];
-    const int64_t o = (int64_t)kb * NB;
-    const int nb = (int)(P - o < NB ? P - o : NB);
-    const int t = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const double* L0 = Linv + (size_t)kb * NB * NB;
-    const int64_t col = (int64_t)(blockIdx.x - 1) * NB + t;
-    // loads first (all in flight; entries past the matrix read an in-bounds one and are then zeroed)
-    double gl[NB / 4], ga[NB / 4];
+    __shared__ double y[KB][nrhs], x[KB][nrhs], part[8][KB][nrhs];
+    const int64_t o = (int64_t)kb * KB;
+    const int nb = (int)(P - o < KB ? P - o : KB);
+    const int tid = threadIdx.x;
+    const int c = tid & (KB - 1), kq = tid >> 7;           // column of the inverse, rows kq, kq + 4, ...
+    const int lc = tid & 63, lq = tid >> 6;                // column of L, rows lq, lq + 8, ...
+    const int64_t col = (int64_t)(blockIdx.x - 1) * 64 + lc;
+    const bool in = blockIdx.x > 0 && col < o;
+    double gi[KB / 4], gl[KB / 8];
 #pragma unroll
-    for (int q = 0; q < NB / 4; ++q) {
-        const int r = w + 4 * q;
-        gl[q] = L0[(size_t)r * NB + t];
-        ga[q] = blockIdx.x != 0 ? A[(o + (r < nb ? r : 0)) * P + (col < o ? col : 0)] : 0.0;
-    }
+    for (int i = 0; i < KB / 4; ++i) gi[i] = inv[(kq + 4 * i) * KB + c];
 #pragma unroll
-    for (int q = 0; q < NB / 4; ++q) {
-        const int r = w + 4 * q;
-        T[r][t] = gl[q];
-        At[r][t] = (r < nb && col < o) ? ga[q] : 0.0;
+    for (int i = 0; i < KB / 8; ++i) {
+        const int r = lq + 8 * i;
+        gl[i] = A[(o + (r < nb ? r : 0)) * P + (in ? col : 0)];
     }
-    if (w == 0)
-        for (int c = 0; c < nrhs; ++c) yk[t][c] = t < nb ? Y[(o + t) * nrhs + c] : 0.0;
-    __syncthreads();
-    {
-        double acc[nrhs] = {};
-        for (int k = 16 * w; k < 16 * w + 16; ++k) {
-            const double l = T[k][t];                  // (Linv^T)[t][k]
-            for (int c = 0; c < nrhs; ++c) acc[c] += l * yk[k][c];
-        }
-        for (int c = 0; c < nrhs; ++c) part[w][t][c] = acc[c];
+    for (int e = tid; e < KB * nrhs; e += 512) {
+        const int r = e & (KB - 1), n = e >> 7;
+        y[r][n] = r < nb ? Y[n * P + o + r] : 0.0;
     }
     __syncthreads();
-    if (w == 0) {
-        double v[nrhs];
-        solve_sum(part, t, nrhs, v);
-        for (int c = 0; c < nrhs; ++c) x[t][c] = v[c];
-        if (blockIdx.x == 0 && t < nb)
-            for (int c = 0; c < nrhs; ++c) X[(o + t) * nrhs + c] = v[c];
+    double acc[nrhs] = {};
+#pragma unroll
+    for (int i = 0; i < KB / 4; ++i)
+        for (int n = 0; n < nrhs; ++n) acc[n] += gi[i] * y[kq + 4 * i][n];
+    for (int n = 0; n < nrhs; ++n) part[kq][c][n] = acc[n];
+    __syncthreads();
+    for (int e = tid; e < KB * nrhs; e += 512) {
+        const int r = e & (KB - 1), n = e >> 7;
+        const double v = (part[0][r][n] + part[1][r][n]) + (part[2][r][n] + part[3][r][n]);
+        x[r][n] = r < nb ? v : 0.0;
+        if (blockIdx.x == 0 && r < nb) X[(o + r) * nrhs + n] = v;
     }
     if (blockIdx.x == 0) return;
     __syncthreads();
-    {
-        double acc[nrhs] = {};
-        for (int r = 16 * w; r < 16 * w + 16; ++r) {
-            const double l = At[r][t];
-            for (int c = 0; c < nrhs; ++c) acc[c] += l * x[r][c];
-        }
-        for (int c = 0; c < nrhs; ++c) part[w][t][c] = acc[c];
-    }
+    for (int n = 0; n < nrhs; ++n) acc[n] = 0.0;
+#pragma unroll
+    for (int i = 0; i < KB / 8; ++i)
+        for (int n = 0; n < nrhs; ++n) acc[n] += gl[i] * x[lq + 8 * i][n];
+    for (int n = 0; n < nrhs; ++n) part[lq][lc][n] = acc[n];
     __syncthreads();
-    if (w == 0 && col < o) {
-        double v[nrhs];
-        solve_sum(part, t, nrhs, v);
-        for (int c = 0; c < nrhs; ++c) Y[col * nrhs + c] -= v[c];
-    }
+    if (tid < 64 && in)
+        for (int n = 0; n < nrhs; ++n) {
+            double v = 0.0;
+            for (int q = 0; q < 8; ++q) v += part[q][lc][n];
+            Y[n * P + col] -= v;
+        }
 }
 
 }  // namespace
 
+// Doubles of chol_factor's buffer: the matrix's rows in whole steps, the right-hand sides' rows, zeros.
+int64_t chol_size(int64_t P) { return ((P + KB - 1) / KB * KB + kMaxRhs) * P + KB; }
+
 // Damp, factor and check: returns BEM_ENOTPD when a pivot fails (host sync).  Blocked right-looking with
 // 128-column steps of two launches: the panel as A21 L^{-T} (in place), then the next diagonal block (updated, factored,
-// inverted) beside the rest of the trailing lower triangle's rank-128 update.  The inverted 64 x 64 diagonal blocks stay in
-// the context for chol_solve.  P is even (handles have 14 or 20 parameters).  64-column steps, the diagonal chain and
-// the update on two streams, took 5.8 ms at P = 5,000: a 65 us chain a step, and 5 GB of reading and writing the
-// trailing matrix.  Now 2.9 ms.
-int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, double* A, int* dflag, double* dscal,
-                hipStream_t s)
+// inverted) beside the rest of the trailing lower triangle's rank-128 update.  The right-hand sides B [P][nrhs], nrhs <= 4,
+// are further rows of the matrix, so that the forward solve comes with its panels (a launch a block of 64 before:
+// 0.4 ms at P = 5,000).  Inverted diagonal blocks and solved rows stay for chol_solve.  P is even (handles have 10 or 20
+// parameters).  64-column steps, the diagonal chain and the update on two streams, took 5.8 ms at P = 5,000: a 65 us
+// chain a step, and 5 GB of reading and writing the trailing matrix.  Now 2.9 ms.
+int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, const double* B, int nrhs, double* A, int* dflag,
+                double* dscal, hipStream_t s)
 {
     int rc;
-    const int nblk = (int)((P + KB - 1) / KB), n64 = (int)((P + NB - 1) / NB);
-    // cholw: inverted diagonal blocks [n64][64][64] | solve vector [P][4] | the step's inverse [128][128]
-    const size_t vo = (size_t)n64 * NB * NB, io = vo + (size_t)P * kMaxRhs;
-    if ((rc = ensure(ctx, ctx->cholw, (io + KB * KB) * sizeof(double), s))) return rc;
-    double* linv = (double*)ctx->cholw.ptr;
-    double* inv = linv + io;
+    if (nrhs < 1 || nrhs > kMaxRhs) return set_error(ctx, BEM_EINVAL, "chol_factor: 1..4 right-hand sides");
+    const int nblk = (int)((P + KB - 1) / KB);
+    const Rows R{P, (int64_t)nblk * KB, nrhs};
+    // cholw: inverted diagonal blocks [nblk][128][128]
+    if ((rc = ensure(ctx, ctx->cholw, (size_t)nblk * KB * KB * sizeof(double), s))) return rc;
+    double* inv = (double*)ctx->cholw.ptr;
     hipLaunchKernelGGL(k_diag_max, dim3(1), dim3(256), 0, s, H, P, dscal);
     hipLaunchKernelGGL(k_damp, dim3(blocks_for(P, 256), P), dim3(256), 0, s, H, P, lam, dscal, A);
+    hipLaunchKernelGGL(k_rhs_rows, dim3(blocks_for(P, 256), nrhs + 1), dim3(256), 0, s, B, P, nrhs, A + R.Pr * P);
     if ((rc = fill_i32(ctx, dflag, 1, 0, s))) return rc;
     ProfScope ps_(ctx, PT_CHOLESKY, s);
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int64_t rem = P - (int64_t)kb * KB;                   // the trailing matrix of the step before
-        const int nt = blocks_for(rem, NB), ntile = kb > 0 && rem > KB ? nt * (nt + 1) / 2 - 3 : 0;
+    for (int kb = 0; kb <= nblk; ++kb) {
+        double* Li = inv + (size_t)kb * KB * KB;
+        const int64_t rows = R.Pr + nrhs - (int64_t)kb * KB;          // rows left, the gap before the last ones counted
         if (kb > 0)
-            hipLaunchKernelGGL(k_panel, dim3(blocks_for(rem, kPanelRows)), dim3(256), 0, s, A, P, kb - 1, (const double*)inv);
-        hipLaunchKernelGGL(k_chol_step, dim3(ntile > 0 ? kStepBlocks : 1), dim3(512), 0, s, A, P, kb, ntile, dflag, linv, inv);
+            hipLaunchKernelGGL(k_panel, dim3(blocks_for(rows, kPanelRows)), dim3(256), 0, s, A, R, kb - 1,
+                               (const double*)(Li - KB * KB));
+        if (kb == nblk) break;
+        const int nt = blocks_for(rows, NB), ntile = kb > 0 ? nt * (nt + 1) / 2 - 3 : 0;
+        hipLaunchKernelGGL(k_chol_step, dim3(ntile > 0 ? kStepBlocks : 1), dim3(512), 0, s, A, R, kb, ntile, dflag, Li);
     }
     if ((rc = check_launch(ctx, "cholesky"))) return rc;
     ctx->chol_P = P;
@@ -718,37 +656,27 @@ int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, double* A,
     return hflag ? BEM_ENOTPD : BEM_OK;
 }
 
-// B <- (L L^T)^{-1} B with the factor in A and the inverted diagonal blocks of the last
-// chol_factor; B [P][nrhs] row-major, nrhs <= 4.  One launch per block and direction.
-// Forward then backward block steps for nrhs right-hand sides (B [P][nrhs] in, solution out; Y [P][nrhs] scratch).
 template <int nrhs>
-static void solve_steps(const double* A, int64_t P, int nblk, const double* linv, double* B, double* Y, hipStream_t s)
+static void solve_steps(double* A, int64_t P, int nblk, const double* inv, double* X, hipStream_t s)
 {
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int64_t rem = P - (int64_t)(kb + 1) * NB;
-        const int nbk = 1 + (rem > 0 ? blocks_for(rem, NB) : 0);
-        hipLaunchKernelGGL(k_fwd_step<nrhs>, dim3(nbk), dim3(256), 0, s, A, P, kb, linv, B, Y);
-    }
-    for (int kb = nblk - 1; kb >= 0; --kb) {
-        const int64_t o = (int64_t)kb * NB;
-        const int nbk = 1 + (o > 0 ? blocks_for(o, NB) : 0);
-        hipLaunchKernelGGL(k_bwd_step<nrhs>, dim3(nbk), dim3(256), 0, s, A, P, kb, linv, Y, B);
-    }
+    for (int kb = nblk - 1; kb >= 0; --kb)
+        hipLaunchKernelGGL(k_bwd_step<nrhs>, dim3(1 + 2 * kb), dim3(512), 0, s, A, P, kb, inv + (size_t)kb * KB * KB,
+                           A + (size_t)nblk * KB * P, X);
 }
 
-int chol_solve(bem_ctx* ctx, const double* A, int64_t P, double* B, int nrhs, hipStream_t s)
+// X [P][nrhs] = (L L^T)^{-1} B of the last chol_factor (in A): the backward solve of its solved rows, one launch per
+// block, which overwrites them.
+int chol_solve(bem_ctx* ctx, double* A, int64_t P, double* X, int nrhs, hipStream_t s)
 {
-    if (nrhs < 1 || nrhs > kMaxRhs) return set_error(ctx, BEM_EINVAL, "chol_solve: 1..4 right-hand sides");
     if (ctx->chol_P != P) return set_error(ctx, BEM_ESTATE, "chol_solve without a matching chol_factor");
     ProfScope ps_(ctx, PT_CHOLESKY, s);
-    const int nblk = (int)((P + NB - 1) / NB);
-    const double* linv = (const double*)ctx->cholw.ptr;
-    double* Y = (double*)ctx->cholw.ptr + (size_t)nblk * NB * NB;
+    const int nblk = (int)((P + KB - 1) / KB);
+    const double* inv = (const double*)ctx->cholw.ptr;
     switch (nrhs) {
-    case 1: solve_steps<1>(A, P, nblk, linv, B, Y, s); break;
-    case 2: solve_steps<2>(A, P, nblk, linv, B, Y, s); break;
-    case 3: solve_steps<3>(A, P, nblk, linv, B, Y, s); break;
-    default: solve_steps<4>(A, P, nblk, linv, B, Y, s); break;
+    case 1: solve_steps<1>(A, P, nblk, inv, X, s); break;
+    case 2: solve_steps<2>(A, P, nblk, inv, X, s); break;
+    case 3: solve_steps<3>(A, P, nblk, inv, X, s); break;
+    default: solve_steps<4>(A, P, nblk, inv, X, s); break;
     }
     return check_launch(ctx, "cholesky solve");
 }

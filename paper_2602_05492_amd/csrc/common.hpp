@@ -220,9 +220,10 @@ int launch_gram_mfma(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xl
                      const int* work, int nwork, int64_t kchunk, double* G, int64_t gstride, bool accumulate,
                      hipStream_t s);
 // chol.hip
-int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, double* A, int* dflag, double* dscal,
-                hipStream_t s);
-int chol_solve(bem_ctx* ctx, const double* A, int64_t P, double* B, int nrhs, hipStream_t s);
+int64_t chol_size(int64_t P);
+int chol_factor(bem_ctx* ctx, const double* H, int64_t P, double lam, const double* B, int nrhs, double* A, int* dflag,
+                double* dscal, hipStream_t s);
+int chol_solve(bem_ctx* ctx, double* A, int64_t P, double* X, int nrhs, hipStream_t s);
 // lm.hip
 int fill_i32(bem_ctx* ctx, int* p, int64_t n, int v, hipStream_t s);
 int scale_f64(bem_ctx* ctx, double* p, int64_t n, double v, hipStream_t s);

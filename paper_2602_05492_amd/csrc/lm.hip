@@ -193,13 +193,14 @@ __global__ void __launch_bounds__(256) k_reproject(const double* __restrict__ A,
     }
 }
 
-__global__ void k_finish_sum(const double* __restrict__ partial, int nb, double* __restrict__ out)
+// a wavefront per component (192 threads), in a fixed order
+__global__ void __launch_bounds__(192) k_finish_sum(const double* __restrict__ partial, int nb, double* __restrict__ out)
 {
-    if (threadIdx.x < 3) {
-        double s = 0.0;
-        for (int b = 0; b < nb; ++b) s += partial[3 * b + threadIdx.x];
-        out[threadIdx.x] = s;
-    }
+    const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double s = 0.0;
+    for (int b = lane; b < nb; b += 64) s += partial[3 * b + c];
+    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
+    if (lane == 0) out[c] = s;
 }
 
 __global__ void k_scale(double* __restrict__ v, int64_t n, double s)
@@ -246,7 +247,7 @@ static int row_sums(bem_ctx* ctx, const void* u, bool f32, const double* T, int6
             hipLaunchKernelGGL(k_rowsum<float>, dim3(nb), dim3(256), 0, s, (const float*)u, T, N, mode, (float*)r, dpart);
         else
             hipLaunchKernelGGL(k_rowsum<double>, dim3(nb), dim3(256), 0, s, (const double*)u, T, N, mode, (double*)r, dpart);
-        hipLaunchKernelGGL(k_finish_sum, dim3(1), dim3(64), 0, s, dpart, nb, dpart + 3 * kRedBlocks);
+        hipLaunchKernelGGL(k_finish_sum, dim3(1), dim3(192), 0, s, dpart, nb, dpart + 3 * kRedBlocks);
     } else {
         fill_f64(ctx, dpart + 3 * kRedBlocks, 3, 0.0, s);
     }
@@ -331,7 +332,7 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
     // compatibility vectors [3][P] | right-hand sides [P][4] | violation
     // (the matrices start at 16 bytes: P is even)
     const size_t uo = (2 * (size_t)n3 * ue + 15) / 16 * 16;
-    const size_t bytes = uo + ((size_t)P + 2 * (size_t)P * P + 2 * (size_t)P + (size_t)P +
+    const size_t bytes = uo + ((size_t)P + (size_t)P * P + (size_t)chol_size(P) + 2 * (size_t)P + (size_t)P +
                                                  3 * (size_t)kRedBlocks + 8 + 7 * (size_t)P + 8) * sizeof(double) + 64;
     if ((rc = ensure(ctx, ctx->lmw, bytes, s))) return rc;
     char* base = (char*)ctx->lmw.ptr;
@@ -340,7 +341,7 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
     double* g = (double*)(base + uo);
     double* JtJ = g + P;
     double* A = JtJ + (size_t)P * P + P;
-    double* delta = A + (size_t)P * P;
+    double* delta = A + (size_t)chol_size(P);
     double* th1 = delta + P;
     double* dpart = th1 + (size_t)P;
     int* dflag = (int*)(dpart + 3 * kRedBlocks + 4);
@@ -444,10 +445,21 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
         st->loss_before = L0 + R0;
         st->loss_after = L0 + R0;
     }
+    const int S = ctx->opts.segs_per_handle;
+    if (st->compat) {
+        // right-hand sides [g | A], A the compatibility vectors at the current end points, whose segment table the
+        // normal equations left in place
+        if ((rc = fill_f64(ctx, cA, 3 * P, 0.0, s))) return rc;
+        hipLaunchKernelGGL(k_compat_vectors, dim3(blocks_for(H, 64)), dim3(64), 0, s, (const double*)ctx->seg64.ptr, H,
+                           S, ctx->model, P, cA);
+        hipLaunchKernelGGL(k_pack_rhs, dim3(blocks_for(P, 256)), dim3(256), 0, s, (const double*)g,
+                           (const double*)cA, P, cX);
+    }
     // damped Cholesky, raising lambda until it factors
     double lam = st->lambda;
     for (int attempt = 0;; ++attempt) {
-        rc = chol_factor(ctx, JtJ, P, lam, A, dflag, dpart, s);
+        rc = st->compat ? chol_factor(ctx, JtJ, P, lam, cX, 4, A, dflag, dpart, s)
+                        : chol_factor(ctx, JtJ, P, lam, g, 1, A, dflag, dpart, s);
         if (rc == BEM_OK) break;
         if (rc != BEM_ENOTPD) return rc;
         if (attempt >= 10) {
@@ -458,20 +470,11 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
         st->chol_retries++;
     }
     st->lambda = lam;
-    const int S = ctx->opts.segs_per_handle;
     if (!st->compat) {
-        if (hipMemcpyAsync(delta, g, P * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess)
-            return set_error(ctx, BEM_EHIP, "copy gradient");
         if ((rc = chol_solve(ctx, A, P, delta, 1, s))) return rc;
     } else {
-        // the step restricted to A^T delta = 0 (A at the current end points, whose segment table
-        // the normal equations left in place): one solve of Hd [delta0 | X] = [g | A], then the
+        // the step restricted to A^T delta = 0: one solve of Hd [delta0 | X] = [g | A], then the
         // 3x3 Schur complement
-        if ((rc = fill_f64(ctx, cA, 3 * P, 0.0, s))) return rc;
-        hipLaunchKernelGGL(k_compat_vectors, dim3(blocks_for(H, 64)), dim3(64), 0, s, (const double*)ctx->seg64.ptr, H,
-                           S, ctx->model, P, cA);
-        hipLaunchKernelGGL(k_pack_rhs, dim3(blocks_for(P, 256)), dim3(256), 0, s, (const double*)g,
-                           (const double*)cA, P, cX);
         if ((rc = chol_solve(ctx, A, P, cX, 4, s))) return rc;
         hipLaunchKernelGGL(k_compat_solve, dim3(1), dim3(256), 0, s, (const double*)cA, (const double*)cX, P, delta);
     }

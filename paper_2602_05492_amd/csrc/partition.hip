@@ -74,8 +74,11 @@ __global__ void __launch_bounds__(1024) k_part_scan_totals(const int64_t* __rest
     if (t == kMaxLabels - 1) off[D] = s[t];
 }
 
-// Scatter of block b's chunk: 256 samples per round; a sample's destination is its label's
-// running position plus the number of earlier samples of the round with the same label.
+// Scatter of block b's chunk: 256 samples per round; a sample's destination is its label's running position plus
+// the number of earlier samples of the round with the same label: within the wavefront from the lanes' label
+// masks, one label after the other, across wavefronts by taking the running positions in their order.  Bound by
+// the masks' loop (up to 64 labels a wavefront); 30,000 samples: 84 us with a scan of the round's 256 labels per
+// sample, now XXX us.
 __global__ void __launch_bounds__(256) k_part_scatter(const int32_t* __restrict__ labels, int64_t N, int D, int nb,
                                                       const int64_t* __restrict__ base, const int64_t* __restrict__ off,
                                                       const double* __restrict__ x,
@@ -83,29 +86,32 @@ __global__ void __launch_bounds__(256) k_part_scatter(const int32_t* __restrict_
                                                       double* __restrict__ To)
 {
     __shared__ int64_t cur[kMaxLabels];
-    __shared__ int lab[256];
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     for (int d = t; d < D; d += 256) cur[d] = off[d] + base[(size_t)d * nb + blockIdx.x];
     const int64_t lo = (int64_t)blockIdx.x * kChunk, hi = lo + kChunk < N ? lo + kChunk : N;
     __syncthreads();
     for (int64_t r0 = lo; r0 < hi; r0 += 256) {
         const int64_t i = r0 + t;
         int l = i < hi ? labels[i] : -1;
-        if (l >= D) l = -1;
-        lab[t] = l < 0 ? -1 : l;
-        __syncthreads();
-        int rank = 0;
-        bool last = true;
-        if (l >= 0) {
-            for (int u = 0; u < 256; ++u) {
-                if (lab[u] != l) continue;
-                if (u < t) ++rank;
-                else if (u > t) last = false;
-            }
+        if (l < 0 || l >= D) l = -1;
+        uint64_t mine = 0;                       // lanes with this lane's label
+        for (uint64_t todo = __ballot(l >= 0); todo != 0;) {
+            const int v = __builtin_amdgcn_readlane(l, __builtin_ctzll(todo));
+            const uint64_t m = __ballot(l == v);
+            if (l == v) mine = m;
+            todo &= ~m;
         }
-        const int64_t dest = l >= 0 ? cur[l] + rank : -1;
-        __syncthreads();
-        if (l >= 0 && last) cur[l] += rank + 1;
+        const int rank = __popcll(mine & ((1ull << lane) - 1ull));
+        const bool first = l >= 0 && rank == 0;
+        int64_t dest = -1;
+        for (int q = 0; q < 4; ++q) {
+            if (w == q) {
+                if (l >= 0) dest = cur[l] + rank;
+                __builtin_amdgcn_wave_barrier();
+                if (first) cur[l] += __popcll(mine);
+            }
+            __syncthreads();
+        }
         if (dest >= 0) {
             xo[2 * dest] = x[2 * i];
             xo[2 * dest + 1] = x[2 * i + 1];
@@ -115,7 +121,6 @@ __global__ void __launch_bounds__(256) k_part_scatter(const int32_t* __restrict_
                 To[3 * dest + 2] = T[3 * i + 2];
             }
         }
-        __syncthreads();
     }
 }
 
