@@ -142,21 +142,24 @@ __device__ inline int g2_lds(int r, int c)   // element offset of chunk c of row
 //   kGramHalf     float16 pairs of rows scaled by powers of two (rscale [row] undoes them): 22 bits instead of 16,
 //                 for the 64 columns a cell that stand for its samples (jtj_cells.hip), whose rounding
 //                 averages over fewer columns.  With bfloat16 pairs the LM step of 8,192 segments was 2.3e-4
-//                 from the float64 step, against 5.4e-5 from all samples.
+//                 from the float64 step, against 5.4e-5 from all samples.  Its runs of columns are short, so that
+//                 adding each into a float64 Gram cost as much as a third of the products (one workgroup a CU, its
+//                 read-modify-write of 512 KiB behind nothing): a run's sums go out in float32 in register order
+//                 (256 KiB a work entry) and k_sum_half adds the runs in float64.  8,192 rows, 83,000 columns in
+//                 39 runs: 13.0 -> 9.0 + 0.75 ms.
 //   kGramCells    bfloat16 pairs of the near rows of grid cells (jtj_cells.hip).  A work entry is (cell,
 //                 row tile, column tile) of the cell's near tile E [n / 32][rows][32]; the cell's 64 projected
 //                 columns Z follow its samples, negated on the column side (E E^T - Z Z^T), as three terms
 //                 h + m + l of bfloat16 (24 bits): a stage multiplies (a, b) (c, d) as ac + ad + bc, so the pairs
 //                 (h, m)(h, l), (h, m)(m, 0), (l, 0)(h, 0) give hh + hl + mh + hm + mm + lh.  The sums are added
-//                 into the entries of the whole Gram that the cell's rows map to (float64 atomics; cells are
-//                 spread over the partial Grams).
+//                 into the entries of the whole Gram that the cell's rows map to (float64 atomics).
 enum { kGramSamples, kGramHalf, kGramCells };
 struct CellGram {
     const uint16_t* zt[5];                                 // Z: h, m, l, zeros; and -Z: h (m, l follow at zstep)
     int64_t zstep;
     const CellInfo* ci;
     const int *hl, *el;
-    int nc, H, M, parts;
+    int nc, H, M;
     Layout L;
     int64_t W;
 };
@@ -199,13 +202,18 @@ template <int Mode>
 __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restrict__ Xh, const uint16_t* __restrict__ Xl,
                                                          int W, int n_all, const int* __restrict__ work,
                                                          int nwork, int kchunk, double* __restrict__ G,
-                                                         int64_t gstride, int accumulate, const float* __restrict__ rscale,
-                                                         CellGram cg)
+                                                         int64_t gstride, int accumulate, int ntiles, CellGram cg)
 {
     constexpr bool Cells = Mode == kGramCells;
     __shared__ __attribute__((aligned(16))) uint16_t sm0[4][G2_T * G2_BK];   // [A hi, A lo, B hi, B lo]
     __shared__ __attribute__((aligned(16))) uint16_t sm1[4][G2_T * G2_BK];
-    const int wi = work_index(nwork);
+    int wi = work_index(nwork);
+    if constexpr (Mode == kGramHalf) {
+        // all XCDs on one run of columns at a time (XCD x the x-th eighth of its tiles): the run's operands (71 MB for 8,192
+        // rows) stay in the memory-side cache, which eight runs at once would overflow
+        const int per = (ntiles + 7) >> 3, b = (int)(blockIdx.x >> 3), t = (int)(blockIdx.x & 7) * per + b % per;
+        wi = t < ntiles ? b / per * ntiles + t : nwork;
+    }
     if (wi >= nwork) return;
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -226,12 +234,11 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
         nE = (q.n + 31) & ~31;
         n = nE + (cell < cg.nc ? 3 * kCellColumns : 0);    // the samples outside the grid have none
         zoff = (int64_t)q.rb * kCellColumns;
-        G += (int64_t)(cell % cg.parts) * gstride;
-    } else {
+    } else if (Mode == kGramSamples) {
         G += (int64_t)work[3 * wi + 2] * gstride;
     }
-    if (!Cells && kb >= n) {                                         // part beyond a ragged last tile
-        if (!accumulate) zero_tile(G, row0, col0, G2_T, W);
+    if (!Cells && kb >= n) {                                         // part beyond a ragged last tile (no run is)
+        if (Mode == kGramSamples && !accumulate) zero_tile(G, row0, col0, G2_T, W);
         return;
     }
     const int wr = wave >> 1, wc = wave & 1;
@@ -382,6 +389,17 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
             }
         return;
     }
+    if constexpr (Mode == kGramHalf) {
+        float* o = (float*)G + (int64_t)wi * (G2_T * G2_T) + wave * 8192 + lane;
+        if (nwork > 0)           // always: a block of their own, without which the stores spill 82 registers of the loop
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                for (int nj = 0; nj < 4; ++nj)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[((mi * 4 + nj) * 16 + r) * 64] = acc[mi][nj][r];
+        return;
+    }
     // epilogue: G += acc (G = acc for the first sample tile).  A tile inside the matrix reads its 16
     // values of an MFMA tile in one batch (one wait instead of 16); tiles at the matrix edge go
     // element by element.
@@ -392,18 +410,6 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
         for (int nj = 0; nj < 4; ++nj) {
             const int ib = row0 + wr * 64 + 32 * mi + 4 * lk;
             const int j = col0 + wc * 128 + 32 * nj + li;
-            if constexpr (Mode == kGramHalf) {             // undo the rows' scales (powers of two)
-                const float sj = j < W ? rscale[j] : 0.0f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = ib + 8 * (r >> 2) + (r & 3);
-                    if (i < W && j < W) {
-                        double* g = G + (int64_t)i * W + j;
-                        *g = (accumulate ? *g : 0.0) + (double)acc[mi][nj][r] * ((double)sj * (double)rscale[i]);
-                    }
-                }
-                continue;
-            }
             if (inside) {
                 double* g = G + (int64_t)ib * W + j;
                 double v[16];
@@ -420,6 +426,33 @@ __global__ void __launch_bounds__(512) k_gram_bf16x3_lds(const uint16_t* __restr
                 }
             }
         }
+}
+
+// G = the runs' sums (register order of k_gram_bf16x3_lds, run p of tile i at entry p ntiles + i) with the rows' scales
+// undone; += with accumulate.  Block (tile, wavefront of the tile).
+__global__ void __launch_bounds__(256) k_sum_half(const float* __restrict__ part, int runs, int ntiles,
+                                                  const int* __restrict__ work, const float* __restrict__ rscale, int W,
+                                                  int accumulate, double* __restrict__ G)
+{
+    const int wave = blockIdx.y, lane = threadIdx.x & 63;
+    const int row0 = work[3 * blockIdx.x] * G2_T + (wave >> 1) * 64 + 4 * (lane >> 5);
+    const int col0 = work[3 * blockIdx.x + 1] * G2_T + (wave & 1) * 128 + (lane & 31);
+    const float* p = part + (int64_t)blockIdx.x * (G2_T * G2_T) + wave * 8192 + lane;
+    const int64_t step = (int64_t)ntiles * (G2_T * G2_T);
+    for (int e0 = threadIdx.x >> 6; e0 < 128; e0 += 16) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int k = 0; k < runs; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] += (double)p[k * step + (e0 + 4 * q) * 64];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = e0 + 4 * q, r = e & 15, i = row0 + 32 * (e >> 6) + 8 * (r >> 2) + (r & 3), j = col0 + 32 * ((e >> 4) & 3);
+            if (i >= W || j >= W) continue;
+            double* g = G + (int64_t)i * W + j;
+            *g = (accumulate ? *g : 0.0) + v[q] * ((double)rscale[j] * (double)rscale[i]);
+        }
+    }
 }
 
 }  // namespace
@@ -439,7 +472,7 @@ int launch_gram_mfma(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xl
             // blocked tile (ld unused); element offsets inside one operand array are 32-bit
             // (W * tile rows < 2^31 is checked by the caller)
             hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramSamples>, dim3(grid), dim3(512), 0, s, (const uint16_t*)Xhi, Xlo, W, (int)n,
-                               work, nwork, (int)kchunk, G, gstride, accumulate ? 1 : 0, (const float*)nullptr, CellGram{});
+                               work, nwork, (int)kchunk, G, gstride, accumulate ? 1 : 0, 0, CellGram{});
         }
     else
         {
@@ -450,28 +483,31 @@ int launch_gram_mfma(bem_ctx* ctx, int gram, const void* Xhi, const uint16_t* Xl
     return check_launch(ctx, "gram_mfma");
 }
 
-// G = Y Y^T (G += with accumulate) of float16 pairs of scaled rows over n columns (blocked tile, work entries with parts)
+// G = Y Y^T (G += with accumulate) of float16 pairs of scaled rows over n columns (blocked tile) in runs of kchunk;
+// work: runs ntiles entries, run-major, part: their sums [runs ntiles][256 * 256]
 int launch_gram_half(bem_ctx* ctx, const uint16_t* Yh, const uint16_t* Yl, int W, int64_t n, const float* rscale,
-                     const int* work, int nwork, int64_t kchunk, double* G, int64_t gstride, bool accumulate,
+                     const int* work, int runs, int ntiles, int64_t kchunk, float* part, double* G, bool accumulate,
                      hipStream_t s)
 {
     ProfScope ps_(ctx, PT_GRAM_MFMA, s);
-    hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramHalf>, dim3(8 * ((nwork + 7) / 8)), dim3(512), 0, s, Yh, Yl, W, (int)n, work,
-                       nwork, (int)kchunk, G, gstride, accumulate ? 1 : 0, rscale, CellGram{});
+    hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramHalf>, dim3(8 * runs * ((ntiles + 7) / 8)), dim3(512), 0, s, Yh, Yl, W, (int)n,
+                       work, runs * ntiles, (int)kchunk, (double*)part, (int64_t)0, 0, ntiles, CellGram{});
+    hipLaunchKernelGGL(k_sum_half, dim3(ntiles, 8), dim3(256), 0, s, (const float*)part, runs, ntiles, work, rscale, W,
+                       accumulate ? 1 : 0, G);
     return check_launch(ctx, "gram_half");
 }
 
-// G += E E^T - Z Z^T of the cells' near rows, into the partial Grams.  Z: the terms h, m, l of Z, zeros, and
+// G += E E^T - Z Z^T of the cells' near rows.  Z: the terms h, m, l of Z, zeros, and
 // those of -Z, each zstep elements after the one before
 int launch_gram_cells(bem_ctx* ctx, const uint16_t* Eh, const uint16_t* El, const uint16_t* Z, int64_t zstep,
                       const CellInfo* ci, int nc, const int* hl, const int* el, int H, int M, const Layout& L, int64_t W,
-                      const int* work, int nwork, double* G, int64_t gstride, hipStream_t s)
+                      const int* work, int nwork, double* G, hipStream_t s)
 {
     if (nwork <= 0) return BEM_OK;
     ProfScope ps_(ctx, PT_GRAM_MFMA, s);
-    const CellGram cg{{Z, Z + zstep, Z + 2 * zstep, Z + 3 * zstep, Z + 4 * zstep}, zstep, ci, hl, el, nc, H, M, kGramParts, L, W};
+    const CellGram cg{{Z, Z + zstep, Z + 2 * zstep, Z + 3 * zstep, Z + 4 * zstep}, zstep, ci, hl, el, nc, H, M, L, W};
     hipLaunchKernelGGL(k_gram_bf16x3_lds<kGramCells>, dim3(8 * ((nwork + 7) / 8)), dim3(512), 0, s, Eh, El, 0, 0, work, nwork,
-                       0, G, gstride, 1, (const float*)nullptr, cg);
+                       0, G, (int64_t)0, 1, 0, cg);
     return check_launch(ctx, "gram_cells");
 }
 

@@ -867,6 +867,21 @@ static int f64_parts(int ntiles, int64_t W)
     return (int)best;
 }
 
+// Sample parts of the split-BF16 Gram, one 256 x 256 tile a CU: at least 3 (float32 runs no longer than a third of a
+// sample tile), and for few tiles those that fill up to three rounds of 256 best (60 straight handles, 15,000 samples,
+// 36 tiles: 3 parts 305 us, 7 parts 95 us and 40 us more to sum them).
+static int bf16_parts(int ntiles, int64_t W)
+{
+    const int64_t most = std::max<int64_t>(3, std::min<int64_t>(16, ((int64_t)2 << 30) / (W * W * 8)));
+    const auto fill = [&](int64_t p) { return (double)(ntiles * p) / (double)((ntiles * p + 255) / 256 * 256); };
+    int64_t best = 3;
+    for (int rounds = 1; rounds <= 3 && ntiles > 0; ++rounds) {
+        const int64_t p = std::min<int64_t>(most, 256 * rounds / ntiles);
+        if (p > 3 && fill(p) > fill(best) + 0.02) best = p;
+    }
+    return (int)best;
+}
+
 namespace {
 // G[0] += G[1] + ... + G[parts - 1] (fixed order) over the ts x ts output tile of work entry
 // blockIdx.x, rows split over gridDim.y blocks (blockDim.x = ts, a thread per column)
@@ -891,10 +906,10 @@ __global__ void __launch_bounds__(256) k_sum_parts(double* __restrict__ G, int p
 
 // The work list lives on the device (tilew); it is uploaded when its configuration changes, the only host
 // synchronisation of bem_jtj apart from workspace growth.
-static int upload_tiles(bem_ctx* ctx, const std::vector<int>& tiles, int64_t W, int H, int gram, hipStream_t s)
+static int upload_tiles(bem_ctx* ctx, const std::vector<int>& tiles, int64_t W, int H, int gram, int parts, hipStream_t s)
 {
     int rc;
-    const int64_t key[4] = {W, H, ctx->model, gram};
+    const int64_t key[4] = {W, H, ctx->model, gram + 8 * (int64_t)parts};
     if (std::memcmp(key, ctx->tiles_key, sizeof(key)) == 0) return BEM_OK;
     ctx->tiles_key[0] = -1;
     if ((rc = ensure(ctx, ctx->tilew, tiles.size() * sizeof(int), s))) return rc;
@@ -1001,12 +1016,11 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
             if (T2 > T) T = T2;
         }
     }
-    // split-BF16 Gram: the sample tile is split into 3 parts with partial Grams of their own,
-    // so that a launch has 3x the blocks (fewer idle CUs in its last round) and stays
+    // the sample tile is split into parts with partial Grams of their own, so that a launch fills the CUs and stays
     // deterministic (no atomics)
     const int ts = gram == BEM_GRAM_FP64_VALU ? 64 : (gram == BEM_GRAM_BF16X3_MFMA ? 256 : 128);
     const std::vector<int> out_tiles = gram_tiles(L, (int)W, ts);
-    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? kGramParts
+    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? bf16_parts((int)out_tiles.size() / 2, W)
                       : gram == BEM_GRAM_FP64 ? f64_parts((int)out_tiles.size() / 2, W) : 1;
     const int64_t kchunk = ((T + parts - 1) / parts + 31) / 32 * 32;
     const bool overlap = shares && N > T;
@@ -1022,7 +1036,7 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     const bool valu = gram == BEM_GRAM_FP64_VALU;
     const std::vector<int> tiles = valu ? out_tiles : gram_work(out_tiles, parts);
     const int ntiles = (int)tiles.size() / (valu ? 2 : 3);
-    if ((rc = upload_tiles(ctx, tiles, W, H, gram, s))) return rc;
+    if ((rc = upload_tiles(ctx, tiles, W, H, gram, parts, s))) return rc;
     const int* dtiles = (const int*)ctx->tilew.ptr;
     // tmp5: the vertex table, then the near-pair corrections and run table of one sample tile
     const int S = ctx->opts.segs_per_handle;
@@ -1109,11 +1123,13 @@ int launch_vertex_table(bem_ctx* ctx, float* vtab, hipStream_t s)
     return check_launch(ctx, "vertex table");
 }
 
-int gram_work_bf16(bem_ctx* ctx, const Layout& L, int64_t W, const int** work, int* nwork, hipStream_t s)
+int gram_tiles_half(const Layout& L, int64_t W) { return (int)gram_tiles(L, (int)W, 256).size() / 2; }
+
+int gram_work_half(bem_ctx* ctx, const Layout& L, int64_t W, int parts, const int** work, int* ntiles, hipStream_t s)
 {
-    const std::vector<int> w = gram_work(gram_tiles(L, (int)W, 256), kGramParts);
-    *nwork = (int)w.size() / 3;
-    const int rc = upload_tiles(ctx, w, W, L.H, BEM_GRAM_BF16X3_MFMA, s);
+    const std::vector<int> w = gram_work(gram_tiles(L, (int)W, 256), parts);
+    *ntiles = (int)w.size() / (3 * parts);
+    const int rc = upload_tiles(ctx, w, W, L.H, BEM_GRAM_BF16X3_MFMA, parts, s);
     *work = (const int*)ctx->tilew.ptr;
     return rc;
 }

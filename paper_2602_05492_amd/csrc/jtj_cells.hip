@@ -21,9 +21,10 @@
 // Rounding.  The split-bfloat16 products of E average over the samples as those of the Gram over all
 // samples do; the fewer columns Y and Z carry 22 and 24 bits instead of 16.  Accumulation in float32 within a
 // run and in float64 beyond is the same.  Pairs by quadrature (seg_math.hpp), so near factors of at least 1.
-// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 8.8 ms, far features
-// 7.7 ms, near Gram 6.8 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
+// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 9.8 ms, far features
+// 7.7 ms, near Gram 3.0 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
 // step against float64: 7.5e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
+#include <algorithm>
 #include <cmath>
 #include <numeric>
 
@@ -679,10 +680,7 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
         elems += nb * 32 * q.rows;
         near += 0.5 * t * (t + 1) * (q.n + 64.0 + 200.0);     // an entry's start and sums cost about 200 samples
     }
-    const int *gwork;
-    int ngwork;
-    if ((rc = gram_work_bf16(ctx, L, W, &gwork, &ngwork, s))) return rc;
-    const double tiles = (double)ngwork / kGramParts;
+    const double tiles = gram_tiles_half(L, W);
     // near and node Gram, and the pairs' share, against the Gram over all samples; the rest (basis, projection,
     // factors) costs up to two fifths of that Gram at the smallest grouped sizes, so cells serve below 0.6
     if (near + tiles * 64.0 * nc > 0.6 * tiles * (double)N || elems > ((int64_t)1 << 30) || rows >= (1 << 24)) return BEM_OK;
@@ -703,7 +701,7 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     // the samples are taken one by one
     auto grow = [&](DevBuf& q, size_t n) { return ensure(ctx, q, n <= q.bytes ? n : n + n / 4, s); };
     auto tiles_instead = [&](int e) {
-        for (DevBuf* q : {&ctx->nezw, &ctx->neew, &ctx->tmp0}) {
+        for (DevBuf* q : {&ctx->nezw, &ctx->neew, &ctx->tmp0, &ctx->tmp2}) {
             if (hipStreamSynchronize(s) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream sync");
             if (q->ptr) hipFree(q->ptr);
             q->ptr = nullptr;
@@ -728,8 +726,21 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     if ((rc = ensure(ctx, ctx->tmp0, 4 * yt, s))) return tiles_instead(rc);
     float* Yf = (float*)ctx->tmp0.ptr;
     uint16_t *Yh = (uint16_t*)((char*)ctx->tmp0.ptr + 2 * yt), *Yl = (uint16_t*)((char*)ctx->tmp0.ptr + 3 * yt);
-    if ((rc = ensure(ctx, ctx->tmp1, (size_t)kGramParts * W * W * sizeof(double), s))) return rc;
+    if ((rc = ensure(ctx, ctx->tmp1, (size_t)W * W * sizeof(double), s))) return rc;
     double* G = (double*)ctx->tmp1.ptr;
+    // Columns summed in float32 before they are added in float64: rounding errors of k-column sums add up to
+    // sqrt(k n) / n of the whole, so that n columns in the place of N samples summed in runs of 10,923
+    // (a third of their tile) take 10,923 sqrt(n / N).  Up to 4 GiB of runs at a time.
+    const int64_t n = (int64_t)64 * nc;
+    const int64_t kchunk = (int64_t)(10923.0 * std::sqrt((double)n / (double)N) / 64.0 + 1.0) * 64;
+    const int64_t run_bytes = (int64_t)tiles * (256 * 256 * sizeof(float));
+    const int64_t all_runs = (n + kchunk - 1) / kchunk, most_runs = std::max<int64_t>(1, ((int64_t)4 << 30) / run_bytes);
+    const int runs = (int)std::min(all_runs, most_runs);
+    if ((rc = ensure(ctx, ctx->tmp2, (size_t)(runs * run_bytes), s))) return tiles_instead(rc);
+    float* part = (float*)ctx->tmp2.ptr;
+    const int* gwork;
+    int ntiles;
+    if ((rc = gram_work_half(ctx, L, W, runs, &gwork, &ntiles, s))) return rc;
     // info and work stay in the context until the next step, past the copies' end
     if (hipMemcpyAsync(ci, info.data(), info.size() * sizeof(CellInfo), hipMemcpyHostToDevice, s) != hipSuccess ||
         (!work.empty() &&
@@ -772,20 +783,16 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
                            (const uint32_t*)rmax, L, W, (int64_t)2 * nc, Yh, Yl, rscale);
     }
     if ((rc = check_launch(ctx, "cell features"))) return rc;
-    // Columns summed in float32 before they are added in float64: rounding errors of k-column sums add up to
-    // sqrt(k n) / n of the whole, so that n columns in the place of N samples summed in runs of 10,923
-    // (a third of their tile) take 10,923 sqrt(n / N)
-    const int64_t n = (int64_t)64 * nc;
-    const int64_t kchunk = (int64_t)(10923.0 * std::sqrt((double)n / (double)N) / 64.0 + 1.0) * 64;
-    for (int64_t k0 = 0; k0 < n; k0 += kGramParts * kchunk) {
-        const int64_t m = n - k0 < kGramParts * kchunk ? n - k0 : kGramParts * kchunk;
-        if ((rc = launch_gram_half(ctx, Yh + k0 * W, Yl + k0 * W, (int)W, m, rscale, gwork, ngwork, kchunk, G, W * W, k0 > 0,
+    for (int64_t r0 = 0; r0 < all_runs; r0 += runs) {
+        const int rs = (int)std::min<int64_t>(runs, all_runs - r0);
+        const int64_t k0 = r0 * kchunk, m = std::min(n - k0, rs * kchunk);
+        if ((rc = launch_gram_half(ctx, Yh + k0 * W, Yl + k0 * W, (int)W, m, rscale, gwork, rs, ntiles, kchunk, part, G, r0 > 0,
                                    s)))
             return rc;
     }
-    if ((rc = launch_gram_cells(ctx, Eh, El, Zt, zstep, ci, nc, hl, el, H, M, L, W, dwork, nnear, G, W * W, s))) return rc;
+    if ((rc = launch_gram_cells(ctx, Eh, El, Zt, zstep, ci, nc, hl, el, H, M, L, W, dwork, nnear, G, s))) return rc;
     const double sc = 1.0 / (norm > 0.0 ? norm : (double)N);
-    if ((rc = contract_gram(ctx, H, L, W, G, kGramParts, 256, gwork, ngwork, Z, sc, JtJ, s))) return rc;
+    if ((rc = contract_gram(ctx, H, L, W, G, 1, 256, gwork, ntiles, Z, sc, JtJ, s))) return rc;
     *done = true;
     return BEM_OK;
 }

@@ -76,9 +76,9 @@ Layout layout_of(const bem_ctx* ctx, int H);
 // Z = A+ dF/dtheta, transposed: [handle rows][M padded by zeros to kGemmPad] -> ctx->tmp4
 int boundary_derivatives(bem_ctx* ctx, int H, hipStream_t s, double** Zout);
 int launch_vertex_table(bem_ctx* ctx, float* vtab, hipStream_t s);
-// the split-BF16 Gram's work list (256 x 256 tiles, kGramParts sample parts) on the device
-constexpr int kGramParts = 3;
-int gram_work_bf16(bem_ctx* ctx, const Layout& L, int64_t W, const int** work, int* nwork, hipStream_t s);
+// work list of 256 x 256 tiles in parts (or runs of columns), part-major, on the device
+int gram_work_half(bem_ctx* ctx, const Layout& L, int64_t W, int parts, const int** work, int* ntiles, hipStream_t s);
+int gram_tiles_half(const Layout& L, int64_t W);            // tiles of that list
 // J^T J of the partial Grams G [parts][W][W]
 int contract_gram(bem_ctx* ctx, int H, const Layout& L, int64_t W, double* G, int parts, int ts, const int* work, int nwork,
                   const double* Z, double sc, double* JtJ, hipStream_t s);
@@ -88,9 +88,10 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
                   bool* done, hipStream_t s);
 // gram_mfma.hip
 int launch_gram_half(bem_ctx* ctx, const uint16_t* Yh, const uint16_t* Yl, int W, int64_t n, const float* rscale,
-                     const int* work, int nwork, int64_t kchunk, double* G, int64_t gstride, bool accumulate, hipStream_t s);
+                     const int* work, int runs, int ntiles, int64_t kchunk, float* part, double* G, bool accumulate,
+                     hipStream_t s);
 int launch_gram_cells(bem_ctx* ctx, const uint16_t* Eh, const uint16_t* El, const uint16_t* Z, int64_t zstep,
                       const CellInfo* ci, int nc, const int* hl, const int* el, int H, int M, const Layout& L, int64_t W,
-                      const int* work, int nwork, double* G, int64_t gstride, hipStream_t s);
+                      const int* work, int nwork, double* G, hipStream_t s);
 
 }  // namespace bem
