@@ -2,7 +2,7 @@
 #pragma once
 
 #include "common.hpp"
-#include "sweep_common.hpp"
+#include "cells.hpp"
 
 namespace bem {
 
@@ -35,8 +35,8 @@ __device__ inline void near_segment_values(const double* __restrict__ s, double 
 }
 
 // vjp_mixed.hip
-int adj_mixed_rows(bem_ctx* ctx, int K, int64_t N, int* seg_rows, int* el_rows);
-int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K, int g, int seg_rows, int el_rows,
+Grouping adj_mixed_rows(bem_ctx* ctx, int K, int64_t N, int* seg_rows, int* el_rows);
+int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K, Grouping g, int seg_rows, int el_rows,
               double* part, double* epart, hipStream_t s);
 
 }  // namespace bem

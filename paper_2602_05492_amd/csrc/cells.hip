@@ -1,6 +1,9 @@
 // cells.hip - the cell plan of the mixed sweeps: samples grouped by grid cell (a stable counting
 // sort without readback) and, per cell, which segments and outer elements are too near for its
 // interpolated far field.
+#include <algorithm>
+#include <cmath>
+
 #include "cells.hpp"
 
 #include <cmath>
@@ -126,69 +129,141 @@ __global__ void __launch_bounds__(256) k_cell_scatter(const double* __restrict__
     }
 }
 
-// Near bits: a lane a segment (or outer element), two words a wavefront.  A segment is far from the cell
-// when its extent stays kFarCells cell widths away from the cell's square in x or in y and no sample of
-// the square can have both of its end points within the near radius (the pairs the mixed sweeps
-// evaluate in float64; margins far above the float32 rounding of that test).  NaN geometry is near
-// everywhere.
-__global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, const float* __restrict__ seg32, int K,
+// Near and far bits: a lane a segment (or outer element), two words a wavefront at a time, kBitWords a wavefront;
+// blockIdx.y a row.  A segment is far from a cell when its extent stays kFarCells cell widths away from the cell's square
+// in x or in y and no sample of the square can have both of its end points within the near radius (the pairs the mixed
+// sweeps evaluate in float64; margins far above the float32 rounding of that test), or when it is far from a cell above
+// it.  NaN geometry is near everywhere.  Far bit: far here, near the parent (top level: far), and the cell holds samples.
+constexpr int kBitWords = 16;
+__global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, CellLevels lv, const int* __restrict__ off,
+                                                   const float* __restrict__ seg32, int K,
                                                    const float* __restrict__ el32, int M, float near2, int seg_words,
-                                                   int words, uint32_t* __restrict__ bits)
+                                                   int words, uint32_t* __restrict__ bits, uint32_t* __restrict__ fbits)
 {
-    const int c = blockIdx.y, lane = threadIdx.x & 63;
-    const int w = blockIdx.x * 8 + (threadIdx.x >> 5);
-    const bool seg = w < seg_words;
-    const int i = seg ? w * 32 + (lane & 31) : (w - seg_words) * 32 + (lane & 31);
-    bool near = false;
-    if (w < words && i < (seg ? K : M)) {
-        float ax, ay, bx, by, L2;
-        if (seg) {
-            const float* s = seg32 + (size_t)i * kSegStride;
-            ax = s[0]; ay = s[1]; bx = s[2]; by = s[3]; L2 = s[6];
-        } else {
-            const float* e = el32 + (size_t)i * kElemStride;
-            ax = e[0]; ay = e[1]; bx = e[0] + e[2]; by = e[1] + e[3]; L2 = e[2] * e[2] + e[3] * e[3];
-        }
-        double cx, cy;
-        cell_corner(g, c, cx, cy);
-        const float m = (float)(kFarCells * g.h);
-        const float x0 = (float)cx, y0 = (float)cy, x1 = (float)(cx + g.h), y1 = (float)(cy + g.h);
-        auto dist2 = [&](float px, float py) {
-            const float dx = fmaxf(0.0f, fmaxf(x0 - px, px - x1)), dy = fmaxf(0.0f, fmaxf(y0 - py, py - y1));
-            return dx * dx + dy * dy;
-        };
-        const bool clear = fminf(ax, bx) >= x1 + m || fmaxf(ax, bx) <= x0 - m || fminf(ay, by) >= y1 + m ||
-                           fmaxf(ay, by) <= y0 - m;
-        const float r2 = 1.01f * near2 * L2 + 1e-9f;
-        near = c == g.nc || !(clear && !(dist2(ax, ay) < r2 && dist2(bx, by) < r2));
+    const int row = blockIdx.y, lane = threadIdx.x & 63;
+    int l = 0, cx = 0, cy = 0;
+    const bool stray = row == g.nc;
+    if (!stray) level_cell(lv, row, l, cx, cy);
+    const bool used = !stray && level_used(lv, off, l, cx, cy);
+    // squares of the cell (0) and the cells above it
+    float x0[kMaxLevels], y0[kMaxLevels], x1[kMaxLevels], y1[kMaxLevels], d[kMaxLevels];
+#pragma unroll
+    for (int m = 0; m < kMaxLevels; ++m) {
+        const double h = g.h * (double)(1 << (l + m));
+        const double X0 = g.x0 + (double)(cx >> m) * h, Y0 = g.y0 + (double)(cy >> m) * h;
+        x0[m] = (float)X0; y0[m] = (float)Y0; x1[m] = (float)(X0 + h); y1[m] = (float)(Y0 + h);
+        d[m] = (float)(kFarCells * h);
     }
-    const uint64_t m = __ballot(near);
-    if ((lane & 31) == 0 && w < words) bits[(size_t)c * words + w] = (uint32_t)(lane ? m >> 32 : m);
+    const int first = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kBitWords;
+    for (int w0 = first; w0 < first + kBitWords && w0 < words; w0 += 2) {
+        const int w = w0 + (lane >> 5);
+        const bool seg = w < seg_words;
+        const int i = (seg ? w : w - seg_words) * 32 + (lane & 31);
+        bool near = false, far = false;
+        if (w < words && i < (seg ? K : M)) {
+            float ax, ay, bx, by, L2;
+            if (seg) {
+                const float* s = seg32 + (size_t)i * kSegStride;
+                ax = s[0]; ay = s[1]; bx = s[2]; by = s[3]; L2 = s[6];
+            } else {
+                const float* e = el32 + (size_t)i * kElemStride;
+                ax = e[0]; ay = e[1]; bx = e[0] + e[2]; by = e[1] + e[3]; L2 = e[2] * e[2] + e[3] * e[3];
+            }
+            const float r2 = 1.01f * near2 * L2 + 1e-9f;
+            const float lox = fminf(ax, bx), hix = fmaxf(ax, bx), loy = fminf(ay, by), hiy = fmaxf(ay, by);
+            near = true;
+#pragma unroll
+            for (int m = kMaxLevels - 1; m >= 0; --m) {
+                if (stray || l + m >= lv.n) continue;
+                auto dist2 = [&](float px, float py) {
+                    const float dx = fmaxf(0.0f, fmaxf(x0[m] - px, px - x1[m]));
+                    const float dy = fmaxf(0.0f, fmaxf(y0[m] - py, py - y1[m]));
+                    return dx * dx + dy * dy;
+                };
+                const bool clear = (lox >= x1[m] + d[m]) | (hix <= x0[m] - d[m]) | (loy >= y1[m] + d[m]) | (hiy <= y0[m] - d[m]);
+                const bool near_m = !(clear && !(dist2(ax, ay) < r2 && dist2(bx, by) < r2));
+                if (m == 0) far = near && !near_m;           // near every cell above
+                near = near && near_m;
+            }
+        }
+        const uint64_t nm = __ballot(near), fm = __ballot(far && used);
+        if ((lane & 31) == 0 && w < words) {
+            bits[(size_t)row * words + w] = (uint32_t)(lane ? nm >> 32 : nm);
+            fbits[(size_t)row * words + w] = (uint32_t)(lane ? fm >> 32 : fm);
+        }
+    }
+}
+
+// cells of the longer side's g a side, the shorter one in proportion
+double aspect_of(const bem_ctx* ctx, bool* ok)
+{
+    const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
+    *ok = bw > 0.0 && bh > 0.0;
+    return bw > bh ? bh / bw : bw / bh;
 }
 
 }  // namespace
 
-// Cells a side.  Direct sums evaluate N (K + M) pairs; a grid of n cells evaluates q^2 n (K + M) at its
-// nodes and about (2 kFarCells + 1)^2 / n of the direct ones sample by sample, in the least time at
-// n = (5 / q) sqrt(ratio N).
-int cells_for(const bem_ctx* ctx, int64_t N, int K, int q, double ratio, double worth)
+// Direct sums evaluate N (K + M) pairs.  With n_l cells at level l, each near some (2 kFarCells + 1)^2 of its own area,
+// the nodes take q^2 n_l pairs of every segment near the parent but not near the cell (top level: not near the
+// cell), and the samples the near ones of the finest level: the least of that over the cells a side and the levels.
+// Where a wavefront's lanes are 64 segments in `places` places, it takes a row for all of them if any needs it.  A row's
+// own work (bits, node sums, coefficients) takes as long as `row` pairs.  Measured, one level at its best against the
+// choice here: 4,096 segments and 1,048,576 samples 1.08 -> 0.69 ms; 500 and 262,144 215 -> 180 us; 512 in float64 (16
+// nodes a side) and 262,144 645 -> 500 us; adjoint of 8,192 and 4,194,304 13.1 -> 10.4 ms.
+Grouping cells_for(const bem_ctx* ctx, int64_t N, int K, int q, double ratio, double worth, double low,
+                   double row, double places)
 {
-    const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
-    if (!(bw > 0.0) || !(bh > 0.0) || N < 8192 || N > ((int64_t)1 << 30)) return 0;
-    const double reach = 2.0 * kFarCells + 1.0;
-    // cells are square: the longer side takes g of them
-    const double aspect = bw > bh ? bh / bw : bw / bh;
-    double g = std::sqrt(reach / q * std::sqrt(ratio * (double)N) / aspect);
-    if (g > kMaxGrid) g = kMaxGrid;
-    const int n = (int)g;
-    const double cells = (double)n * std::ceil(n * aspect);
-    const double share = q * q * cells / (double)N + reach * reach / cells;
-    return n >= 2 && (1.0 - share) * (double)N * ((double)K + 0.4 * ctx->M) > worth ? n : 0;
+    Grouping best;
+    bool ok;
+    const double aspect = aspect_of(ctx, &ok);
+    if (!ok || N < 8192 || N > ((int64_t)1 << 30)) return best;
+    const double reach = (2.0 * kFarCells + 1.0) * (2.0 * kFarCells + 1.0);
+    double least = 0.0, share = 1.0;
+    for (int levels = 1; levels <= kMaxLevels; ++levels)
+        for (int g = levels > 1 ? 1 << (levels - 1) : 2; g <= kMaxGrid; g += 1 << (levels - 1)) {     // (no ragged parents)
+            int nx = g, ny = (int)std::ceil(g * aspect);
+            double nodes = 0.0, rows = 0.0, near0 = 1.0, n = (double)nx * ny, near = std::min(1.0, reach / n);
+            near0 = near;
+            for (int l = 0; l < levels; ++l) {
+                const double above = (double)((nx + 1) / 2) * ((ny + 1) / 2);
+                const double up = l + 1 < levels ? std::min(1.0, reach / above) : 1.0;
+                nodes += (l + 1 < levels ? low : 1.0) * q * q * n * std::min(1.0, places * (up - near));
+                rows += n;
+                nx = (nx + 1) / 2;
+                ny = (ny + 1) / 2;
+                n = above;
+                near = up;
+            }
+            const double cost = nodes + ratio * (double)N * near0 + rows * row / ((double)K + 0.4 * ctx->M);
+            if (best.g == 0 || cost < least) {
+                best.g = g;
+                best.levels = levels;
+                least = cost;
+                share = nodes / (double)N + near0;
+            }
+        }
+    if (!((1.0 - share) * (double)N * ((double)K + 0.4 * ctx->M) > worth)) best.g = 0;
+    return best;
 }
 
-int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s)
+// q^2 n + (2 kFarCells + 1)^2 ratio N / n is least at n = ((2 kFarCells + 1) / q) sqrt(ratio N).
+int cells_one_level(const bem_ctx* ctx, int64_t N, int q, double ratio)
+{
+    bool ok;
+    const double aspect = aspect_of(ctx, &ok);
+    if (!ok || N < 8192 || N > ((int64_t)1 << 30)) return 0;
+    const double g = std::sqrt((2.0 * kFarCells + 1.0) / q * std::sqrt(ratio * (double)N) / aspect);
+    const int n = (int)(g > kMaxGrid ? kMaxGrid : g);
+    const double cells = (double)n * std::ceil(n * aspect);
+    const double share = q * q * cells / (double)N + (2.0 * kFarCells + 1.0) * (2.0 * kFarCells + 1.0) / cells;
+    return n >= 2 && share < 1.0 ? n : 0;
+}
+
+int cell_plan(bem_ctx* ctx, const double* x, int64_t N, Grouping choice, CellPlan* p, hipStream_t s)
 {
     int rc;
+    const int g = choice.g;
     const double bw = ctx->bbox[2] - ctx->bbox[0], bh = ctx->bbox[3] - ctx->bbox[1];
     CellGrid& G = p->grid;
     G.x0 = ctx->bbox[0];
@@ -203,6 +278,15 @@ int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipS
     G.ny = cells(bh);
     G.nc = G.nx * G.ny;
     const int nlab = G.nc + 1;
+    CellLevels& lv = p->lv;
+    lv.n = choice.levels;
+    for (int l = 0, next = 0; l < lv.n; ++l) {
+        lv.nx[l] = l ? (lv.nx[l - 1] + 1) / 2 : G.nx;
+        lv.ny[l] = l ? (lv.ny[l - 1] + 1) / 2 : G.ny;
+        lv.base[l] = next;
+        next += lv.nx[l] * lv.ny[l] + (l == 0);
+        lv.rows = next;
+    }
     int chunk = 256;
     while (chunk < 4096 && N / chunk > 512) chunk *= 2;
     const int nb = blocks_for(N, chunk);
@@ -244,12 +328,14 @@ int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, bool mixed, hipStream_t s
     const double nf = mixed ? near_radius(ctx->opts.near_factor) : 0.0;
     p->seg_words = (K + 31) / 32;
     p->words = p->seg_words + (M + 31) / 32;
-    const int64_t n = (int64_t)(p->grid.nc + 1) * p->words;
-    if ((rc = ensure(ctx, ctx->cellb, (size_t)n * sizeof(uint32_t), s))) return rc;
-    hipLaunchKernelGGL(k_cell_bits, dim3(blocks_for(p->words, 8), p->grid.nc + 1), dim3(256), 0, s, p->grid, (const float*)ctx->seg32.ptr, K,
-                       (const float*)ctx->elem32.ptr, M, (float)(nf * nf), p->seg_words, p->words,
-                       (uint32_t*)ctx->cellb.ptr);
-    p->bits = (const uint32_t*)ctx->cellb.ptr;
+    const int64_t n = (int64_t)p->lv.rows * p->words;
+    if ((rc = ensure(ctx, ctx->cellb, (size_t)n * 2 * sizeof(uint32_t), s))) return rc;
+    uint32_t* bits = (uint32_t*)ctx->cellb.ptr;
+    hipLaunchKernelGGL(k_cell_bits, dim3(blocks_for(p->words, 4 * kBitWords), p->lv.rows), dim3(256), 0, s, p->grid, p->lv, p->off,
+                       (const float*)ctx->seg32.ptr, K, (const float*)ctx->elem32.ptr, M, (float)(nf * nf), p->seg_words,
+                       p->words, bits, bits + n);
+    p->bits = bits;
+    p->far = bits + n;
     return check_launch(ctx, "cell bits");
 }
 

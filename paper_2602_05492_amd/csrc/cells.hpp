@@ -11,6 +11,12 @@
 // segments of 1/100): below the float32 rounding of a pair.
 // The other pairs of the cell, and those the mixed precision evaluates in float64, are evaluated
 // sample by sample.
+//
+// Levels.  2 x 2 cells form a cell of the next level, up to kMaxLevels of them.  A segment far from a cell is
+// summed at the nodes of the largest cell above it that it is far from (the top level sums every far segment, the
+// levels below only those near the parent, of some 75 cell areas), and node sums are carried down exactly: a
+// polynomial's values at the children's nodes.  Far from the parent implies far from the child (the bits say so by
+// construction), so that every pair is counted once.
 #pragma once
 
 #include "common.hpp"
@@ -34,6 +40,33 @@ struct CellGrid {
     double x0, y0, h, inv_h;
     int nx, ny, nc;
 };
+
+// Levels of the grid: rows of the bit tables and node sums, level 0 (the cells, then the stray label nc) first; level
+// l's cells from base[l] on.
+constexpr int kMaxLevels = 3;
+struct CellLevels {
+    int n = 1, rows = 0;
+    int nx[kMaxLevels] = {}, ny[kMaxLevels] = {}, base[kMaxLevels] = {};
+    __host__ __device__ int top_cells() const { return nx[n - 1] * ny[n - 1]; }
+    __host__ __device__ int low_rows() const { return n > 1 ? base[n - 1] : 0; }         // rows below the top level
+};
+__device__ inline void level_cell(const CellLevels& lv, int row, int& l, int& cx, int& cy)
+{
+    l = 0;
+    while (l + 1 < lv.n && row >= lv.base[l + 1]) ++l;
+    cx = (row - lv.base[l]) % lv.nx[l];
+    cy = (row - lv.base[l]) / lv.nx[l];
+}
+__device__ inline int level_row(const CellLevels& lv, int l, int cx, int cy) { return lv.base[l] + cy * lv.nx[l] + cx; }
+// whether a cell of level l holds samples (off: first sample of every level-0 cell)
+__device__ inline bool level_used(const CellLevels& lv, const int* __restrict__ off, int l, int cx, int cy)
+{
+    const int x0 = cx << l, x1 = (cx + 1) << l < lv.nx[0] ? (cx + 1) << l : lv.nx[0];
+    const int y1 = (cy + 1) << l < lv.ny[0] ? (cy + 1) << l : lv.ny[0];
+    for (int y = cy << l; y < y1; ++y)
+        if (off[y * lv.nx[0] + x1] > off[y * lv.nx[0] + x0]) return true;
+    return false;
+}
 
 __device__ inline int cell_of(const CellGrid& g, double X, double Y)
 {
@@ -70,6 +103,13 @@ __device__ inline void cell_node(const CellGrid& g, int c, int node, double& X, 
     X += 0.5 * g.h * (1.0 + cheb_node<Q>(node & (Q - 1)));
     Y += 0.5 * g.h * (1.0 + cheb_node<Q>(node / Q));
 }
+template <int Q>
+__device__ inline void level_node(const CellGrid& g, int l, int cx, int cy, int node, double& X, double& Y)
+{
+    const double h = g.h * (double)(1 << l);
+    X = g.x0 + (double)cx * h + 0.5 * h * (1.0 + cheb_node<Q>(node & (Q - 1)));
+    Y = g.y0 + (double)cy * h + 0.5 * h * (1.0 + cheb_node<Q>(node / Q));
+}
 // T_0 .. T_{Q-1} at t
 template <class T, int Q>
 __device__ inline void cheb_values(T t, T (&v)[Q])
@@ -80,12 +120,33 @@ __device__ inline void cheb_values(T t, T (&v)[Q])
     for (int k = 2; k < Q; ++k) v[k] = T(2) * t * v[k - 1] - v[k - 2];
 }
 
+// Values of a polynomial of degree Q - 1 a side, given at a cell's Q x Q nodes, at those of its child on side s (0 lower,
+// 1 upper) of one axis: I[s][i][n] = l_n((t_i + 2 s - 1) / 2).  Threads t of n; cs[k] = cos(k pi / (2 Q)), k < 4 Q.
+template <int Q>
+__device__ inline void child_matrix(int t, int n, const double* cs, double (*I)[Q][Q])
+{
+    for (int e = t; e < 2 * Q * Q; e += n) {
+        const int s = e / (Q * Q), i = e / Q % Q, k = e % Q;
+        double T[Q];
+        cheb_values<double, Q>(0.5 * (cheb_node<Q>(i) + 2.0 * s - 1.0), T);
+        double v = 1.0 / Q;
+        for (int a = 1; a < Q; ++a) v += 2.0 / Q * T[a] * cs[(a * (2 * k + 1)) & (4 * Q - 1)];
+        I[s][i][k] = v;
+    }
+}
+
+// Cells a side of the finest level, levels; g = 0: direct sums.
+struct Grouping {
+    int g = 0, levels = 1;
+};
+
 // The samples of a call in cell order, on the device (workspace of the context, valid until the
 // next plan): sorted sample i is sample perm[i]; cell c holds the sorted samples off[c] ..
 // off[c + 1] - 1 and the wavefronts wave0[c] .. wave0[c + 1] - 1 of 64 of them (the last one
 // short), and likewise the runs run0[c] .. of `run` samples.
 struct CellPlan {
     CellGrid grid;
+    CellLevels lv;
     const int* perm = nullptr;
     const double* xs = nullptr;
     const int* off = nullptr;
@@ -96,15 +157,20 @@ struct CellPlan {
     // near bits of the current tables: word w of cell c at bits[c * words + w]; the segments' words
     // first (bit k % 32 of word k / 32), then the outer elements'
     const uint32_t* bits = nullptr;
+    const uint32_t* far = nullptr;             // the pairs a row's nodes take; likewise, row r of every level at far[r * words]
     int seg_words = 0, words = 0;
 };
 
-// Cells a side for N samples with q nodes a side, or 0 where the direct sums are the better choice; ratio:
-// time of a near pair over that of a far one; worth: pairs that take as long as the plan, the bits and
-// the node sums' launches.
-int cells_for(const bem_ctx* ctx, int64_t N, int K, int q, double ratio, double worth);
-int cell_plan(bem_ctx* ctx, const double* x, int64_t N, int g, CellPlan* p, hipStream_t s);
-// near bits of the segment and element tables (expanded before) for every cell of the plan; mixed: the
+// The grid for N samples with q nodes a side, g = 0 where the direct sums are the better choice; ratio: time of a near
+// pair over that of a far one; worth: pairs that take as long as the plan, the bits and the node sums' launches; low:
+// time of a far pair below the top level over one at it; row: pairs that take as long as a row's own work; places:
+// where lanes are segments, how many places 64 of them lie in.
+Grouping cells_for(const bem_ctx* ctx, int64_t N, int K, int q, double ratio, double worth, double low, double row,
+                   double places = 1.0);
+// Cells a side where every cell costs q^2 pairs of its own (one level)
+int cells_one_level(const bem_ctx* ctx, int64_t N, int q, double ratio);
+int cell_plan(bem_ctx* ctx, const double* x, int64_t N, Grouping g, CellPlan* p, hipStream_t s);
+// near and far bits of the segment and element tables (expanded before) for every cell of the plan; mixed: the
 // pairs of the near radius as well
 int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, bool mixed, hipStream_t s);
 

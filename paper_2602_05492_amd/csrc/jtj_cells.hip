@@ -625,11 +625,11 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     const Layout L = layout_of(ctx, H);
     const int64_t W = L.handle_rows() + M;
     // a tile of the caller's own size is kept to
-    const int g = near2 >= 4.0f && ctx->opts.tile_rows <= 0 ? cells_for(ctx, N, K, kFarQ, kNeRatio, 0.0) : 0;
+    const int g = near2 >= 4.0f && ctx->opts.tile_rows <= 0 ? cells_one_level(ctx, N, kFarQ, kNeRatio) : 0;
     if (g == 0) return BEM_OK;
     CellPlan p;
     if ((rc = launch_expand(ctx, theta, H, s))) return rc;
-    if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
+    if ((rc = cell_plan(ctx, x, N, Grouping{g, 1}, &p, s))) return rc;
     if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
     const int nc = p.grid.nc, nl = nc + 1;
     if (W * 64 * (int64_t)nc >= ((int64_t)1 << 31)) return BEM_OK;            // 32-bit offsets in the Gram

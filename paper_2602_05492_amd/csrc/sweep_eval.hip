@@ -8,13 +8,13 @@
 // Few samples (k_sweep_direct): blocks of 256 samples times chunks of the tables, so that a thousand
 // samples still fill the chip; the chunks' float64 sums are added in a fixed order (k_sweep_sum).
 // Many samples (cells.hpp): samples grouped by cell; the segments and elements far from a cell are
-// summed at its 64 nodes (k_far_nodes), turned into Chebyshev coefficients (k_far_coef) and expanded at
+// summed at its 64 nodes or those of a cell above it (k_far_nodes), turned into Chebyshev coefficients (k_far_coef) and expanded at
 // its samples, which evaluate only the near ones pair by pair (k_sweep_cells).
 // Both are bound by the float32 vector ALUs (about 110 flops a pair).  The line between them is
 // cells_for's count of pairs.  Measured against one thread a sample over all pairs, one MI355X: 128
-// segments and 1,000 samples 316 -> 41 us a call; 500 segments and 262,144 samples 720 -> 238 us; 4,096
-// segments and 1,048,576 samples 9.91 -> 1.15 ms; the error against float64 went down with it (6.9e-7 ->
-// 1.9e-7 for the last).
+// segments and 1,000 samples 316 -> 32 us a call; 500 segments and 262,144 samples 720 -> 188 us; 4,096
+// segments and 1,048,576 samples 9.91 -> 0.69 ms; the error against float64 went down with it (6.9e-7 ->
+// 1.4e-7 for the last).
 #include "cells.hpp"
 
 namespace bem {
@@ -172,30 +172,67 @@ __global__ void __launch_bounds__(256) k_sweep_sum(const double* __restrict__ pa
     u[i] = (float)v;
 }
 
-// Far sums at the nodes: a wavefront a cell, lane = node, four cells a block share the staged records;
-// chunk y takes groups [y gpc, (y + 1) gpc) as in k_sweep_direct.  The float32 sums of a group of 32
-// are added in float64.  Cells without samples are left out (their wavefront only stages).
-__global__ void __launch_bounds__(256) k_far_nodes(CellGrid g, const int* __restrict__ off, Tables t,
-                                                   const uint32_t* __restrict__ bits, int seg_words, int words, int gpc,
-                                                   double* __restrict__ part)
+// Far sums at the nodes, lane = node.  First the top level: a wavefront a cell, four cells a block share the staged
+// records; chunk y takes groups [y gpc, (y + 1) gpc) as in k_sweep_direct, sums to part [y][cell].  Then a block a row of the
+// levels below, whose wavefronts share the words of its few far segments (wave-uniform loads), sums to low [row].  The float32 sums of a group of 32 are added in float64.  Cells without samples have no far bits.
+__global__ void __launch_bounds__(256) k_far_nodes(CellPlan p, Tables t, int gpc, int nparts, double* __restrict__ part,
+                                                   double* __restrict__ low)
 {
     __shared__ float4 stage[kStage * (kSegStride / 4)];
-    const int c = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    const bool used = c < g.nc && off[c + 1] > off[c];
-    double Xd = 0.0, Yd = 0.0;
-    if (used) cell_node<kFarQ>(g, c, lane, Xd, Yd);
+    const CellLevels& lv = p.lv;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ntop = lv.top_cells(), bt = (ntop + 3) >> 2;
+    const bool top = (int)blockIdx.x < bt * nparts;
+    const int y = top ? (int)blockIdx.x / bt : 0;
+    const int i = top ? (int)blockIdx.x % bt * 4 + wave : (int)blockIdx.x - bt * nparts;       // cell of the top level, or row
+    const bool used = top ? i < ntop : i != p.grid.nc;
+    const int row = !used ? 0 : top ? lv.base[lv.n - 1] + i : i;
+    int l = 0, cx = 0, cy = 0;
+    level_cell(lv, row, l, cx, cy);
+    double Xd, Yd;
+    level_node<kFarQ>(p.grid, l, cx, cy, lane, Xd, Yd);
     const float X = (float)Xd, Y = (float)Yd;
-    const uint32_t* row = bits + (size_t)(used ? c : 0) * words;
-    const int g0 = blockIdx.y * gpc, g1 = g0 + gpc;
-    const int k0 = g0 * 32, k1 = g1 < seg_words ? g1 * 32 : t.K;
-    const float short_len = (float)(kFarCells * g.h / kQuadFar);
+    const uint32_t* far_bits = p.far + (size_t)row * p.words;
+    const float short_len = (float)(kFarCells * p.grid.h * (1 << l) / kQuadFar);
     const bool outside = t.near2 >= 4.0f;
     auto add_far = [&](const float* s, float (&f)[3]) {
         if (s[kLen] <= short_len) add_segment_quad<4>(s, X, Y, t.eps2f, f);
         else if (outside) add_segment_quad<6>(s, X, Y, t.eps2f, f);
         else add_segment(s, load_geom(s), X, Y, t.eps2f, false, f);
     };
+    auto add_far_element = [&](int j, float (&f)[3]) {
+        const float* e = t.el32 + (size_t)j * kElemStride;
+        const float beta = element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y);
+        f[0] += beta * e[4]; f[1] += beta * e[5]; f[2] += beta * e[6];
+    };
     double d[3] = {0.0, 0.0, 0.0};
+    if (!top) {
+        if (!used) return;
+        double(*red)[3][kFarNodes] = (double(*)[3][kFarNodes])stage;
+        int turn = 0;
+        for (int w0 = 0; w0 < p.words; w0 += 64) {
+            const uint32_t mine = w0 + lane < p.words ? far_bits[w0 + lane] : 0u;
+            for (uint64_t some = __ballot(mine != 0); some; some &= some - 1) {
+                if ((turn++ & 3) != wave) continue;
+                const int w = w0 + __builtin_ctzll(some);
+                float f[3] = {0.f, 0.f, 0.f};
+                for (uint32_t far = __builtin_amdgcn_readlane(mine, w - w0); far; far &= far - 1u) {
+                    const int k = __builtin_ctz(far);
+                    if (w < p.seg_words) add_far(t.seg32 + (size_t)(w * 32 + k) * kSegStride, f);
+                    else add_far_element((w - p.seg_words) * 32 + k, f);
+                }
+                for (int q = 0; q < 3; ++q) d[q] += (double)f[q];
+            }
+        }
+        for (int q = 0; q < 3; ++q) red[wave][q][lane] = d[q];
+        __syncthreads();
+        if (threadIdx.x < 3 * kFarNodes)
+            low[(size_t)row * 3 * kFarNodes + threadIdx.x] =
+                (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
+        return;
+    }
+    const int g0 = y * gpc, g1 = g0 + gpc;
+    const int k0 = g0 * 32, k1 = g1 < p.seg_words ? g1 * 32 : t.K;
     for (int s0 = k0; s0 < k1; s0 += kStage) {
         const int n = k1 - s0 < kStage ? k1 - s0 : kStage;
         __syncthreads();
@@ -204,54 +241,57 @@ __global__ void __launch_bounds__(256) k_far_nodes(CellGrid g, const int* __rest
         __syncthreads();
         if (!used) continue;
         for (int q = 0; q < n; q += 32) {
-            const int m = n - q < 32 ? n - q : 32;
-            uint32_t far = ~row[(s0 + q) >> 5];
+            uint32_t far = far_bits[(s0 + q) >> 5];
             float f[3] = {0.f, 0.f, 0.f};
             if (far == 0xFFFFFFFFu) {
-                for (int k = q; k < q + m; ++k) add_far(reinterpret_cast<const float*>(stage + k * (kSegStride / 4)), f);
+                for (int k = q; k < q + 32; ++k) add_far(reinterpret_cast<const float*>(stage + k * (kSegStride / 4)), f);
             } else {
-                if (m < 32) far &= (1u << m) - 1u;
-                while (far) {
-                    const int k = q + __builtin_ctz(far);
-                    far &= far - 1u;
-                    add_far(reinterpret_cast<const float*>(stage + k * (kSegStride / 4)), f);
-                }
+                for (; far; far &= far - 1u)
+                    add_far(reinterpret_cast<const float*>(stage + (q + __builtin_ctz(far)) * (kSegStride / 4)), f);
             }
             for (int q3 = 0; q3 < 3; ++q3) d[q3] += (double)f[q3];
         }
     }
     if (!used) return;
-    const int e0 = g0 > seg_words ? g0 - seg_words : 0, e1 = g1 - seg_words < words - seg_words ? g1 - seg_words : words - seg_words;
-    for (int w = e0; w < e1; ++w) {
-        const int j0 = w * 32, m = t.M - j0 < 32 ? t.M - j0 : 32;
-        uint32_t far = ~row[seg_words + w];
-        if (m < 32) far &= (1u << m) - 1u;
+    for (int w = g0 > p.seg_words ? g0 : p.seg_words; w < g1 && w < p.words; ++w) {
         float f[3] = {0.f, 0.f, 0.f};
-        while (far) {
-            const int j = j0 + __builtin_ctz(far);
-            far &= far - 1u;
-            const float* e = t.el32 + (size_t)j * kElemStride;
-            const float beta = element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y);
-            f[0] += beta * e[4]; f[1] += beta * e[5]; f[2] += beta * e[6];
-        }
+        for (uint32_t far = far_bits[w]; far; far &= far - 1u) add_far_element((w - p.seg_words) * 32 + __builtin_ctz(far), f);
         for (int q3 = 0; q3 < 3; ++q3) d[q3] += (double)f[q3];
     }
-    for (int q = 0; q < 3; ++q) part[(((size_t)blockIdx.y * g.nc + c) * 3 + q) * kFarNodes + lane] = d[q];
+    for (int q = 0; q < 3; ++q) part[(((size_t)y * ntop + i) * 3 + q) * kFarNodes + lane] = d[q];
 }
 
-// Node sums to Chebyshev coefficients, a block a cell (thread (channel, node)): values v at the nodes
-// (t_i, t_j) have c_ab = s_a s_b sum_ij v_ij T_a(t_i) T_b(t_j), s_0 = 1 / kFarQ, s_a = 2 / kFarQ.
-__global__ void __launch_bounds__(192) k_far_coef(const double* __restrict__ part, int nparts, int nc,
-                                                  const int* __restrict__ off, float* __restrict__ coef)
+// Node sums to Chebyshev coefficients, a block a cell (thread (channel, node)): the sums of its cells above carried
+// down level by level, then values v at the nodes (t_i, t_j) have
+// c_ab = s_a s_b sum_ij v_ij T_a(t_i) T_b(t_j), s_0 = 1 / kFarQ, s_a = 2 / kFarQ.
+__global__ void __launch_bounds__(192) k_far_coef(const double* __restrict__ part, int nparts,
+                                                  const double* __restrict__ low, CellPlan pl, float* __restrict__ coef)
 {
-    __shared__ double v[3][kFarNodes], h[3][kFarNodes], cs[32];
+    __shared__ double v[3][kFarNodes], h[3][kFarNodes], cs[32], I[2][kFarQ][kFarQ];
+    const CellLevels& lv = pl.lv;
     const int c = blockIdx.x;
-    if (off[c + 1] == off[c]) return;
+    if (pl.off[c + 1] == pl.off[c]) return;
     const int ch = threadIdx.x >> 6, n = threadIdx.x & 63, a = n & 7, b = n >> 3;
     if (threadIdx.x < 32) cs[threadIdx.x] = cospi((double)threadIdx.x / 16.0);
+    const int cx = c % lv.nx[0], cy = c / lv.nx[0], top = lv.n - 1, ntop = lv.top_cells();
+    const int ct = (cy >> top) * lv.nx[top] + (cx >> top);
     double s = 0.0;
 #pragma unroll 8
-    for (int p = 0; p < nparts; ++p) s += part[(((size_t)p * nc + c) * 3 + ch) * kFarNodes + n];
+    for (int p = 0; p < nparts; ++p) s += part[(((size_t)p * ntop + ct) * 3 + ch) * kFarNodes + n];
+    __syncthreads();
+    if (top > 0) child_matrix<kFarQ>(threadIdx.x, 192, cs, I);
+    for (int l = top - 1; l >= 0; --l) {
+        const int sx = (cx >> l) & 1, sy = (cy >> l) & 1;
+        v[ch][n] = s;
+        __syncthreads();
+        double r = 0.0;
+        for (int i = 0; i < kFarQ; ++i) r += I[sx][a][i] * v[ch][8 * b + i];
+        h[ch][n] = r;
+        __syncthreads();
+        r = low[((size_t)level_row(lv, l, cx >> l, cy >> l) * 3 + ch) * kFarNodes + n];
+        for (int j = 0; j < kFarQ; ++j) r += I[sy][b][j] * h[ch][8 * j + a];
+        s = r;
+    }
     v[ch][n] = s;
     __syncthreads();
     // T_a(t_i) = cos(a (2 i + 1) pi / 16): entry m = a (2 i + 1) mod 32 of a cosine table
@@ -365,9 +405,9 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     const Tables t{(const float*)ctx->seg32.ptr, (const double*)ctx->seg64.ptr, (const float*)ctx->elem32.ptr,
                    (const double*)ctx->elem64.ptr, K, M, (float)eps2, (float)(nf * nf), eps2};
     const int64_t groups = (K + 31) / 32 + (M + 31) / 32;
-    const int g = cells_for(ctx, N, K, kFarQ, kEvalRatio, 2e7);
+    const Grouping g = cells_for(ctx, N, K, kFarQ, kEvalRatio, 2e7, 2.0, 12000.0);
     ProfScope ps_(ctx, PT_SWEEP_MIXED, s);
-    if (g == 0) {
+    if (g.g == 0) {
         const int64_t nb = blocks_for(N, 256);
         const int gpc = groups_per_chunk(groups, nb);
         const int nparts = (int)((groups + gpc - 1) / gpc);
@@ -386,16 +426,16 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     CellPlan p;
     if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
     if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
-    const int nc = p.grid.nc;
-    const int gpc = groups_per_chunk(groups, (nc + 3) / 4);
+    const int nc = p.grid.nc, ntop = p.lv.top_cells(), nlow = p.lv.low_rows();
+    const int gpc = groups_per_chunk(groups, (ntop + 3) / 4);
     const int nparts = (int)((groups + gpc - 1) / gpc);
-    const size_t pb = (size_t)nparts * nc * 3 * kFarNodes * sizeof(double);
-    if ((rc = ensure(ctx, ctx->farw, pb + (size_t)nc * 3 * kFarNodes * sizeof(float), s))) return rc;
+    const size_t cell = 3 * kFarNodes * sizeof(double), pb = (size_t)nparts * ntop * cell, lb = (size_t)nlow * cell;
+    if ((rc = ensure(ctx, ctx->farw, pb + lb + (size_t)nc * 3 * kFarNodes * sizeof(float), s))) return rc;
     double* part = (double*)ctx->farw.ptr;
-    float* coef = (float*)((char*)ctx->farw.ptr + pb);
-    hipLaunchKernelGGL(k_far_nodes, dim3((nc + 3) / 4, nparts), dim3(256), 0, s, p.grid, p.off, t, p.bits, p.seg_words,
-                       p.words, gpc, part);
-    hipLaunchKernelGGL(k_far_coef, dim3(nc), dim3(192), 0, s, (const double*)part, nparts, nc, p.off, coef);
+    double* low = (double*)((char*)ctx->farw.ptr + pb);
+    float* coef = (float*)((char*)ctx->farw.ptr + pb + lb);
+    hipLaunchKernelGGL(k_far_nodes, dim3(nlow + (ntop + 3) / 4 * nparts), dim3(256), 0, s, p, t, gpc, nparts, part, low);
+    hipLaunchKernelGGL(k_far_coef, dim3(nc), dim3(192), 0, s, (const double*)part, nparts, (const double*)low, p, coef);
     hipLaunchKernelGGL(k_sweep_cells, dim3((p.max_waves + 3) / 4), dim3(256), 0, s, p, t, (const float*)coef, cbar[0],
                        cbar[1], cbar[2], u);
     return check_launch(ctx, "sweep_cells");

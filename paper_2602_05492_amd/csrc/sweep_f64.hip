@@ -2,11 +2,11 @@
 //
 // Few samples: blocks of 256 samples times chunks of the tables (k_sweep_f64), whose sums are added in a
 // fixed order (k_sweep_f64_sum), so that 16,384 samples still fill the chip.  Many samples (cells.hpp):
-// the segments and elements far from a cell are summed at its 256 nodes (k_far_nodes_f64), turned into
+// the segments and elements far from a cell are summed at its 256 nodes or those of a cell above it (k_far_nodes_f64), turned into
 // Chebyshev coefficients (k_far_coef_f64) and expanded at its samples, which take only the near ones pair
 // by pair (k_sweep_cells_f64).  Results are reproducible: every sum has a fixed order.
 // Bound by the float64 vector ALUs (about 155 instructions a segment pair, 55 an element's).  Measured
-// against one thread a sample over all pairs, one MI355X: 512 segments and 262,144 samples 1.75 -> 0.63 ms
+// against one thread a sample over all pairs, one MI355X: 512 segments and 262,144 samples 1.75 -> 0.49 ms
 // a call; 128 segments and 16,384 samples (the sweep) 564 -> 83 us; errors against float64 sums of the same
 // formulas 7e-16 before and after.
 #include "cells.hpp"
@@ -73,44 +73,77 @@ __global__ void __launch_bounds__(256) k_sweep_f64_sum(const double* __restrict_
     u[i] = v;
 }
 
-// Far sums at the nodes: block (cell, chunk), thread = node.  Cells without samples are left out.
-__global__ void __launch_bounds__(256) k_far_nodes_f64(CellGrid g, const int* __restrict__ off, Tables64 t,
-                                                       const uint32_t* __restrict__ bits, int seg_words, int words,
-                                                       int gpc, double* __restrict__ part)
+constexpr int kLowParts = 4;
+
+// Far sums at the nodes, thread = node.  First the top level, chunk y of it words [y gpc, (y + 1) gpc), sums to
+// part [y][cell]; then kLowParts blocks a row of the levels below,
+// which take its words by turns, sums to low [part][row].  Cells without samples have no
+// far bits.
+__global__ void __launch_bounds__(256) k_far_nodes_f64(CellPlan p, Tables64 t, int gpc, int nparts,
+                                                       double* __restrict__ part, double* __restrict__ low)
 {
-    const int c = blockIdx.x, n = threadIdx.x;
-    if (off[c + 1] == off[c]) return;
+    const CellLevels& lv = p.lv;
+    const int ntop = lv.top_cells(), n = threadIdx.x;
+    const bool top = (int)blockIdx.x < ntop * nparts;
+    const int nlow = lv.low_rows(), lb = (int)blockIdx.x - ntop * nparts;
+    const int y = top ? (int)blockIdx.x / ntop : lb / nlow, i = top ? (int)blockIdx.x % ntop : lb % nlow;
+    if (!top && i == p.grid.nc) return;
+    const int row = top ? lv.base[lv.n - 1] + i : i;
+    int l, cx, cy;
+    level_cell(lv, row, l, cx, cy);
     double X, Y;
-    cell_node<kFarQ64>(g, c, n, X, Y);
-    const uint32_t* row = bits + (size_t)c * words;
-    const int w1 = (int)(blockIdx.y + 1) * gpc < words ? (blockIdx.y + 1) * gpc : words;
+    level_node<kFarQ64>(p.grid, l, cx, cy, n, X, Y);
+    const uint32_t* far_bits = p.far + (size_t)row * p.words;
+    const int w0 = top ? y * gpc : 0, w1 = !top || w0 + gpc > p.words ? p.words : w0 + gpc;
     double f[3] = {0.0, 0.0, 0.0};
-    for (int w = blockIdx.y * gpc; w < w1; ++w) {
-        const bool seg = w < seg_words;
-        const int i0 = 32 * (seg ? w : w - seg_words), m = (seg ? t.K : t.M) - i0;
-        uint32_t far = ~row[w];
-        if (m < 32) far &= (1u << m) - 1u;
+    int turn = 0;
+    for (int w = w0; w < w1; ++w) {
+        const bool seg = w < p.seg_words;
+        const int i0 = 32 * (seg ? w : w - p.seg_words);
+        uint32_t far = far_bits[w];
+        if (!top && far != 0 && (turn++ & (kLowParts - 1)) != y) continue;
         for (; far; far &= far - 1u) {
-            const int i = i0 + __builtin_ctz(far);
-            if (seg) add_segment(t, i, X, Y, f);
-            else add_element(t, i, X, Y, f);
+            const int k = i0 + __builtin_ctz(far);
+            if (seg) add_segment(t, k, X, Y, f);
+            else add_element(t, k, X, Y, f);
         }
     }
-    for (int q = 0; q < 3; ++q) part[(((size_t)blockIdx.y * g.nc + c) * 3 + q) * kFarNodes64 + n] = f[q];
+    double* o = top ? part + ((size_t)y * ntop + i) * 3 * kFarNodes64 : low + ((size_t)y * nlow + row) * 3 * kFarNodes64;
+    for (int q = 0; q < 3; ++q) o[q * kFarNodes64 + n] = f[q];
 }
 
 // Node sums to Chebyshev coefficients, block (cell, channel): as k_far_coef, 16 nodes a side.
-__global__ void __launch_bounds__(256) k_far_coef_f64(const double* __restrict__ part, int nparts, int nc,
-                                                      const int* __restrict__ off, double* __restrict__ coef)
+__global__ void __launch_bounds__(256) k_far_coef_f64(const double* __restrict__ part, int nparts,
+                                                      const double* __restrict__ low, CellPlan pl,
+                                                      double* __restrict__ coef)
 {
     constexpr int Q = kFarQ64;
-    __shared__ double v[kFarNodes64], h[kFarNodes64], cs[4 * Q];
+    __shared__ double v[kFarNodes64], h[kFarNodes64], cs[4 * Q], I[2][Q][Q];
+    const CellLevels& lv = pl.lv;
     const int c = blockIdx.x, ch = blockIdx.y, n = threadIdx.x, a = n & (Q - 1), b = n / Q;
-    if (off[c + 1] == off[c]) return;
+    if (pl.off[c + 1] == pl.off[c]) return;
     if (n < 4 * Q) cs[n] = cospi((double)n / (2.0 * Q));
+    const int cx = c % lv.nx[0], cy = c / lv.nx[0], top = lv.n - 1, ntop = lv.top_cells();
+    const int ct = (cy >> top) * lv.nx[top] + (cx >> top);
     double s = 0.0;
 #pragma unroll 4
-    for (int p = 0; p < nparts; ++p) s += part[(((size_t)p * nc + c) * 3 + ch) * kFarNodes64 + n];
+    for (int p = 0; p < nparts; ++p) s += part[(((size_t)p * ntop + ct) * 3 + ch) * kFarNodes64 + n];
+    __syncthreads();
+    if (top > 0) child_matrix<Q>(n, 256, cs, I);
+    for (int l = top - 1; l >= 0; --l) {
+        const int sx = (cx >> l) & 1, sy = (cy >> l) & 1;
+        v[n] = s;
+        __syncthreads();
+        double r = 0.0;
+        for (int i = 0; i < Q; ++i) r += I[sx][a][i] * v[Q * b + i];
+        h[n] = r;
+        __syncthreads();
+        r = 0.0;
+        for (int j = 0; j < Q; ++j) r += I[sy][b][j] * h[Q * j + a];
+        for (int p = 0; p < kLowParts; ++p)
+            r += low[(((size_t)p * lv.low_rows() + level_row(lv, l, cx >> l, cy >> l)) * 3 + ch) * kFarNodes64 + n];
+        s = r;
+    }
     v[n] = s;
     __syncthreads();
     double r = 0.0;
@@ -178,9 +211,9 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
     const int M = ctx->M;
     const Tables64 t{(const double*)ctx->seg64.ptr, (const double*)ctx->elem64.ptr, K, M, ctx->opts.eps * ctx->opts.eps};
     const int64_t groups = (K + 31) / 32 + (M + 31) / 32;
-    const int g = cells_for(ctx, N, K, kFarQ64, 1.0, 1e7);
+    const Grouping g = cells_for(ctx, N, K, kFarQ64, 1.0, 1e7, 1.0, 3000.0);
     ProfScope ps_(ctx, PT_SWEEP_F64, s);
-    if (g == 0) {
+    if (g.g == 0) {
         const int64_t nb = blocks_for(N, 256);
         const int gpc = groups_per_chunk(groups, nb);
         const int nparts = (int)((groups + gpc - 1) / gpc);
@@ -199,16 +232,16 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
     CellPlan p;
     if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
     if ((rc = cell_bits(ctx, &p, K, M, false, s))) return rc;
-    const int nc = p.grid.nc;
-    const int gpc = groups_per_chunk(groups, nc);
+    const int nc = p.grid.nc, ntop = p.lv.top_cells(), nlow = p.lv.low_rows();
+    const int gpc = groups_per_chunk(groups, ntop);
     const int nparts = (int)((groups + gpc - 1) / gpc);
-    const size_t pb = (size_t)nparts * nc * 3 * kFarNodes64 * sizeof(double);
-    if ((rc = ensure(ctx, ctx->farw, pb + (size_t)nc * 3 * kFarNodes64 * sizeof(double), s))) return rc;
+    const size_t cell = 3 * kFarNodes64 * sizeof(double), pb = (size_t)nparts * ntop * cell, lb = (size_t)kLowParts * nlow * cell;
+    if ((rc = ensure(ctx, ctx->farw, pb + lb + nc * cell, s))) return rc;
     double* part = (double*)ctx->farw.ptr;
-    double* coef = (double*)((char*)ctx->farw.ptr + pb);
-    hipLaunchKernelGGL(k_far_nodes_f64, dim3(nc, nparts), dim3(256), 0, s, p.grid, p.off, t, p.bits, p.seg_words, p.words,
-                       gpc, part);
-    hipLaunchKernelGGL(k_far_coef_f64, dim3(nc, 3), dim3(256), 0, s, (const double*)part, nparts, nc, p.off, coef);
+    double* low = (double*)((char*)ctx->farw.ptr + pb);
+    double* coef = (double*)((char*)ctx->farw.ptr + pb + lb);
+    hipLaunchKernelGGL(k_far_nodes_f64, dim3(kLowParts * nlow + ntop * nparts), dim3(256), 0, s, p, t, gpc, nparts, part, low);
+    hipLaunchKernelGGL(k_far_coef_f64, dim3(nc, 3), dim3(256), 0, s, (const double*)part, nparts, (const double*)low, p, coef);
     hipLaunchKernelGGL(k_sweep_cells_f64, dim3((p.max_waves + 3) / 4), dim3(256), 0, s, p, t, (const double*)coef, cbar[0],
                        cbar[1], cbar[2], u);
     return check_launch(ctx, "sweep_cells_f64");

@@ -217,7 +217,7 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     int ns = N > 0 ? chunks_for(N, kgroups, chunk_s) : 0;
     const int ng = chunks_for(3 * (int64_t)M, kgroups, chunk_g);
     int ne = N > 0 ? chunks_for(N, mgroups, chunk_e) : 0;
-    const int grid = mixed && N > 0 ? adj_mixed_rows(ctx, K, N, &ns, &ne) : 0;
+    const Grouping grid = mixed && N > 0 ? adj_mixed_rows(ctx, K, N, &ns, &ne) : Grouping{};
     const size_t seg_part = (size_t)(ns + ng) * K * kV;
     const size_t el_rows = (size_t)(ne > 0 ? ne : 1);
     const size_t seg_n = (size_t)(K > 0 ? K : 1) * kSegStride;

@@ -3,8 +3,8 @@
 //
 // Many samples (cells.hpp) take the transpose of the forward sweep's split.  The far part of a
 // cell is linear in its node values, u = sum_n phi_n(x) v_n, so its cotangents are moved to the nodes,
-// gbar_n = sum_x gbar(x) phi_n(x) (k_cell_moments, k_node_cotangent), and every segment sums its far
-// cells' 64 nodes instead of their samples (k_adj_far_segments, k_adj_far_elements).  The near
+// gbar_n = sum_x gbar(x) phi_n(x) (k_cell_moments, k_node_cotangent), and every segment sums the 64 nodes
+// of its far cells, of every level, instead of their samples (k_adj_far_segments, k_adj_far_elements).  The near
 // segments and elements of a cell sum its samples pair by pair (k_adj_near), pairs within the near
 // radius in float64.  Few samples: k_adj_near takes every segment and element for runs of samples in
 // their own order.
@@ -14,7 +14,7 @@
 // reduced in a fixed order; the near sums are added with atomics into kNearCopies partial rows.
 // Bound by the float32 vector ALUs (about 200 flops a pair).  Measured against one pass of all pairs (closed
 // forms), with the forward sweep of the same step, one MI355X: 8,192 segments and 4,194,304 samples 215 ->
-// 16.4 ms; 500 segments and 100,003 samples 2.84 -> 0.65 ms.  Gradient error against float64 for white
+// 11.3 ms; 500 segments and 100,003 samples 2.84 -> 0.53 ms.  Gradient error against float64 for white
 // cotangents 1.7e-5 -> 6.6e-7 (8,192 segments, 1,048,576 samples), 6.1e-5 -> 1.2e-7 (128 segments, one
 // sample): the quadrature does not cancel where the closed forms do.
 #include "adjoint.hpp"
@@ -94,31 +94,71 @@ __global__ void __launch_bounds__(256) k_cell_moments(CellPlan p, const float* _
     }
 }
 
-// Node records of a cell (block a cell, thread (channel, node)): gbar_ij = sum_ab s_a s_b T_a(t_i) T_b(t_j) m_ab,
-// the transpose of k_far_coef.
-__global__ void __launch_bounds__(192) k_node_cotangent(const double* __restrict__ part, CellGrid g,
-                                                        const int* __restrict__ off, float* __restrict__ rec)
+// Node records of a row (block a row, thread (channel, node)): gbar_ij = sum_ab s_a s_b T_a(t_i) T_b(t_j) m_ab,
+// the transpose of k_far_coef.  A cell of a higher level takes its moments from those of its level-0 cells: with r of them
+// a side, T_a((t + o) / r) = sum_k S_o[a][k] T_k(t), o = 1 - r, 3 - r, .., r - 1.
+__global__ void __launch_bounds__(192) k_node_cotangent(const double* __restrict__ part, CellPlan pl,
+                                                        float* __restrict__ rec)
 {
-    __shared__ double v[3][kFarNodes], h[3][kFarNodes], cs[32];
-    const int c = blockIdx.x;
-    if (off[c + 1] == off[c]) return;
-    const int ch = threadIdx.x >> 6, n = threadIdx.x & 63, i = n & 7, j = n >> 3;
+    constexpr int kMost = 1 << (kMaxLevels - 1);
+    __shared__ double v[3][kFarNodes], h[3][kFarNodes], cs[32], S[kMost][kFarQ][kFarQ];
+    const CellLevels& lv = pl.lv;
+    const int row = blockIdx.x;
+    if (row == pl.grid.nc) return;
+    int l, cx, cy;
+    level_cell(lv, row, l, cx, cy);
+    if (!level_used(lv, pl.off, l, cx, cy)) return;
+    const int ch = threadIdx.x >> 6, n = threadIdx.x & 63, i = n & 7, j = n >> 3, r = 1 << l;
     if (threadIdx.x < 32) cs[threadIdx.x] = cospi((double)threadIdx.x / 16.0);
-    double s = 0.0;
-    for (int p = 0; p < kMomParts; ++p) s += part[(((size_t)p * g.nc + c) * 3 + ch) * kFarNodes + n];
-    v[ch][n] = s * (i == 0 ? 0.125 : 0.25) * (j == 0 ? 0.125 : 0.25);
     __syncthreads();
-    double r = 0.0;                               // over a: T_a(t_i) = cos(a (2 i + 1) pi / 16)
-    for (int a = 0; a < kFarQ; ++a) r += v[ch][8 * j + a] * cs[(a * (2 * i + 1)) & 31];
-    h[ch][n] = r;
+    if (l > 0) {
+        for (int e = threadIdx.x; e < r * kFarNodes; e += 192) {
+            const int o = e >> 6, a = (e >> 3) & 7, k = e & 7;
+            double s = 0.0;
+            for (int m = 0; m < kFarQ; ++m) {
+                double T[kFarQ];
+                cheb_values<double, kFarQ>((cheb_node<kFarQ>(m) + (double)(2 * o + 1 - r)) / (double)r, T);
+                double t = T[0];
+                for (int q = 1; q < kFarQ; ++q) t = q == a ? T[q] : t;
+                s += t * cs[(k * (2 * m + 1)) & 31];
+            }
+            S[o][a][k] = s * (k == 0 ? 0.125 : 0.25);
+        }
+    }
+    double m = 0.0;
+    const int x1 = (cx + 1) << l < lv.nx[0] ? (cx + 1) << l : lv.nx[0], y1 = (cy + 1) << l < lv.ny[0] ? (cy + 1) << l : lv.ny[0];
+    for (int fy = cy << l; fy < y1; ++fy)
+        for (int fx = cx << l; fx < x1; ++fx) {
+            const int c = fy * lv.nx[0] + fx;
+            if (pl.off[c + 1] == pl.off[c]) continue;                  // its moments were not written
+            double s = 0.0;
+            for (int p = 0; p < kMomParts; ++p) s += part[(((size_t)p * pl.grid.nc + c) * 3 + ch) * kFarNodes + n];
+            if (l == 0) {
+                m = s;
+                continue;
+            }
+            v[ch][n] = s;
+            __syncthreads();
+            s = 0.0;
+            for (int k = 0; k < kFarQ; ++k) s += S[fx - (cx << l)][i][k] * v[ch][8 * j + k];
+            h[ch][n] = s;
+            __syncthreads();
+            for (int k = 0; k < kFarQ; ++k) m += S[fy - (cy << l)][j][k] * h[ch][8 * k + i];
+        }
     __syncthreads();
-    r = 0.0;
-    for (int b = 0; b < kFarQ; ++b) r += h[ch][8 * b + i] * cs[(b * (2 * j + 1)) & 31];
-    float* o = rec + ((size_t)c * kFarNodes + n) * kRec;
-    o[2 + ch] = (float)r;
+    v[ch][n] = m * (i == 0 ? 0.125 : 0.25) * (j == 0 ? 0.125 : 0.25);
+    __syncthreads();
+    double s = 0.0;                               // over a: T_a(t_i) = cos(a (2 i + 1) pi / 16)
+    for (int a = 0; a < kFarQ; ++a) s += v[ch][8 * j + a] * cs[(a * (2 * i + 1)) & 31];
+    h[ch][n] = s;
+    __syncthreads();
+    s = 0.0;
+    for (int b = 0; b < kFarQ; ++b) s += h[ch][8 * b + i] * cs[(b * (2 * j + 1)) & 31];
+    float* o = rec + ((size_t)row * kFarNodes + n) * kRec;
+    o[2 + ch] = (float)s;
     if (ch == 0) {
         double X, Y;
-        cell_node<kFarQ>(g, c, n, X, Y);
+        level_node<kFarQ>(pl.grid, l, cx, cy, n, X, Y);
         o[0] = (float)X;
         o[1] = (float)Y;
     }
@@ -145,17 +185,15 @@ __device__ inline void adj_pair(const SegGeom<float>& g, float len, float ilen, 
     }
 }
 
-// Far cells of 64 segments: wavefronts split the cells [blockIdx.y cpb, (blockIdx.y + 1) cpb).
-__global__ void __launch_bounds__(256) k_adj_far_segments(const float* __restrict__ rec, const int* __restrict__ off,
-                                                          const uint32_t* __restrict__ bits, int words, int seg_words,
-                                                          int nc, int cpb, const float* __restrict__ seg32, int K,
-                                                          float eps2f, float short_len, bool outside,
+// Far rows of 64 segments: the wavefronts of the grid's y share the rows by turns (a segment's far rows below the top
+// level lie together).
+__global__ void __launch_bounds__(256) k_adj_far_segments(const float* __restrict__ rec, CellPlan p,
+                                                          const float* __restrict__ seg32, int K, float eps2f, bool outside,
                                                           double* __restrict__ partial)
 {
     __shared__ double red[3][64][kV + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int k = blockIdx.x * 64 + lane, w0 = blockIdx.x * 2;
-    const int c1 = (blockIdx.y + 1) * cpb < nc ? (blockIdx.y + 1) * cpb : nc;
     double acc[kV];
     for (int v = 0; v < kV; ++v) acc[v] = 0.0;
     const float* s32 = seg32 + (size_t)(k < K ? k : 0) * kSegStride;
@@ -164,17 +202,21 @@ __global__ void __launch_bounds__(256) k_adj_far_segments(const float* __restric
         float w[12];
         for (int c = 0; c < 12; ++c) w[c] = s32[kWdA + c];
         const float len = s32[kLen], ilen = s32[kILen];
-        const bool all_short = !__any(len > short_len);
-        for (int c = blockIdx.y * cpb + wave; c < c1; c += 4) {
-            if (off[c + 1] == off[c]) continue;
-            const uint32_t* row = bits + (size_t)c * words + w0;
-            const uint64_t near = row[0] | (w0 + 1 < seg_words ? (uint64_t)row[1] << 32 : 0ull);
-            if (near == ~0ull) continue;
-            const bool on = !((near >> lane) & 1ull);
-            const float* r = rec + (size_t)c * kFarNodes * kRec;
+        // levels whose far distance is four lengths for every lane
+        const float reach = (float)(kFarCells * p.grid.h / kQuadFar);
+        int first_short = 0;
+        while (first_short < kMaxLevels && __any(len > reach * (float)(1 << first_short))) ++first_short;
+        int l = 0;
+        for (int row = blockIdx.y * 4 + wave; row < p.lv.rows; row += 4 * gridDim.y) {
+            const uint32_t* fb = p.far + (size_t)row * p.words + w0;
+            const uint64_t far = fb[0] | (w0 + 1 < p.seg_words ? (uint64_t)fb[1] << 32 : 0ull);
+            if (far == 0) continue;
+            while (l + 1 < p.lv.n && row >= p.lv.base[l + 1]) ++l;
+            const bool on = (far >> lane) & 1ull;
+            const float* r = rec + (size_t)row * kFarNodes * kRec;
             float af[kV];
             for (int v = 0; v < kV; ++v) af[v] = 0.0f;
-            if (all_short)
+            if (l >= first_short)
                 for (int n = 0; n < kFarNodes; ++n) adj_pair<4>(g, len, ilen, w, r + n * kRec, on, eps2f, af);
             else if (outside)
                 for (int n = 0; n < kFarNodes; ++n) adj_pair<6>(g, len, ilen, w, r + n * kRec, on, eps2f, af);
@@ -192,26 +234,23 @@ __global__ void __launch_bounds__(256) k_adj_far_segments(const float* __restric
     }
 }
 
-// Far cells of 64 outer elements, as k_adj_far_segments.
-__global__ void __launch_bounds__(256) k_adj_far_elements(const float* __restrict__ rec, const int* __restrict__ off,
-                                                          const uint32_t* __restrict__ bits, int words, int seg_words,
-                                                          int nc, int cpb, const float* __restrict__ el32, int M,
+// Far rows of 64 outer elements, as k_adj_far_segments.
+__global__ void __launch_bounds__(256) k_adj_far_elements(const float* __restrict__ rec, CellPlan p,
+                                                          const float* __restrict__ el32, int M,
                                                           double* __restrict__ partial)
 {
     __shared__ double red[3][64][3];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = blockIdx.x * 64 + lane, w0 = seg_words + blockIdx.x * 2;
-    const int c1 = (blockIdx.y + 1) * cpb < nc ? (blockIdx.y + 1) * cpb : nc;
+    const int j = blockIdx.x * 64 + lane, w0 = p.seg_words + blockIdx.x * 2;
     double acc[3] = {0.0, 0.0, 0.0};
     const float* e = el32 + (size_t)(j < M ? j : 0) * kElemStride;
     const float ax = e[0], ay = e[1], vx = e[2], vy = e[3];
-    for (int c = blockIdx.y * cpb + wave; c < c1; c += 4) {
-        if (off[c + 1] == off[c]) continue;
-        const uint32_t* row = bits + (size_t)c * words + w0;
-        const uint64_t near = row[0] | (w0 + 1 < words ? (uint64_t)row[1] << 32 : 0ull);
-        if (near == ~0ull) continue;
-        const bool on = !((near >> lane) & 1ull);
-        const float* r = rec + (size_t)c * kFarNodes * kRec;
+    for (int row = blockIdx.y * 4 + wave; row < p.lv.rows; row += 4 * gridDim.y) {
+        const uint32_t* fb = p.far + (size_t)row * p.words + w0;
+        const uint64_t far = fb[0] | (w0 + 1 < p.words ? (uint64_t)fb[1] << 32 : 0ull);
+        if (far == 0) continue;
+        const bool on = (far >> lane) & 1ull;
+        const float* r = rec + (size_t)row * kFarNodes * kRec;
         float f[3] = {0.f, 0.f, 0.f};
         for (int n = 0; n < kFarNodes; ++n) {
             const float* q = r + n * kRec;
@@ -405,22 +444,24 @@ __global__ void __launch_bounds__(64, Singular ? 2 : 4)
 }  // namespace
 
 // Rows of segment partials (times K x 16) and of element partials (times M x 3) that adj_mixed writes.
-int adj_mixed_rows(bem_ctx* ctx, int K, int64_t N, int* seg_rows, int* el_rows)
+Grouping adj_mixed_rows(bem_ctx* ctx, int K, int64_t N, int* seg_rows, int* el_rows)
 {
-    const int g = cells_for(ctx, N, K, kFarQ, kAdjRatio, 2e7);
+    // 64 segments are 64 / S handles, each some places long
+    const int S = ctx->opts.segs_per_handle;
+    const Grouping g = cells_for(ctx, N, K, kFarQ, kAdjRatio, 2e7, 1.0, 12000.0, S < 64 ? 128.0 / S : 2.0);
     auto rows = [&](int n) {
         const int groups = (n + 63) / 64;
         const int r = (2048 + groups - 1) / (groups > 0 ? groups : 1);
-        return r < 1 ? 1 : (r > g * g / 4 ? (g * g + 3) / 4 : r);
+        return r < 1 ? 1 : (r > g.g * g.g / 4 ? (g.g * g.g + 3) / 4 : r);
     };
-    *seg_rows = kNearCopies + (g ? rows(K) : 0);
-    *el_rows = kNearCopies + (g ? rows(ctx->M) : 0);
+    *seg_rows = kNearCopies + (g.g ? rows(K) : 0);
+    *el_rows = kNearCopies + (g.g ? rows(ctx->M) : 0);
     return g;
 }
 
 // The sample sums of the mixed adjoint into partial rows part [seg_rows][K][16] and epart
 // [el_rows][M][3] (every entry written), the tables of theta expanded before.
-int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K, int g, int seg_rows, int el_rows,
+int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K, Grouping g, int seg_rows, int el_rows,
               double* part, double* epart, hipStream_t s)
 {
     int rc;
@@ -434,7 +475,7 @@ int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K
     if ((rc = fill_f64(ctx, epart, (int64_t)kNearCopies * M * 3, 0.0, s))) return rc;
     CellPlan p;
     int64_t runs;
-    if (g) {
+    if (g.g) {
         if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
         if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
         runs = p.max_runs;
@@ -454,27 +495,25 @@ int adj_mixed(bem_ctx* ctx, const double* x, int64_t N, const float* gbar, int K
     const int split = (int)(want < 4 ? (most < 4 ? most : 4) : (want < most ? want : most));
     const int nc = p.grid.nc;
     const size_t rb = ((size_t)N * kRec * sizeof(float) + 255) / 256 * 256;
-    const size_t nb = g ? (size_t)nc * kFarNodes * kRec * sizeof(float) : 0;
-    const size_t mb = g ? (size_t)kMomParts * nc * 3 * kFarNodes * sizeof(double) : 0;
+    const size_t nb = g.g ? (size_t)p.lv.rows * kFarNodes * kRec * sizeof(float) : 0;
+    const size_t mb = g.g ? (size_t)kMomParts * nc * 3 * kFarNodes * sizeof(double) : 0;
     if ((rc = ensure(ctx, ctx->farw, rb + nb + mb, s))) return rc;
     float* rec = (float*)ctx->farw.ptr;
     float* nrec = (float*)((char*)ctx->farw.ptr + rb);
     double* mpart = (double*)((char*)ctx->farw.ptr + rb + nb);
     hipLaunchKernelGGL(k_sample_records, dim3(blocks_for(N, 256)), dim3(256), 0, s, p.xs, gbar, p.perm, N, rec);
-    if (g) {
+    if (g.g) {
         hipLaunchKernelGGL(k_cell_moments, dim3(nc, kMomParts), dim3(256), 0, s, p, gbar, mpart);
-        hipLaunchKernelGGL(k_node_cotangent, dim3(nc), dim3(192), 0, s, (const double*)mpart, p.grid, p.off, nrec);
+        hipLaunchKernelGGL(k_node_cotangent, dim3(p.lv.rows), dim3(192), 0, s, (const double*)mpart, p, nrec);
         const int rs = seg_rows - kNearCopies, re = el_rows - kNearCopies;
         {
             ProfScope ps_(ctx, PT_VJP_SEGMENTS, s);
-            hipLaunchKernelGGL(k_adj_far_segments, dim3((K + 63) / 64, rs), dim3(256), 0, s, (const float*)nrec, p.off,
-                               p.bits, p.words, p.seg_words, nc, (nc + rs - 1) / rs, seg32, K, (float)eps2,
-                               (float)(kFarCells * p.grid.h / kQuadFar), near2 >= 4.0f,
-                               part + (size_t)kNearCopies * K * kV);
+            hipLaunchKernelGGL(k_adj_far_segments, dim3((K + 63) / 64, rs), dim3(256), 0, s, (const float*)nrec, p, seg32, K,
+                               (float)eps2, near2 >= 4.0f, part + (size_t)kNearCopies * K * kV);
         }
         ProfScope ps_(ctx, PT_VJP_ELEMENTS, s);
-        hipLaunchKernelGGL(k_adj_far_elements, dim3((M + 63) / 64, re), dim3(256), 0, s, (const float*)nrec, p.off, p.bits,
-                           p.words, p.seg_words, nc, (nc + re - 1) / re, el32, M, epart + (size_t)kNearCopies * M * 3);
+        hipLaunchKernelGGL(k_adj_far_elements, dim3((M + 63) / 64, re), dim3(256), 0, s, (const float*)nrec, p, el32, M,
+                           epart + (size_t)kNearCopies * M * 3);
     }
     const double* seg64 = (const double*)ctx->seg64.ptr;
     const double* el64 = (const double*)ctx->elem64.ptr;

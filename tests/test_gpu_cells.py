@@ -98,6 +98,27 @@ def test_grouped_samples_in_a_region():
     ctx.close()
 
 
+@pytest.mark.parametrize("H,S,n,width", [(256, 32, 400003, 0.37), (12, 8, 500000, 1.0)])
+def test_levels_of_cells_in_a_narrow_region(H, S, n, width):
+    """Enough samples for two and three levels of cells, in a region whose cells a side do not divide by the levels,
+    half of the region without samples; few handles lie far from most cells, many fill them."""
+    poly = np.array([[0.0, 0.0], [width, 0.0], [width, 1.0], [0.0, 1.0]])
+    el = []
+    for p, q, k in zip(poly, np.roll(poly, -1, 0), (57, 127, 57, 127)):
+        t = np.linspace(0, 1, k + 1)[:, None]
+        v = p * (1 - t) + q * t
+        el.append(np.concatenate([v[:-1], v[1:]], 1))
+    ctx = B.Context(segs_per_handle=S, elements=np.concatenate(el))
+    x = W.random_points(n, n, 0.01, 0.99) * np.array([width, 1.0])
+    x[: n // 2, 1] *= 0.3
+    th = W.random_handles(H, H, spread=0.05, centre_lo=0.08, centre_hi=0.3)
+    _check(ctx, th, x)
+    u = host(ctx.eval(dev(th), dev(x), CBAR, "fp64"))
+    r = host(ctx.eval(dev(th), dev(x[::101]), CBAR, "fp64"))               # few samples: the direct sums
+    assert np.abs(u[::101] - r).max() < 1e-12 * max(1.0, np.abs(r).max())
+    ctx.close()
+
+
 def test_grouped_samples_view_off_16_bytes():
     ctx, th = ctx_for(32), dev(W.random_handles(9, 100))
     flat = dev(np.concatenate([[0.5], W.random_points(9, 20001, 0.01, 0.99).ravel()]))
