@@ -21,8 +21,8 @@
 // Rounding.  The split-bfloat16 products of E average over the samples as those of the Gram over all
 // samples do; the fewer columns Y and Z carry 22 and 24 bits instead of 16.  Accumulation in float32 within a
 // run and in float64 beyond is the same.  Pairs by quadrature (seg_math.hpp), so near factors of at least 1.
-// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 9.8 ms, far features
-// 7.7 ms, near Gram 3.0 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
+// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 9.6 ms, far features
+// 5.4 ms, near Gram 2.9 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
 // step against float64: 7.5e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
 #include <algorithm>
 #include <cmath>
@@ -459,10 +459,25 @@ __global__ void __launch_bounds__(256) k_near_project(const CellInfo* __restrict
         }
 }
 
-// Y of one cell: block (cell, part), four wavefronts that share the cell's R.  A wavefront takes a handle (or
-// kFeatVals elements) at a time: the far part at the 64 nodes (lane = node) into LDS, then lane k sums
-// column k of V R, adds Z on near rows and stores the value (float32); rmax: largest magnitude of every row, as
-// float bits.
+// largest of 32 lanes (each half of the wavefront by itself), values >= 0 or NaN
+__device__ inline float half_max(float v)
+{
+    auto step = [&](float u) { v = fmaxf(v, u); };
+    step(__int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, false)));       // row_ror:8
+    step(__int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xf, 0xf, false)));
+    step(__int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x122, 0xf, 0xf, false)));
+    step(__int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xf, 0xf, false)));
+    step(__shfl_xor(v, 16));
+    return v;
+}
+
+// Y of one cell: block (cell, part), four wavefronts that share the cell's R.  A wavefront takes up to 32 rows at a time
+// (a cubic handle, two straight ones, 32 elements): the far part at the 64 nodes (lane = node) into LDS, times R on
+// float32 MFMA, plus Z on near rows; float32 to Yf.  rmax: largest magnitude of every row, as float bits; an atomic
+// only where the value read beforehand is smaller.  LDS rows of kFarLd floats: 32 rows at one pair of nodes fall in
+// distinct banks.  Bound by the vector ALUs (the pairs); with the product by vector ALU out of LDS and an atomic a row and
+// cell 7.7 ms (8,192 segments, 1,296 cells) and 1.38 ms (500 straight handles, 289 cells), now 5.4 and 0.54 ms.
+constexpr int kFarLd = 66;
 __global__ void __launch_bounds__(256, 2)
     k_far_features(CellGrid g, const int* __restrict__ off, const CellInfo* __restrict__ ci,
                    const int* __restrict__ hpos, const int* __restrict__ epos, const uint32_t* __restrict__ bits, int words,
@@ -472,10 +487,13 @@ __global__ void __launch_bounds__(256, 2)
                    uint32_t* __restrict__ rmax)
 {
     constexpr int NN = kFarNodes;
-    __shared__ float R[NN][NN];
-    __shared__ __attribute__((aligned(16))) float V[4][kFeatVals][NN];
+    __shared__ float Rt[NN][kFarLd];                     // R transposed: [column][node]
+    __shared__ float V[4][32][kFarLd];
     const int c = blockIdx.x, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    for (int e = threadIdx.x; e < NN * NN; e += 256) R[e >> 6][e & 63] = Rf[(size_t)c * NN * NN + e];
+    const int li = lane & 31, lk = lane >> 5;
+    for (int e = threadIdx.x; e < NN * NN; e += 256) Rt[e & 63][e >> 6] = Rf[(size_t)c * NN * NN + e];
+    float(*v)[kFarLd] = V[wv];
+    for (int i = 28; i < 32; ++i) v[i][lane] = 0.0f;
     __syncthreads();
     const bool used = off[c + 1] > off[c];
     const int nh = ci[c].nh;
@@ -486,102 +504,116 @@ __global__ void __launch_bounds__(256, 2)
     const float short_len = (float)(kFarCells * g.h / kQuadFar);
     // the cells' columns are dealt out in a stride permutation: in cell order the float32 sums over
     // consecutive columns see long coherent runs, and their partial sums wander
-    const size_t yb = (size_t)(2 * ((int64_t)c * stride % g.nc) + (lane >> 5)) * ((size_t)W << 5) + (lane & 31);
-    float(*v)[NN] = V[wv];
-    auto put = [&](int64_t f, float t) {
-        Yf[yb + ((size_t)f << 5)] = t;
-        const float m = wave_max(fabsf(t));
-        if (lane == 0 && m > 0.0f) atomicMax(rmax + f, __float_as_uint(m));
-    };
-    const int batches = (M + kFeatVals - 1) / kFeatVals;
-    for (int it = wv + 4 * blockIdx.y; it < L.H + batches; it += 4 * gridDim.y) {
-        const bool handle = it < L.H;
-        const int j0 = (it - L.H) * kFeatVals;
-        if (used) {
-            if (handle) {
+    const size_t yb = (size_t)(2 * ((int64_t)c * stride % g.nc)) * ((size_t)W << 5) + li;
+    const float* z0 = Zf + (size_t)ci[c].rb * NN + li;
+    const int per = model == 1 ? 2 : 1;                  // handles an item
+    const int hitems = (L.H + per - 1) / per, items = hitems + (M + 31) / 32;
+    for (int it = wv + 4 * blockIdx.y; it < items; it += 4 * gridDim.y) {
+        const bool handle = it < hitems;
+        const int h0 = it * per, j0 = (it - hitems) * 32;
+        // row i = li of the item: its row of Y (-1: none), its near row (-1: not near), and the largest magnitude so far
+        int my_f = -1, my_z = -1;
+        if (!handle) {
+            if (j0 + li < M) {
+                my_f = (int)L.handle_rows() + j0 + li;
+                const int p = used ? epos[(size_t)c * M + j0 + li] : -1;
+                if (p >= 0) my_z = (3 * L.G + L.C) * nh + p;
+            }
+        } else {
+            const int all = 3 * L.G + L.C, sub = li >= all, e = li - all * sub, h = h0 + sub;
+            if (sub < per && e < all && h < L.H) {
+                const int p = used ? hpos[(size_t)c * L.H + h] : -1, q = e / L.G, k = e % L.G;
+                my_f = q < 3 ? q * (int)L.Gp + L.G * h + k : 3 * (int)L.Gp + L.C * h + (e - 3 * L.G);
+                if (p >= 0) my_z = q < 3 ? (q * nh + p) * L.G + k : 3 * L.G * nh + L.C * p + (e - 3 * L.G);
+            }
+        }
+        const uint32_t seen = my_f >= 0 ? rmax[my_f] : 0;
+        if (used && handle) {
+            for (int sub = 0; sub < per; ++sub) {
+                const int h = h0 + sub;
                 float geo[3][8], col[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
 #pragma unroll
                     for (int k = 0; k < 8; ++k) geo[q][k] = 0.f;
-                for (int j = 0; j < S; ++j) {
-                    const int k = it * S + j;
-                    if ((row[k >> 5] >> (k & 31)) & 1u) continue;
-                    const float* s = seg32 + (size_t)k * kSegStride;
-                    const float* B = vtab + 8 * j;
-                    if (s[kLen] <= short_len) add_pair_features<4>(s, B, B + 8, X, Y, eps2f, true, geo, col);
-                    else add_pair_features<6>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+                const int k1 = h < L.H ? (h + 1) * S : 0;
+                for (int k0 = h * S; k0 < k1; k0 = (k0 | 31) + 1) {
+                    // far segments of this handle in the word that holds k0
+                    uint32_t far = ~row[k0 >> 5] & (~0u << (k0 & 31));
+                    if (k1 <= (k0 | 31)) far &= (1u << (k1 & 31)) - 1u;
+                    for (; far; far &= far - 1u) {
+                        const int k = (k0 & ~31) + __builtin_ctz(far);
+                        const float* s = seg32 + (size_t)k * kSegStride;
+                        const float* B = vtab + 8 * (k - h * S);
+                        if (s[kLen] <= short_len) add_pair_features<4>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+                        else add_pair_features<6>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+                    }
                 }
+                if (model == 1) {
+                    float(*u)[kFarLd] = v + 14 * sub;
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+                    for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[8 * q + k][lane] = geo[q][k];
+                        for (int k = 0; k < 4; ++k) u[4 * q + k][lane] = geo[q][k];
+                    u[12][lane] = col[0] + col[1];
+                    u[13][lane] = col[2] + col[3];
+                } else {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) v[24 + k][lane] = col[k];
-            } else {
+                    for (int q = 0; q < 3; ++q)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) v[8 * q + k][lane] = geo[q][k];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[24 + k][lane] = col[k];
+                }
+            }
+        } else if (used) {
 #pragma unroll 4
-                for (int i = 0; i < kFeatVals; ++i) {
-                    const int j = j0 + i < M ? j0 + i : M - 1;
-                    const float* e = el32 + (size_t)j * kElemStride;
-                    const bool far = !((row[seg_words + (j >> 5)] >> (j & 31)) & 1u);
-                    v[i][lane] = far ? element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y) : 0.0f;
-                }
+            for (int i = 0; i < 32; ++i) {
+                const int j = j0 + i < M ? j0 + i : M - 1;
+                const float* e = el32 + (size_t)j * kElemStride;
+                const bool far = !((row[seg_words + (j >> 5)] >> (j & 31)) & 1u);
+                v[i][lane] = far ? element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y) : 0.0f;
             }
         }
         __threadfence_block();
-        float y[kFeatVals];
+        floatx16 acc[2];
 #pragma unroll
-        for (int i = 0; i < kFeatVals; ++i) y[i] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
         if (used) {
-#pragma unroll 2
-            for (int n = 0; n < NN; n += 4) {
-                const float r0 = R[n][lane], r1 = R[n + 1][lane], r2 = R[n + 2][lane], r3 = R[n + 3][lane];
-#pragma unroll
-                for (int i = 0; i < kFeatVals; ++i) {
-                    const float4 q = *reinterpret_cast<const float4*>(&v[i][n]);
-                    y[i] += (q.x * r0 + q.y * r1) + (q.z * r2 + q.w * r3);
-                }
+#pragma unroll 4
+            for (int n = 2 * lk; n < NN; n += 4) {
+                const float2 a = *reinterpret_cast<const float2*>(&v[li][n]);
+                const float2 b0 = *reinterpret_cast<const float2*>(&Rt[li][n]);
+                const float2 b1 = *reinterpret_cast<const float2*>(&Rt[32 + li][n]);
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b0.x, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b1.x, acc[1], 0, 0, 0);
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b0.y, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1.y, acc[1], 0, 0, 0);
             }
         }
         __threadfence_block();
-        if (handle) {
-            const int hp = used ? hpos[(size_t)c * L.H + it] : -1;
-            const float* z = Zf + (size_t)ci[c].rb * NN + lane;
-            if (model == 1) {
-                float o[14];
+        // outputs: lane i (and i + 32) keeps row i's maximum
+        float most = 0.0f;
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) o[4 * q + k] = y[8 * q + k];
-                o[12] = y[24] + y[25];
-                o[13] = y[26] + y[27];
-#pragma unroll
-                for (int i = 0; i < 14; ++i) {
-                    const int q = i >> 2, k = i & 3;
-                    if (hp >= 0) o[i] += z[(size_t)(i < 12 ? (q * nh + hp) * 4 + k : 12 * nh + 2 * hp + (i - 12)) * NN];
-                    const int64_t f = i < 12 ? (int64_t)q * L.Gp + 4 * it + k : 3 * L.Gp + 2 * it + (i - 12);
-                    put(f, o[i]);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < kFeatVals; ++i) {
-                    const int q = i >> 3, k = i & 7;
-                    if (hp >= 0) y[i] += z[(size_t)(i < 24 ? (q * nh + hp) * 8 + k : 24 * nh + 4 * hp + (i - 24)) * NN];
-                    const int64_t f = i < 24 ? (int64_t)q * L.Gp + 8 * it + k : 3 * L.Gp + 4 * it + (i - 24);
-                    put(f, y[i]);
-                }
+        for (int r = 0; r < 16; ++r) {
+            const int i = 8 * (r >> 2) + 4 * lk + (r & 3);
+            const int f = __shfl(my_f, i), z = __shfl(my_z, i);
+            if (z >= 0) {
+                acc[0][r] += z0[(size_t)z * NN];
+                acc[1][r] += z0[(size_t)z * NN + 32];
             }
-        } else {
-            const int b0 = (3 * L.G + L.C) * nh;
-#pragma unroll
-            for (int i = 0; i < kFeatVals; ++i) {
-                const int j = j0 + i;
-                if (j >= M) break;
-                const int ep = used ? epos[(size_t)c * M + j] : -1;
-                if (ep >= 0) y[i] += Zf[((size_t)ci[c].rb + b0 + ep) * NN + lane];
-                put(L.handle_rows() + j, y[i]);
+            if (f >= 0) {
+                float* o = Yf + yb + ((size_t)f << 5);
+                o[0] = acc[0][r];
+                o[(size_t)W << 5] = acc[1][r];
             }
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float m = half_max(fmaxf(fabsf(acc[0][r]), fabsf(acc[1][r])));
+            if (li == 8 * (r >> 2) + 4 * lk + (r & 3)) most = m;
+        }
+        if (my_f >= 0 && __float_as_uint(most) > seen) atomicMax(rmax + my_f, __float_as_uint(most));
     }
 }
 
@@ -770,7 +802,7 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     if ((rc = fill_i32(ctx, (int*)rmax, W, 0, s))) return rc;
     {
         ProfScope ps_(ctx, PT_FEATURES, s);
-        const int items = H + (M + kFeatVals - 1) / kFeatVals;
+        const int items = (L.G == 4 ? (H + 1) / 2 : H) + (M + 31) / 32;
         int split = (items + 3) / 4;
         const int most = 1 + 4096 / nc;
         if (split > most) split = most;
