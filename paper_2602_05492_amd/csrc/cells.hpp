@@ -181,6 +181,25 @@ inline int groups_per_chunk(int64_t groups, int64_t blocks)
     return (int)(n < 1 ? 1 : (n > groups ? groups : n));
 }
 
+// Segments or elements a group of the direct sums over nb blocks of samples: 32, or 8 where those leave most of the
+// chip idle (1,000 samples, 128 segments, 1,024 elements: 144 blocks, sweep 16 us; 576 blocks, 8 us).
+inline int direct_group(int64_t nb, int K, int M) { return nb * (((int64_t)K + M + 63) / 32) < 512 ? 8 : 32; }
+
+// Sum of the chunks' partial results i (chunks n apart): a block of 256 threads 64 results, each wavefront every fourth
+// chunk, in a fixed order; the result is in the first wavefront.
+__device__ inline double sum_chunks(const double* __restrict__ part, int nparts, int64_t n, int64_t i, double (*red)[64])
+{
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double v = 0.0;
+    if (i < n) {
+#pragma unroll 8
+        for (int p = w; p < nparts; p += 4) v += part[(size_t)p * n + i];
+    }
+    if (w > 0) red[w - 1][lane] = v;
+    __syncthreads();
+    return w == 0 ? ((v + red[0][lane]) + red[1][lane]) + red[2][lane] : 0.0;
+}
+
 // label of unit u in a first-unit table t[0 .. nl] (t[nl] = number of units > u)
 __device__ inline int unit_label(const int* __restrict__ t, int nl, int u)
 {

@@ -102,9 +102,9 @@ __device__ inline void add_segment_quad(const float* __restrict__ s, float X, fl
 
 constexpr int kStage = 128;                          // segment records staged at a time (12 KiB)
 
-// Groups of 32 segments, then of 32 elements; chunk y of a launch takes groups [y gpc, (y + 1) gpc).
+// Groups of gs segments, then of gs elements; chunk y of a launch takes groups [y gpc, (y + 1) gpc).
 // part == null (one chunk): u is written here.
-__global__ void __launch_bounds__(256, 4) k_sweep_direct(const double* __restrict__ x, int64_t N, Tables t, int gpc,
+__global__ void __launch_bounds__(256, 4) k_sweep_direct(const double* __restrict__ x, int64_t N, Tables t, int gs, int gpc,
                                                       double c0, double c1, double c2, double* __restrict__ part,
                                                       float* __restrict__ u)
 {
@@ -117,9 +117,9 @@ __global__ void __launch_bounds__(256, 4) k_sweep_direct(const double* __restric
     NearBuf& b = nb[w];
     for (int c = 0; c < 3; ++c) b.acc[64 * c + lane] = 0.0;
     const float X = live ? (float)x[2 * i] : 0.0f, Y = live ? (float)x[2 * i + 1] : 0.0f;
-    const int nsg = (t.K + 31) / 32;
+    const int nsg = (t.K + gs - 1) / gs;
     const int g0 = blockIdx.y * gpc, g1 = g0 + gpc;
-    const int k0 = g0 * 32, k1 = g1 < nsg ? g1 * 32 : t.K;
+    const int k0 = g0 * gs, k1 = g1 < nsg ? g1 * gs : t.K;
     float f[3] = {0.f, 0.f, 0.f}, e3[3] = {0.f, 0.f, 0.f};
     int cnt = 0;
     for (int s0 = k0; s0 < k1; s0 += kStage) {
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(256, 4) k_sweep_direct(const double* __restric
             if (cnt > kListFull) flush_near(t, xw, b, cnt);
         }
     }
-    const int j0 = (g0 > nsg ? g0 - nsg : 0) * 32, j1 = (g1 - nsg) * 32 < t.M ? (g1 - nsg) * 32 : t.M;
+    const int j0 = (g0 > nsg ? g0 - nsg : 0) * gs, j1 = (g1 - nsg) * gs < t.M ? (g1 - nsg) * gs : t.M;
     for (int j = j0; j < j1;) {
         for (; j < j1 && cnt <= kListFull; ++j) {
             const float* e = t.el32 + (size_t)j * kElemStride;
@@ -161,15 +161,14 @@ __global__ void __launch_bounds__(256, 4) k_sweep_direct(const double* __restric
     }
 }
 
+// a block 64 results, each wavefront every fourth chunk
 __global__ void __launch_bounds__(256) k_sweep_sum(const double* __restrict__ part, int nparts, int64_t N, double c0,
                                                    double c1, double c2, float* __restrict__ u)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= 3 * N) return;
-    double v = i % 3 == 0 ? c0 : (i % 3 == 1 ? c1 : c2);
-#pragma unroll 8
-    for (int p = 0; p < nparts; ++p) v += part[(size_t)p * 3 * N + i];
-    u[i] = (float)v;
+    __shared__ double red[3][64];
+    const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+    const double v = sum_chunks(part, nparts, 3 * N, i, red);
+    if (threadIdx.x < 64 && i < 3 * N) u[i] = (float)((i % 3 == 0 ? c0 : (i % 3 == 1 ? c1 : c2)) + v);
 }
 
 // Far sums at the nodes, lane = node.  First the top level: a wavefront a cell, four cells a block share the staged
@@ -409,6 +408,8 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     ProfScope ps_(ctx, PT_SWEEP_MIXED, s);
     if (g.g == 0) {
         const int64_t nb = blocks_for(N, 256);
+        const int gs = direct_group(nb, K, M);
+        const int64_t groups = blocks_for(K, gs) + blocks_for(M, gs);
         const int gpc = groups_per_chunk(groups, nb);
         const int nparts = (int)((groups + gpc - 1) / gpc);
         double* part = nullptr;
@@ -416,10 +417,10 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
             if ((rc = ensure(ctx, ctx->farw, (size_t)nparts * 3 * N * sizeof(double), s))) return rc;
             part = (double*)ctx->farw.ptr;
         }
-        hipLaunchKernelGGL(k_sweep_direct, dim3(nb, nparts), dim3(256), 0, s, x, N, t, gpc, cbar[0], cbar[1], cbar[2],
+        hipLaunchKernelGGL(k_sweep_direct, dim3(nb, nparts), dim3(256), 0, s, x, N, t, gs, gpc, cbar[0], cbar[1], cbar[2],
                            part, u);
         if (part)
-            hipLaunchKernelGGL(k_sweep_sum, dim3(blocks_for(3 * N, 256)), dim3(256), 0, s, (const double*)part, nparts, N,
+            hipLaunchKernelGGL(k_sweep_sum, dim3(blocks_for(3 * N, 64)), dim3(256), 0, s, (const double*)part, nparts, N,
                                cbar[0], cbar[1], cbar[2], u);
         return check_launch(ctx, "sweep_direct");
     }

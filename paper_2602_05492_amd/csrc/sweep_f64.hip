@@ -37,23 +37,23 @@ __device__ inline void add_element(const Tables64& t, int j, double X, double Y,
     f[0] += beta * e[4]; f[1] += beta * e[5]; f[2] += beta * e[6];
 }
 
-// Chunk y takes groups [y gpc, (y + 1) gpc) of 32 segments, then of 32 elements.  part == null (one chunk):
+// Chunk y takes groups [y gpc, (y + 1) gpc) of gs segments, then of gs elements.  part == null (one chunk):
 // u is written here.
-__global__ void __launch_bounds__(256) k_sweep_f64(const double* __restrict__ x, int64_t N, Tables64 t, int gpc,
+__global__ void __launch_bounds__(256) k_sweep_f64(const double* __restrict__ x, int64_t N, Tables64 t, int gs, int gpc,
                                                    double c0, double c1, double c2, double* __restrict__ part,
                                                    double* __restrict__ u)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= N) return;
     const double X = x[2 * i], Y = x[2 * i + 1];
-    const int nsg = (t.K + 31) / 32;
+    const int nsg = (t.K + gs - 1) / gs;
     const int g0 = blockIdx.y * gpc, g1 = g0 + gpc;
-    const int k1 = g1 < nsg ? g1 * 32 : t.K;
+    const int k1 = g1 < nsg ? g1 * gs : t.K;
     double f[3] = {0.0, 0.0, 0.0}, b[3] = {0.0, 0.0, 0.0};
-    for (int k = g0 * 32; k < k1; ++k) add_segment(t, k, X, Y, f);
-    const int j1 = (g1 - nsg) * 32 < t.M ? (g1 - nsg) * 32 : t.M;
+    for (int k = g0 * gs; k < k1; ++k) add_segment(t, k, X, Y, f);
+    const int j1 = (g1 - nsg) * gs < t.M ? (g1 - nsg) * gs : t.M;
 #pragma unroll 2
-    for (int j = (g0 > nsg ? g0 - nsg : 0) * 32; j < j1; ++j) add_element(t, j, X, Y, b);
+    for (int j = (g0 > nsg ? g0 - nsg : 0) * gs; j < j1; ++j) add_element(t, j, X, Y, b);
     const double c[3] = {c0, c1, c2};
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -65,12 +65,10 @@ __global__ void __launch_bounds__(256) k_sweep_f64(const double* __restrict__ x,
 __global__ void __launch_bounds__(256) k_sweep_f64_sum(const double* __restrict__ part, int nparts, int64_t N, double c0,
                                                        double c1, double c2, double* __restrict__ u)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= 3 * N) return;
-    double v = i % 3 == 0 ? c0 : (i % 3 == 1 ? c1 : c2);
-#pragma unroll 8
-    for (int p = 0; p < nparts; ++p) v += part[(size_t)p * 3 * N + i];
-    u[i] = v;
+    __shared__ double red[3][64];
+    const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+    const double v = sum_chunks(part, nparts, 3 * N, i, red);
+    if (threadIdx.x < 64 && i < 3 * N) u[i] = (i % 3 == 0 ? c0 : (i % 3 == 1 ? c1 : c2)) + v;
 }
 
 constexpr int kLowParts = 4;
@@ -215,6 +213,8 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
     ProfScope ps_(ctx, PT_SWEEP_F64, s);
     if (g.g == 0) {
         const int64_t nb = blocks_for(N, 256);
+        const int gs = direct_group(nb, K, M);
+        const int64_t groups = blocks_for(K, gs) + blocks_for(M, gs);
         const int gpc = groups_per_chunk(groups, nb);
         const int nparts = (int)((groups + gpc - 1) / gpc);
         double* part = nullptr;
@@ -222,10 +222,10 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
             if ((rc = ensure(ctx, ctx->farw, (size_t)nparts * 3 * N * sizeof(double), s))) return rc;
             part = (double*)ctx->farw.ptr;
         }
-        hipLaunchKernelGGL(k_sweep_f64, dim3(nb, nparts), dim3(256), 0, s, x, N, t, gpc, cbar[0], cbar[1], cbar[2], part,
+        hipLaunchKernelGGL(k_sweep_f64, dim3(nb, nparts), dim3(256), 0, s, x, N, t, gs, gpc, cbar[0], cbar[1], cbar[2], part,
                            u);
         if (part)
-            hipLaunchKernelGGL(k_sweep_f64_sum, dim3(blocks_for(3 * N, 256)), dim3(256), 0, s, (const double*)part, nparts,
+            hipLaunchKernelGGL(k_sweep_f64_sum, dim3(blocks_for(3 * N, 64)), dim3(256), 0, s, (const double*)part, nparts,
                                N, cbar[0], cbar[1], cbar[2], u);
         return check_launch(ctx, "sweep_f64");
     }
