@@ -76,19 +76,9 @@ __device__ inline double log_ratio_f64(double a, double b, double d)
     return fma((double)e, kLn2Hi, t + fma((double)e, kLn2Lo, t * (z * atanh_poly(z))));
 }
 
-// atan2(y, x): the octant's ratio n / d in [0, 1] is turned by 0, pi/8 or pi/4 (the nearest), as a
-// quotient of the turned terms, and the remaining angle (at most pi/16) by a polynomial.
-__device__ inline double atan2_f64(double y, double x)
+// atan(t) = t + t z p(z), z = t^2, |t| <= tan(pi / 16)
+__device__ inline double atan_poly(double z)
 {
-    const double ax = fabs(x), ay = fabs(y);
-    const double d = fmax(ax, ay), n = fmin(ax, ay);
-    const bool m1 = n > 0.198912367379658 * d, m2 = n > 0.6681786379192989 * d;
-    const double c = m2 ? 1.0 : (m1 ? 0.41421356237309503 : 0.0);
-    const double base = m2 ? 0.7853981633974483 : (m1 ? 0.39269908169872414 : 0.0);
-    const double low = m2 ? 3.061616997868383e-17 : (m1 ? 3.060132146563891e-18 : 0.0);      // atan(c) - base
-    const double num = fma(-c, d, n), den = fma(c, n, d);
-    const double t = d > 0.0 ? div_f64(num, den) : 0.0;
-    const double z = t * t;
     double p = -0.044903172480189366;
     p = fma(p, z, 0.05826811643531537);
     p = fma(p, z, -0.06664480286107828);
@@ -97,8 +87,29 @@ __device__ inline double atan2_f64(double y, double x)
     p = fma(p, z, 0.11111111105850788);
     p = fma(p, z, -0.14285714285694098);
     p = fma(p, z, 0.1999999999999997);
-    p = fma(p, z, -0.3333333333333333);
-    double r = base + (t + fma(t * z, p, low));
+    return fma(p, z, -0.3333333333333333);
+}
+
+// atan2(y, x): the octant's ratio n / d in [0, 1] is turned by 0, pi/8 or pi/4 (the nearest), as a
+// quotient of the turned terms, and the remaining angle (at most pi/16) by a polynomial.  Where every lane's angle
+// is small already (a segment or element five of its lengths away from all samples of the wavefront: most pairs) the
+// turns and quadrants are left out, with the same result: 24 instructions instead of 55.
+__device__ inline double atan2_f64(double y, double x)
+{
+    const double ax = fabs(x), ay = fabs(y);
+    if (__all(ay < 0.198912367379658 * x)) {
+        const double t = div_f64(y, x), z = t * t;
+        return t + fma(t * z, atan_poly(z), 0.0);
+    }
+    const double d = fmax(ax, ay), n = fmin(ax, ay);
+    const bool m1 = n > 0.198912367379658 * d, m2 = n > 0.6681786379192989 * d;
+    const double c = m2 ? 1.0 : (m1 ? 0.41421356237309503 : 0.0);
+    const double base = m2 ? 0.7853981633974483 : (m1 ? 0.39269908169872414 : 0.0);
+    const double low = m2 ? 3.061616997868383e-17 : (m1 ? 3.060132146563891e-18 : 0.0);      // atan(c) - base
+    const double num = fma(-c, d, n), den = fma(c, n, d);
+    const double t = d > 0.0 ? div_f64(num, den) : 0.0;
+    const double z = t * t;
+    double r = base + (t + fma(t * z, atan_poly(z), low));
     r = ay > ax ? 1.5707963267948966 - (r - 6.123233995736766e-17) : r;
     r = x < 0.0 ? 3.141592653589793 - (r - 1.2246467991473532e-16) : r;
     r = __builtin_isunordered(x, y) ? x + y : r;
