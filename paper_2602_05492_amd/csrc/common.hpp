@@ -255,6 +255,10 @@ struct DevF32 {
     __device__ static float atan2(float y, float x)
     {
         const float ax = fabsf(x), ay = fabsf(y);
+        if (__all(ay < 0.2f * x)) {          // most wavefronts (see atan2_f64): atan's series, next term 9e-9 of z
+            const float z = y * __builtin_amdgcn_rcpf(x), s = z * z;
+            return z + z * s * (-3.333333433e-01f + s * (2.000000030e-01f + s * (-1.428571492e-01f + s * 1.111111119e-01f)));
+        }
         const float mx = fmaxf(ax, ay), mn = fminf(ax, ay);
         const float z = mx > 0.0f ? mn * __builtin_amdgcn_rcpf(mx) : 0.0f;
         const float s = z * z;
