@@ -102,7 +102,11 @@ __global__ void k_zero_pad(OutT* __restrict__ Xt, uint16_t* __restrict__ Xlo, in
 //
 // Float64 (Mixed = false), or mixed with near pairs inline in float64: the latter
 // runs only for the samples flagged in `only` (their near-pair list overflowed).
-template <bool Mixed, class OutT>
+//
+// Split = 4 (float64): a block takes 64 points, wavefront w the w-th quarter of the handle's segments, summed
+// in LDS; for few points and handles, whose blocks of 256 points leave most of the chip idle (4 handles x 32 segments
+// and 16,384 points: 256 blocks, 52 us; 1,024, 32 us).
+template <bool Mixed, class OutT, int Split = 1>
 __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, int64_t npts,
                                                   const double* __restrict__ seg64, const float* __restrict__ seg32,
                                                   int H, int S, int model, int64_t gp, double eps2, float eps2f,
@@ -114,9 +118,14 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
     // all points: one per thread; only the flagged ones (only != null): a few blocks stride
     // over the tile, so that a tile with few or no flagged samples costs a small launch
     const int64_t stride = only ? (int64_t)gridDim.x * blockDim.x : npts;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < npts; t += stride) {
+    const int part = Split > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int j0 = S * part / Split, j1 = S * (part + 1) / Split;
+    const int64_t first = Split > 1 ? (int64_t)blockIdx.x * 64 + (threadIdx.x & 63)
+                                    : (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t t = first; t < npts || Split > 1; t += stride) {
         if (only && !only[t]) continue;
-        const double X = x[2 * t], Y = x[2 * t + 1];
+        const int64_t tl = t < npts ? t : npts - 1;
+        const double X = x[2 * tl], Y = x[2 * tl + 1];
         const float Xf = (float)X, Yf = (float)Y;
         A geo[3][8];
         A col[4];
@@ -126,14 +135,16 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
             pv[c][0] = pv[c][1] = A(0);
         }
         for (int q = 0; q < 4; ++q) col[q] = A(0);
-        for (int j = 0; j <= S; ++j) {
-            // contributions to vertex j: a end of segment j (if j < S) + b end of segment j-1 (carried)
+        double tb = (double)j0 / (double)S;
+        for (int j = j0; j <= j1; ++j) {
+            // contributions to vertex j: a end of segment j (if j < j1) + b end of segment j-1 (carried)
+            const double ta = tb;
+            tb = (double)(j + 1) / (double)S;
             A va[3][2] = {{A(0), A(0)}, {A(0), A(0)}, {A(0), A(0)}};
             A vb[3][2] = {{A(0), A(0)}, {A(0), A(0)}, {A(0), A(0)}};
-            if (j < S) {
+            if (j < j1) {
                 const int k = h * S + j;
                 const double* s64 = seg64 + (size_t)k * kSegStride;
-                const double ta = (double)j / (double)S, tb = (double)(j + 1) / (double)S;
                 Moments<A> m{A(0), A(0), A(0), A(0)};
                 bool done = false;
                 if (s64[6] == 0.0) done = true;                  // degenerate segment: nothing
@@ -157,9 +168,11 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
                     const PairState<double> st = pair_forward<double, DevF64, true>(g, X, Y, eps2);
                     const Moments<double> md = pair_moments(g, st);
                     m = Moments<A>{(A)md.da, (A)md.db, (A)md.sa, (A)md.sb};
+                    // the end-point gradient is linear in the channel's end densities: one matrix per pair serves
+                    // the three channels
+                    const GradMatrix<double> G = pair_grad_matrix(g, st, eps2);
                     for (int c = 0; c < 3; ++c) {
-                        const Grad4<double> gr = pair_backward(g, st, eps2, s64[kWdA + c], s64[kWdB + c], s64[kWcA + c],
-                                                               s64[kWcB + c]);
+                        const Grad4<double> gr = grad_apply(G, s64[kWdA + c], s64[kWdB + c], s64[kWcA + c], s64[kWcB + c]);
                         va[c][0] = (A)gr.ax; va[c][1] = (A)gr.ay; vb[c][0] = (A)gr.bx; vb[c][1] = (A)gr.by;
                     }
                 }
@@ -169,7 +182,7 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
                 col[3] += m.sa * (A)ta + m.sb * (A)tb;
             }
             double B[4];
-            vertex_weights(model, (double)j / (double)S, B);
+            vertex_weights(model, ta, B);
             for (int c = 0; c < 3; ++c) {
                 const A gx = va[c][0] + pv[c][0], gy = va[c][1] + pv[c][1];
                 for (int q = 0; q < 4; ++q) {
@@ -180,7 +193,24 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ x, 
                 pv[c][1] = vb[c][1];
             }
         }
+        if constexpr (Split > 1) {
+            __shared__ A red[Split - 1][28][64];
+            const int lane = threadIdx.x & 63;
+            if (part > 0) {
+                for (int c = 0; c < 3; ++c)
+                    for (int q = 0; q < 8; ++q) red[part - 1][8 * c + q][lane] = geo[c][q];
+                for (int q = 0; q < 4; ++q) red[part - 1][24 + q][lane] = col[q];
+            }
+            __syncthreads();
+            if (part > 0 || t >= npts) return;
+            for (int p = 0; p < Split - 1; ++p) {
+                for (int c = 0; c < 3; ++c)
+                    for (int q = 0; q < 8; ++q) geo[c][q] += red[p][8 * c + q][lane];
+                for (int q = 0; q < 4; ++q) col[q] += red[p][24 + q][lane];
+            }
+        }
         store_handle_rows(model, Xt, Xlo, H, h, t, ld, gp, geo, col);
+        if (Split > 1) return;
     }
 }
 
@@ -735,9 +765,11 @@ static int launch_features(bem_ctx* ctx, const double* x, int64_t npts, int H, b
                                Xt, Xlo, ld);
         } else {
             ProfScope ps_(ctx, PT_FEATURES, s);
-            hipLaunchKernelGGL((k_features<false, OutT>), grid, dim3(256), 0, s, x, npts, (const double*)ctx->seg64.ptr,
-                               (const float*)ctx->seg32.ptr, H, S, model, gp, eps2, (float)eps2, near2,
-                               (const uint8_t*)nullptr, Xt, Xlo, ld);
+            const bool split = S >= 8 && (int64_t)grid.x * grid.y < 1024;
+            hipLaunchKernelGGL((split ? k_features<false, OutT, 4> : k_features<false, OutT>),
+                               split ? dim3(blocks_for(npts, 64), H) : grid, dim3(256), 0, s, x, npts,
+                               (const double*)ctx->seg64.ptr, (const float*)ctx->seg32.ptr, H, S, model, gp, eps2, (float)eps2,
+                               near2, (const uint8_t*)nullptr, Xt, Xlo, ld);
         }
     }
     if (H > 0 && gp > L.geo()) {
