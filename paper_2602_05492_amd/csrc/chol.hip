@@ -82,11 +82,13 @@ __device__ inline double bcast16(double v)
 // A panel is one wavefront's: each of its four rows of 16 lanes holds the panel's 16 x 16 diagonal block, three of
 // them 16 rows below it as well and the fourth an identity, so that a pivot's broadcasts (within 16 lanes, no
 // scalar registers) serve the factor, the rows below and the inverse of the 16 x 16 block at once.  Everything else
-// (trailing updates, the inverse's off-diagonal blocks) is float64 MFMA out of LDS, spread over 8 wavefronts.  LDS rows of kLd doubles: the 16 rows x 4 k of an operand read fall in distinct
+// (trailing updates, the inverse's off-diagonal blocks) is float64 MFMA out of LDS, spread over 8 wavefronts, and where
+// nothing waits for it beside the panels.  LDS rows of kLd doubles: the 16 rows x 4 k of an operand read fall in distinct
 // banks.  Operand and accumulator layout of v_mfma_f64_16x16x4f64 (lane l, rr = l mod 16, lk = l / 16): A[rr][lk],
 // B[lk][rr], element q of the accumulator is row 4 q + lk, column rr; so element q of a product is the B operand of
 // k step q of the next product.
-// Measured: 45 us a block of 128, 57 us with its update (blocks of 64 by broadcast sums: 2 x 47 us).
+// Measured: 45 us a block of 128 with its update (55 us with the whole update first and the inverse after; blocks of
+// 64 by broadcast sums: 2 x 47 us); the 8 panels are 15 us of it.
 typedef double d4_t __attribute__((ext_vector_type(4)));
 constexpr int DB = 16, kLd = 68;
 typedef double Tile[NB][kLd];
@@ -124,44 +126,72 @@ __device__ __forceinline__ void panel_factor(double (&a)[DB], double (&b)[DB], b
         ...);
 }
 
-// S [64][64] (lower triangle) -> its factor in place, X (zeros) -> the inverse (lower triangle).  All 8 wavefronts.
-__device__ __forceinline__ void factor_block(Tile& S, Tile& X, bool& bad)
+// Every LDS access before is done, in every wavefront; global stores stay in flight (__syncthreads waits for them).
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// S [64][64] (lower triangle) -> its factor in place, X -> the inverse (lower triangle).  All 8 wavefronts; while one
+// factors panel p the others do side(p).
+template <class Side>
+__device__ __forceinline__ void factor_block(Tile& S, Tile& X, bool& bad, Side side)
 {
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rr = lane & 15, lk = lane >> 4;
+#pragma unroll 1                                     // (unrolled, the code outgrows the instruction cache)
     for (int p = 0; p < NB / DB; ++p) {
         const int d0 = p * DB;
         if (w == 0) {
+            __builtin_amdgcn_s_setprio(3);
             const int r = d0 + DB * (lk + 1) + rr;       // this lane's row below the diagonal block
             const bool below = lk < 3 && r < NB;
             double a[DB], b[DB];
 #pragma unroll
-            for (int k = 0; k < DB; ++k) {
-                const double v = S[d0 + rr][d0 + k], u = S[below ? r : 0][d0 + k];
-                a[k] = k <= rr ? v : 0.0;
-                b[k] = below ? u : (lk == 3 && k == rr ? 1.0 : 0.0);
+            for (int k = 0; k < DB; k += 2) {
+                const d2_t v = *(const d2_t*)&S[d0 + rr][d0 + k], u = *(const d2_t*)&S[below ? r : 0][d0 + k];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    a[k + h] = k + h <= rr ? v[h] : 0.0;
+                    b[k + h] = below ? u[h] : (lk == 3 && k + h == rr ? 1.0 : 0.0);
+                }
             }
             panel_factor(a, b, bad, std::make_integer_sequence<int, DB>{});
+            // (above the diagonal S gets values that nothing reads, X its zeros)
+            if (lk == 0) {
 #pragma unroll
-            for (int k = 0; k < DB; ++k) {
-                if (lk == 0 && k <= rr) S[d0 + rr][d0 + k] = a[k];
-                if (below) S[r][d0 + k] = b[k];
-                if (lk == 3 && k >= rr) X[d0 + k][d0 + rr] = b[k];       // (L^-T)[rr][k]
+                for (int k = 0; k < DB; k += 2) *(d2_t*)&S[d0 + rr][d0 + k] = d2_t{a[k], a[k + 1]};
             }
+            if (below) {
+#pragma unroll
+                for (int k = 0; k < DB; k += 2) *(d2_t*)&S[r][d0 + k] = d2_t{b[k], b[k + 1]};
+            }
+            if (lk == 3) {
+#pragma unroll
+                for (int k = 0; k < DB; ++k) X[d0 + k][d0 + rr] = b[k];       // (L^-T)[rr][k]
+            }
+            __builtin_amdgcn_s_setprio(0);
+        } else {
+            side(p);
         }
-        __syncthreads();
+        lds_barrier();
         // trailing 16 x 16 tiles (I, J), I >= J: S -= L L^T
         const int t = NB / DB - 1 - p;
-        for (int i = w; i < t * (t + 1) / 2; i += 8) {
-            const int I = i < 1 ? 0 : i < 3 ? 1 : 2, J = i - I * (I + 1) / 2;
+        if (w < t * (t + 1) / 2) {
+            const int I = w < 1 ? 0 : w < 3 ? 1 : 2, J = w - I * (I + 1) / 2;
             const int r0 = d0 + DB * (I + 1), c0 = d0 + DB * (J + 1);
             d4_t acc = {0.0, 0.0, 0.0, 0.0};
+            double c[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] = S[r0 + 4 * q + lk][c0 + rr];
 #pragma unroll
             for (int k = 0; k < DB; k += 4) acc = mfma(S[r0 + rr][d0 + k + lk], S[c0 + rr][d0 + k + lk], acc);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) S[r0 + 4 * q + lk][c0 + rr] -= acc[q];
+            for (int q = 0; q < 4; ++q) S[r0 + 4 * q + lk][c0 + rr] = c[q] - acc[q];
         }
-        __syncthreads();
+        if (t > 0) lds_barrier();
     }
     // off-diagonal blocks of the inverse, X_10 = -X_11 (L_10 X_00): of the two 32 x 32 blocks, then of the whole
     if (w < 2) {
@@ -174,20 +204,30 @@ __device__ __forceinline__ void factor_block(Tile& S, Tile& X, bool& bad)
 #pragma unroll
         for (int q = 0; q < 4; ++q) X[o + DB + 4 * q + lk][o + rr] = -v[q];
     }
-    __syncthreads();
+    lds_barrier();
     if (w < 4) {
         const int I = 2 + (w >> 1), J = w & 1;
-        d4_t v = {0.0, 0.0, 0.0, 0.0};
-        for (int K = 2; K <= I; ++K) {
-            d4_t t = {0.0, 0.0, 0.0, 0.0};
-            for (int k = DB * J; k < 2 * DB; k += 4) t = mfma(S[DB * K + rr][k + lk], X[k + lk][DB * J + rr], t);
+        // (L_10 X_00)(K, J), K = 2, 3; X_00's upper block is zero, and skipped
+        d4_t t[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}}, v = t[0];
+        auto add = [&](int k0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v = mfma(X[DB * I + rr][DB * K + 4 * q + lk], t[q], v);
+            for (int k = k0; k < k0 + DB; k += 4)
+#pragma unroll
+                for (int K = 0; K < 2; ++K)
+                    t[K] = mfma(S[DB * (K + 2) + rr][k + lk], X[k + lk][DB * J + rr], t[K]);
+        };
+        if (J == 0) add(0);
+        add(DB);
+#pragma unroll
+        for (int K = 0; K < 2; ++K) {
+            if (K + 2 > I) continue;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v = mfma(X[DB * I + rr][DB * (K + 2) + 4 * q + lk], t[K][q], v);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) X[DB * I + 4 * q + lk][DB * J + rr] = -v[q];
     }
-    __syncthreads();
+    lds_barrier();
 }
 
 // LDS of a step's workgroup: the diagonal block's four tiles, or the slabs [2 groups][2 stages][A, B][64][16] of the
@@ -210,6 +250,9 @@ __device__ inline void loads_landed()
 
 // Update diagonal block kb (128 columns) with the panel of block kb - 1 (kb > 0) and factor it in place (lower
 // triangle); its inverse to inv [128][128].  Rows and columns past the matrix are an identity block.
+// Only the first 64 x 64 block's update is waited for.  Beside its panels, which are one wavefront's, the
+// others update the rest, a quarter of the previous panel's columns each time, and beside the second block's they finish
+// that block's update, take the inverse's first product and store what is done.
 __device__ __forceinline__ void diag_block(double* lds, double* __restrict__ A, int64_t P, int kb, int* __restrict__ flag,
                                            double* __restrict__ inv)
 {
@@ -221,145 +264,209 @@ __device__ __forceinline__ void diag_block(double* lds, double* __restrict__ A, 
     const int nb = (int)(P - o < KB ? P - o : KB);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rr = lane & 15, lk = lane >> 4;
-    // wavefront w takes rows w, w + 8, ... of each block, a lane a column; all loads in flight at once (entries
-    // outside load the block's first element and are then replaced)
-    double g[3][NB / 8];
+    // rows 8 i .. 8 i + 7 of slab s of the previous panel's rows at this block, to row 8 i of sl
+    auto load = [&](int s, int i, double (*sl)[kSlab]) {
+        const int r = 8 * i + (lane >> 3);
+        load_lds(A + (o + (r < nb ? r : 0)) * P + (o - KB) + kSlab * s + slab_pos(r, lane & 7), &sl[8 * i][0]);
+    };
+    // acc += L L^T, 16 x 16 tile (R, C) of a slab
+    auto product = [&](int R, int C, double (*sl)[kSlab], d4_t& acc) {
+        const int ra = DB * R + rr, rb = DB * C + rr;
 #pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-        for (int q = 0; q < NB / 8; ++q) {
-            const int r = (b > 0 ? NB : 0) + w + 8 * q, c = (b > 1 ? NB : 0) + lane;
-            const bool in = r < nb && c <= r;
-            g[b][q] = A[(o + (in ? r : 0)) * P + o + (in ? c : 0)];
-        }
-    // L L^T of the panel's rows at this block: 36 tiles (R, C), C <= R < 8, wavefront w takes w, w + 8, ...
-    d4_t acc[5];
-    int tr[5], tc[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        const int t = w + 8 * i;
-        int R = 0;
-        while ((R + 1) * (R + 2) / 2 <= t) ++R;
-        tr[i] = R;
-        tc[i] = t - R * (R + 1) / 2;
-        acc[i] = d4_t{0.0, 0.0, 0.0, 0.0};
-    }
-    if (kb > 0) {
-        double(*sl)[KB][kSlab] = (double(*)[KB][kSlab])&B1;        // two stages
-        const double* gp[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = 16 * w + 8 * i + (lane >> 3);
-            gp[i] = A + (o + (r < nb ? r : 0)) * P + (o - KB) + slab_pos(r, lane & 7);
-        }
-        auto load = [&](int buf, int s) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) load_lds(gp[i] + kSlab * s, &sl[buf][16 * w + 8 * i][0]);
-        };
-        load(0, 0);
-        loads_landed();
-        for (int s = 0; s < KB / kSlab; ++s) {
-            const int cur = s & 1;
-            if (s + 1 < KB / kSlab) load(cur ^ 1, s + 1);
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                if (w + 8 * i >= 36) continue;
-                const int ra = DB * tr[i] + rr, rb = DB * tc[i] + rr;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const d2_t a = *(const d2_t*)&sl[cur][ra][slab_pos(ra, 4 * h + lk)];
-                    const d2_t b = *(const d2_t*)&sl[cur][rb][slab_pos(rb, 4 * h + lk)];
-                    acc[i] = mfma(a[0], b[0], acc[i]);
-                    acc[i] = mfma(a[1], b[1], acc[i]);
-                }
-            }
-            loads_landed();
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-        for (int q = 0; q < NB / 8; ++q) {
-            const int r = (b > 0 ? NB : 0) + w + 8 * q, c = (b > 1 ? NB : 0) + lane;
-            const double v = r < nb && c <= r ? g[b][q] : (r == c && r >= nb ? 1.0 : 0.0);
-            Tile& T = b == 0 ? B0 : b == 1 ? S10 : S11;
-            T[w + 8 * q][lane] = v;
-            if (b == 0) B1[w + 8 * q][lane] = 0.0;
-        }
-    __syncthreads();
-    if (kb > 0) {
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            if (w + 8 * i >= 36) continue;
-            Tile& T = tr[i] < 4 ? B0 : tc[i] < 4 ? S10 : S11;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (DB * tr[i] + 4 * q + lk < nb) T[(DB * tr[i] & 63) + 4 * q + lk][(DB * tc[i] & 63) + rr] -= acc[i][q];
-        }
-        __syncthreads();
-    }
-    bool bad = false;
-    factor_block(B0, B1, bad);                     // B0 = L_00, B1 = X_00
-    // L_10 = S_10 X_00^T: two 16 x 16 tiles a wavefront
-    const int I = w & 3, Ja = w >> 2, Jb = 3 - Ja;
-    d4_t t0 = {0.0, 0.0, 0.0, 0.0}, t1 = t0;
-    for (int k = 0; k < DB * (Ja + 1); k += 4) t0 = mfma(S10[DB * I + rr][k + lk], B1[DB * Ja + rr][k + lk], t0);
-    for (int k = 0; k < DB * (Jb + 1); k += 4) t1 = mfma(S10[DB * I + rr][k + lk], B1[DB * Jb + rr][k + lk], t1);
-    auto put = [&](const Tile& T, int r0, int c0) {
-#pragma unroll
-        for (int q = 0; q < NB / 8; ++q) {
-            const int r = r0 + w + 8 * q, c = c0 + lane;
-            if (r < nb && c <= r) A[(o + r) * P + o + c] = T[w + 8 * q][lane];
+        for (int h = 0; h < 2; ++h) {
+            const d2_t a = *(const d2_t*)&sl[ra][slab_pos(ra, 4 * h + lk)];
+            const d2_t b = *(const d2_t*)&sl[rb][slab_pos(rb, 4 * h + lk)];
+            acc = mfma(a[0], b[0], acc);
+            acc = mfma(a[1], b[1], acc);
         }
     };
-    put(B0, 0, 0);
-    __syncthreads();
+    // tile (R, C) of the matrix (outside it the first element is read and then replaced), and less acc into LDS
+    auto read = [&](int R, int C, double (&v)[4]) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        S10[DB * I + 4 * q + lk][DB * Ja + rr] = t0[q];
-        S10[DB * I + 4 * q + lk][DB * Jb + rr] = t1[q];
+        for (int q = 0; q < 4; ++q) {
+            const int r = DB * R + 4 * q + lk, c = DB * C + rr;
+            const bool in = r < nb && c <= r;
+            v[q] = A[(o + (in ? r : 0)) * P + o + (in ? c : 0)];
+        }
+    };
+    auto place = [&](int R, int C, const double (&v)[4], const d4_t& acc) {
+        Tile& T = R < 4 ? B0 : C < 4 ? S10 : S11;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = DB * R + 4 * q + lk, c = DB * C + rr;
+            T[r & (NB - 1)][c & (NB - 1)] = r >= nb ? (r == c ? 1.0 : 0.0) : c <= r ? v[q] - acc[q] : 0.0;
+        }
+    };
+    constexpr int kFirst = 10, kTiles = 36;          // tiles (R, C), C <= R < 8, row by row; those of the first block
+    auto tile_of = [](int t, int& R, int& C) {
+        R = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : t < 10 ? 3 : t < 15 ? 4 : t < 21 ? 5 : t < 28 ? 6 : 7;
+        C = t - R * (R + 1) / 2;
+    };
+    // the first block's rows whole in B1 and S10, the first quarter of all rows in S11; quarters 1 and 3 go to S10
+    constexpr int kSlabs = KB / kSlab, kQuarter = kSlabs / (NB / DB), kRows8 = KB / 8;
+    double(*whole)[NB][kSlab] = (double(*)[NB][kSlab])&B1;
+    double(*quarter[2])[KB][kSlab] = {(double(*)[KB][kSlab])&S11, (double(*)[KB][kSlab])&S10};
+    static_assert(kSlabs * sizeof(*whole) <= 2 * sizeof(Tile) && kQuarter * sizeof(*quarter[0]) <= sizeof(Tile), "");
+    if (kb > 0) {
+#pragma unroll
+        for (int s = 0; s < kSlabs; ++s) load(s, w, whole[s]);
+#pragma unroll
+        for (int j = 0; j < kQuarter * kRows8 / 8; ++j) load(j >> 1, w + 8 * (j & 1), quarter[0][j >> 1]);
     }
-#pragma unroll
-    for (int q = 0; q < NB / 8; ++q) B0[w + 8 * q][lane] = 0.0;
-    __syncthreads();
-    // S_11 -= L_10 L_10^T
-    for (int i = w; i < 10; i += 8) {
-        const int R = i < 1 ? 0 : i < 3 ? 1 : i < 6 ? 2 : 3, C = i - R * (R + 1) / 2;
-        d4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < NB; k += 4) acc = mfma(S10[DB * R + rr][k + lk], S10[DB * C + rr][k + lk], acc);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) S11[DB * R + 4 * q + lk][DB * C + rr] -= acc[q];
-    }
-    put(S10, NB, 0);
-    __syncthreads();
-    factor_block(S11, B0, bad);                    // S11 = L_11, B0 = X_11
-    put(S11, NB, NB);
-    if (tid == 0 && bad) flag[0] = 1;
-    // X_10 = -X_11 (L_10 X_00): wavefront w column tile w mod 4, row tiles 0, 1 or 2, 3
     {
-        const int J = w & 3, I0 = 2 * (1 - (w >> 2));
-        d4_t v[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-        for (int K = 0; K <= I0 + 1; ++K) {
-            d4_t t = {0.0, 0.0, 0.0, 0.0};
-            for (int k = DB * J; k < NB; k += 4) t = mfma(S10[DB * K + rr][k + lk], B1[k + lk][DB * J + rr], t);
+        double v[2][4];
+        d4_t acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+        int R[2], C[2];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                v[1] = mfma(B0[DB * (I0 + 1) + rr][DB * K + 4 * q + lk], t[q], v[1]);
-                if (K <= I0) v[0] = mfma(B0[DB * I0 + rr][DB * K + 4 * q + lk], t[q], v[0]);
+        for (int i = 0; i < 2; ++i) {
+            tile_of(w + 8 * i < kFirst ? w + 8 * i : 0, R[i], C[i]);
+            read(R[i], C[i], v[i]);
+        }
+        if (kb > 0) {
+            loads_landed();
+#pragma unroll
+            for (int s = 0; s < kSlabs; ++s) {
+                product(R[0], C[0], whole[s], acc[0]);
+                if (w + 8 < kFirst) product(R[1], C[1], whole[s], acc[1]);
             }
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) inv[(NB + DB * (I0 + i) + 4 * q + lk) * KB + DB * J + rr] = -v[i][q];
+        place(R[0], C[0], v[0], acc[0]);
+        if (w + 8 < kFirst) place(R[1], C[1], v[1], acc[1]);
+        lds_barrier();
     }
+    bool bad = false;
+    // the other 26: four for wavefronts 1 to 3 and 5 to 7, two for 4, which shares the panel's SIMD
+    constexpr int kSide = 4;
+    const int side = w == 0 ? kTiles : w == 4 ? kTiles - 2 : kFirst + w - (w < 4 ? 1 : 2), side_step = w == 4 ? 1 : 6;
+    d4_t acc[kSide];
+    double v[kSide][4];
+    int tr[kSide], tc[kSide];
 #pragma unroll
-    for (int q = 0; q < NB / 8; ++q) {
-        const int r = w + 8 * q;
-        inv[r * KB + lane] = B1[r][lane];
-        inv[r * KB + NB + lane] = 0.0;
-        inv[(NB + r) * KB + NB + lane] = B0[r][lane];
+    for (int i = 0; i < kSide; ++i) {
+        acc[i] = d4_t{0.0, 0.0, 0.0, 0.0};
+        const int t = side + side_step * i;
+        tile_of(t < kTiles ? t : kTiles - 1, tr[i], tc[i]);
+    }
+    factor_block(B0, B1, bad, [&](int p) {           // B0 = L_00, B1 = X_00
+        if (kb > 0) {
+            if (p + 1 < NB / DB)
+                for (int j = w - 1; j < kQuarter * kRows8; j += 7)
+                    load(kQuarter * (p + 1) + j / kRows8, j % kRows8, quarter[(p + 1) & 1][j / kRows8]);
+#pragma unroll
+            for (int s = 0; s < kQuarter; ++s)
+#pragma unroll
+                for (int i = 0; i < kSide; ++i)
+                    if (side + side_step * i < kTiles) product(tr[i], tc[i], quarter[p & 1][s], acc[i]);
+        }
+        if (p + 1 == NB / DB) {
+#pragma unroll
+            for (int i = 0; i < kSide; ++i) read(tr[i], tc[i], v[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0);               // the next quarter has landed
+    });
+    // rows first, first + step, ... of a factor's tile to the matrix
+    auto put = [&](const Tile& T, int r0, int c0, int first, auto step) {
+#pragma unroll
+        for (int i = 0; i < NB; i += decltype(step)::value) {
+            const int r = r0 + i + first, c = c0 + lane;
+            const double x = T[i + first][lane];
+            if (r < nb && c <= r) A[(o + r) * P + o + c] = x;
+        }
+    };
+    put(B0, 0, 0, w, std::integral_constant<int, 8>{});
+#pragma unroll
+    for (int i = 0; i < kSide; ++i)
+        if (side + side_step * i < kTiles) place(tr[i], tc[i], v[i], acc[i]);
+    lds_barrier();
+    // L_10 = S_10 X_00^T: two 16 x 16 tiles a wavefront, columns J and 3 - J
+    const int I = w & 3;
+    d4_t t0 = {0.0, 0.0, 0.0, 0.0}, t1 = t0;
+    auto solve = [&](auto first) {
+        constexpr int Ja = decltype(first)::value, Jb = 3 - Ja;
+#pragma unroll
+        for (int k = 0; k < DB * (Jb + 1); k += 4) {
+            const double a = S10[DB * I + rr][k + lk];
+            if (k < DB * (Ja + 1)) t0 = mfma(a, B1[DB * Ja + rr][k + lk], t0);
+            t1 = mfma(a, B1[DB * Jb + rr][k + lk], t1);
+        }
+    };
+    if (w < 4) solve(std::integral_constant<int, 0>{});
+    else solve(std::integral_constant<int, 1>{});
+    lds_barrier();
+    {
+        const int Ja = w >> 2, Jb = 3 - Ja;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = DB * I + 4 * q + lk;
+            S10[r][DB * Ja + rr] = t0[q];
+            S10[r][DB * Jb + rr] = t1[q];
+            if (NB + r < nb) {
+                A[(o + NB + r) * P + o + DB * Ja + rr] = t0[q];
+                A[(o + NB + r) * P + o + DB * Jb + rr] = t1[q];
+            }
+        }
+    }
+    lds_barrier();
+    // S_11 -= L_10 L_10^T: the first tile column now, the other six tiles beside the first panel
+    auto reduce = [&](int R, int C) {
+        d4_t s[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int k = 0; k < NB; k += 4)
+            s[(k >> 2) & 1] = mfma(S10[DB * R + rr][k + lk], S10[DB * C + rr][k + lk], s[(k >> 2) & 1]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) S11[DB * R + 4 * q + lk][DB * C + rr] -= s[0][q] + s[1][q];
+    };
+    if (w < 4) reduce(w, 0);
+    lds_barrier();
+    // wavefronts 4 to 7: tile column J of T = L_10 X_00, in registers; 1 to 3: X_00 to inv
+    const int J = 7 - w;
+    d4_t T[NB / DB];
+#pragma unroll
+    for (int K = 0; K < NB / DB; ++K) T[K] = d4_t{0.0, 0.0, 0.0, 0.0};
+    factor_block(S11, B0, bad, [&](int p) {          // S11 = L_11, B0 = X_11
+        if (p == 0 && w < 7) {
+            const int R = w < 2 ? 1 : w < 4 ? 2 : 3;
+            reduce(R, w - R * (R - 1) / 2);
+        }
+        if (w >= 4) {
+            d4_t t = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k0 = 0; k0 < NB; k0 += DB) {
+                if (k0 < DB * J) continue;           // X_00 is zero there
+#pragma unroll
+                for (int k = k0; k < k0 + DB; k += 4)
+                    t = mfma(S10[DB * p + rr][k + lk], B1[k + lk][DB * J + rr], t);
+            }
+#pragma unroll
+            for (int K = 0; K < NB / DB; ++K)
+                if (K == p) T[K] = t;
+        } else {
+            for (int i = DB * p + w - 1; i < DB * (p + 1); i += 3) {
+                inv[i * KB + lane] = lane <= i ? B1[i][lane] : 0.0;
+                inv[i * KB + NB + lane] = 0.0;
+            }
+        }
+    });
+    if (tid == 0 && bad) flag[0] = 1;
+    if (w >= 4) {                                    // X_10 = -X_11 T
+#pragma unroll
+        for (int i = 0; i < NB / DB; ++i) {
+            d4_t x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int K = 0; K <= i; ++K)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x = mfma(B0[DB * i + rr][DB * K + 4 * q + lk], T[K][q], x);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) inv[(NB + DB * i + 4 * q + lk) * KB + DB * J + rr] = -x[q];
+        }
+    } else {
+        put(S11, NB, NB, w, std::integral_constant<int, 4>{});
+#pragma unroll
+        for (int i = 0; i < NB; i += 4) {
+            const double x = B0[i + w][lane];
+            inv[(NB + i + w) * KB + NB + lane] = lane <= i + w ? x : 0.0;
+        }
     }
 }
 
