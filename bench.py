@@ -32,8 +32,8 @@ sys.path.insert(0, ROOT)
 METRIC = "sample×segment pairs/s and LM steps/s, FP32-mixed vs FP64 at 1e-4 color err"
 PEAKS = {"fp32_vector": 157.3e12, "fp64_vector": 78.6e12, "fp32_mfma": 157.3e12, "fp64_mfma": 78.6e12,
          "bf16_mfma": 2.5e15}
-# Counters of the hot kernels (rocprofv3 --pmc passes over `bench.py --pmc-probe`: two 32,768-sample
-# tiles of the LM workload, kernels serialised), each with the SHA-256 of the sources it was taken from
+# Counters of kernels that sum pairs directly, if recorded (rocprofv3 --pmc passes over `bench.py --pmc-probe`,
+# kernels serialised), each with the SHA-256 of the sources it was taken from
 PMC_FILE = os.path.join(ROOT, "profiles", "lm_workload_counters.json")
 CSRC = os.path.join(ROOT, "paper_2602_05492_amd", "csrc")
 GRAM_TILE = 32768          # samples per split-BF16 Gram launch (the library's default tile)
@@ -164,9 +164,8 @@ def valu_fraction(kernel: str, pairs_per_s_in_step):
 
 
 def pmc_probe() -> int:
-    """Small run for counters: one mixed split-BF16 LM step of the LM workload on batch 0 (its forward
-    sweeps on the cell-ordered samples, its 64 J tiles of 32,768 samples and their Gram launches,
-    exactly as in the timed step), one mixed adjoint of the adjoint workload (4,194,304 samples, as
+    """Small run for counters: one mixed split-BF16 LM step of the LM workload on batch 0,
+    exactly as in the timed step, one mixed adjoint of the adjoint workload (4,194,304 samples, as
     `--workload adjoint` times it; the cotangent's values do not change the work), then a plain
     256 MiB device copy whose counters calibrate FETCH_SIZE / WRITE_SIZE."""
     import torch

@@ -69,7 +69,9 @@ typedef enum {
 } bem_status;
 
 /* Arithmetic of the sample x segment sweeps.
- * FP64 : every pair in float64; u and cotangents are float64.
+ * FP64 : every pair in float64; u and cotangents are float64.  With many samples bem_eval
+ *        sums the far segments and outer elements of a grid cell at its 256 Chebyshev nodes
+ *        and interpolates (within 1e-14 of a segment's part).
  * MIXED: pairs in float32 except near-singular pairs (both segment end points
  *        within max(2 nf, nf + 1)*L of the sample, nf = near_factor, which
  *        contains every sample closer than nf*L to the segment), which are
@@ -87,7 +89,8 @@ typedef enum {
  *        of context workspace; samples outside the outer boundary's bounding box are
  *        evaluated against every segment); the segments and outer elements two
  *        cell widths off a cell, none of whose pairs there is near, are summed at the cell's 64
- *        Chebyshev nodes and interpolated (relative error below 1e-7).  Float32 pairs of the
+ *        Chebyshev nodes and interpolated (relative error below 1e-7), or at those of the largest
+ *        of up to three levels of cells they are as far from.  Float32 pairs of the
  *        interpolated sums and of the adjoint use Gauss-Legendre quadrature.
  *        lm_step and bem_jtj list their near pairs with a per-context capacity
  *        per 64 samples (1024 at first, at most 16384 and 4 GiB of list); the
@@ -367,7 +370,7 @@ int bem_get_matrix(bem_ctx* ctx, int32_t which, double* out, hipStream_t stream)
 /* Number of outer elements M (host); 0 for a null context. */
 int32_t bem_num_elements(const bem_ctx* ctx);
 
-/* Near-pair list capacity of the MIXED sweeps in slots per 64 samples (the
+/* Near-pair list capacity of the MIXED J tiles (lm_step, bem_jtj) in slots per 64 samples (the
  * description of bem_prec says how it grows); 0 for a null context. */
 int32_t bem_near_capacity(const bem_ctx* ctx);
 
@@ -379,7 +382,7 @@ int bem_factor_info(const bem_ctx* ctx, double* sigma_n, double* shift);
  * bem_profile_read waits for the recorded events and returns the total time in
  * milliseconds and the number of launches of one kernel family (tag in
  * [0, 12): 0 sweep_f64, 1 sweep_mixed, 2 vjp_segments, 3 vjp_elements,
- * 4 features, 5 beta_rows, 6 gram_f64, 7 gram_mfma, 8 xr, 9 cholesky,
+ * 4 features, 5 beta_rows, 6 gram_f64, 7 gram_mfma, 8 xr (not used), 9 cholesky,
  * 10 boundary, 11 near_pairs); bem_profile_name gives the family's name (static string,
  * "" for a bad tag).  Errors: EINVAL (null context or bad tag). */
 int bem_profile(bem_ctx* ctx, int32_t enable);

@@ -21,8 +21,8 @@
 // Rounding.  The split-bfloat16 products of E average over the samples as those of the Gram over all
 // samples do; the fewer columns Y and Z carry 22 and 24 bits instead of 16.  Accumulation in float32 within a
 // run and in float64 beyond is the same.  Pairs by quadrature (seg_math.hpp), so near factors of at least 1.
-// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 9.6 ms, far features
-// 5.4 ms, near Gram 2.9 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
+// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 8.7 ms, far features
+// 5.4 ms, near Gram 2.9 ms, near features 5.5 ms, where the tiles over all samples took 360 ms.  Error of the
 // step against float64: 7.5e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
 #include <algorithm>
 #include <cmath>
