@@ -268,14 +268,41 @@ __global__ void __launch_bounds__(256) k_adj_far_elements(const float* __restric
     }
 }
 
-constexpr int kAdjCap = 320, kAdjFull = kAdjCap - 64;
+constexpr int kAdjTake = 4, kAdjCap = 512, kAdjFull = kAdjCap - 64 * kAdjTake;
 constexpr int kSumLd = kV + 1;
+
+// Appends (sample << 6 | lane) of the near pairs of samples s, s + 1, ... to the list until it is full or the samples
+// end; returns the next sample.  Four at a time: one by one, each sample's record is waited for.
+template <class Near>
+__device__ inline int list_near(const float* __restrict__ rec, int s, int ns, uint32_t* list, int& cnt, Near near)
+{
+    const int lane = threadIdx.x;
+    for (; s < ns && cnt <= kAdjFull; s += kAdjTake) {
+        bool n[kAdjTake];
+        bool any = false;
+#pragma unroll
+        for (int q = 0; q < kAdjTake; ++q) {
+            const float* r = rec + (s + q < ns ? s + q : s) * kRec;
+            n[q] = (s + q < ns) & near(r[0], r[1]);
+            any |= n[q];
+        }
+        if (__ballot(any) == 0) continue;
+#pragma unroll
+        for (int q = 0; q < kAdjTake; ++q) {
+            const uint64_t mask = __ballot(n[q]);
+            if (n[q]) list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = ((uint32_t)(s + q) << 6) | lane;
+            cnt += __popcll(mask);
+        }
+    }
+    return s < ns ? s : ns;
+}
 
 // A run of samples against the segments and elements whose near bits are set (bits == null: all of
 // them).  One wavefront a block: it counts the set bits of 64 words at a time and takes every
 // gridDim.y-th group of 64 of them (groups hold one kind: segments, or elements), a lane each.
 // Singular = false: the pairs outside the near radius, in float32.  Singular = true: only those inside
-// it, listed in LDS and evaluated in float64 a pair a lane; a kernel of its own, so that the float32
+// it, listed in LDS and evaluated in float64 a pair a lane (bound by its waits, 1.37 ms at 4,194,304 samples x 8,192
+// segments, 1.54 with the samples tested one by one); a kernel of its own, so that the float32
 // loop keeps twice the wavefronts (the test it repeats is 10 of 330 instructions a pair).
 template <bool Singular, bool Quad>
 __global__ void __launch_bounds__(64, Singular ? 2 : 4)
@@ -346,14 +373,9 @@ __global__ void __launch_bounds__(64, Singular ? 2 : 4)
                 if constexpr (Singular) {
                     int cnt = 0;
                     for (int s = 0; s < ns;) {
-                        for (; s < ns && cnt <= kAdjFull; ++s) {
-                            const float* r = rec + s * kRec;
-                            const bool near = some & near_segment(g.ax, g.ay, g.bx, g.by, g.L2, r[0], r[1], near2);
-                            const uint64_t mask = __ballot(near);
-                            if (mask == 0) continue;
-                            if (near) list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = ((uint32_t)s << 6) | lane;
-                            cnt += __popcll(mask);
-                        }
+                        s = list_near(rec, s, ns, list, cnt, [&](float X, float Y) {
+                            return some & near_segment(g.ax, g.ay, g.bx, g.by, g.L2, X, Y, near2);
+                        });
                         __threadfence_block();
                         for (int e = lane; e < cnt; e += 64) {
                             const int sl = list[e] >> 6, ln = list[e] & 63;
@@ -395,14 +417,9 @@ __global__ void __launch_bounds__(64, Singular ? 2 : 4)
                 if constexpr (Singular) {
                     int cnt = 0;
                     for (int s = 0; s < ns;) {
-                        for (; s < ns && cnt <= kAdjFull; ++s) {
-                            const float* r = rec + s * kRec;
-                            const bool near = own & near_element(ax, ay, vx, vy, r[0], r[1], near2);
-                            const uint64_t mask = __ballot(near);
-                            if (mask == 0) continue;
-                            if (near) list[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = ((uint32_t)s << 6) | lane;
-                            cnt += __popcll(mask);
-                        }
+                        s = list_near(rec, s, ns, list, cnt, [&](float X, float Y) {
+                            return own & near_element(ax, ay, vx, vy, X, Y, near2);
+                        });
                         __threadfence_block();
                         for (int n = lane; n < cnt; n += 64) {
                             const int sl = list[n] >> 6, ln = list[n] & 63;
