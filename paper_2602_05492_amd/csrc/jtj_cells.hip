@@ -15,6 +15,7 @@
 //   k_cell_basis      Q in split bfloat16, 32-sample blocks
 //   k_near_features   E in split bfloat16, 32-sample blocks; pairs within the near radius in float64
 //   k_near_project    Z on bf16 MFMA
+//   k_far_parents     V's part of the segments far from 2 x 2 cells, at the nodes of those
 //   k_far_features    V at the nodes, times R, plus Z: Y in float32
 //   k_split_half      Y as scaled float16 pairs
 //   launch_gram_half  Y Y^T, launch_gram_cells: E E^T - Z Z^T, added into the same float64 Gram
@@ -22,8 +23,8 @@
 // samples do; the fewer columns Y and Z carry 22 and 24 bits instead of 16.  Accumulation in float32 within a
 // run and in float64 beyond is the same.  Pairs by quadrature (seg_math.hpp), so near factors of at least 1.
 // Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 8.7 ms, far features
-// 5.4 ms, near Gram 2.9 ms, near features 5.5 ms, where the tiles over all samples took 360 ms.  Error of the
-// step against float64: 7.5e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
+// 3.3 ms, near Gram 2.9 ms, near features 5.5 ms, where the tiles over all samples took 360 ms.  Error of the
+// step against float64: 8.1e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
 #include <algorithm>
 #include <cmath>
 #include <numeric>
@@ -471,46 +472,185 @@ __device__ inline float half_max(float v)
     return v;
 }
 
-// Y of one cell: block (cell, part), four wavefronts that share the cell's R.  A wavefront takes up to 32 rows at a time
-// (a cubic handle, two straight ones, 32 elements): the far part at the 64 nodes (lane = node) into LDS, times R on
-// float32 MFMA, plus Z on near rows; float32 to Yf.  rmax: largest magnitude of every row, as float bits; an atomic
-// only where the value read beforehand is smaller.  LDS rows of kFarLd floats: 32 rows at one pair of nodes fall in
-// distinct banks.  Bound by the vector ALUs (the pairs); with the product by vector ALU out of LDS and an atomic a row and
-// cell 7.7 ms (8,192 segments, 1,296 cells) and 1.38 ms (500 straight handles, 289 cells), now 5.4 and 0.54 ms.
+// Rows of an item: a cubic handle, two straight ones, or 32 elements.
 constexpr int kFarLd = 66;
+struct FarItems {
+    int H, S, M, model, seg_words, per, handles, all;    // handles an item, items of handles, items
+    __host__ __device__ FarItems(int H_, int S_, int M_, int model_, int seg_words_)
+        : H(H_), S(S_), M(M_), model(model_), seg_words(seg_words_), per(model_ == 1 ? 2 : 1), handles((H_ + per - 1) / per),
+          all(handles + (M_ + 31) / 32)
+    {
+    }
+    // whether any of the item's segments or elements is far in a row of far bits
+    __device__ bool any(int it, const uint32_t* __restrict__ far) const
+    {
+        if (it >= handles) return far[seg_words + it - handles] != 0;
+        const int a = it * per * S, h1 = (it + 1) * per < H ? (it + 1) * per : H, e = h1 * S;
+        uint32_t some = 0;
+        for (int k0 = a; k0 < e; k0 = (k0 | 31) + 1) some |= word(far, k0, e);
+        return some != 0;
+    }
+    // far segments k0 .. e - 1 in the word that holds k0
+    __device__ static uint32_t word(const uint32_t* __restrict__ far, int k0, int e)
+    {
+        uint32_t w = far[k0 >> 5] & (~0u << (k0 & 31));
+        if (e <= (k0 | 31)) w &= (1u << (e & 31)) - 1u;
+        return w;
+    }
+};
+
+// The item's rows over the far pairs of a row of far bits at the node (X, Y) of this lane, to v[row][lane].
+__device__ __forceinline__ void far_rows(const FarItems& I, int it, const uint32_t* __restrict__ far, float X, float Y,
+                                         float short_len, float eps2f, const float* __restrict__ seg32,
+                                         const float* __restrict__ el32, const float* __restrict__ vtab, float (*v)[kFarLd])
+{
+    const int lane = threadIdx.x & 63;
+    if (it >= I.handles) {
+        const int j0 = (it - I.handles) * 32;
+        const uint32_t w = far[I.seg_words + it - I.handles];
+#pragma unroll 4
+        for (int i = 0; i < 32; ++i) {
+            float b = 0.0f;
+            if ((w >> i) & 1u) {
+                const float* e = el32 + (size_t)(j0 + i) * kElemStride;
+                b = element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y);
+            }
+            v[i][lane] = b;
+        }
+        return;
+    }
+    for (int sub = 0; sub < I.per; ++sub) {
+        const int h = it * I.per + sub;
+        float geo[3][8], col[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) geo[q][k] = 0.f;
+        const int k1 = h < I.H ? (h + 1) * I.S : 0;
+        for (int k0 = h * I.S; k0 < k1; k0 = (k0 | 31) + 1)
+            for (uint32_t w = FarItems::word(far, k0, k1); w; w &= w - 1u) {
+                const int k = (k0 & ~31) + __builtin_ctz(w);
+                const float* s = seg32 + (size_t)k * kSegStride;
+                const float* B = vtab + 8 * (k - h * I.S);
+                if (s[kLen] <= short_len) add_pair_features<4>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+                else add_pair_features<6>(s, B, B + 8, X, Y, eps2f, true, geo, col);
+            }
+        if (I.model == 1) {
+            float(*u)[kFarLd] = v + 14 * sub;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) u[4 * q + k][lane] = geo[q][k];
+            u[12][lane] = col[0] + col[1];
+            u[13][lane] = col[2] + col[3];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[8 * q + k][lane] = geo[q][k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[24 + k][lane] = col[k];
+        }
+    }
+}
+
+// Two levels save an item the pairs that are far from the 2 x 2 cells above and cost it a second product, which takes as
+// long as some six pairs, and a launch: where an item has 16 segments or more and a quarter of the grid at most lies within
+// reach of a cell above.  Steps at one level and at two: 256 cubic handles x 32 segments and 2,097,152 samples (36 cells
+// a side) 41.5 and 39.6 ms, 128 x 32 and 262,144 (20) 10.25 and 10.15, 32 x 16 (20) 3.88 and 3.87, 128 x 32 and 65,536 (14)
+// 7.65 and 7.70; 500 straight handles (two segments an item, 16) 10.45 and 10.53.
+bool two_levels(int g, int S, int model) { return S * (model == 1 ? 2 : 1) >= 16 && g >= 20; }
+
+// Far rows of the cells of 2 x 2 at their own nodes: block (cell, part), a wavefront an item at a time.  To Vp, 16 steps
+// of 64 lanes' pairs an item, in the operand order of the product in k_far_features.
 __global__ void __launch_bounds__(256, 2)
-    k_far_features(CellGrid g, const int* __restrict__ off, const CellInfo* __restrict__ ci,
-                   const int* __restrict__ hpos, const int* __restrict__ epos, const uint32_t* __restrict__ bits, int words,
-                   int seg_words, Layout L, int S, int M, int model, const float* __restrict__ seg32,
-                   const float* __restrict__ el32, const float* __restrict__ vtab, float eps2f, const float* __restrict__ Rf,
-                   const float* __restrict__ Zf, int64_t W, int stride, float* __restrict__ Yf,
-                   uint32_t* __restrict__ rmax)
+    k_far_parents(CellGrid g, CellLevels lv, const int* __restrict__ off, const uint32_t* __restrict__ far, int words,
+                  FarItems I, const float* __restrict__ seg32, const float* __restrict__ el32, const float* __restrict__ vtab,
+                  float eps2f, float2* __restrict__ Vp)
+{
+    __shared__ float V[4][32][kFarLd];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 31, lk = lane >> 5;
+    const int cx = blockIdx.x % lv.nx[1], cy = blockIdx.x / lv.nx[1];
+    if (!level_used(lv, off, 1, cx, cy)) return;
+    float(*v)[kFarLd] = V[wv];
+    for (int i = 28; i < 32; ++i) v[i][lane] = 0.0f;
+    double Xd, Yd;
+    level_node<kFarQ>(g, 1, cx, cy, lane, Xd, Yd);
+    const uint32_t* row = far + (size_t)level_row(lv, 1, cx, cy) * words;
+    for (int it = wv + 4 * blockIdx.y; it < I.all; it += 4 * gridDim.y) {
+        if (!I.any(it, row)) continue;
+        far_rows(I, it, row, (float)Xd, (float)Yd, (float)(2.0 * kFarCells * g.h / kQuadFar), eps2f, seg32, el32, vtab, v);
+        __threadfence_block();
+        float2* o = Vp + ((size_t)blockIdx.x * I.all + it) * (16 * 64) + lane;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) o[64 * s] = *reinterpret_cast<const float2*>(&v[li][4 * s + 2 * lk]);
+        __threadfence_block();
+    }
+}
+
+// Y of one cell: block (cell, part), four wavefronts that share the cell's R.  A wavefront takes an item (up to 32 rows)
+// at a time: the far part at the 64 nodes (lane = node) into LDS, times R on float32 MFMA, plus Z on near rows; float32
+// to Yf.  With two levels (lv.n = 2) the pairs far from the 2 x 2 cells above are in Vp at that cell's nodes, times A^T R
+// with A the child's values of its nodes' polynomials.  rmax: largest magnitude of every row, as float bits; an atomic
+// only where the value read beforehand is smaller.  LDS rows of kFarLd floats: 32 rows at one pair of nodes fall in
+// distinct banks.  One level was bound by the vector ALUs (the pairs): 5.4 ms (8,192 segments, 1,296 cells) and 0.45 ms
+// (500 straight handles, 289 cells); two levels 2.4 ms and 0.9 ms for the cells above, bound by the products and Y's stores.
+template <bool Two>
+__global__ void __launch_bounds__(256, 2)
+    k_far_features(CellGrid g, CellLevels lv, const int* __restrict__ off, const CellInfo* __restrict__ ci,
+                   const int* __restrict__ hpos, const int* __restrict__ epos, const uint32_t* __restrict__ far, int words,
+                   FarItems I, Layout L, const float* __restrict__ seg32, const float* __restrict__ el32,
+                   const float* __restrict__ vtab, float eps2f, const float* __restrict__ Rf, const float* __restrict__ Zf,
+                   const float2* __restrict__ Vp, int64_t W, int stride, float* __restrict__ Yf, uint32_t* __restrict__ rmax)
 {
     constexpr int NN = kFarNodes;
-    __shared__ float Rt[NN][kFarLd];                     // R transposed: [column][node]
+    __shared__ float Rt[1 + Two][NN][kFarLd];            // R transposed: [column][node]; then A^T R
     __shared__ float V[4][32][kFarLd];
     const int c = blockIdx.x, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int li = lane & 31, lk = lane >> 5;
-    for (int e = threadIdx.x; e < NN * NN; e += 256) Rt[e & 63][e >> 6] = Rf[(size_t)c * NN * NN + e];
+    const int cx = c % g.nx, cy = c / g.nx, M = I.M;
+    const bool used = off[c + 1] > off[c];
+    for (int e = threadIdx.x; e < NN * NN; e += 256) Rt[0][e & 63][e >> 6] = Rf[(size_t)c * NN * NN + e];
+    if constexpr (Two) {
+        __shared__ double cs[4 * kFarQ], A[2][kFarQ][kFarQ];
+        float(*t)[kFarLd] = V[0];                        // [column][node], over two wavefronts' rows
+        if (threadIdx.x < 4 * kFarQ) cs[threadIdx.x] = cospi((double)threadIdx.x / (2 * kFarQ));
+        __syncthreads();
+        child_matrix<kFarQ>(threadIdx.x, 256, cs, A);
+        __syncthreads();
+        for (int e = threadIdx.x; e < NN * NN; e += 256) {
+            const int k = e >> 6, n = e & 63;
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < kFarQ; ++i) s += A[cx & 1][i][n & 7] * (double)Rt[0][k][(n & ~7) + i];
+            t[k][n] = (float)s;
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < NN * NN; e += 256) {
+            const int k = e >> 6, n = e & 63;
+            double s = 0.0;
+#pragma unroll
+            for (int j = 0; j < kFarQ; ++j) s += A[cy & 1][j][n >> 3] * (double)t[k][8 * j + (n & 7)];
+            Rt[1][k][n] = (float)s;
+        }
+    }
+    __syncthreads();
     float(*v)[kFarLd] = V[wv];
     for (int i = 28; i < 32; ++i) v[i][lane] = 0.0f;
-    __syncthreads();
-    const bool used = off[c + 1] > off[c];
     const int nh = ci[c].nh;
     double Xd, Yd;
     cell_node<kFarQ>(g, c, lane, Xd, Yd);
-    const float X = (float)Xd, Y = (float)Yd;
-    const uint32_t* row = bits + (size_t)c * words;
+    const uint32_t* row = far + (size_t)c * words;
+    const int above = (cy >> 1) * lv.nx[1] + (cx >> 1);
+    const uint32_t* up = Two ? far + (size_t)(lv.base[1] + above) * words : row;
     const float short_len = (float)(kFarCells * g.h / kQuadFar);
     // the cells' columns are dealt out in a stride permutation: in cell order the float32 sums over
     // consecutive columns see long coherent runs, and their partial sums wander
     const size_t yb = (size_t)(2 * ((int64_t)c * stride % g.nc)) * ((size_t)W << 5) + li;
     const float* z0 = Zf + (size_t)ci[c].rb * NN + li;
-    const int per = model == 1 ? 2 : 1;                  // handles an item
-    const int hitems = (L.H + per - 1) / per, items = hitems + (M + 31) / 32;
-    for (int it = wv + 4 * blockIdx.y; it < items; it += 4 * gridDim.y) {
-        const bool handle = it < hitems;
-        const int h0 = it * per, j0 = (it - hitems) * 32;
+    for (int it = wv + 4 * blockIdx.y; it < I.all; it += 4 * gridDim.y) {
+        const bool handle = it < I.handles;
+        const int h0 = it * I.per, j0 = (it - I.handles) * 32;
         // row i = li of the item: its row of Y (-1: none), its near row (-1: not near), and the largest magnitude so far
         int my_f = -1, my_z = -1;
         if (!handle) {
@@ -521,77 +661,41 @@ __global__ void __launch_bounds__(256, 2)
             }
         } else {
             const int all = 3 * L.G + L.C, sub = li >= all, e = li - all * sub, h = h0 + sub;
-            if (sub < per && e < all && h < L.H) {
+            if (sub < I.per && e < all && h < L.H) {
                 const int p = used ? hpos[(size_t)c * L.H + h] : -1, q = e / L.G, k = e % L.G;
                 my_f = q < 3 ? q * (int)L.Gp + L.G * h + k : 3 * (int)L.Gp + L.C * h + (e - 3 * L.G);
                 if (p >= 0) my_z = q < 3 ? (q * nh + p) * L.G + k : 3 * L.G * nh + L.C * p + (e - 3 * L.G);
             }
         }
         const uint32_t seen = my_f >= 0 ? rmax[my_f] : 0;
-        if (used && handle) {
-            for (int sub = 0; sub < per; ++sub) {
-                const int h = h0 + sub;
-                float geo[3][8], col[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) geo[q][k] = 0.f;
-                const int k1 = h < L.H ? (h + 1) * S : 0;
-                for (int k0 = h * S; k0 < k1; k0 = (k0 | 31) + 1) {
-                    // far segments of this handle in the word that holds k0
-                    uint32_t far = ~row[k0 >> 5] & (~0u << (k0 & 31));
-                    if (k1 <= (k0 | 31)) far &= (1u << (k1 & 31)) - 1u;
-                    for (; far; far &= far - 1u) {
-                        const int k = (k0 & ~31) + __builtin_ctz(far);
-                        const float* s = seg32 + (size_t)k * kSegStride;
-                        const float* B = vtab + 8 * (k - h * S);
-                        if (s[kLen] <= short_len) add_pair_features<4>(s, B, B + 8, X, Y, eps2f, true, geo, col);
-                        else add_pair_features<6>(s, B, B + 8, X, Y, eps2f, true, geo, col);
-                    }
-                }
-                if (model == 1) {
-                    float(*u)[kFarLd] = v + 14 * sub;
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) u[4 * q + k][lane] = geo[q][k];
-                    u[12][lane] = col[0] + col[1];
-                    u[13][lane] = col[2] + col[3];
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) v[8 * q + k][lane] = geo[q][k];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) v[24 + k][lane] = col[k];
-                }
-            }
-        } else if (used) {
-#pragma unroll 4
-            for (int i = 0; i < 32; ++i) {
-                const int j = j0 + i < M ? j0 + i : M - 1;
-                const float* e = el32 + (size_t)j * kElemStride;
-                const bool far = !((row[seg_words + (j >> 5)] >> (j & 31)) & 1u);
-                v[i][lane] = far ? element_beta<float, DevF32>(e[0], e[1], e[2], e[3], X, Y) : 0.0f;
-            }
-        }
-        __threadfence_block();
         floatx16 acc[2];
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
-        if (used) {
-#pragma unroll 4
-            for (int n = 2 * lk; n < NN; n += 4) {
-                const float2 a = *reinterpret_cast<const float2*>(&v[li][n]);
-                const float2 b0 = *reinterpret_cast<const float2*>(&Rt[li][n]);
-                const float2 b1 = *reinterpret_cast<const float2*>(&Rt[32 + li][n]);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b0.x, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b1.x, acc[1], 0, 0, 0);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b0.y, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1.y, acc[1], 0, 0, 0);
+        auto product = [&](const float (*R)[kFarLd], int n, float2 a) {
+            const float2 b0 = *reinterpret_cast<const float2*>(&R[li][n]);
+            const float2 b1 = *reinterpret_cast<const float2*>(&R[32 + li][n]);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b0.x, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b1.x, acc[1], 0, 0, 0);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b0.y, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1.y, acc[1], 0, 0, 0);
+        };
+        if constexpr (Two) {
+            if (used && I.any(it, up)) {
+                const float2* q = Vp + ((size_t)above * I.all + it) * (16 * 64) + lane;
+                float2 a[16];
+#pragma unroll
+                for (int n = 0; n < 16; ++n) a[n] = q[64 * n];
+#pragma unroll
+                for (int n = 0; n < 16; ++n) product(Rt[1], 4 * n + 2 * lk, a[n]);
             }
         }
-        __threadfence_block();
+        if (used && I.any(it, row)) {
+            far_rows(I, it, row, (float)Xd, (float)Yd, short_len, eps2f, seg32, el32, vtab, v);
+            __threadfence_block();
+#pragma unroll 4
+            for (int n = 2 * lk; n < NN; n += 4) product(Rt[0], n, *reinterpret_cast<const float2*>(&v[li][n]));
+            __threadfence_block();
+        }
         // outputs: lane i (and i + 32) keeps row i's maximum
         float most = 0.0f;
 #pragma unroll
@@ -661,7 +765,7 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     if (g == 0) return BEM_OK;
     CellPlan p;
     if ((rc = launch_expand(ctx, theta, H, s))) return rc;
-    if ((rc = cell_plan(ctx, x, N, Grouping{g, 1}, &p, s))) return rc;
+    if ((rc = cell_plan(ctx, x, N, two_levels(g, S, ctx->model) ? Grouping{g & ~1, 2} : Grouping{g, 1}, &p, s))) return rc;
     if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
     const int nc = p.grid.nc, nl = nc + 1;
     if (W * 64 * (int64_t)nc >= ((int64_t)1 << 31)) return BEM_OK;            // 32-bit offsets in the Gram
@@ -756,6 +860,8 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     // Y in float32, then its float16 pairs
     const size_t yt = up((size_t)W * 64 * nc * sizeof(uint16_t));
     if ((rc = ensure(ctx, ctx->tmp0, 4 * yt, s))) return tiles_instead(rc);
+    if (p.lv.n > 1 && (size_t)p.lv.nx[1] * p.lv.ny[1] * FarItems(H, S, M, ctx->model, p.seg_words).all * 8192 > 2 * yt)
+        return tiles_instead(BEM_ENOMEM);                // (not at any shape of cells: a fourth to a half as many)
     float* Yf = (float*)ctx->tmp0.ptr;
     uint16_t *Yh = (uint16_t*)((char*)ctx->tmp0.ptr + 2 * yt), *Yl = (uint16_t*)((char*)ctx->tmp0.ptr + 3 * yt);
     if ((rc = ensure(ctx, ctx->tmp1, (size_t)W * W * sizeof(double), s))) return rc;
@@ -802,15 +908,20 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     if ((rc = fill_i32(ctx, (int*)rmax, W, 0, s))) return rc;
     {
         ProfScope ps_(ctx, PT_FEATURES, s);
-        const int items = (L.G == 4 ? (H + 1) / 2 : H) + (M + 31) / 32;
-        int split = (items + 3) / 4;
-        const int most = 1 + 4096 / nc;
-        if (split > most) split = most;
+        const FarItems items(H, S, M, ctx->model, p.seg_words);
+        auto parts = [&](int cells) { return std::min((items.all + 3) / 4, 1 + 4096 / cells); };
+        // the rows of the cells above lie where Y's halves go afterwards
+        float2* Vp = (float2*)Yh;
+        if (p.lv.n > 1) {
+            const int np = p.lv.nx[1] * p.lv.ny[1];
+            hipLaunchKernelGGL(k_far_parents, dim3(np, parts(np)), dim3(256), 0, s, p.grid, p.lv, p.off, p.far, p.words, items,
+                               seg32, el32, (const float*)vtab, (float)eps2, Vp);
+        }
         int stride = (int)(0.382 * nc) | 1;
         while (std::gcd(stride, nc) != 1) stride += 2;
-        hipLaunchKernelGGL(k_far_features, dim3(nc, split), dim3(256), 0, s, p.grid, p.off, (const CellInfo*)ci,
-                           (const int*)hpos, (const int*)epos, p.bits, p.words, p.seg_words, L, S, M, ctx->model, seg32, el32,
-                           (const float*)vtab, (float)eps2, (const float*)Rf, (const float*)Zf, W, stride, Yf, rmax);
+        hipLaunchKernelGGL(p.lv.n > 1 ? k_far_features<true> : k_far_features<false>, dim3(nc, parts(nc)), dim3(256), 0, s, p.grid, p.lv, p.off, (const CellInfo*)ci,
+                           (const int*)hpos, (const int*)epos, p.far, p.words, items, L, seg32, el32, (const float*)vtab,
+                           (float)eps2, (const float*)Rf, (const float*)Zf, (const float2*)Vp, W, stride, Yf, rmax);
         hipLaunchKernelGGL(k_split_half, dim3(blocks_for((int64_t)nc * 16 * W, 256)), dim3(256), 0, s, (const float*)Yf,
                            (const uint32_t*)rmax, L, W, (int64_t)2 * nc, Yh, Yl, rscale);
     }

@@ -76,3 +76,18 @@ def test_strays_and_clustered_samples():
     x = 0.4 + 0.2 * W.random_points(13, 60000, 1e-3, 1 - 1e-3)
     x[::3] = W.random_points(14, len(x[::3]), 1e-3, 1 - 1e-3)
     _check(th, x, 16, "cubic")
+
+
+# from 204,800 samples on the far rows of items of 16 segments take two levels of cells: the smallest grid (20 cells a
+# side), an odd one (21, made even), a last item of one straight handle, and samples that leave cells of 2 x 2 empty or
+# in part empty
+@pytest.mark.parametrize("S,H,n,model,part", [(16, 12, 204801, "cubic", 0), (32, 9, 250007, "cubic", 0),
+                                              (8, 41, 215000, "straight", 0), (16, 12, 230000, "cubic", 1)])
+def test_far_rows_over_two_levels(S, H, n, model, part):
+    th = W.random_handles(H, H, spread=0.1) if model == "cubic" else _straight(H, H, 0.1)
+    x = W.random_points(H + n, n, 1e-3, 1 - 1e-3)
+    if part:
+        x[:] = np.where(np.arange(n)[:, None] % 3 == 0, x, 0.42 + 0.16 * x)
+        x[x[:, 0] < 0.23] += 0.5
+        x = np.minimum(x, 1 - 1e-3)
+    _check(th, x, S, model)
