@@ -305,20 +305,24 @@ __global__ void __launch_bounds__(192) k_far_coef(const double* __restrict__ par
 }
 
 // A wavefront of up to 64 samples of one cell: the cell's near segments and elements pair by pair, the
-// far ones from its coefficients.  The records are read by wave-uniform (scalar) loads.
+// far ones from its coefficients.  The records are read by wave-uniform (scalar) loads.  Split 4: a block's four
+// wavefronts share the samples and take every fourth bit each.  Bound by the vector ALUs (0.20 of 0.25 issue).
+template <int Split>
 __global__ void __launch_bounds__(256, 4) k_sweep_cells(CellPlan p, Tables t, const float* __restrict__ coef, double c0,
                                                      double c1, double c2, float* __restrict__ u)
 {
     __shared__ NearBuf nb[4];
-    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, part = wave % Split;
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * (4 / Split) + wave / Split);
     const int nl = p.grid.nc + 1;
-    if (w >= p.wave0[nl]) return;
+    if (w >= p.wave0[nl]) return;                    // (Split 4: the whole block)
     const int c = unit_label(p.wave0, nl, w);
     const int i0 = p.off[c] + (w - p.wave0[c]) * 64;
     const int i = i0 + lane;
     const bool live = i < p.off[c + 1];
     const double* xw = p.xs + 2 * (size_t)i0;
-    NearBuf& b = nb[threadIdx.x >> 6];
+    constexpr uint32_t kMine = Split == 4 ? 0x11111111u : 0xFFFFFFFFu;
+    NearBuf& b = nb[wave];
     for (int q = 0; q < 3; ++q) b.acc[64 * q + lane] = 0.0;
     const double Xd = live ? xw[2 * lane] : 0.0, Yd = live ? xw[2 * lane + 1] : 0.0;
     const float X = (float)Xd, Y = (float)Yd;
@@ -335,7 +339,7 @@ __global__ void __launch_bounds__(256, 4) k_sweep_cells(CellPlan p, Tables t, co
                     w0 += 64;
                     if (w0 >= p.words) done = true;
                     else {
-                        mine = w0 + lane < p.words ? row[w0 + lane] : 0u;
+                        mine = w0 + lane < p.words ? row[w0 + lane] & (kMine << part) : 0u;
                         some = __ballot(mine != 0);
                     }
                 }
@@ -365,6 +369,18 @@ __global__ void __launch_bounds__(256, 4) k_sweep_cells(CellPlan p, Tables t, co
         }
         flush_near(t, xw, b, cnt);
     }
+    double sum[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) sum[q] = ((double)e3[q] + (double)f[q]) + b.acc[3 * lane + q];
+    if constexpr (Split > 1) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) b.acc[3 * lane + q] = sum[q];
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            sum[q] = (sum[q] + nb[1].acc[3 * lane + q]) + (nb[2].acc[3 * lane + q] + nb[3].acc[3 * lane + q]);
+    }
     float far[3] = {0.f, 0.f, 0.f};
     if (c < p.grid.nc) {
         double cx, cy;
@@ -389,10 +405,15 @@ __global__ void __launch_bounds__(256, 4) k_sweep_cells(CellPlan p, Tables t, co
     const double cb[3] = {c0, c1, c2};
 #pragma unroll
     for (int q = 0; q < 3; ++q)
-        u[o + q] = (float)(cb[q] + (((double)e3[q] + (double)f[q]) + ((double)far[q] + b.acc[3 * lane + q])));
+        u[o + q] = (float)(cb[q] + (sum[q] + (double)far[q]));
 }
 
 }  // namespace
+
+// Below this many wavefronts of samples, each cell's near pairs go to four wavefronts a unit: with one, 100,000 samples are
+// 1.5 wavefronts a SIMD.  500 straight handles, 100,003 samples (1,900 units) 82 and 59 us with one and four, 262,144
+// (5,000) 102 and 93; from 6,144 on the chip is full.
+constexpr int64_t kSplitWaves = 6144;
 
 int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const double* cbar, float* u, hipStream_t s)
 {
@@ -437,8 +458,12 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     float* coef = (float*)((char*)ctx->farw.ptr + pb + lb);
     hipLaunchKernelGGL(k_far_nodes, dim3(nlow + (ntop + 3) / 4 * nparts), dim3(256), 0, s, p, t, gpc, nparts, part, low);
     hipLaunchKernelGGL(k_far_coef, dim3(nc), dim3(192), 0, s, (const double*)part, nparts, (const double*)low, p, coef);
-    hipLaunchKernelGGL(k_sweep_cells, dim3((p.max_waves + 3) / 4), dim3(256), 0, s, p, t, (const float*)coef, cbar[0],
-                       cbar[1], cbar[2], u);
+    if (p.max_waves < kSplitWaves)
+        hipLaunchKernelGGL(k_sweep_cells<4>, dim3(p.max_waves), dim3(256), 0, s, p, t, (const float*)coef, cbar[0], cbar[1],
+                           cbar[2], u);
+    else
+        hipLaunchKernelGGL(k_sweep_cells<1>, dim3((p.max_waves + 3) / 4), dim3(256), 0, s, p, t, (const float*)coef, cbar[0],
+                           cbar[1], cbar[2], u);
     return check_launch(ctx, "sweep_cells");
 }
 

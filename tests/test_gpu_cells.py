@@ -148,3 +148,16 @@ def test_few_samples_fp64_matches_oracle(n):
     assert np.abs(u - uo).max() < 1e-10
     a, b = host(ctx.vjp(dev(th), dev(x), dev(g), "fp64")), O.vjp(th, x, g, 8, 1e-2)
     assert np.abs(a - b).max() < 1e-10 * np.abs(b).max()
+
+
+# 340,000 samples: four wavefronts to a unit of 64 samples; 400,000: one.  130 segments and the elements leave every
+# fourth-bit share uneven, and samples on the segments fill the lists.
+@pytest.mark.parametrize("n", [340000, 400000])
+def test_units_of_four_wavefronts_and_of_one(n):
+    ctx, theta = ctx_for(1, handle_model="straight"), _straight(21, 130, 0.05)
+    x = W.random_points(22, n, 1e-3, 1 - 1e-3)
+    t = np.arange(2000) / 2000.0
+    x[:2000] = theta[7, 0:2] + t[:, None] * (theta[7, 2:4] - theta[7, 0:2]) + 1e-5
+    u, r = (host(ctx.eval(dev(theta), dev(x), CBAR, p)) for p in ("mixed", "fp64"))
+    assert np.isfinite(r).all()
+    assert np.abs(u - r).max() < 1e-5 * max(1.0, np.abs(r).max())
