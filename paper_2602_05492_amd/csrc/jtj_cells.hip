@@ -2,12 +2,12 @@
 //
 // Over the n samples of a cell every feature row is X = V Phi + E: Phi [64][n] the cell's interpolation
 // weights, V [W][64] the row's far part at the cell's nodes, and E the part of the near segments and elements,
-// zero but for the rows of the handles and elements near the cell.  With Phi Phi^T = R R^T (Cholesky, 64 x 64)
-// and Q = R^-1 Phi, whose rows are orthonormal,
+// zero but for the rows of the handles and elements near the cell.  With R R^T = Phi Phi^T (64 x 64, pivoted:
+// cell_factor.hpp) and R Q = Phi,
 //     sum over the cell of X X^T = Y Y^T + E E^T - Z Z^T,     Z = E Q^T,   Y = V R + Z.
 // So 64 columns Y stand for the cell's samples in the Gram of all W rows, and the samples themselves
-// enter only the Gram of the cell's near rows.  The identity needs R R^T = Phi Phi^T and R Q = Phi only, so
-// a rank-deficient cell (fewer than 64 samples) is exact as well: its empty pivots are dropped.
+// enter only the Gram of the cell's near rows.  A cell whose samples do not determine all 64 node functions (fewer
+// samples, or samples in a corner or strip of it) has fewer columns, the others zero.
 //
 //   k_cell_rows       near handles and elements of every cell
 //   k_cell_gramian    Phi Phi^T from the 15 x 15 Chebyshev moments of the samples (float64)
@@ -29,6 +29,7 @@
 #include <cmath>
 #include <numeric>
 
+#include "cell_factor.hpp"
 #include "cells.hpp"
 #include "normal.hpp"
 
@@ -42,7 +43,6 @@ typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kFeatVals = 28;                  // geo[3][8], col[4] of a handle at a point
 constexpr double kNeRatio = 2.0;               // near pair over far pair, in time
-constexpr int kMom = 16;                       // moments a side (15 used)
 constexpr int kGramianParts = 4;
 
 // Near handles (any near segment) and near elements of every cell, in order; hpos / epos the place of a
@@ -134,14 +134,34 @@ __global__ void __launch_bounds__(256) k_cell_gramian(CellPlan p, double* __rest
     part[((size_t)blockIdx.y * p.grid.nc + c) * 256 + t] = (red[t] + red[256 + t]) + (red[512 + t] + red[768 + t]);
 }
 
-// Block a cell.  A = D^T M D, M[(a, b), (a', b')] = sum T_a T_b T_a' T_b' from the moments (T_a T_a' is the
-// mean of T_{a + a'} and T_{|a - a'|}) and D the nodes' Chebyshev coefficients; its Cholesky factor R
-// (Rf [n][k], float32) and C = R^-1 D^T ([k][ab], float64).  Pivots below 1e-12 of the largest are dropped.
+// One workgroup's threads in cell_factor: every wavefront looks for the pivot by itself, the low six bits of a value
+// replaced by its node (the first of equal ones).
+struct BlockTeam {
+    int t;
+    static constexpr int n = 256;
+    __device__ void sync() const { __syncthreads(); }
+    __device__ int largest(const double (*A)[kFarNodes + 1], const int* step) const
+    {
+        const int lane = t & 63;
+        const double v = A[lane][lane];
+        unsigned long long key = step[lane] < 0 && v > 0.0 ? ((unsigned long long)__double_as_longlong(v) & ~63ull) | (63 - lane) : 0ull;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long u = __shfl_xor(key, o);
+            key = u > key ? u : key;
+        }
+        return key ? 63 - (int)(key & 63ull) : -1;
+    }
+};
+
+// Block a cell: the factor R of its Gramian (Rf [n][k], float32) and C with which q(x) = C T(x) ([k][ab], float64).
+// Bound by the factor's chain of 64 steps.
 __global__ void __launch_bounds__(256) k_cell_factor(const double* __restrict__ part, int nc, const int* __restrict__ off,
                                                      float* __restrict__ Rf, double* __restrict__ Cq)
 {
     constexpr int Q = kFarQ, NN = kFarNodes;
-    __shared__ double A[NN][NN + 1], B[NN][NN + 1], mu[256], d[Q][Q], dinv[NN];
+    static_assert(Q == kFactorSide, "");
+    __shared__ CellFactor w;
     const int c = blockIdx.x, t = threadIdx.x;
     if (off[c + 1] == off[c]) {
         for (int e = t; e < NN * NN; e += 256) Rf[(size_t)c * NN * NN + e] = 0.0f;
@@ -149,82 +169,17 @@ __global__ void __launch_bounds__(256) k_cell_factor(const double* __restrict__ 
     }
     double s = 0.0;
     for (int p = 0; p < kGramianParts; ++p) s += part[((size_t)p * nc + c) * 256 + t];
-    mu[t] = s;                                       // mu[q * 16 + p]
+    w.mu[t] = s;
     if (t < Q * Q) {
-        const int a = t / Q, i = t % Q;              // d[a][i] = s_a T_a(t_i)
-        d[a][i] = cospi((double)(a * (2 * i + 1)) / (2.0 * Q)) * (a == 0 ? 1.0 / Q : 2.0 / Q);
+        const int a = t / Q, i = t % Q;
+        w.d[a][i] = cospi((double)(a * (2 * i + 1)) / (2.0 * Q)) * (a == 0 ? 1.0 / Q : 2.0 / Q);
     }
     __syncthreads();
-    // index of (a, b): b * 8 + a, of node (i, j): j * 8 + i
+    cell_factor(BlockTeam{t}, w);
     for (int e = t; e < NN * NN; e += 256) {
-        const int r = e >> 6, q = e & 63;
-        const int a = r & 7, b = r >> 3, a2 = q & 7, b2 = q >> 3;
-        const int ad = a > a2 ? a - a2 : a2 - a, bd = b > b2 ? b - b2 : b2 - b;
-        A[r][q] = 0.25 * ((mu[(b + b2) * 16 + a + a2] + mu[(b + b2) * 16 + ad]) + (mu[bd * 16 + a + a2] + mu[bd * 16 + ad]));
+        Rf[(size_t)c * NN * NN + e] = (float)w.R[e >> 6][e & 63];
+        Cq[(size_t)c * NN * NN + e] = w.A[e >> 6][e & 63];
     }
-    __syncthreads();
-    // the four index transforms a -> i, b -> j, a' -> i', b' -> j'
-    for (int e = t; e < NN * NN; e += 256) {
-        const int r = e >> 6, q = e & 63, i = r & 7, b = r >> 3;
-        double v = 0.0;
-        for (int a = 0; a < Q; ++a) v += d[a][i] * A[b * 8 + a][q];
-        B[r][q] = v;
-    }
-    __syncthreads();
-    for (int e = t; e < NN * NN; e += 256) {
-        const int r = e >> 6, q = e & 63, i = r & 7, j = r >> 3;
-        double v = 0.0;
-        for (int b = 0; b < Q; ++b) v += d[b][j] * B[b * 8 + i][q];
-        A[r][q] = v;
-    }
-    __syncthreads();
-    for (int e = t; e < NN * NN; e += 256) {
-        const int r = e >> 6, q = e & 63, i = q & 7, b = q >> 3;
-        double v = 0.0;
-        for (int a = 0; a < Q; ++a) v += d[a][i] * A[r][b * 8 + a];
-        B[r][q] = v;
-    }
-    __syncthreads();
-    for (int e = t; e < NN * NN; e += 256) {
-        const int r = e >> 6, q = e & 63, i = q & 7, j = q >> 3;
-        double v = 0.0;
-        for (int b = 0; b < Q; ++b) v += d[b][j] * B[r][b * 8 + i];
-        A[r][q] = v;
-    }
-    __syncthreads();
-    double top = 0.0;
-    for (int k = 0; k < NN; ++k) top = fmax(top, A[k][k]);
-    __syncthreads();
-    for (int k = 0; k < NN; ++k) {                   // right-looking, lower triangle
-        const double piv = A[k][k];
-        const bool keep = piv > 1e-12 * top;
-        const double inv = keep ? 1.0 / sqrt(piv) : 0.0;
-        __syncthreads();
-        if (t >= k && t < NN) A[t][k] = t == k ? piv * inv : A[t][k] * inv;
-        if (t == 0) dinv[k] = inv;
-        __syncthreads();
-        const int m = NN - 1 - k;
-        for (int e = t; e < m * m; e += 256) {
-            const int r = k + 1 + e / m, q = k + 1 + e % m;
-            if (q <= r) A[r][q] -= A[r][k] * A[q][k];
-        }
-        __syncthreads();
-    }
-    for (int e = t; e < NN * NN; e += 256) {
-        const int r = e >> 6, q = e & 63;
-        Rf[(size_t)c * NN * NN + e] = q <= r ? (float)A[r][q] : 0.0f;
-    }
-    // C = R^-1 D^T, column ab by forward substitution
-    if (t < NN) {
-        const int a = t & 7, b = t >> 3;
-        for (int k = 0; k < NN; ++k) {
-            double v = d[a][k & 7] * d[b][k >> 3];
-            for (int m = 0; m < k; ++m) v -= A[k][m] * B[m][t];
-            B[k][t] = v * dinv[k];
-        }
-    }
-    __syncthreads();
-    for (int e = t; e < NN * NN; e += 256) Cq[(size_t)c * NN * NN + e] = B[e >> 6][e & 63];
 }
 
 __device__ inline void put_split(uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, size_t i, float v)
