@@ -133,11 +133,16 @@ __global__ void __launch_bounds__(256) k_cell_scatter(const double* __restrict__
 // blockIdx.y a row.  A segment is far from a cell when its extent stays kFarCells cell widths away from the cell's square
 // in x or in y and no sample of the square can have both of its end points within the near radius (the pairs the mixed
 // sweeps evaluate in float64; margins far above the float32 rounding of that test), or when it is far from a cell above
-// it.  NaN geometry is near everywhere.  Far bit: far here, near the parent (top level: far), and the cell holds samples.
+// it.  Coordinates are taken from the grid's origin in the sweep's own precision T before the test's float32: a float64
+// sweep's domain may lie anywhere (from float32 coordinates, segments of a unit domain at 1e7 were far from cells that
+// they cross); the mixed sweeps' pairs are those of the float32 tables themselves (4,096 segments, 1,048,576 samples: a
+// call takes 678 us, with the float64 tables 703).
+// Far bit: far here, near the parent (top level: far), and the cell holds samples.
 constexpr int kBitWords = 16;
+template <class T>
 __global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, CellLevels lv, const int* __restrict__ off,
-                                                   const float* __restrict__ seg32, int K,
-                                                   const float* __restrict__ el32, int M, float near2, int seg_words,
+                                                   const T* __restrict__ segs, int K,
+                                                   const T* __restrict__ els, int M, float near2, int seg_words,
                                                    int words, uint32_t* __restrict__ bits, uint32_t* __restrict__ fbits)
 {
     const int row = blockIdx.y, lane = threadIdx.x & 63;
@@ -145,12 +150,13 @@ __global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, CellLevels lv, co
     const bool stray = row == g.nc;
     if (!stray) level_cell(lv, row, l, cx, cy);
     const bool used = !stray && level_used(lv, off, l, cx, cy);
+    const T ox = (T)g.x0, oy = (T)g.y0;
     // squares of the cell (0) and the cells above it
     float x0[kMaxLevels], y0[kMaxLevels], x1[kMaxLevels], y1[kMaxLevels], d[kMaxLevels];
 #pragma unroll
     for (int m = 0; m < kMaxLevels; ++m) {
         const double h = g.h * (double)(1 << (l + m));
-        const double X0 = g.x0 + (double)(cx >> m) * h, Y0 = g.y0 + (double)(cy >> m) * h;
+        const double X0 = (double)(cx >> m) * h, Y0 = (double)(cy >> m) * h;
         x0[m] = (float)X0; y0[m] = (float)Y0; x1[m] = (float)(X0 + h); y1[m] = (float)(Y0 + h);
         d[m] = (float)(kFarCells * h);
     }
@@ -163,11 +169,16 @@ __global__ void __launch_bounds__(256) k_cell_bits(CellGrid g, CellLevels lv, co
         if (w < words && i < (seg ? K : M)) {
             float ax, ay, bx, by, L2;
             if (seg) {
-                const float* s = seg32 + (size_t)i * kSegStride;
-                ax = s[0]; ay = s[1]; bx = s[2]; by = s[3]; L2 = s[6];
+                const T* s = segs + (size_t)i * kSegStride;
+                ax = (float)(s[0] - ox); ay = (float)(s[1] - oy);
+                bx = (float)(s[2] - ox); by = (float)(s[3] - oy);
+                L2 = (float)s[6];
             } else {
-                const float* e = el32 + (size_t)i * kElemStride;
-                ax = e[0]; ay = e[1]; bx = e[0] + e[2]; by = e[1] + e[3]; L2 = e[2] * e[2] + e[3] * e[3];
+                const T* e = els + (size_t)i * kElemStride;
+                const T x = e[0] - ox, y = e[1] - oy;
+                ax = (float)x; ay = (float)y;
+                bx = (float)(x + e[2]); by = (float)(y + e[3]);
+                L2 = (float)(e[2] * e[2] + e[3] * e[3]);
             }
             const float r2 = 1.01f * near2 * L2 + 1e-9f;
             const float lox = fminf(ax, bx), hix = fmaxf(ax, bx), loy = fminf(ay, by), hiy = fmaxf(ay, by);
@@ -331,9 +342,13 @@ int cell_bits(bem_ctx* ctx, CellPlan* p, int K, int M, bool mixed, hipStream_t s
     const int64_t n = (int64_t)p->lv.rows * p->words;
     if ((rc = ensure(ctx, ctx->cellb, (size_t)n * 2 * sizeof(uint32_t), s))) return rc;
     uint32_t* bits = (uint32_t*)ctx->cellb.ptr;
-    hipLaunchKernelGGL(k_cell_bits, dim3(blocks_for(p->words, 4 * kBitWords), p->lv.rows), dim3(256), 0, s, p->grid, p->lv, p->off,
-                       (const float*)ctx->seg32.ptr, K, (const float*)ctx->elem32.ptr, M, (float)(nf * nf), p->seg_words,
-                       p->words, bits, bits + n);
+    const dim3 grid(blocks_for(p->words, 4 * kBitWords), p->lv.rows);
+    if (mixed)
+        hipLaunchKernelGGL(k_cell_bits<float>, grid, dim3(256), 0, s, p->grid, p->lv, p->off, (const float*)ctx->seg32.ptr, K,
+                           (const float*)ctx->elem32.ptr, M, (float)(nf * nf), p->seg_words, p->words, bits, bits + n);
+    else
+        hipLaunchKernelGGL(k_cell_bits<double>, grid, dim3(256), 0, s, p->grid, p->lv, p->off, (const double*)ctx->seg64.ptr, K,
+                           (const double*)ctx->elem64.ptr, M, 0.0f, p->seg_words, p->words, bits, bits + n);
     p->bits = bits;
     p->far = bits + n;
     return check_launch(ctx, "cell bits");
