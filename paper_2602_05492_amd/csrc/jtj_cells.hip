@@ -703,12 +703,10 @@ __global__ void __launch_bounds__(256) k_split_half(const float* __restrict__ Yf
     if (i < W * 32 && (i & 31) == 0) rscale[f] = __builtin_amdgcn_ldexpf(1.0f, -e);
 }
 
-}  // namespace
-
-int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, double* JtJ, double norm,
-                  bool* done, hipStream_t s)
+// As run_jtj_cells, BEM_ENOMEM without memory for its workspaces (J^T J is written last).
+int over_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, double* JtJ, double norm, bool* done,
+               hipStream_t s)
 {
-    *done = false;
     int rc;
     const int S = ctx->opts.segs_per_handle, K = H * S, M = ctx->M;
     const double nf = near_radius(ctx->opts.near_factor), eps2 = ctx->opts.eps * ctx->opts.eps;
@@ -720,7 +718,8 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     if (g == 0) return BEM_OK;
     CellPlan p;
     if ((rc = launch_expand(ctx, theta, H, s))) return rc;
-    if ((rc = cell_plan(ctx, x, N, two_levels(g, S, ctx->model) ? Grouping{g & ~1, 2} : Grouping{g, 1}, &p, s))) return rc;
+    if ((rc = cell_plan(ctx, x, N, two_levels(g, S, ctx->model) ? Grouping{g & ~1, 2} : Grouping{g, 1}, &p, s)))
+        return rc;
     if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
     const int nc = p.grid.nc, nl = nc + 1;
     if (W * 64 * (int64_t)nc >= ((int64_t)1 << 31)) return BEM_OK;            // 32-bit offsets in the Gram
@@ -788,19 +787,9 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     const size_t wb = up(work.size() * sizeof(int)), qt = up((size_t)blocks * kFarNodes * 32 * sizeof(uint16_t)),
                  zf = up((size_t)rows * kFarNodes * sizeof(float)), zs = up((size_t)rows * kFarNodes * sizeof(uint16_t)),
                  mb = up((size_t)W * sizeof(float));
-    // the sizes follow the parameters, so that a buffer that grows takes a quarter more; with no memory for them
-    // the samples are taken one by one
+    // the sizes follow the parameters, so that a buffer that grows takes a quarter more
     auto grow = [&](DevBuf& q, size_t n) { return ensure(ctx, q, n <= q.bytes ? n : n + n / 4, s); };
-    auto tiles_instead = [&](int e) {
-        for (DevBuf* q : {&ctx->nezw, &ctx->neew, &ctx->tmp0, &ctx->tmp2}) {
-            if (hipStreamSynchronize(s) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream sync");
-            if (q->ptr) hipFree(q->ptr);
-            q->ptr = nullptr;
-            q->bytes = 0;
-        }
-        return e == BEM_ENOMEM ? BEM_OK : e;
-    };
-    if ((rc = grow(ctx->nezw, wb + 2 * qt + zf + 7 * zs + 2 * mb + 256))) return tiles_instead(rc);
+    if ((rc = grow(ctx->nezw, wb + 2 * qt + zf + 7 * zs + 2 * mb + 256))) return rc;
     b = (char*)ctx->nezw.ptr;
     int* dwork = (int*)take(wb);
     uint16_t *Qh = (uint16_t*)take(qt), *Ql = (uint16_t*)take(qt);
@@ -810,13 +799,13 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     uint32_t* rmax = (uint32_t*)take(mb);
     float* rscale = (float*)take(mb);
     const size_t et = up((size_t)elems * sizeof(uint16_t));
-    if ((rc = grow(ctx->neew, 2 * et + 256))) return tiles_instead(rc);
+    if ((rc = grow(ctx->neew, 2 * et + 256))) return rc;
     uint16_t *Eh = (uint16_t*)ctx->neew.ptr, *El = (uint16_t*)((char*)ctx->neew.ptr + et);
     // Y in float32, then its float16 pairs
     const size_t yt = up((size_t)W * 64 * nc * sizeof(uint16_t));
-    if ((rc = ensure(ctx, ctx->tmp0, 4 * yt, s))) return tiles_instead(rc);
+    if ((rc = ensure(ctx, ctx->tmp0, 4 * yt, s))) return rc;
     if (p.lv.n > 1 && (size_t)p.lv.nx[1] * p.lv.ny[1] * FarItems(H, S, M, ctx->model, p.seg_words).all * 8192 > 2 * yt)
-        return tiles_instead(BEM_ENOMEM);                // (not at any shape of cells: a fourth to a half as many)
+        return BEM_ENOMEM;                               // (not at any shape of cells: a fourth to a half as many)
     float* Yf = (float*)ctx->tmp0.ptr;
     uint16_t *Yh = (uint16_t*)((char*)ctx->tmp0.ptr + 2 * yt), *Yl = (uint16_t*)((char*)ctx->tmp0.ptr + 3 * yt);
     if ((rc = ensure(ctx, ctx->tmp1, (size_t)W * W * sizeof(double), s))) return rc;
@@ -829,7 +818,7 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     const int64_t run_bytes = (int64_t)tiles * (256 * 256 * sizeof(float));
     const int64_t all_runs = (n + kchunk - 1) / kchunk, most_runs = std::max<int64_t>(1, ((int64_t)4 << 30) / run_bytes);
     const int runs = (int)std::min(all_runs, most_runs);
-    if ((rc = ensure(ctx, ctx->tmp2, (size_t)(runs * run_bytes), s))) return tiles_instead(rc);
+    if ((rc = ensure(ctx, ctx->tmp2, (size_t)(runs * run_bytes), s))) return rc;
     float* part = (float*)ctx->tmp2.ptr;
     const int* gwork;
     int ntiles;
@@ -892,6 +881,25 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     const double sc = 1.0 / (norm > 0.0 ? norm : (double)N);
     if ((rc = contract_gram(ctx, H, L, W, G, 1, 256, gwork, ntiles, Z, sc, JtJ, s))) return rc;
     *done = true;
+    return BEM_OK;
+}
+
+}  // namespace
+
+int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N, double* JtJ, double norm,
+                  bool* done, hipStream_t s)
+{
+    *done = false;
+    const int rc = over_cells(ctx, theta, H, x, N, JtJ, norm, done, s);
+    if (rc != BEM_ENOMEM) return rc;
+    // the samples are taken one by one, and what the workspaces held is given back
+    if (hipStreamSynchronize(s) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream sync");
+    for (DevBuf* q : {&ctx->cellw, &ctx->cellb, &ctx->necw, &ctx->nezw, &ctx->neew, &ctx->tmp0, &ctx->tmp1, &ctx->tmp2}) {
+        if (q->ptr) hipFree(q->ptr);
+        q->ptr = nullptr;
+        q->bytes = 0;
+    }
+    ctx->err.clear();
     return BEM_OK;
 }
 

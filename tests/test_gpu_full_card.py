@@ -1,0 +1,82 @@
+"""Calls on a card whose memory is taken but for some tens of MiB: where the grouped sums' workspaces find no memory, the
+calls take their other form, with the same result.
+
+Every kernel that may run has run before, in other contexts, so that the card is full only for the library's own
+allocations.
+"""
+import contextlib
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_05492_amd import bem as B
+from paper_2602_05492_amd import workload as W
+from helpers import dev, host, mixed_step_tol
+
+pytestmark = pytest.mark.gpu
+CBAR = (0.3, 0.5, 0.7)
+MIB = 1 << 20
+
+
+@contextlib.contextmanager
+def _full(leave):
+    """All of the card's memory taken but `leave` bytes and what is no multiple of 2 MiB."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    spare = torch.empty(leave, dtype=torch.uint8, device="cuda")
+    held, size = [], 1 << 36
+    try:
+        while size >= 2 * MIB:
+            try:
+                held.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+            except torch.OutOfMemoryError:
+                size //= 2
+        del spare
+        torch.cuda.empty_cache()
+        yield
+    finally:
+        torch.cuda.synchronize()
+        held.clear()
+        torch.cuda.empty_cache()
+
+
+def _scene(H, n):
+    rng = np.random.default_rng(H)
+    a = rng.uniform(0.2, 0.8, (H, 2))
+    th = np.concatenate([a, a + 0.02, W.draw_straight_colours(rng, H)], 1)
+    x = torch.rand(n, 2, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(H)) * 0.998 + 1e-3
+    return dev(th), x
+
+
+def test_lm_step():
+    """A context that has the workspaces of the tiles (bem_jtj in split BF16, a step of another Gram) but not of the cells."""
+    th, x = _scene(60, 2_000_000)                # 35 cells a side, 57 KiB each
+    kw = dict(segs_per_handle=1, elems_per_side=32, handle_model="straight")
+    want, ctx = B.Context(**kw), B.Context(**kw)
+    T = want.eval(th, x, CBAR, "fp64") + 0.05 * torch.randn(len(x), 3, dtype=torch.float64, device="cuda",
+                                                            generator=torch.Generator("cuda").manual_seed(1))
+    r32 = torch.zeros(len(x), 3, device="cuda")
+
+    def step(c, gram, prec):
+        t, st = th.clone(), B.new_lm_state(1.0)
+        c.lm_step(t, x, T, st, gram, prec)
+        return t, st
+
+    t64, s64 = step(want, "fp64", "fp64")
+    JtJ, _ = want.jtj(th, x, torch.zeros_like(T), "fp64", "fp64")
+    want.profile(True)
+    step(want, "bf16x3_mfma", "mixed")                       # the cells' kernels
+    assert want.profile_read()["beta_rows"][1] == 0
+    want.close()
+    ctx.jtj(th, x, r32, "bf16x3_mfma", "mixed")
+    step(ctx, "fp32_mfma", "mixed")
+    ctx.profile(True)
+    t, st = th.clone(), B.new_lm_state(1.0)
+    with _full(32 * MIB):
+        ctx.lm_step(t, x, T, st, "bf16x3_mfma", "mixed")
+        tiles = ctx.profile_read()["beta_rows"][1]
+    d, d64 = host(t - th), host(t64 - th)
+    assert tiles > 0 and st.accepted == s64.accepted == 1
+    assert np.abs(d - d64).max() < mixed_step_tol(host(JtJ), 1.0) * np.abs(d64).max()
+    ctx.close()
