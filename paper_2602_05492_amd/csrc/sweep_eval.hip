@@ -425,18 +425,48 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
     const Tables t{(const float*)ctx->seg32.ptr, (const double*)ctx->seg64.ptr, (const float*)ctx->elem32.ptr,
                    (const double*)ctx->elem64.ptr, K, M, (float)eps2, (float)(nf * nf), eps2};
     const int64_t groups = (K + 31) / 32 + (M + 31) / 32;
-    const Grouping g = cells_for(ctx, N, K, kFarQ, kEvalRatio, 2e7, 2.0, 12000.0);
+    Grouping g = cells_for(ctx, N, K, kFarQ, kEvalRatio, 2e7, 2.0, 12000.0);
     ProfScope ps_(ctx, PT_SWEEP_MIXED, s);
+    CellPlan p;
+    int nc = 0, ntop = 0, nlow = 0, gpc = 0, nparts = 0;
+    size_t pb = 0, lb = 0;
+    if (g.g) {
+        rc = cell_plan(ctx, x, N, g, &p, s);
+        if (!rc) rc = cell_bits(ctx, &p, K, M, true, s);
+        if (!rc) {
+            nc = p.grid.nc;
+            ntop = p.lv.top_cells();
+            nlow = p.lv.low_rows();
+            gpc = groups_per_chunk(groups, (ntop + 3) / 4);
+            nparts = (int)((groups + gpc - 1) / gpc);
+            const size_t cell = 3 * kFarNodes * sizeof(double);
+            pb = (size_t)nparts * ntop * cell;
+            lb = (size_t)nlow * cell;
+            rc = ensure(ctx, ctx->farw, pb + lb + (size_t)nc * 3 * kFarNodes * sizeof(float), s);
+        }
+        if (rc && rc != BEM_ENOMEM) return rc;
+        if (rc) {                            // no memory for them: the direct sums
+            ctx->err.clear();
+            g.g = 0;
+        }
+    }
     if (g.g == 0) {
         const int64_t nb = blocks_for(N, 256);
         const int gs = direct_group(nb, K, M);
         const int64_t groups = blocks_for(K, gs) + blocks_for(M, gs);
-        const int gpc = groups_per_chunk(groups, nb);
-        const int nparts = (int)((groups + gpc - 1) / gpc);
+        gpc = groups_per_chunk(groups, nb);
+        nparts = (int)((groups + gpc - 1) / gpc);
         double* part = nullptr;
         if (nparts > 1) {
-            if ((rc = ensure(ctx, ctx->farw, (size_t)nparts * 3 * N * sizeof(double), s))) return rc;
-            part = (double*)ctx->farw.ptr;
+            rc = ensure(ctx, ctx->farw, (size_t)nparts * 3 * N * sizeof(double), s);
+            if (rc && rc != BEM_ENOMEM) return rc;
+            if (rc) {                        // no memory for the chunks' sums: one chunk
+                ctx->err.clear();
+                gpc = (int)groups;
+                nparts = 1;
+            } else {
+                part = (double*)ctx->farw.ptr;
+            }
         }
         hipLaunchKernelGGL(k_sweep_direct, dim3(nb, nparts), dim3(256), 0, s, x, N, t, gs, gpc, cbar[0], cbar[1], cbar[2],
                            part, u);
@@ -445,14 +475,6 @@ int launch_sweep_eval(bem_ctx* ctx, const double* x, int64_t N, int K, const dou
                                cbar[0], cbar[1], cbar[2], u);
         return check_launch(ctx, "sweep_direct");
     }
-    CellPlan p;
-    if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
-    if ((rc = cell_bits(ctx, &p, K, M, true, s))) return rc;
-    const int nc = p.grid.nc, ntop = p.lv.top_cells(), nlow = p.lv.low_rows();
-    const int gpc = groups_per_chunk(groups, (ntop + 3) / 4);
-    const int nparts = (int)((groups + gpc - 1) / gpc);
-    const size_t cell = 3 * kFarNodes * sizeof(double), pb = (size_t)nparts * ntop * cell, lb = (size_t)nlow * cell;
-    if ((rc = ensure(ctx, ctx->farw, pb + lb + (size_t)nc * 3 * kFarNodes * sizeof(float), s))) return rc;
     double* part = (double*)ctx->farw.ptr;
     double* low = (double*)((char*)ctx->farw.ptr + pb);
     float* coef = (float*)((char*)ctx->farw.ptr + pb + lb);

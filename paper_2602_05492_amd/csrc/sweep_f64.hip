@@ -209,18 +209,48 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
     const int M = ctx->M;
     const Tables64 t{(const double*)ctx->seg64.ptr, (const double*)ctx->elem64.ptr, K, M, ctx->opts.eps * ctx->opts.eps};
     const int64_t groups = (K + 31) / 32 + (M + 31) / 32;
-    const Grouping g = cells_for(ctx, N, K, kFarQ64, 1.0, 1e7, 1.0, 3000.0);
+    Grouping g = cells_for(ctx, N, K, kFarQ64, 1.0, 1e7, 1.0, 3000.0);
     ProfScope ps_(ctx, PT_SWEEP_F64, s);
+    CellPlan p;
+    int nc = 0, ntop = 0, nlow = 0, gpc = 0, nparts = 0;
+    size_t pb = 0, lb = 0;
+    if (g.g) {
+        rc = cell_plan(ctx, x, N, g, &p, s);
+        if (!rc) rc = cell_bits(ctx, &p, K, M, false, s);
+        if (!rc) {
+            nc = p.grid.nc;
+            ntop = p.lv.top_cells();
+            nlow = p.lv.low_rows();
+            gpc = groups_per_chunk(groups, ntop);
+            nparts = (int)((groups + gpc - 1) / gpc);
+            const size_t cell = 3 * kFarNodes64 * sizeof(double);
+            pb = (size_t)nparts * ntop * cell;
+            lb = (size_t)kLowParts * nlow * cell;
+            rc = ensure(ctx, ctx->farw, pb + lb + nc * cell, s);
+        }
+        if (rc && rc != BEM_ENOMEM) return rc;
+        if (rc) {                            // no memory for them: the direct sums
+            ctx->err.clear();
+            g.g = 0;
+        }
+    }
     if (g.g == 0) {
         const int64_t nb = blocks_for(N, 256);
         const int gs = direct_group(nb, K, M);
         const int64_t groups = blocks_for(K, gs) + blocks_for(M, gs);
-        const int gpc = groups_per_chunk(groups, nb);
-        const int nparts = (int)((groups + gpc - 1) / gpc);
+        gpc = groups_per_chunk(groups, nb);
+        nparts = (int)((groups + gpc - 1) / gpc);
         double* part = nullptr;
         if (nparts > 1) {
-            if ((rc = ensure(ctx, ctx->farw, (size_t)nparts * 3 * N * sizeof(double), s))) return rc;
-            part = (double*)ctx->farw.ptr;
+            rc = ensure(ctx, ctx->farw, (size_t)nparts * 3 * N * sizeof(double), s);
+            if (rc && rc != BEM_ENOMEM) return rc;
+            if (rc) {                        // no memory for the chunks' sums: one chunk
+                ctx->err.clear();
+                gpc = (int)groups;
+                nparts = 1;
+            } else {
+                part = (double*)ctx->farw.ptr;
+            }
         }
         hipLaunchKernelGGL(k_sweep_f64, dim3(nb, nparts), dim3(256), 0, s, x, N, t, gs, gpc, cbar[0], cbar[1], cbar[2], part,
                            u);
@@ -229,14 +259,6 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
                                N, cbar[0], cbar[1], cbar[2], u);
         return check_launch(ctx, "sweep_f64");
     }
-    CellPlan p;
-    if ((rc = cell_plan(ctx, x, N, g, &p, s))) return rc;
-    if ((rc = cell_bits(ctx, &p, K, M, false, s))) return rc;
-    const int nc = p.grid.nc, ntop = p.lv.top_cells(), nlow = p.lv.low_rows();
-    const int gpc = groups_per_chunk(groups, ntop);
-    const int nparts = (int)((groups + gpc - 1) / gpc);
-    const size_t cell = 3 * kFarNodes64 * sizeof(double), pb = (size_t)nparts * ntop * cell, lb = (size_t)kLowParts * nlow * cell;
-    if ((rc = ensure(ctx, ctx->farw, pb + lb + nc * cell, s))) return rc;
     double* part = (double*)ctx->farw.ptr;
     double* low = (double*)((char*)ctx->farw.ptr + pb);
     double* coef = (double*)((char*)ctx->farw.ptr + pb + lb);

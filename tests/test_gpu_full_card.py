@@ -49,6 +49,22 @@ def _scene(H, n):
     return dev(th), x
 
 
+@pytest.mark.parametrize("prec,bar", [("fp64", 1e-12), ("mixed", 1e-5)])
+def test_eval(prec, bar):
+    th, x = _scene(64, 6_000_000)                # 24 bytes a sample: 144 MB of cell order
+    kw = dict(segs_per_handle=1, elems_per_side=32, handle_model="straight")
+    want, few = B.Context(**kw), x[:9000].contiguous()
+    r, rf = want.eval(th, x, CBAR, prec), want.eval(th, few, CBAR, prec)
+    ctx, out = B.Context(**kw), torch.empty_like(r)
+    ctx.eval(th, few, CBAR, prec, out=out[:9000])
+    with _full(64 * MIB):
+        ctx.eval(th, x, CBAR, prec, out=out)
+        torch.cuda.synchronize()
+    big = max(1.0, float(r.abs().max()))
+    assert float((out - r).abs().max()) < bar * big and float((out[:9000] - rf).abs().max()) < bar * big
+    ctx.close(), want.close()
+
+
 def test_lm_step():
     """A context that has the workspaces of the tiles (bem_jtj in split BF16, a step of another Gram) but not of the cells."""
     th, x = _scene(60, 2_000_000)                # 35 cells a side, 57 KiB each
