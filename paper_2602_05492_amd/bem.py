@@ -346,16 +346,17 @@ def lm_step_subdomains(contexts, thetas, x, target, labels, states, gram: str = 
     Eq. losshessian and Eq. lossjacobian do."""
     xs, Ts, off = contexts[0].partition(labels, x, target, len(contexts))
     N = x.shape[0]
+    parts = list(zip(contexts, thetas, states))          # any iterables, as many as the shortest has
 
     def step(d):
-        states[d].data_count = N
-        contexts[d].lm_step(thetas[d], xs[off[d]:off[d + 1]], Ts[off[d]:off[d + 1]], states[d], gram, prec)
+        ctx, th, st = parts[d]
+        st.data_count = N
+        ctx.lm_step(th, xs[off[d]:off[d + 1]], Ts[off[d]:off[d + 1]], st, gram, prec)
 
-    n = min(len(contexts), len(thetas), len(states))
-    if n > 1 and _independent(contexts[:n], thetas[:n], states[:n]):
-        _side_by_side(step, n, thetas, states)
+    if len(parts) > 1 and _independent(*zip(*parts)):
+        _side_by_side(step, len(parts), *list(zip(*parts))[1:])
     else:
-        for d in range(n):
+        for d in range(len(parts)):
             step(d)
     return states
 
