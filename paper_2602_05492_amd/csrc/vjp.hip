@@ -165,11 +165,11 @@ __global__ void __launch_bounds__(64) k_chain_theta(const double* __restrict__ s
 }
 
 // Chunks of N samples over `groups` groups of 64 segments or elements: about 4,096 blocks, each with at least
-// 256 samples, or 32 while there are fewer than 1,024 blocks.
-int chunks_for(int64_t N, int groups, int64_t& chunk)
+// 256 samples, or (fine) 32 while there are fewer than 1,024 blocks.
+int chunks_for(int64_t N, int groups, bool fine, int64_t& chunk)
 {
     int64_t nch = (4096 + groups - 1) / groups;
-    const int64_t few = (N + 31) / 32 < 1024 / groups ? (N + 31) / 32 : 1024 / groups;
+    const int64_t few = !fine ? 0 : (N + 31) / 32 < 1024 / groups ? (N + 31) / 32 : 1024 / groups;
     const int64_t cap = (N + 255) / 256 > few ? (N + 255) / 256 : few;
     if (nch > cap) nch = cap;
     if (nch < 1) nch = 1;
@@ -186,13 +186,13 @@ int chunks_for(int64_t N, int groups, int64_t& chunk)
 // (tables, partial sums, psi, mu, boundary Gauss points, segment sums), each piece 256-aligned.
 static size_t carve_round(size_t b) { return (b + 255) / 256 * 256; }
 
-size_t vjp_f64_workspace_bytes(int K, int M, int64_t N)
+size_t vjp_f64_workspace_bytes(int K, int M, int64_t N, bool fine)
 {
     const int kgroups = (K + 63) / 64, mgroups = (M + 63) / 64;
     int64_t c = 1;
-    const int ns = N > 0 ? chunks_for(N, kgroups, c) : 0;
-    const int ng = chunks_for(3 * (int64_t)M, kgroups, c);
-    const int ne = N > 0 ? chunks_for(N, mgroups, c) : 0;
+    const int ns = N > 0 ? chunks_for(N, kgroups, fine, c) : 0;
+    const int ng = chunks_for(3 * (int64_t)M, kgroups, fine, c);
+    const int ne = N > 0 ? chunks_for(N, mgroups, fine, c) : 0;
     const size_t k1 = (size_t)(K > 0 ? K : 1);
     return carve_round(k1 * kSegStride * sizeof(double)) + carve_round(k1 * kSegStride * sizeof(float)) +
            carve_round((size_t)M * kElemStride * sizeof(double)) + carve_round((size_t)M * kElemStride * sizeof(float)) +
@@ -214,9 +214,10 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     const int kgroups = (K + 63) / 64, mgroups = (M + 63) / 64;
     int64_t chunk_s = 1, chunk_g = 1, chunk_e = 1;
     // partial rows of the segment and element sums: the samples', then the boundary Gauss points'
-    int ns = N > 0 ? chunks_for(N, kgroups, chunk_s) : 0;
-    const int ng = chunks_for(3 * (int64_t)M, kgroups, chunk_g);
-    int ne = N > 0 ? chunks_for(N, mgroups, chunk_e) : 0;
+    const bool fine = !carve || vjp_f64_workspace_bytes(K, M, N, true) <= carve->bytes;
+    int ns = N > 0 ? chunks_for(N, kgroups, fine, chunk_s) : 0;
+    const int ng = chunks_for(3 * (int64_t)M, kgroups, fine, chunk_g);
+    int ne = N > 0 ? chunks_for(N, mgroups, fine, chunk_e) : 0;
     const Grouping grid = mixed && N > 0 ? adj_mixed_rows(ctx, K, N, &ns, &ne) : Grouping{};
     const size_t seg_part = (size_t)(ns + ng) * K * kV;
     const size_t el_rows = (size_t)(ne > 0 ? ne : 1);
@@ -225,9 +226,10 @@ int run_vjp(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     float *seg32w, *el32w;
     if (carve) {
         // every workspace from the caller's device memory, in the order vjp_f64_workspace_bytes counts
-        if (vjp_f64_workspace_bytes(K, M, N) > carve->bytes)
+        const size_t need = vjp_f64_workspace_bytes(K, M, N, fine);
+        if (need > carve->bytes)
             return set_error(ctx, BEM_EINVAL, "%zu bytes of workspace for K = %d, M = %d, N = %lld exceed the %zu "
-                             "available", vjp_f64_workspace_bytes(K, M, N), K, M, (long long)N, carve->bytes);
+                             "available", need, K, M, (long long)N, carve->bytes);
         char* p = carve->base;
         auto take = [&](size_t b) { char* q = p; p += carve_round(b); return q; };
         seg64w = (double*)take(seg_n * sizeof(double));
@@ -339,7 +341,7 @@ extern "C" int bem_vjp_noalloc(bem_ctx* ctx, const double* theta, int32_t H, con
     if (N > 0 && !gbar) return set_error(ctx, BEM_EINVAL, "gbar is null");
     if (H > 0 && !grad) return set_error(ctx, BEM_EINVAL, "grad is null");
     const int K = H * ctx->opts.segs_per_handle;
-    const size_t need = vjp_f64_workspace_bytes(K, ctx->M, N);
+    const size_t need = vjp_f64_workspace_bytes(K, ctx->M, N, false);       // the least run_vjp can do with
     if (need > kScratchBytes)
         return set_error(ctx, BEM_EINVAL, "bem_vjp_noalloc: %zu bytes of workspace for K = %d segments, M = %d "
                          "elements, N = %lld samples exceed its %zu-byte scratch", need, K, ctx->M, (long long)N,
