@@ -1177,20 +1177,25 @@ int run_jacobian(bem_ctx* ctx, const double* theta, int H, const double* x, int6
     if ((rc = launch_expand(ctx, theta, H, s))) return rc;
     double* Z = nullptr;
     if ((rc = boundary_derivatives(ctx, H, s, &Z))) return rc;
-    const int64_t ld = N;
+    // beta rows are transposed and multiplied 16,384 samples at a time: their copy of all samples was as large as the
+    // features
+    const int64_t ld = N, P = (int64_t)L.params() * H, step = N < 16384 ? N : 16384;
     const int Mp = gemm_pad(M);
     const size_t xs = ((size_t)W * N + 1) / 2 * 2;
-    if ((rc = ensure(ctx, ctx->tmp0, (xs + (size_t)N * Mp + (size_t)N * nf) * sizeof(double), s))) return rc;
+    if ((rc = ensure(ctx, ctx->tmp0, (xs + (size_t)step * Mp + (size_t)step * nf) * sizeof(double), s))) return rc;
     double* Xt = (double*)ctx->tmp0.ptr;
     double* Bt = Xt + xs;
-    double* BZ = Bt + (size_t)N * Mp;
+    double* BZ = Bt + (size_t)step * Mp;
     if ((rc = launch_features<double>(ctx, x, N, H, false, true, Xt, nullptr, ld, s))) return rc;
-    // BZ[t][f] = sum_i beta_i(t) Z[f][i]  (beta rows of Xt transposed)
-    hipLaunchKernelGGL(k_pad, dim3(blocks_for(N * Mp, 256)), dim3(256), 0, s, (const double*)(Xt + (size_t)nf * ld), ld, true, N, M, N, Mp,
-                       Bt);
-    if ((rc = gemm_f64(ctx, Gemm64{(int)N, nf, Mp, 1.0, Bt, Mp, Z, Mp, 0.0, BZ, nf}, 1, s))) return rc;
-    hipLaunchKernelGGL(k_assemble_jacobian, dim3(blocks_for((int64_t)L.params() * H, 256), N), dim3(256), 0, s, Xt, ld,
-                       BZ, L, N, J);
+    for (int64_t t0 = 0; t0 < N; t0 += step) {
+        const int64_t n = N - t0 < step ? N - t0 : step;
+        // BZ[t][f] = sum_i beta_i(t) Z[f][i]  (beta rows of Xt transposed)
+        hipLaunchKernelGGL(k_pad, dim3(blocks_for(n * Mp, 256)), dim3(256), 0, s, (const double*)(Xt + (size_t)nf * ld + t0), ld,
+                           true, n, M, n, Mp, Bt);
+        if ((rc = gemm_f64(ctx, Gemm64{(int)n, nf, Mp, 1.0, Bt, Mp, Z, Mp, 0.0, BZ, nf}, 1, s))) return rc;
+        hipLaunchKernelGGL(k_assemble_jacobian, dim3(blocks_for(P, 256), n), dim3(256), 0, s, Xt + t0, ld, BZ, L, n,
+                           J + (size_t)t0 * 3 * P);
+    }
     return check_launch(ctx, "jacobian");
 }
 
