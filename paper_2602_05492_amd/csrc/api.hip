@@ -125,7 +125,7 @@ static void prof_resolve(bem_ctx* ctx)
     hipGetLastError();
 }
 
-static void release(DevBuf& b)
+void release(DevBuf& b)
 {
     if (b.ptr) hipFree(b.ptr);
     b.ptr = nullptr;

@@ -136,6 +136,7 @@ struct ProfScope {
     ~ProfScope() { prof_end(ctx, tag, s, start); }
 };
 int ensure(bem_ctx* ctx, DevBuf& b, size_t bytes, hipStream_t stream);
+void release(DevBuf& b);         // (no kernel queued may use it)
 // argument checks shared by the per-call entry points; makes the context's device current
 int check_common(bem_ctx* ctx, const double* theta, int32_t H, const double* x, int64_t N);
 int aux_stream(bem_ctx* ctx, hipStream_t* out);

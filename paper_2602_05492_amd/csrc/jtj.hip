@@ -1052,16 +1052,29 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     // deterministic (no atomics)
     const int ts = gram == BEM_GRAM_FP64_VALU ? 64 : (gram == BEM_GRAM_BF16X3_MFMA ? 256 : 128);
     const std::vector<int> out_tiles = gram_tiles(L, (int)W, ts);
-    const int parts = gram == BEM_GRAM_BF16X3_MFMA ? bf16_parts((int)out_tiles.size() / 2, W)
-                      : gram == BEM_GRAM_FP64 ? f64_parts((int)out_tiles.size() / 2, W) : 1;
+    const int least = gram == BEM_GRAM_BF16X3_MFMA ? 3 : 1;
+    int parts = gram == BEM_GRAM_BF16X3_MFMA ? bf16_parts((int)out_tiles.size() / 2, W)
+                : gram == BEM_GRAM_FP64 ? f64_parts((int)out_tiles.size() / 2, W) : 1;
+    // tmp0: feature tile(s); tmp1: G [parts][W][W].  With no memory for them the fewest parts, then (float64) smaller tiles
+    bool overlap;
+    size_t tile_bytes;
+    for (;;) {
+        overlap = shares && N > T;
+        tile_bytes = ((size_t)W * T * elem + 255) / 256 * 256;
+        rc = ensure(ctx, ctx->tmp0, tile_bytes * (overlap ? 2 : 1), s);
+        if (!rc) rc = ensure(ctx, ctx->tmp1, (size_t)parts * W * W * sizeof(double), s);
+        if (!rc) break;
+        const bool smaller = f64 && ctx->opts.tile_rows <= 0 && T > 16384;
+        if (rc != BEM_ENOMEM || !(parts > least || smaller)) return rc;
+        if (parts > least) parts = least;
+        else T = (T / 2 + 63) / 64 * 64;
+        if (hipStreamSynchronize(s) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream sync");
+        release(ctx->tmp0);
+        ctx->err.clear();
+    }
     const int64_t kchunk = ((T + parts - 1) / parts + 31) / 32 * 32;
-    const bool overlap = shares && N > T;
-    const size_t tile_bytes = ((size_t)W * T * elem + 255) / 256 * 256;
     hipStream_t sg = s;
     if (overlap && (rc = aux_stream(ctx, &sg))) return rc;
-    // tmp0: feature tile(s); tmp1: G [parts][W][W]
-    if ((rc = ensure(ctx, ctx->tmp0, tile_bytes * (overlap ? 2 : 1), s))) return rc;
-    if ((rc = ensure(ctx, ctx->tmp1, (size_t)parts * W * W * sizeof(double), s))) return rc;
     double* G = (double*)ctx->tmp1.ptr;
     // the first sample tile's Gram writes G (every entry of its tile list, in every part)
     if (N == 0 && (rc = fill_f64(ctx, G, (int64_t)parts * W * W, 0.0, s))) return rc;

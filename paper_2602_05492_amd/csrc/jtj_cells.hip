@@ -894,11 +894,7 @@ int run_jtj_cells(bem_ctx* ctx, const double* theta, int H, const double* x, int
     if (rc != BEM_ENOMEM) return rc;
     // the samples are taken one by one, and what the workspaces held is given back
     if (hipStreamSynchronize(s) != hipSuccess) return set_error(ctx, BEM_EHIP, "stream sync");
-    for (DevBuf* q : {&ctx->cellw, &ctx->cellb, &ctx->necw, &ctx->nezw, &ctx->neew, &ctx->tmp0, &ctx->tmp1, &ctx->tmp2}) {
-        if (q->ptr) hipFree(q->ptr);
-        q->ptr = nullptr;
-        q->bytes = 0;
-    }
+    for (DevBuf* q : {&ctx->cellw, &ctx->cellb, &ctx->necw, &ctx->nezw, &ctx->neew, &ctx->tmp0, &ctx->tmp1, &ctx->tmp2}) release(*q);
     ctx->err.clear();
     return BEM_OK;
 }

@@ -96,3 +96,21 @@ def test_lm_step():
     assert tiles > 0 and st.accepted == s64.accepted == 1
     assert np.abs(d - d64).max() < mixed_step_tol(host(JtJ), 1.0) * np.abs(d64).max()
     ctx.close()
+
+
+def test_jtj_fp64():
+    """32,768 samples in tiles of 16,384 where a tile of all of them (298 MB) does not fit."""
+    th, x = dev(W.random_handles(4, 4, spread=0.1)), dev(W.random_points(5, 32768, 0.01, 0.99))
+    r = dev(W.random_vector(6, (len(x), 3)))
+    want, ctx = B.Context(segs_per_handle=4), B.Context(segs_per_handle=4)
+    J, g = want.jtj(th, x, r)
+    want.close()
+    few = x[:2000].contiguous()
+    ctx.jtj(th, few, r[:2000].contiguous())                  # all but the tile of samples
+    ctx.vjp(th, x, r)
+    with _full(160 * MIB):
+        J1, g1 = ctx.jtj(th, x, r)
+        torch.cuda.synchronize()
+    assert float((J1 - J).abs().max()) < 1e-12 * float(J.abs().max())
+    assert float((g1 - g).abs().max()) < 1e-12 * float(g.abs().max())
+    ctx.close()
