@@ -62,11 +62,12 @@ __global__ void k_expand(const double* __restrict__ theta, int H, int S, int mod
     if (!live) {
         // float32 record of a degenerate segment: a point far outside the domain with v = 0, kd = ks = 0 and no
         // densities, whose moments and end-point gradients evaluate to exactly 0 without special cases, by the closed
-        // forms and by quadrature (whose gradient has a term of the double layer's density that no length multiplies)
+        // forms and by quadrature (whose gradient has a term of the double layer's density that no length multiplies);
+        // a density that is not finite stays so
         o32[0] = o32[2] = 1.0e6f;
         o32[1] = o32[3] = 1.0e6f;
         o32[4] = o32[5] = 0.0f;
-        for (int c = kWdA; c < kWcB + 3; ++c) o32[c] = 0.0f;
+        for (int c = kWdA; c < kWcB + 3; ++c) o32[c] = (float)(0.0 * rec[c]);
     }
 }
 

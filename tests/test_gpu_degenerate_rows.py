@@ -50,3 +50,14 @@ def test_step_leaves_them(model, S, tile_rows):
     assert st.accepted and tiles == (tile_rows > 0)
     moved = np.abs(host(t) - th).max(1)
     assert not moved[list(GONE)].any() and (moved > 0).sum() == 38
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n", [500, 60000])                         # direct and grouped sums
+@pytest.mark.parametrize("what", ["jump", "all"])
+def test_values_that_are_not_finite_show(value, n, what):
+    """A handle of no length (or of none that is a number) hides no jump that is not finite."""
+    th = _theta("straight", 400)
+    th[GONE[0], 5 if what == "jump" else slice(None)] = value
+    u = ctx_for(1, handle_model="straight").eval(dev(th), dev(W.random_points(11, n, 1e-3, 1 - 1e-3)), CBAR, "mixed")
+    assert not np.isfinite(host(u)).all(1).any()
