@@ -82,7 +82,8 @@ __device__ inline void flush_near(const Tables& t, const double* __restrict__ x,
 __device__ inline void add_segment(const float* __restrict__ s, const SegGeom<float>& g, float X, float Y, float eps2f,
                                    bool near, float (&f)[3])
 {
-    const Moments<float> m = seg_moments<float, DevF32, false>(g, X, Y, eps2f);
+    // (a near pair counts zero times; regularised as if eps = 1, so that it is finite on an end point as well)
+    const Moments<float> m = seg_moments<float, DevF32, false>(g, X, Y, near ? 1.0f : eps2f);
     const float on = near ? 0.0f : 1.0f;
 #pragma unroll
     for (int c = 0; c < 3; ++c)

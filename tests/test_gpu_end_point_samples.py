@@ -1,4 +1,5 @@
-"""Colours and gradients at samples on the ends of outer elements, to the smallest distances that float64 holds."""
+"""Colours at samples on end points: of handles without regularisation, in mixed precision (a near pair's float32 form is
+not finite there and has to leave no trace), and of outer elements to the smallest distances that float64 holds."""
 import numpy as np
 import pytest
 import torch
@@ -8,6 +9,21 @@ from helpers import ctx_for, dev, host
 
 pytestmark = pytest.mark.gpu
 CBAR = (0.3, 0.5, 0.7)
+
+
+@pytest.mark.parametrize("H,n", [(40, 300), (900, 30000)])          # direct, grouped
+@pytest.mark.parametrize("nf", [0.5, 1.0])
+def test_on_handle_ends(H, n, nf):
+    rng = np.random.default_rng(H)
+    a = rng.uniform(0.15, 0.85, (H, 2))
+    b = a + rng.choice([0.2, 0.05, 0.005], H)[:, None] * rng.uniform(-0.7, 0.7, (H, 2))
+    th = dev(np.concatenate([a, b, W.draw_straight_colours(rng, H)], 1))
+    x = rng.uniform(0.01, 0.99, (n, 2))
+    x[:80] = np.concatenate([a[:40], b[:40]])
+    ctx = ctx_for(1, eps=0.0, near_factor=nf, per_side=32, handle_model="straight")
+    u, r = (host(ctx.eval(th, dev(x), CBAR, p)) for p in ("mixed", "fp64"))
+    assert np.isfinite(r).all() and np.isfinite(u).all()
+    assert np.abs(u - r).max() < 1e-4 * max(1.0, np.abs(r).max())
 
 
 @pytest.mark.parametrize("n", [300, 30000])
