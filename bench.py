@@ -20,7 +20,6 @@ the same workload and extrapolates linearly.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -32,47 +31,6 @@ sys.path.insert(0, ROOT)
 METRIC = "sample×segment pairs/s and LM steps/s, FP32-mixed vs FP64 at 1e-4 color err"
 PEAKS = {"fp32_vector": 157.3e12, "fp64_vector": 78.6e12, "fp32_mfma": 157.3e12, "fp64_mfma": 78.6e12,
          "bf16_mfma": 2.5e15}
-# Counters of kernels that sum pairs directly, if recorded (rocprofv3 --pmc passes over `bench.py --pmc-probe`,
-# kernels serialised), each with the SHA-256 of the sources it was taken from
-PMC_FILE = os.path.join(ROOT, "profiles", "lm_workload_counters.json")
-CSRC = os.path.join(ROOT, "paper_2602_05492_amd", "csrc")
-GRAM_TILE = 32768          # samples per split-BF16 Gram launch (the library's default tile)
-
-
-def sources_sha(names) -> str:
-    h = hashlib.sha256()
-    for nm in names:
-        h.update(open(os.path.join(CSRC, nm), "rb").read())
-    return h.hexdigest()
-
-
-def gram_tile_pairs(H: int, M: int, model: str) -> int:
-    """256 x 256 output tiles the split-BF16 Gram computes: the upper triangle of the feature
-    rows' tiles (three channel geometry blocks, each padded to 256 rows, then the shared colour
-    and beta rows) without the pairs that lie in two different channels' geometry blocks."""
-    G, C = (8, 4) if model == "cubic" else (4, 2)
-    gp = -(-G * H // 256) * 256
-    nt = -(-(3 * gp + C * H + M) // 256)
-
-    def region(t):
-        lo, hi = 256 * t, 256 * t + 255
-        if lo >= 3 * gp:
-            return -1
-        if hi >= 3 * gp or lo // gp != hi // gp:
-            return -2
-        return lo // gp
-
-    return sum(1 for i in range(nt) for j in range(i, nt)
-               if not (region(i) >= 0 and region(j) >= 0 and region(i) != region(j)))
-
-
-def pmc_record():
-    try:
-        return json.load(open(PMC_FILE))
-    except (OSError, ValueError):
-        return None
-
-
 # algorithmic work per unit (float32 flops, FMA = 2)
 F_HANDLE_PAIR = 110.0      # forward: one sample x one handle segment
 F_BOUNDARY_PAIR = 40.0     # forward / adjoint: one sample x one outer element
@@ -111,56 +69,6 @@ def gram_entries(H: int, M: int, model: str = "cubic") -> int:
     fg, fc = FEATURE_ROWS[model]
     g, s = fg * H, fc * H + M
     return 3 * (g * (g + 1) // 2) + 3 * g * s + s * (s + 1) // 2
-
-
-def counters(kernel: str):
-    """The committed counter record of a kernel, or None when there is none or its sources have
-    changed since it was taken."""
-    rec = pmc_record()
-    k = rec.get("kernels", {}).get(kernel) if rec else None
-    try:
-        return k if k and k.get("source_sha256") == sources_sha(k.get("source_files", [])) else None
-    except OSError:                     # a source of that record is gone
-        return None
-
-
-def gram_alg_bytes(H: int, M: int, model: str) -> float:
-    """Algorithmic HBM bytes of one split-BF16 Gram launch: the feature tile read once (hi and lo
-    planes, W rows x the tile's samples) and the partial-Gram tiles of its work list read and
-    written once (8-byte entries, 3 parts)."""
-    fg, fc = FEATURE_ROWS[model]
-    W = 3 * (-(-fg * H // 256) * 256) + fc * H + M
-    return W * GRAM_TILE * 4.0 + 2 * 3 * gram_tile_pairs(H, M, model) * 256 * 256 * 8.0
-
-
-def gram_traffic(samples_per_launch: int):
-    """HBM bytes per Gram launch from the committed counter run (FETCH_SIZE and WRITE_SIZE scaled by
-    what they read for a plain copy), or None."""
-    g = counters("k_gram_bf16x3_lds")
-    if not g or samples_per_launch != GRAM_TILE:
-        return None
-    return g["hbm_bytes"]
-
-
-def valu_fraction(kernel: str, pairs_per_s_in_step):
-    """float32 VALU rate of a sweep-type kernel: the counter flops per pair (FMA = 2) times its pair
-    rate, in the timed step (shared with other kernels) and alone (the counter run), against the
-    float32 vector peak (packed) and the non-packed FMA ceiling (half of it)."""
-    k = counters(kernel)
-    if not k or "fp32_flops_per_pair" not in k:
-        return None
-    fpp = k["fp32_flops_per_pair"]
-    out = {"kernel": kernel, "fp32_flops_per_pair": fpp, "valu_insts_per_pair": k["valu_insts_per_pair"],
-           "compiler": k.get("compiler"),
-           "alone": {"pairs_per_s": k["pairs_per_s_alone"], "tflops": k["tflops_alone"],
-                     "frac": k["tflops_alone"] / (PEAKS["fp32_vector"] / 1e12),
-                     "frac_of_unpacked_peak": k["tflops_alone"] / (PEAKS["fp32_vector"] / 2e12),
-                     "clock_ghz": k["clock_ghz"]}}
-    if pairs_per_s_in_step:
-        tf = fpp * pairs_per_s_in_step / 1e12
-        out["in_step"] = {"pairs_per_s": pairs_per_s_in_step, "tflops": tf, "frac": tf / (PEAKS["fp32_vector"] / 1e12),
-                          "frac_of_unpacked_peak": tf / (PEAKS["fp32_vector"] / 2e12)}
-    return out
 
 
 def pmc_probe() -> int:
@@ -514,8 +422,6 @@ def adjoint_mode(steps: int, warmup: int, do_cpu: bool) -> int:
     ms64 = (time.perf_counter() - t0) * 1e3
     rel = float((gm - gd).abs().max() / gd.abs().max())
     pairs = N * (K + M)
-    seg_ms = prof["vjp_segments"][0] / steps if prof["vjp_segments"][1] else None
-    vjp_valu = valu_fraction("k_vjp_segments", N * K / (seg_ms * 1e-3) if seg_ms else None)
     out = {"metric": "sample x segment pairs/s (mixed adjoint, bem_vjp)", "value": pairs / (ms * 1e-3),
            "unit": "pairs/s", "n_gpus": 1, "steps": steps, "warmup": warmup, "ms_per_step": ms,
            "higher_is_better": True, "dtype": "f32", "data": "synthetic",
@@ -523,7 +429,7 @@ def adjoint_mode(steps: int, warmup: int, do_cpu: bool) -> int:
                       "params": wl.P, "outer_elements": M},
            "handle_pairs_per_s": N * K / (ms * 1e-3), "fp64_gpu_ms": ms64, "fp64_pairs_per_s": pairs / (ms64 * 1e-3),
            "speedup_vs_fp64_gpu": ms64 / ms,
-           "grad_rel_err_vs_fp64": {"max_abs_over_max": rel, "bar": 1e-3}, "vjp_valu": vjp_valu,
+           "grad_rel_err_vs_fp64": {"max_abs_over_max": rel, "bar": 1e-3},
            "kernel_ms_per_vjp": {k: v[0] / steps for k, v in prof.items() if v[1] > 0},
            "cpu_baseline": cpu}
     print(json.dumps(out), flush=True)
@@ -679,42 +585,14 @@ def main() -> int:
     bound, peak = peak_of[dom]
     grouped = not (dom == "gram_f64" or (args.prec == "fp64" and dom in ("vjp_segments", "vjp_elements", "features"))
                    or (dom == "gram_mfma" and (args.gram == "fp32_mfma" or args.tile_rows)))
-    # the committed byte counters were taken on the LM workload's Gram
-    traffic = (gram_traffic(GRAM_TILE) if (dom == "gram_mfma" and args.gram == "bf16x3_mfma" and args.workload == "lm"
-                                           and args.tile_rows in (0, GRAM_TILE)) else None)
     roofline = {"bound": bound, "kernel": dom, "achieved": achieved, "peak": peak / 1e12, "unit": "TFLOP/s",
                 "work": "direct sums, far field expanded over cells" if grouped else "direct sums",
-                "frac": None if grouped else achieved / (peak / 1e12), "traffic": traffic, "launches": launches,
+                "frac": None if grouped else achieved / (peak / 1e12), "traffic": None, "launches": launches,
                 "avg_launch_ms": tot_ms / launches}
-    if traffic is not None:
-        # context from the same counter run: the clock under the Gram launch alone (GRBM_GUI_ACTIVE
-        # per XCD over its duration) and the MFMA work it issues (3 products per entry) against
-        # the dense bf16 peak at that clock
-        g = counters("k_gram_bf16x3_lds")
-        issued = gram_tile_pairs(H, M, wl.spec.model) * 256 * 256 * 2.0 * GRAM_TILE * 3
-        roofline["alone"] = {"ms": g["duration_ms"], "clock_ghz": g["clock_ghz"],
-                             "mfma_issued_pflops": issued / (g["duration_ms"] * 1e-3) / 1e15,
-                             "frac_of_peak_at_clock": issued / (g["duration_ms"] * 1e-3) / (2.5e15 * g["clock_ghz"] / 2.4),
-                             "algorithmic_bytes": (gram_alg_bytes(H, M, wl.spec.model)
-                                                   if wl.spec.model == "cubic" else None)}
     fwd_ms = prof["sweep_mixed" if args.prec == "mixed" else "sweep_f64"]
     pairs_fwd = (N * (K + M)) / (fwd_ms[0] / fwd_ms[1] * 1e-3) if fwd_ms[1] else None
     vjp_ms = prof["vjp_segments"][0] + prof["vjp_elements"][0]
     pairs_vjp = steps * (N * (K + M)) / (vjp_ms * 1e-3) if vjp_ms > 0 else None
-    feat_ms = prof["features"][0]
-    pairs_feat = steps * N * K / (feat_ms * 1e-3) if feat_ms > 0 else None
-
-    # the VALU kernels against the float32 vector peak (packed FP32 counts twice; without it the
-    # vector ceiling is half of that), from the committed counters of the LM workload
-    lm_mixed = args.prec == "mixed" and args.workload == "lm"
-    sweep_valu = valu_fraction("k_sweep_far", pairs_fwd) if lm_mixed else None
-    if sweep_valu:
-        sw = counters("k_sweep_far")
-        samples_per_s = pairs_fwd / (K + M)
-        sweep_valu["transcendental_frac"] = sw["trans_per_pair"] * pairs_fwd / (PEAKS["fp32_vector"] / 16)
-        sweep_valu["hbm_gbps"] = sw["hbm_bytes"] / 65536 * samples_per_s / 1e9
-    features_valu = valu_fraction("k_features_far", pairs_feat) if lm_mixed else None
-
     # colour error of the mixed forward against the float64 path at the start parameters, over
     # every sample of the first batch (the metric's "at 1e-4 color err")
     x0 = batches[0][0]
@@ -776,7 +654,7 @@ def main() -> int:
         "fp64_gpu": fp64, "speedup_vs_fp64_gpu": speedup,
         "step_direction_rel_err_vs_fp64": step_err,
         "kernel_ms_per_step": {k: v[0] / steps for k, v in timed.items()},
-        "sweep_valu": sweep_valu, "features_valu": features_valu, "roofline": roofline, "cpu_baseline": cpu,
+        "roofline": roofline, "cpu_baseline": cpu,
     }
     print(json.dumps(out), flush=True)
     return 0
