@@ -71,7 +71,8 @@ typedef enum {
 /* Arithmetic of the sample x segment sweeps.
  * FP64 : every pair in float64; u and cotangents are float64.  With many samples bem_eval
  *        sums the far segments and outer elements of a grid cell at its 256 Chebyshev nodes
- *        and interpolates (within 1e-14 of a segment's part).
+ *        and interpolates (within 1e-14 of a segment's part, or the rounding of the coordinates
+ *        in a domain far from the origin).
  * MIXED: pairs in float32 except near-singular pairs (both segment end points
  *        within max(2 nf, nf + 1)*L of the sample, nf = near_factor, which
  *        contains every sample closer than nf*L to the segment), which are
@@ -90,7 +91,8 @@ typedef enum {
  *        evaluated against every segment); the segments and outer elements two
  *        cell widths off a cell, none of whose pairs there is near, are summed at the cell's 64
  *        Chebyshev nodes and interpolated (relative error below 1e-7), or at those of the largest
- *        of up to three levels of cells they are as far from.  Float32 pairs of the
+ *        of up to three levels of cells they are as far from.  bem_eval takes the direct sums
+ *        where its workspaces find no memory.  Float32 pairs of the
  *        interpolated sums and of the adjoint use Gauss-Legendre quadrature.
  *        lm_step and bem_jtj list their near pairs with a per-context capacity
  *        per 64 samples (1024 at first, at most 16384 and 4 GiB of list); the

@@ -22,8 +22,8 @@
 // Rounding.  The split-bfloat16 products of E average over the samples as those of the Gram over all
 // samples do; the fewer columns Y and Z carry 22 and 24 bits instead of 16.  Accumulation in float32 within a
 // run and in float64 beyond is the same.  Pairs by quadrature (seg_math.hpp), so near factors of at least 1.
-// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 8.7 ms, far features
-// 3.3 ms, near Gram 2.9 ms, near features 5.5 ms, where the tiles over all samples took 360 ms.  Error of the
+// Measured, 2,097,152 samples, 256 cubic handles x 32 segments (W = 8,192 rows): Y Y^T 8.6 ms, far features
+// 3.3 ms, near Gram 3.1 ms, near features 5.4 ms, where the tiles over all samples took 360 ms.  Error of the
 // step against float64: 8.1e-4 at lambda = 1e-3 and 1.7e-5 at 0.1, against 1.1e-3 and 5.4e-5.
 #include <algorithm>
 #include <cmath>
@@ -155,7 +155,7 @@ struct BlockTeam {
 };
 
 // Block a cell: the factor R of its Gramian (Rf [n][k], float32) and C with which q(x) = C T(x) ([k][ab], float64).
-// Bound by the factor's chain of 64 steps.
+// Bound by the factor's chain of 64 steps: 0.16 ms for 289 cells, 0.50 ms for 1,296 (in node order 0.12 and 0.37).
 __global__ void __launch_bounds__(256) k_cell_factor(const double* __restrict__ part, int nc, const int* __restrict__ off,
                                                      float* __restrict__ Rf, double* __restrict__ Cq)
 {

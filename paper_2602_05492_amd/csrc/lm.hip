@@ -360,8 +360,8 @@ int run_lm_step(bem_ctx* ctx, double* theta, int H, const double* x, int64_t N, 
     const bem_prec prec = mixed ? BEM_PREC_MIXED : BEM_PREC_FP64;
     st->accepted = 0;
     st->chol_retries = 0;
-    // J^T J over grid cells where that pays (it needs the samples only): the step of 8,192 segments and
-    // 2,097,152 samples 434 -> 56 ms, of 500 segments and 100,000 samples 24.8 -> 16.5 ms; otherwise the tiles
+    // J^T J over grid cells where that pays (it needs the samples only): by this alone the step of 8,192 segments
+    // and 2,097,152 samples 434 -> 56 ms, of 500 segments and 100,000 samples 24.8 -> 16.5 ms; otherwise the tiles
     // of the normal equations want neighbours in a wavefront: samples and targets reordered into a workspace,
     // cell by cell and then with the cell-ordered wavefronts dealt out (the step's results depend on the
     // order only through rounding)

@@ -12,8 +12,8 @@
 // its samples, which evaluate only the near ones pair by pair (k_sweep_cells).
 // Both are bound by the float32 vector ALUs (about 110 flops a pair).  The line between them is
 // cells_for's count of pairs.  Measured against one thread a sample over all pairs, one MI355X: 128
-// segments and 1,000 samples 316 -> 32 us a call; 500 segments and 262,144 samples 720 -> 188 us; 4,096
-// segments and 1,048,576 samples 9.91 -> 0.69 ms; the error against float64 went down with it (6.9e-7 ->
+// segments and 1,000 samples 315 -> 26 us a call; 500 segments and 262,144 samples 722 -> 180 us; 4,096
+// segments and 1,048,576 samples 9.85 -> 0.69 ms; the error against float64 went down with it (6.9e-7 ->
 // 1.4e-7 for the last).
 #include "cells.hpp"
 

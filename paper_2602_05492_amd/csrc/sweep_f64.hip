@@ -6,7 +6,7 @@
 // Chebyshev coefficients (k_far_coef_f64) and expanded at its samples, which take only the near ones pair
 // by pair (k_sweep_cells_f64).  Results are reproducible: every sum has a fixed order.
 // Bound by the float64 vector ALUs (about 155 instructions a segment pair, 55 an element's).  Measured
-// against one thread a sample over all pairs, one MI355X: 512 segments and 262,144 samples 1.75 -> 0.49 ms
+// against one thread a sample over all pairs, one MI355X: 512 segments and 262,144 samples 1.75 -> 0.43 ms
 // a call; 128 segments and 16,384 samples (the sweep) 564 -> 83 us; errors against float64 sums of the same
 // formulas 7e-16 before and after.
 #include "cells.hpp"

@@ -14,7 +14,7 @@
 // reduced in a fixed order; the near sums are added with atomics into kNearCopies partial rows.
 // Bound by the float32 vector ALUs (about 200 flops a pair).  Measured against one pass of all pairs (closed
 // forms), with the forward sweep of the same step, one MI355X: 8,192 segments and 4,194,304 samples 215 ->
-// 11.3 ms; 500 segments and 100,003 samples 2.84 -> 0.53 ms.  Gradient error against float64 for white
+// 10.9 ms; 500 segments and 100,003 samples 2.77 -> 0.50 ms.  Gradient error against float64 for white
 // cotangents 1.7e-5 -> 6.6e-7 (8,192 segments, 1,048,576 samples), 6.1e-5 -> 1.2e-7 (128 segments, one
 // sample): the quadrature does not cancel where the closed forms do.
 #include "adjoint.hpp"

@@ -1,8 +1,8 @@
 """The mixed LM step with its normal equations over grid cells (split-BF16 Gram) against the FP64 step and
 against the same step over tiles of samples (a context with a tile size of its own).
 
-Sizes at the edges: cells with fewer samples than nodes (the node basis has no full rank there), samples nearly
-all in a few cells, cells without samples, samples outside the outer boundary's box, segment counts that leave
+Sizes at the edges: cells with some 100 samples (fewer than nodes, and samples in part of a cell, are in
+test_gpu_cell_normal_regions.py), samples nearly all in a few cells, cells without samples, samples outside the outer boundary's box, segment counts that leave
 partial 32-groups of the near bitmaps, one segment and many segments a handle, every handle near (no cell is
 worth it: tiles), and near factors either side of the quadrature's reach.
 
