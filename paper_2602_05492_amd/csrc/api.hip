@@ -470,7 +470,7 @@ void bem_destroy(bem_ctx* ctx)
                       &ctx->tmp0, &ctx->tmp1, &ctx->tmp2, &ctx->tmp3, &ctx->tmp4, &ctx->tmp5, &ctx->lmw,
                       &ctx->nearf, &ctx->regw, &ctx->egeo, &ctx->cholw, &ctx->sortw, &ctx->boxw, &ctx->cellw, &ctx->cellb, &ctx->farw,
                       &ctx->necw, &ctx->nezw, &ctx->neew, &ctx->gemmw,
-                      &ctx->tilew};
+                      &ctx->tilew.buf, &ctx->halfw.buf};
     for (DevBuf* b : bufs) release(*b);
     for (hipEvent_t e : ctx->ev)
         if (e) hipEventDestroy(e);

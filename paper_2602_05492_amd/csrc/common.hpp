@@ -65,6 +65,12 @@ struct DevBuf {
     size_t bytes = 0;
 };
 
+// A work list on the device and the configuration it was made for
+struct WorkList {
+    DevBuf buf;
+    int64_t key[4] = {-1, -1, -1, -1};
+};
+
 }  // namespace bem
 
 namespace bem {
@@ -116,8 +122,8 @@ struct bem_ctx {
     std::vector<int> ne_work;
     // Gram work list of the normal equations on the device, uploaded once per (W, H, handle
     // model, Gram arithmetic) and kept, so that later calls enqueue without a host synchronisation
-    bem::DevBuf tilew;
-    int64_t tiles_key[4] = {-1, -1, -1, -1};
+    // (that over cells has its own, so that steps between calls of bem_jtj leave theirs in place)
+    bem::WorkList tilew, halfw;
 };
 
 namespace bem {

@@ -936,19 +936,20 @@ __global__ void __launch_bounds__(256) k_sum_parts(double* __restrict__ G, int p
 }
 }  // namespace
 
-// The work list lives on the device (tilew); it is uploaded when its configuration changes, the only host
+// A work list lives on the device; it is uploaded when its configuration changes, the only host
 // synchronisation of bem_jtj apart from workspace growth.
-static int upload_tiles(bem_ctx* ctx, const std::vector<int>& tiles, int64_t W, int H, int gram, int parts, hipStream_t s)
+static int upload_tiles(bem_ctx* ctx, WorkList& list, const std::vector<int>& tiles, int64_t W, int H, int gram, int parts,
+                        hipStream_t s)
 {
     int rc;
     const int64_t key[4] = {W, H, ctx->model, gram + 8 * (int64_t)parts};
-    if (std::memcmp(key, ctx->tiles_key, sizeof(key)) == 0) return BEM_OK;
-    ctx->tiles_key[0] = -1;
-    if ((rc = ensure(ctx, ctx->tilew, tiles.size() * sizeof(int), s))) return rc;
-    if (hipMemcpyAsync(ctx->tilew.ptr, tiles.data(), tiles.size() * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
+    if (std::memcmp(key, list.key, sizeof(key)) == 0) return BEM_OK;
+    list.key[0] = -1;
+    if ((rc = ensure(ctx, list.buf, tiles.size() * sizeof(int), s))) return rc;
+    if (hipMemcpyAsync(list.buf.ptr, tiles.data(), tiles.size() * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)           // the host copy goes out of scope at the caller
         return set_error(ctx, BEM_EHIP, "tile list upload");
-    std::memcpy(ctx->tiles_key, key, sizeof(key));
+    std::memcpy(list.key, key, sizeof(key));
     return BEM_OK;
 }
 
@@ -1081,8 +1082,8 @@ int run_jtj(bem_ctx* ctx, const double* theta, int H, const double* x, int64_t N
     const bool valu = gram == BEM_GRAM_FP64_VALU;
     const std::vector<int> tiles = valu ? out_tiles : gram_work(out_tiles, parts);
     const int ntiles = (int)tiles.size() / (valu ? 2 : 3);
-    if ((rc = upload_tiles(ctx, tiles, W, H, gram, parts, s))) return rc;
-    const int* dtiles = (const int*)ctx->tilew.ptr;
+    if ((rc = upload_tiles(ctx, ctx->tilew, tiles, W, H, gram, parts, s))) return rc;
+    const int* dtiles = (const int*)ctx->tilew.buf.ptr;
     // tmp5: the vertex table, then the near-pair corrections and run table of one sample tile
     const int S = ctx->opts.segs_per_handle;
     const size_t vtab_bytes = ((size_t)(S + 1) * 8 * sizeof(float) + 255) / 256 * 256;
@@ -1174,8 +1175,8 @@ int gram_work_half(bem_ctx* ctx, const Layout& L, int64_t W, int parts, const in
 {
     const std::vector<int> w = gram_work(gram_tiles(L, (int)W, 256), parts);
     *ntiles = (int)w.size() / (3 * parts);
-    const int rc = upload_tiles(ctx, w, W, L.H, BEM_GRAM_BF16X3_MFMA, parts, s);
-    *work = (const int*)ctx->tilew.ptr;
+    const int rc = upload_tiles(ctx, ctx->halfw, w, W, L.H, BEM_GRAM_BF16X3_MFMA, parts, s);
+    *work = (const int*)ctx->halfw.buf.ptr;
     return rc;
 }
 
