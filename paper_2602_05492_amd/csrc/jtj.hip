@@ -535,19 +535,19 @@ __global__ void k_gauss_points(int M, const double* __restrict__ eg, double* __r
 __global__ void k_boundary_features(const double* __restrict__ Xg, int nf, int M, int Mp, const double* __restrict__ eg,
                                     double* __restrict__ dF)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t f = e / Mp;
-    const int i = (int)(e % Mp);
-    if (f >= nf) return;
-    double v = 0.0;
-    if (i < M) {
-        double ax, ay, bx, by;
-        load_element(eg, i, ax, ay, bx, by);
-        const double half = 0.5 * sqrt((bx - ax) * (bx - ax) + (by - ay) * (by - ay));
-        const double* r = Xg + f * 3 * M + 3 * i;
-        v = half * (kGaussW0 * r[0] + kGaussW1 * r[1] + kGaussW0 * r[2]);
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < (int64_t)nf * Mp; e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t f = e / Mp;
+        const int i = (int)(e % Mp);
+        double v = 0.0;
+        if (i < M) {
+            double ax, ay, bx, by;
+            load_element(eg, i, ax, ay, bx, by);
+            const double half = 0.5 * sqrt((bx - ax) * (bx - ax) + (by - ay) * (by - ay));
+            const double* r = Xg + f * 3 * M + 3 * i;
+            v = half * (kGaussW0 * r[0] + kGaussW1 * r[1] + kGaussW0 * r[2]);
+        }
+        dF[e] = v;
     }
-    dF[e] = v;
 }
 
 // X [rows][ldx] (transposed: [cols][ldx]) into Y [rp][cp], zeros outside
@@ -826,7 +826,8 @@ int boundary_derivatives(bem_ctx* ctx, int H, hipStream_t s, double** Zout)
     }
     hipLaunchKernelGGL(k_gauss_points, dim3(blocks_for(3 * M, 256)), dim3(256), 0, s, M, (const double*)ctx->egeo.ptr, gx);
     if ((rc = launch_features<double>(ctx, gx, 3 * (int64_t)M, H, false, false, Xg, nullptr, 3 * (int64_t)M, s))) return rc;
-    hipLaunchKernelGGL(k_boundary_features, dim3(blocks_for((int64_t)nf * Mp, 256)), dim3(256), 0, s, Xg, nf, M, Mp,
+    // (a launch holds fewer than 2^32 threads)
+    hipLaunchKernelGGL(k_boundary_features, dim3(std::min(blocks_for((int64_t)nf * Mp, 256), 1 << 22)), dim3(256), 0, s, Xg, nf, M, Mp,
                        (const double*)ctx->egeo.ptr, dF);
     if ((rc = check_launch(ctx, "boundary features"))) return rc;
     if ((rc = gemm_f64(ctx, Gemm64{nf, Mp, Mp, 1.0, dF, Mp, Ap, Mp, 0.0, Z, Mp}, 1, s))) return rc;
