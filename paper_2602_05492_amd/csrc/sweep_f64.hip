@@ -71,9 +71,23 @@ __global__ void __launch_bounds__(256) k_sweep_f64_sum(const double* __restrict_
     if (threadIdx.x < 64 && i < 3 * N) u[i] = (i % 3 == 0 ? c0 : (i % 3 == 1 ? c1 : c2)) + v;
 }
 
+// The tables' coordinates from the grid's origin: a node's place in the domain rounds with the domain's distance from 0 (at
+// 1e4 the colours were off by 9e-13, now 7e-16), its place in the grid and the records' differences to the origin do not.
+__global__ void __launch_bounds__(256) k_relative(Tables64 t, double x0, double y0, double* __restrict__ seg,
+                                                  double* __restrict__ el)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= t.K + t.M) return;
+    const bool s = i < t.K;
+    const int n = s ? kSegStride : kElemStride;
+    const double* from = s ? t.seg + (size_t)i * kSegStride : t.el + (size_t)(i - t.K) * kElemStride;
+    double* to = s ? seg + (size_t)i * kSegStride : el + (size_t)(i - t.K) * kElemStride;
+    for (int k = 0; k < n; ++k) to[k] = from[k] - (k < (s ? 4 : 2) ? (k & 1 ? y0 : x0) : 0.0);
+}
+
 constexpr int kLowParts = 4;
 
-// Far sums at the nodes, thread = node.  First the top level, chunk y of it words [y gpc, (y + 1) gpc), sums to
+// Far sums at the nodes, thread = node, tables and grid from the grid's origin.  First the top level, chunk y of it words [y gpc, (y + 1) gpc), sums to
 // part [y][cell]; then kLowParts blocks a row of the levels below,
 // which take its words by turns, sums to low [part][row].  Cells without samples have no
 // far bits.
@@ -173,11 +187,11 @@ __global__ void __launch_bounds__(256) k_sweep_cells_f64(CellPlan p, Tables64 t,
             add_element(t, 32 * (q - p.seg_words) + __builtin_ctz(word), X, Y, b);
     double far[3] = {0.0, 0.0, 0.0};
     if (c < p.grid.nc) {
-        double cx, cy;
-        cell_corner(p.grid, c, cx, cy);
+        // (from the grid's origin, as the nodes)
+        const double cx = (double)(c % p.grid.nx) * p.grid.h, cy = (double)(c / p.grid.nx) * p.grid.h;
         double Ta[kFarQ64];
-        cheb_values<double, kFarQ64>((X - cx) * (2.0 * p.grid.inv_h) - 1.0, Ta);
-        const double y = (Y - cy) * (2.0 * p.grid.inv_h) - 1.0;
+        cheb_values<double, kFarQ64>(((X - p.grid.x0) - cx) * (2.0 * p.grid.inv_h) - 1.0, Ta);
+        const double y = ((Y - p.grid.y0) - cy) * (2.0 * p.grid.inv_h) - 1.0;
         const double* cf = coef + (size_t)c * 3 * kFarNodes64;
         double T0 = 1.0, T1 = y;                     // T_j(y), T_{j+1}(y)
         for (int j = 0; j < kFarQ64; ++j) {
@@ -213,7 +227,7 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
     ProfScope ps_(ctx, PT_SWEEP_F64, s);
     CellPlan p;
     int nc = 0, ntop = 0, nlow = 0, gpc = 0, nparts = 0;
-    size_t pb = 0, lb = 0;
+    size_t pb = 0, lb = 0, cb = 0;
     if (g.g) {
         rc = cell_plan(ctx, x, N, g, &p, s);
         if (!rc) rc = cell_bits(ctx, &p, K, M, false, s);
@@ -226,7 +240,10 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
             const size_t cell = 3 * kFarNodes64 * sizeof(double);
             pb = (size_t)nparts * ntop * cell;
             lb = (size_t)kLowParts * nlow * cell;
-            rc = ensure(ctx, ctx->farw, pb + lb + nc * cell, s);
+            cb = nc * cell;
+            const bool away = p.grid.x0 != 0.0 || p.grid.y0 != 0.0;
+            const size_t rb = away ? ((size_t)K * kSegStride + (size_t)M * kElemStride) * sizeof(double) : 0;
+            rc = ensure(ctx, ctx->farw, pb + lb + cb + rb, s);
         }
         if (rc && rc != BEM_ENOMEM) return rc;
         if (rc) {                            // no memory for them: the direct sums
@@ -262,7 +279,17 @@ int launch_sweep_f64(bem_ctx* ctx, const double* x, int64_t N, int K, const doub
     double* part = (double*)ctx->farw.ptr;
     double* low = (double*)((char*)ctx->farw.ptr + pb);
     double* coef = (double*)((char*)ctx->farw.ptr + pb + lb);
-    hipLaunchKernelGGL(k_far_nodes_f64, dim3(kLowParts * nlow + ntop * nparts), dim3(256), 0, s, p, t, gpc, nparts, part, low);
+    Tables64 tf = t;
+    CellPlan pf = p;
+    pf.grid.x0 = pf.grid.y0 = 0.0;
+    if (p.grid.x0 != 0.0 || p.grid.y0 != 0.0) {
+        double* seg = (double*)((char*)ctx->farw.ptr + pb + lb + cb);
+        double* el = seg + (size_t)K * kSegStride;
+        hipLaunchKernelGGL(k_relative, dim3(blocks_for(K + M, 256)), dim3(256), 0, s, t, p.grid.x0, p.grid.y0, seg, el);
+        tf.seg = seg;
+        tf.el = el;
+    }
+    hipLaunchKernelGGL(k_far_nodes_f64, dim3(kLowParts * nlow + ntop * nparts), dim3(256), 0, s, pf, tf, gpc, nparts, part, low);
     hipLaunchKernelGGL(k_far_coef_f64, dim3(nc, 3), dim3(256), 0, s, (const double*)part, nparts, (const double*)low, p, coef);
     hipLaunchKernelGGL(k_sweep_cells_f64, dim3((p.max_waves + 3) / 4), dim3(256), 0, s, p, t, (const double*)coef, cbar[0],
                        cbar[1], cbar[2], u);
